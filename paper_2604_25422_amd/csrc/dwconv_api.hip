@@ -79,10 +79,10 @@ RowsPlan plan_rows(const Shape &s)
     const long long elems = (long long)s.B * s.C * s.L;
     // (seven to sixteen offsets, fp32: only while the gaps stay below half a row - with a filter as long as the row half of
     // the virtual row is gap, and the tall-row kernels below do better: B3200 C128 L160 K160 fwd 354 us here)
-    // (rows that end inside a 16-byte granule - fp32 lengths that are not multiples of four, bf16 even lengths that are not
-    // multiples of eight: the kernels that load rows straight into LDS, up to six offsets; bf16 rows of odd length do not
-    // start on a dword)
-    const bool vrows = (s.dtype == DWCONV_F32 ? ((s.L % 4) == 0 || nd <= kMfmaMaxND) : (s.L % 2) == 0) &&
+    // (rows that end inside a 16-byte granule - fp32 lengths that are not multiples of four, bf16 lengths that are not
+    // multiples of eight: the kernels that load rows straight into LDS, up to six offsets; bf16 rows of odd length start
+    // on a dword every other time and are shifted to one, see rows_odd_start: P >= L + 1 + halo leaves room for it)
+    const bool vrows = (s.dtype == DWCONV_BF16 || (s.L % 4) == 0 || nd <= kMfmaMaxND) &&
                        (nd <= kMfmaMaxND || (s.dtype == DWCONV_F32 && (s.L % 4) == 0 && nd <= kMfmaMaxNDDw && 2 * P <= 3 * (long long)s.L)) &&
                        4 * padded > 5 * P && elems * es <= (1ll << 30) &&
                        (long long)s.B * P * P < (1ll << 32) && (long long)s.B * P < (1ll << 31);

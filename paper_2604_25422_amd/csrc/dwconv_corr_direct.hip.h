@@ -230,12 +230,16 @@ __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void co
 // in which case the rest of it is cleared in LDS once it has landed: rows_granule8_byte_offset): the walk's "row" is the virtual segment, its
 // "segment" the channel (walk_segs = segs_per_row = C), every lane translates the position of its granule on the memory
 // side of the loads, and the outputs of a group of four go to their row or nowhere.
-template <int ND, bool ROWS = false>
+// ODD: rows that do not all start on a dword (odd lengths, tensors that are only 2-byte aligned), shifted to the dword in
+// which they start (rows_odd_start and what follows it); both forms of row.  What it costs over rows of even length is
+// the clearing of the foreign elements and the group stores that straddle cache lines: B32 C256 L4097 K64 see the launcher.
+template <int ND, bool ROWS = false, bool ODD = false>
 __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void corr_direct_bf16_kernel(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ f, bf16_t *__restrict__ out, const CorrGeom g,
     const RowsMap rm)
 {
     static_assert(ND >= 2 && 16 * (ND - 1) <= 128, "window tail is one 128-element load");
+    static_assert(!ODD || 16 * ND < 512, "the first position of a row lies in the first half of its window");
     constexpr int XWE = kSegLen + 16 * (ND - 1);   // elements of the window that are ever read
     __shared__ __align__(16) short s_in[kCorrWavesPerBlock][kBf16FusedWin];
 
@@ -289,36 +293,52 @@ __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void co
     uintx4 rg;
     int g_shift;
     int vg0 = 0;            // ROWS: virtual position of the first element of the window
+    int s_next = 0;         // ODD: first position of the row (ROWS: of the channel's first row) the next loads belong to
     auto aim = [&](int prow, int pseg) {
+        if constexpr (ODD) s_next = (((ROWS ? pseg : prow) & g.L) ^ g.par0) & 1;
         if constexpr (ROWS) {
             g_shift = 0;
             if (prow < g.rows) {
                 vg0 = prow * kSegLen + 16 * g.dmin;
-                const unsigned long long a0 = reinterpret_cast<unsigned long long>(in + (size_t)pseg * (size_t)g.L);
-                rg = uintx4{(unsigned)a0, (unsigned)(a0 >> 32) & 0xffffu, rm.bytes - (unsigned)(pseg * g.L) * 2u, kBufferFlags};
+                const unsigned long long a0 = reinterpret_cast<unsigned long long>(in + (size_t)pseg * (size_t)g.L - (ODD ? s_next : 0));
+                unsigned nbytes = rm.bytes - (unsigned)(pseg * g.L) * 2u;
+                if constexpr (ODD) nbytes = (nbytes + 2u * (unsigned)s_next + 3u) & ~3u;
+                rg = uintx4{(unsigned)a0, (unsigned)(a0 >> 32) & 0xffffu, nbytes, kBufferFlags};
             } else {
                 rg = uintx4{0u, 0u, 0u, kBufferFlags};
             }
         } else if (prow < g.rows) {
             const int v0 = 2 * (pseg * kSegLen + 16 * g.dmin);
             g_shift = v0 < 0 ? v0 : 0;
-            rg = row_tail_resource(in + (size_t)prow * (size_t)g.L, g.L, v0 > 0 ? v0 : 0);
+            if constexpr (ODD)
+                rg = row_tail_resource(in + ((size_t)prow * (size_t)g.L - (size_t)s_next), (s_next + g.L + 1) & ~1, v0 > 0 ? v0 : 0);
+            else
+                rg = row_tail_resource(in + (size_t)prow * (size_t)g.L, g.L, v0 > 0 ? v0 : 0);
         } else {
             g_shift = 0;
             rg = uintx4{0u, 0u, 0u, kBufferFlags};
         }
     };
     int live_next[2] = {8, 8}, live_cur[2] = {8, 8};   // ROWS: see rows_granule8_byte_offset
+    int dead_next = 0, dead_cur = 0;                   // ROWS, ODD: see rows_pair_odd_byte_offset (the tail load)
     auto load_half = [&](auto hc) {
         constexpr int h = decltype(hc)::value;
-        if constexpr (ROWS)
+        if constexpr (ROWS && ODD)
+            buffer_load_x4_to_lds_keep(rg, rows_granule8_odd_byte_offset(rm, vg0 + (off_g >> 1) + 512 * h, s_next, live_next[h]),
+                                       lds_g + 1024u * (unsigned)h);
+        else if constexpr (ROWS)
             buffer_load_x4_to_lds_keep(rg, rows_granule8_byte_offset(rm, vg0 + (off_g >> 1) + 512 * h, live_next[h]),
                                        lds_g + 1024u * (unsigned)h);
         else
             buffer_load_x4_to_lds_keep(rg, off_g + (1024 * h + g_shift), lds_g + 1024u * (unsigned)h);
     };
     auto load_tail = [&]() {
-        if constexpr (ROWS)
+        if constexpr (ROWS && ODD) {
+            int dead;
+            const int off = rows_pair_odd_byte_offset(rm, vg0 + (off_gt >> 1), s_next, dead);
+            dead_next = off_gt == kOutOfRow ? 0 : dead;
+            buffer_load_x1_to_lds_keep(rg, off_gt == kOutOfRow ? kOutOfRow : off, lds_g + 2048u);
+        } else if constexpr (ROWS)
             buffer_load_x1_to_lds_keep(rg, off_gt == kOutOfRow ? kOutOfRow : rows_byte_offset<2>(rm, vg0 + (off_gt >> 1)), lds_g + 2048u);
         else
             buffer_load_x1_to_lds_keep(rg, off_gt == kOutOfRow ? kOutOfRow : off_gt + g_shift, lds_g + 2048u);
@@ -348,24 +368,39 @@ __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void co
             c_n -= c_n >= g.C ? g.C : 0;
             if constexpr (ROWS) c_n = seg_n;
         }
-        bf16_t *out_seg = ROWS ? out + (size_t)c * (size_t)g.L                         // (ROWS: the channel's first row)
-                               : out + (size_t)row * (size_t)g.L + (size_t)(seg * kSegLen);   // wave-uniform
-        const bool whole = ROWS ? false : (seg + 1) * kSegLen <= g.L;
+        const int s_cur = ODD ? s_next : 0;
+        const int row_end = s_cur + g.L;
+        bf16_t *out_seg = (ROWS ? out + (size_t)c * (size_t)g.L                        // (ROWS: the channel's first row)
+                                : out + (size_t)row * (size_t)g.L + (size_t)(seg * kSegLen)) - s_cur;   // wave-uniform
+        const bool whole = ROWS ? false : (seg + 1) * kSegLen <= row_end;
         const int t_seg = ROWS ? row * kSegLen : seg * kSegLen;
         aim(row_n, seg_n);
         if (c != cur_c) {
             load_filter(c);
             cur_c = c;
         }
-        if constexpr (ROWS) { live_cur[0] = live_next[0]; live_cur[1] = live_next[1]; }
+        if constexpr (ROWS) { live_cur[0] = live_next[0]; live_cur[1] = live_next[1]; dead_cur = dead_next; }
         static_for<0, 4>([&](auto cc) {
             constexpr int c4 = decltype(cc)::value;
             // three loads per segment (g0 g1 gt); one load of the next segment is out after chunk 1
             constexpr int need = c4 == 0 ? 0 : (c4 < 3 ? 1 : 2), issued = c4 >= 2 ? 1 : 0;
             wait_vmcnt_at_most<(2 - need) + issued>();
-            if constexpr (ROWS && c4 < 2) zero_slot_tail(sg + 512 * c4 + 8 * lane, live_cur[c4]);     // g_{c4} has just landed
+            // what has just landed: g_{c4} before chunks 0 and 1, gt before chunk 3
+            if constexpr (ROWS && ODD) {
+                if constexpr (c4 < 2) zero_slot_odd(sg + 512 * c4 + 8 * lane, live_cur[c4]);
+                if constexpr (c4 == 3) zero_pair_odd(sg + 1024 + 2 * lane, dead_cur);
+            } else if constexpr (ROWS) {
+                if constexpr (c4 < 2) zero_slot_tail(sg + 512 * c4 + 8 * lane, live_cur[c4]);
+            } else if constexpr (ODD && c4 != 2) {
+                // the foreign elements of this segment's window (wave-uniform): position 0 of a row that starts at 1, and
+                // the position behind a row that ends in the middle of a dword
+                constexpr int lo = c4 == 3 ? 1024 : 512 * c4, hi = c4 == 3 ? XWE : 512 * c4 + 512;
+                const int head = -(t_seg + 16 * g.dmin), tail = row_end + head;
+                if (c4 == 0 && s_cur && head >= 0) const_cast<short *>(sg)[bf16_dy_pos(head >> 4, head & 15)] = 0;
+                if ((row_end & 1) && tail >= lo && tail < hi) const_cast<short *>(sg)[bf16_dy_pos(tail >> 4, tail & 15)] = 0;
+            }
             // (a chunk wholly past the end of the row has no outputs: its matrix work is skipped)
-            const bool live = ROWS || whole || t_seg + 256 * c4 < g.L;
+            const bool live = ROWS || whole || t_seg + 256 * c4 < row_end;
             floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
             if (live) {
                 shortx4 bv[ND];
@@ -382,7 +417,14 @@ __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void co
             }
             // lane (block j = i16, row group kg) owns outputs 16 j + 4 kg + 0..3 of the chunk
             const int lt = 256 * c4 + 16 * i16 + 4 * kg;
-            if constexpr (ROWS) {
+            if constexpr (ROWS && ODD) {
+                int first, n;
+                const int e = rows_element_group_odd(rm, t_seg + lt, s_cur, first, n);
+                if (e >= 0) st_group_range(out_seg + e, make_float4(acc[0], acc[1], acc[2], acc[3]), first, n);
+            } else if constexpr (ODD) {
+                const int t = t_seg + lt;
+                st_group_range(out_seg + lt, make_float4(acc[0], acc[1], acc[2], acc[3]), t < s_cur ? 1 : 0, row_end - t);
+            } else if constexpr (ROWS) {
                 int n;
                 const int e = rows_element_group(rm, t_seg + lt, n);    // four outputs: one row, one gap, or the end of a row
                 if (e >= 0) st_rows_group(out_seg + e, make_float4(acc[0], acc[1], acc[2], acc[3]), n);

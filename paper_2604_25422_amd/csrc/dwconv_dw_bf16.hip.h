@@ -39,12 +39,15 @@ __host__ __device__ constexpr int bf16_block_pos(int nb) { return (nb & ~3) | ((
 // row length even: a 16-byte granule lies in one row or in one gap, or holds the last two, four or six elements of a row, in
 // which case the rest of it is cleared in LDS once it has landed: rows_granule8_byte_offset); B is then 1 and segs_per_row the number of segments of the
 // virtual row.  Every lane translates the position of its granule on the memory side of the loads.
-template <int ND, int W, bool ROWS = false>
+// ODD: rows that do not all start on a dword, shifted to the dword in which they start (rows_odd_start; par0: 1 when the
+// tensors themselves do not start on one): the foreign elements at their ends are cleared in both windows.
+template <int ND, int W, bool ROWS = false, bool ODD = false>
 __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_kernel(
     const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy, float *__restrict__ part, bf16_t *__restrict__ dw_out,
     int B, int C, int L, int K, int pad, int dmin, int segs_per_row, int j0, int j1, int seg0, int own_only,
-    const RowsMap rm)
+    const RowsMap rm, int par0)
 {
+    static_assert(!ODD || 16 * ND < 512, "the first position of a row lies in the first half of its x window");
     // seg0, own_only: as in dw_partial_direct_kernel (the first segment of every row this launch walks; write the
     // owned taps only)
     // [j0, j1): the taps this launch owns (0, K unless the block offsets of the filter are split over two launches);
@@ -109,6 +112,8 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
     uintx4 rx, rg;
     int x_shift;        // negative when the x window starts before the row: added to the lane offsets
     int vx0 = 0, vg0 = 0;   // ROWS: virtual positions of the first elements of the two windows
+    int s_next = 0;         // ODD: first position of the row (ROWS: of the channel's first row) the next loads belong to
+    int t_next = 0;         // ODD: first position of its segment
     auto aim = [&](int pb, int pseg) {
         if constexpr (ROWS) {
             x_shift = 0;
@@ -117,9 +122,11 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
                 const int t0 = (segs_per_row - 1 - pseg) * kSegLen;
                 vx0 = t0 + 16 * dmin;
                 vg0 = t0;
-                const unsigned nbytes = rm.bytes - (unsigned)(c * L) * 2u;
-                const unsigned long long ax0 = reinterpret_cast<unsigned long long>(x + (size_t)c * (size_t)L);
-                const unsigned long long ag0 = reinterpret_cast<unsigned long long>(dy + (size_t)c * (size_t)L);
+                if constexpr (ODD) s_next = ((c & L) ^ par0) & 1;
+                unsigned nbytes = rm.bytes - (unsigned)(c * L) * 2u;
+                if constexpr (ODD) nbytes = (nbytes + 2u * (unsigned)s_next + 3u) & ~3u;
+                const unsigned long long ax0 = reinterpret_cast<unsigned long long>(x + (size_t)c * (size_t)L - (ODD ? s_next : 0));
+                const unsigned long long ag0 = reinterpret_cast<unsigned long long>(dy + (size_t)c * (size_t)L - (ODD ? s_next : 0));
                 rx = uintx4{(unsigned)ax0, (unsigned)(ax0 >> 32) & 0xffffu, nbytes, kBufferFlags};
                 rg = uintx4{(unsigned)ag0, (unsigned)(ag0 >> 32) & 0xffffu, nbytes, kBufferFlags};
             } else {
@@ -133,9 +140,17 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
             const int t0 = (seg0 + pseg) * kSegLen;
             const int u0 = 2 * (t0 + 16 * dmin);
             x_shift = u0 < 0 ? u0 : 0;
+            if constexpr (ODD) {
+                s_next = ((((B - 1 - pb) * C + c) & L) ^ par0) & 1;
+                t_next = t0;
+                const int len = (s_next + L + 1) & ~1;
+                rx = row_tail_resource(x + (row - (size_t)s_next), len, u0 > 0 ? min(u0, 2 * len) : 0);
+                rg = row_tail_resource(dy + (row - (size_t)s_next), len, 2 * t0);
+            } else {
             // (a window that starts past the end of the row - the second of two launches - gets an empty resource)
             rx = row_tail_resource(x + row, L, u0 > 0 ? min(u0, 2 * L) : 0);
             rg = row_tail_resource(dy + row, L, 2 * t0);
+            }
         } else {
             x_shift = 0;
             rx = uintx4{0u, 0u, 0u, kBufferFlags};
@@ -144,9 +159,14 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
     };
     // ROWS: elements of the lane's granules x0 g0 x1 g1 that belong to a row which ends inside them (rows_granule8_byte_offset)
     int live_next[4] = {8, 8, 8, 8}, live_cur[4] = {8, 8, 8, 8};
+    int dead_next = 0, dead_cur = 0;        // ROWS, ODD: see rows_pair_odd_byte_offset (the tail load)
     auto load_half = [&](auto hc) {         // x_h then g_h
         constexpr int h = decltype(hc)::value;
-        if constexpr (ROWS) {
+        if constexpr (ROWS && ODD) {
+            const int e = (off_main >> 1) + 512 * h;
+            buffer_load_x4_to_lds_sel(keep_lines, rx, rows_granule8_odd_byte_offset(rm, vx0 + e, s_next, live_next[2 * h]), lds_x + 1024u * (unsigned)h);
+            buffer_load_x4_to_lds_sel(keep_lines, rg, rows_granule8_odd_byte_offset(rm, vg0 + e, s_next, live_next[2 * h + 1]), lds_g + 1024u * (unsigned)h);
+        } else if constexpr (ROWS) {
             const int e = (off_main >> 1) + 512 * h;        // the lane's granule: elements e .. e + 7 of the windows
             buffer_load_x4_to_lds_sel(keep_lines, rx, rows_granule8_byte_offset(rm, vx0 + e, live_next[2 * h]), lds_x + 1024u * (unsigned)h);
             buffer_load_x4_to_lds_sel(keep_lines, rg, rows_granule8_byte_offset(rm, vg0 + e, live_next[2 * h + 1]), lds_g + 1024u * (unsigned)h);
@@ -156,7 +176,12 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
         }
     };
     auto tail_offset = [&](int t) {
-        if constexpr (ROWS) return off_tail[t] == kOutOfRow ? kOutOfRow : rows_byte_offset<2>(rm, vx0 + (off_tail[t] >> 1));
+        if constexpr (ROWS && ODD) {                        // (one tail load: up to eight block offsets)
+            int dead;
+            const int off = rows_pair_odd_byte_offset(rm, vx0 + (off_tail[t] >> 1), s_next, dead);
+            dead_next = off_tail[t] == kOutOfRow ? 0 : dead;
+            return off_tail[t] == kOutOfRow ? kOutOfRow : off;
+        } else if constexpr (ROWS) return off_tail[t] == kOutOfRow ? kOutOfRow : rows_byte_offset<2>(rm, vx0 + (off_tail[t] >> 1));
         else return off_tail[t] + x_shift;
     };
     auto load_tail = [&]() {
@@ -174,10 +199,13 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
         const int carry = seg_n >= segs_per_row ? 1 : 0;
         seg_n -= carry ? segs_per_row : 0;
         const int b_n = b + step_b + carry;
+        const int head = ODD ? -(t_next + 16 * dmin) : 0;                       // ODD: window index of position 0 of the row
+        const int s_cur = s_next, row_end = s_next + L, t_cur = t_next;
         aim(b_n, seg_n);
         if constexpr (ROWS) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) live_cur[i] = live_next[i];
+            dead_cur = dead_next;
         }
         // 256-position chunk c4 (x blocks 16 c4 .. 16 c4 + 15 + ND + 2): before it, load number need(c4) of this
         // segment has landed
@@ -186,7 +214,32 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
             constexpr int c4 = decltype(cc)::value;
             constexpr int need = c4 == 3 ? NLOADS - 1 : c4 + 1, issued = c4 >= 2 ? 2 : 0;
             wait_vmcnt_at_most<(NLOADS - 1 - need) + issued>();
-            if constexpr (ROWS) {
+            if constexpr (ROWS && ODD) {
+                if constexpr (c4 == 0) { zero_slot_odd(sx + 8 * lane, live_cur[0]); zero_slot_odd(sg + 8 * lane, live_cur[1]); }
+                if constexpr (c4 == 1) zero_slot_odd(sx + 512 + 8 * lane, live_cur[2]);
+                if constexpr (c4 == 2) zero_slot_odd(sg + 512 + 8 * lane, live_cur[3]);
+                if constexpr (c4 == 3) zero_pair_odd(sx + 1024 + 2 * lane, dead_cur);
+            } else if constexpr (ODD) {
+                // the foreign elements of the windows (wave-uniform)
+                short *wx = const_cast<short *>(sx), *wg = const_cast<short *>(sg);
+                const int xt = row_end + head, gt = row_end - t_cur;
+                if constexpr (c4 == 0) {
+                    if (s_cur && head >= 0) {
+                        wx[16 * bf16_block_pos(head >> 4) + (head & 15)] = 0;
+                        if (t_cur == 0) wg[0] = 0;
+                    }
+                }
+                if (row_end & 1) {
+                    if constexpr (c4 != 2) {
+                        constexpr int lo = c4 == 3 ? 1024 : 512 * c4, hi = c4 == 3 ? XWE : 512 * c4 + 512;
+                        if (xt >= lo && xt < hi) wx[16 * bf16_block_pos(xt >> 4) + (xt & 15)] = 0;
+                    }
+                    if constexpr (c4 == 0 || c4 == 2) {
+                        constexpr int lo = 256 * c4;
+                        if (gt >= lo && gt < lo + 512) wg[16 * bf16_block_pos(gt >> 4) + (gt & 15)] = 0;
+                    }
+                }
+            } else if constexpr (ROWS) {
                 // what has just landed: x0 and g0 before chunk 0, x1 before chunk 1, g1 before chunk 2
                 if constexpr (c4 == 0) { zero_slot_tail(sx + 8 * lane, live_cur[0]); zero_slot_tail(sg + 8 * lane, live_cur[1]); }
                 if constexpr (c4 == 1) zero_slot_tail(sx + 512 + 8 * lane, live_cur[2]);

@@ -104,6 +104,14 @@ inline bool ragged_rows_ok(const Shape &s, int nd)
     return s.K >= kMfmaMinK && nd >= 2 && nd <= (s.dtype == DWCONV_F32 ? kRaggedMaxNDF32 : kMfmaMaxND) && s.L >= kRaggedRowsMinL &&
            (s.dtype == DWCONV_F32 || (s.L % 2) == 0);
 }
+// bf16 rows that do not all start on a dword: rows of odd length, tensors that are only 2-byte aligned.  The forward /
+// input-gradient and weight-gradient kernels that load rows straight into LDS take them (ODD variants, two to six block
+// offsets) when the two tensors of a call start on the same half of a dword; the fused backward kernel does not.
+// (Measured against the vector-ALU kernels: three to six times faster, figures at the launchers.)
+inline bool bf16_odd_rows(const Shape &s, const void *a, const void *b)
+{
+    return s.dtype == DWCONV_BF16 && ((s.L % 2) != 0 || !aligned_to(a, 4) || !aligned_to(b, 4));
+}
 inline bool ragged_rows_fused_ok(const Shape &s, int nd) { return ragged_rows_ok(s, nd) && s.L >= kRaggedMinL; }
 constexpr int kComputeUnits = 256;     // MI355X
 constexpr int kMfmaMaxL = 1 << 27;      // byte offsets inside a row stay below the out-of-row marker of the buffer loads
@@ -120,6 +128,12 @@ struct RowsPlan {
     dwconv::RowsMap map;
 };
 RowsPlan plan_rows(const Shape &s);
+// (ordinary rows from 129 positions as for even lengths; virtual rows of any length; not the sixteen-row kernels)
+inline bool bf16_odd_rows_ok(const Shape &s, const void *a, const void *b, const RowsPlan &rp)
+{
+    return aligned_to(a, 4) == aligned_to(b, 4) && !rp.batch && !rp.tall && (rp.on ? (rp.map.P % 8) == 0 && rp.map.P > s.L : s.L >= kRaggedRowsMinL) &&
+           (long long)s.B * s.C < (1ll << 31);
+}
 
 // The same idea for the generic vector-ALU kernels, which take any row length and alignment: short rows are walked as
 // the virtual row of their channel (pitch L + max(pad, K-1-pad), no rounding: these kernels load by element) when at

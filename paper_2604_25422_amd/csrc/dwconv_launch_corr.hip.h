@@ -196,7 +196,11 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     // LDS (up to six offsets)
     const bool rows_direct_bf16 = sizeof(T) == 2 && rp.on && (s.L % 2) == 0 && (rp.map.P % 8) == 0 && aligned_to(in, 4) && aligned_to(out, 4);
     const bool rows_direct_f32 = sizeof(T) == 4 && rp.on && nd <= kMfmaMaxND;
-    if (!granular && !rows_direct_bf16 && !rows_direct_f32 && (!ragged_rows_ok(s, nd) || !aligned_to(in, 4) || !aligned_to(out, 4))) return -1;
+    const bool odd = bf16_odd_rows(s, in, out);
+    // (rows of a dozen positions are all gap as virtual rows: B50000 C128 L9 K9 fwd 249 us on the vector-ALU kernel, 323 us
+    // here; L25 K7 320 against 309 us)
+    if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24))) return -1;
+    if (!odd && !granular && !rows_direct_bf16 && !rows_direct_f32 && (!ragged_rows_ok(s, nd) || !aligned_to(in, 4) || !aligned_to(out, 4))) return -1;
     // block offsets the long-filter kernel takes too (fp32 eleven to sixteen, bf16 seven to sixteen): only where rows
     // fill their 1024-position segments to three quarters (shorter rows do less work on the long-filter kernel,
     // which contracts in-row block pairs only)
@@ -204,7 +208,8 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
         4ll * s.L < 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen))
         return -1;
     const long long rows = (long long)s.B * s.C;
-    const long long segs_per_row = (s.L + dwconv::kSegLen - 1) / dwconv::kSegLen;
+    const int L_walk = odd ? s.L + 1 : s.L;             // (a shifted row may reach one position further)
+    const long long segs_per_row = (L_walk + dwconv::kSegLen - 1) / dwconv::kSegLen;
     const long long total_segs = rows * segs_per_row;
     if (total_segs > 0x3fffffffLL) return -1;           // the kernel's segment walk is 32-bit
     dwconv::CorrGeom g;
@@ -212,6 +217,7 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     g.pad = pad_eff; g.reverse = reverse; g.dmin = dmin;
     g.segs_per_row = (int)segs_per_row;
     g.walk_segs = (int)segs_per_row; g.n_main = 0; g.n_light = 0; g.step_c_light = 0;
+    g.par0 = odd && !aligned_to(in, 4) ? 1 : 0;
     constexpr int kThreads = 64 * dwconv::kCorrWavesPerBlock;
     const dwconv::RowsMap no_rows{0, 0, 0, 0, 0u, 0u};
     // One resident round of waves, each walking segments wave, wave + n_waves, ...
@@ -231,7 +237,7 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     auto launch = [&](auto kernel, auto *pi, auto *pf, auto *po, long long slot_cap = kTargetWaves,
                       long long balance_target = 0, bool own_light_waves = false) -> int {
         const long long capacity = balance_target > 0 ? resident_waves(kernel, kThreads) : corr_wave_slots(kernel, kThreads);
-        const int last = s.L % dwconv::kSegLen;
+        const int last = L_walk % dwconv::kSegLen;
         long long n_light = 0;
         if (own_light_waves && balance_target > 0 && last != 0 && last <= dwconv::kSegLen / 2 && segs_per_row >= 2) {
             // a light segment costs its wave about a microsecond (a memory round trip), a row of the walk about
@@ -286,6 +292,29 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, pi, pf, po, g, no_rows);
         return launch_status();
     };
+    if constexpr (sizeof(T) == 2) {
+        if (odd) {
+            // bf16 rows that do not all start on a dword, shifted to the dword in which they start (rows_odd_start).
+            // Vector-ALU kernel -> here: B32 C256 L4097 K64 fwd 109 -> 30 us (L4096: 22.7), B128 C768 L1025 K32 442 -> 81 us,
+            // virtual rows B4096 C128 L199 K48 314 -> 118 us, L47 K48 361 -> 150 us
+            const bf16_t *pi = static_cast<const bf16_t *>(in), *pf = static_cast<const bf16_t *>(f);
+            bf16_t *po = static_cast<bf16_t *>(out);
+            const long long balance = (L_walk % dwconv::kSegLen) != 0 ? kTargetWaves : 0;
+            auto go = [&](auto ndc) -> int {
+                constexpr int N = decltype(ndc)::value;
+                if (rp.on) return launch_corr_vrows_kernel<T>(dwconv::corr_direct_bf16_kernel<N, true, true>, g, rp, in, f, out, s, st);
+                return launch(dwconv::corr_direct_bf16_kernel<N, false, true>, pi, pf, po, kTargetWaves, balance, true);
+            };
+            switch (nd) {
+            case 2: return go(std::integral_constant<int, 2>{});
+            case 3: return go(std::integral_constant<int, 3>{});
+            case 4: return go(std::integral_constant<int, 4>{});
+            case 5: return go(std::integral_constant<int, 5>{});
+            case 6: return go(std::integral_constant<int, 6>{});
+            default: return -1;
+            }
+        }
+    }
     if (!granular && rp.on && !rows_direct_bf16 && !rows_direct_f32) return -1;
     {
         // longer short rows: segments of the virtual row of a channel, slots ordered (virtual segment, channel)

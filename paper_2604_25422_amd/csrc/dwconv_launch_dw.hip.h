@@ -110,6 +110,25 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
                                static_cast<float *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map,
                                0, s.K, 0, 0);
         }
+    } else if (bf16_odd_rows(s, x, dy)) {
+        // bf16 rows that do not all start on a dword: the same kernels on rows shifted to the dword in which they start
+        // (four waves whatever the plan says: workgroups of more are compiled for the aligned forms only).  Vector-ALU
+        // kernel -> here: B32 C256 L4097 K64 159 -> 27 us, B4096 C128 L199 K48 618 -> 86 us, B50000 C128 L9 K9 359 -> 147 us
+        if constexpr (W != dwconv::kWavesPerBlock) {
+            return launch_dw_partial_mfma_ndw<T, ND, dwconv::kWavesPerBlock>(x, dy, part, dw_out, s, p, dmin, st);
+        } else {
+            constexpr size_t lds = dwconv::dw_bf16_lds_bytes(ND, W);
+            static_assert(lds <= 64 * 1024, "LDS budget");
+            auto go = [&](auto kernel, int B, int segs) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
+                                   static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
+                                   static_cast<bf16_t *>(dw_out), B, s.C, s.L, s.K, s.pad, dmin, segs, 0, s.K, 0, 0,
+                                   p.rows.map, aligned_to(x, 4) ? 0 : 1);
+            };
+            if (p.rows.on) go(dwconv::dw_partial_bf16_kernel<ND, W, true, true>, 1, p.tiles_per_row);
+            // (a shifted row may reach one position into a segment more)
+            else go(dwconv::dw_partial_bf16_kernel<ND, W, false, true>, s.B, (s.L + 1 + dwconv::kSegLen - 1) / dwconv::kSegLen);
+        }
     } else if (p.rows.on && (s.L % 2) == 0 && (p.rows.map.P % 8) == 0 && aligned_to(x, 4) && aligned_to(dy, 4)) {
         // bf16 short rows of even length (they start on a dword): the virtual row of a channel on the bf16 matrix instruction,
         // raw rows straight into LDS (B4096 C128 L200 K48: 247 -> 88 us against the widening kernel below)
@@ -120,7 +139,7 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
         hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                            static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
                            static_cast<bf16_t *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, 0, s.K, 0, 0,
-                           p.rows.map);
+                           p.rows.map, 0);
     } else if (p.rows.on) {
         // bf16 short rows (longer than 64 positions): the virtual row of a channel, widened to fp32 through registers
         auto kernel = dwconv::dw_partial_mfma_kernel<T, ND, W, true>;
@@ -139,7 +158,7 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
         hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                            static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
                            static_cast<bf16_t *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, 0, s.K, 0, 0,
-                           dwconv::RowsMap{0, 0, 0, 0, 0u, 0u});
+                           dwconv::RowsMap{0, 0, 0, 0, 0u, 0u}, 0);
     } else {
         auto kernel = dwconv::dw_partial_mfma_kernel<T, ND, W, false>;
         constexpr size_t lds = dwconv::dw_mfma_lds_bytes(ND, W);
@@ -195,7 +214,9 @@ int launch_dw_partial_mfma(const void *x, const void *dy, float *part, void *dw_
     const bool rows_direct_bf16 = sizeof(T) == 2 && p.rows.on && (s.L % 2) == 0 && (p.rows.map.P % 8) == 0;
     const bool rows_direct_f32 = sizeof(T) == 4 && p.rows.on && nd <= kMfmaMaxND;
     const bool rows_direct = (rows_direct_bf16 || rows_direct_f32) && aligned_to(x, 4) && aligned_to(dy, 4);
-    if (!granular && !rows_direct && (!ragged_rows_ok(s, nd) || p.rows.on || !aligned_to(x, 4) || !aligned_to(dy, 4))) return -1;
+    if (bf16_odd_rows(s, x, dy)) {
+        if (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, x, dy, p.rows)) return -1;
+    } else if (!granular && !rows_direct && (!ragged_rows_ok(s, nd) || p.rows.on || !aligned_to(x, 4) || !aligned_to(dy, 4))) return -1;
     if constexpr (std::is_same<T, float>::value) {
         if (nd > kMfmaMaxND) return launch_dw_partial_wide_f32(x, dy, part, dw_out, s, p, dmin, nd, st);
     } else {

@@ -68,6 +68,7 @@ struct CorrGeom {
     int n_main;
     int n_light;
     int step_c_light;   // n_light % C
+    int par0 = 0;       // bf16 rows that do not start on a dword: 1 when the tensors themselves do not
 };
 
 // Row access through buffer instructions.  A buffer resource describes (the tail of) ONE row
@@ -163,6 +164,79 @@ __device__ __forceinline__ void zero_slot_tail(const short *slot, int live)
         if (live <= 2) p[1] = 0u;
         if (live <= 4) p[2] = 0u;
         p[3] = 0u;
+    }
+}
+// bf16 rows that do not start on a dword (odd lengths: every other row; tensors that are only 2-byte aligned: all of
+// them).  Loads into LDS move whole dwords, so such a row is taken from the dword in which it starts: shifted by
+// s = 1 element, its positions are s .. s + L - 1 and position 0 belongs to the row before it in memory; a row whose end
+// s + L is odd brings one element of the row behind it.  Both are cleared in LDS once they have landed, and only
+// the row's own outputs of the first and last group of four are stored.  The operator does not change: inputs and outputs
+// shift alike (they have to start on the same half of a dword).  The dword in which the first or last row of a tensor
+// starts or ends may hold two bytes next to the tensor; they are never written.
+// First position of row b of a channel whose first row starts at position sc (RowsMap::CL odd: the rows alternate).
+__device__ __forceinline__ int rows_odd_start(const RowsMap &m, int b, int sc) { return ((b & m.CL) ^ sc) & 1; }
+// rows_granule8_byte_offset for such rows, relative to the dword in which the channel's first row starts; live: elements up
+// to the end of the row (1 .. 8), + 16 when the first element is not the row's.
+__device__ __forceinline__ int rows_granule8_odd_byte_offset(const RowsMap &m, int u, int sc, int &live)
+{
+    const int b = (int)__umulhi((unsigned)u, m.M);
+    const int t = u - b * m.P;
+    const int s = rows_odd_start(m, b, sc);
+    const bool in = (unsigned)u < (unsigned)m.Lv && t < s + m.L;
+    const int left = s + m.L - t;
+    live = ((in && left < 8) ? left : 8) + ((in && t < s) ? 16 : 0);
+    return in ? 2 * (b * m.CL + t - s + sc) : kOutOfRow;
+}
+__device__ __forceinline__ void zero_slot_odd(const short *slot, int live)
+{
+    if (live != 8) {
+        short *p = const_cast<short *>(slot);
+        const int n = live & 15;
+        if (live & 16) p[0] = 0;
+#pragma unroll
+        for (int i = 1; i < 8; ++i)
+            if (i >= n) p[i] = 0;
+    }
+}
+// ... for two positions u, u + 1 (u even); dead: 1 when the first is not the row's, + 2 when the second is not
+__device__ __forceinline__ int rows_pair_odd_byte_offset(const RowsMap &m, int u, int sc, int &dead)
+{
+    const int b = (int)__umulhi((unsigned)u, m.M);
+    const int t = u - b * m.P;
+    const int s = rows_odd_start(m, b, sc);
+    const bool in = (unsigned)u < (unsigned)m.Lv && t < s + m.L;
+    dead = ((in && t < s) ? 1 : 0) + ((in && t + 1 >= s + m.L) ? 2 : 0);
+    return in ? 2 * (b * m.CL + t - s + sc) : kOutOfRow;
+}
+__device__ __forceinline__ void zero_pair_odd(const short *slot, int dead)
+{
+    short *p = const_cast<short *>(slot);
+    if (dead & 1) p[0] = 0;
+    if (dead & 2) p[1] = 0;
+}
+// Four outputs at virtual positions u .. u + 3 (u a multiple of 4): element offset of the first (from the dword in which the
+// channel's first row starts; -1: none is stored), and the outputs [first, n) that belong to the row.
+__device__ __forceinline__ int rows_element_group_odd(const RowsMap &m, int u, int sc, int &first, int &n)
+{
+    const int b = (int)__umulhi((unsigned)u, m.M);
+    const int t = u - b * m.P;
+    const int s = rows_odd_start(m, b, sc);
+    const bool in = (unsigned)u < (unsigned)m.Lv && t < s + m.L;
+    const int left = s + m.L - t;
+    n = left < 4 ? left : 4;
+    first = t < s ? 1 : 0;
+    return in ? b * m.CL + t - s + sc : -1;
+}
+template <typename T>
+__device__ __forceinline__ void st_group_range(T *p, float4 v, int first, int n)
+{
+    if (first == 0 && n >= 4) {
+        st_elem4_stream(p, v);
+    } else {
+        if (first <= 0 && n > 0) st_elem(p, v.x);
+        if (first <= 1 && n > 1) st_elem(p + 1, v.y);
+        if (first <= 2 && n > 2) st_elem(p + 2, v.z);
+        if (first <= 3 && n > 3) st_elem(p + 3, v.w);
     }
 }
 // The same for fp32 rows of any length (pitch a multiple of 4): a 16-byte granule of four floats that starts at virtual

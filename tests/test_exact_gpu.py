@@ -164,6 +164,34 @@ def test_exact_on_partly_aligned_views(oracle_mod, B, C, L, K, p, dtype, offset)
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=5, offset=offset)
 
 
+# bf16 rows that do not all start on a dword: lengths around a segment and around a granule of eight, both starting halves,
+# filters of two to six block offsets and the one-tap filter (no gap between the rows of a virtual row)
+@pytest.mark.parametrize("offset", [0, 1, 3])
+@pytest.mark.parametrize("B,C,L,K,p", [
+    (3, 5, 1023, 64, 63), (2, 3, 1025, 66, 0), (5, 2, 2047, 7, 3), (2, 7, 3073, 48, 24), (3, 3, 1535, 31, 30), (2, 4, 2048, 33, 16),
+    (40, 3, 55, 55, 54), (33, 4, 9, 9, 4), (70, 5, 63, 16, 15), (21, 3, 121, 64, 32), (17, 2, 127, 66, 65), (30, 3, 200, 1, 0),
+    (50, 4, 1, 3, 1), (12, 3, 767, 48, 0), (9, 256, 129, 20, 19), (7, 3, 1279, 2, 1),
+])
+def test_exact_bf16_rows_off_a_dword(oracle_mod, B, C, L, K, p, offset):
+    print(f"case exact bf16 off a dword B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, "bf16", seed=11 + B + 3 * C + 5 * L, offset=offset)
+
+
+# ... and tensors of one call on different halves of a dword
+def test_exact_bf16_tensors_on_different_halves(oracle_mod):
+    B, C, L, K, p = 3, 5, 1027, 40, 11
+    tdt = torch.bfloat16
+    x, w, dy = small_ints((B, C, L), 1, LIM, tdt), small_ints((C, K), 2, LIM, tdt), small_ints((B, C, L), 3, LIM, tdt)
+    xn, wn, dyn = as_f32_numpy(x), as_f32_numpy(w), as_f32_numpy(dy)
+    y = binding.dwconv_fwd(to_device(x, 1), to_device(w), p, out=empty_device((B, C, L), tdt))
+    dx = binding.dwconv_bwd_input(to_device(dy), to_device(w), p, out=empty_device((B, C, L), tdt, 1))
+    dw = binding.dwconv_bwd_weight(to_device(x, 1), to_device(dy), K, p)
+    torch.cuda.synchronize()
+    _same("fwd", y, oracle_mod.fwd(xn, wn, p)[0], tdt, "halves")
+    _same("dx", dx, oracle_mod.bwd_input(dyn, wn, p)[0], tdt, "halves")
+    _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "halves")
+
+
 def _random_exact_shapes(n, seed):
     """Seeded shapes around every threshold of the dispatch (block-offset counts, row-length classes, channel counts
     that change the weight-gradient plan), each with a storage type and an element offset of the views."""
