@@ -231,8 +231,8 @@ __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void co
 // "segment" the channel (walk_segs = segs_per_row = C), every lane translates the position of its granule on the memory
 // side of the loads, and the outputs of a group of four go to their row or nowhere.
 // ODD: rows that do not all start on a dword (odd lengths, tensors that are only 2-byte aligned), shifted to the dword in
-// which they start (rows_odd_start and what follows it); both forms of row.  What it costs over rows of even length is
-// the clearing of the foreign elements and the group stores that straddle cache lines: B32 C256 L4097 K64 see the launcher.
+// which they start (rows_odd_start and what follows it); both forms of row.  What it costs over whole rows is the
+// clearing of the foreign elements and the stores that straddle cache lines: B32 C256 K64 30 us at L = 4097, 22.7 at 4096.
 template <int ND, bool ROWS = false, bool ODD = false>
 __global__ __launch_bounds__(64 * kCorrWavesPerBlock, kMfmaWavesPerSimd) void corr_direct_bf16_kernel(
     const bf16_t *__restrict__ in, const bf16_t *__restrict__ f, bf16_t *__restrict__ out, const CorrGeom g,
