@@ -1,0 +1,536 @@
+// Forward / input gradient (Sec. IV-A eq. (dwconv) and its adjoint) for filters of more than six 16-blocks, up to any
+// length, on rows of any length and alignment: the blocked-Toeplitz contraction on v_mfma_f32_32x32x16_bf16, the bf16
+// instruction in either storage type.
+//
+//   Y[t + r][col] = sum_e sum_k Toep_e[r][k] X[t + 16 e + k][col],    Toep_e[r][k] = w[16 e + k - r + pad]
+//
+// A tile is 32 output positions (r) x 32 columns; a column is one 32-position block of one row, and the columns of a
+// tile are NB consecutive blocks of 32 / NB batch entries of a channel.  Its operands: A (lane r, half kg) eight
+// consecutive taps, B (lane col, half kg) eight consecutive positions.
+//
+// fp32 storage on the bf16 instruction: every operand is the exact sum of three bf16 limbs (24 = 8 + 8 + 8 significant bits,
+// rounded to nearest, so a limb is at most 2^-9 of the one before it); products of limbs are exact in fp32, sums fp32.
+// Six of the nine limb products are kept; the three left out are below 2^-25 of the product, half an fp32 rounding.
+// The instruction does sixteen times the fp32 one's products a cycle, so six of them are 2.7 times cheaper (an fp32
+// matrix kernel is bound by the matrix pipe from about seven block offsets on).
+//
+// A workgroup (four waves) works on items of RW rows x PB blocks of a channel and walks the filter in chunks of F taps.  Per
+// chunk the taps and the input window the chunk reaches (zeros outside the row) are staged as limbs, the window through
+// registers that are loaded while the stage before it is multiplied; blocks of 32 positions are 80 bytes apart, so the
+// 16-byte operand reads of eight neighbouring lanes fall on different banks (measured 220 bytes a cycle and compute
+// unit; 63 at the natural 64 bytes).  The waves split the tiles TG ways and the e of a chunk KS = 4 / TG ways, so
+// a wave has up to T tiles per A operand: 3 + 3 T reads for 6 T instructions.  Rounds through LDS add the KS parts in a fixed
+// order and turn the tiles into whole rows for the stores.
+#pragma once
+#include "dwconv_common.hip.h"
+#include "dwconv_mfma.hip.h"
+#include "dwconv_dw_direct.hip.h"
+
+namespace dwconv {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Two fp32 values -> one dword of two bf16, rounded to nearest even.
+__device__ __forceinline__ unsigned pack_bf16(float x, float y)
+{
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{x, y}), bf16x2));
+}
+// The next limbs of a pair: what is left of it afterwards goes back to x, y.  CLAMP (first limb): the rounding must not
+// turn a finite value into infinity; the excess of a value beyond the largest bf16 (infinity and NaN among them) stays
+// in the second limb.
+template <bool CLAMP>
+__device__ __forceinline__ unsigned take_limb(float &x, float &y)
+{
+    constexpr float kMaxBf16 = 0x1.fep127f;
+    const unsigned p = CLAMP ? pack_bf16(__builtin_amdgcn_fmed3f(x, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(y, -kMaxBf16, kMaxBf16))
+                             : pack_bf16(x, y);
+    x -= __uint_as_float(p << 16);
+    y -= __uint_as_float(p & 0xffff0000u);
+    return p;
+}
+template <int NL>
+__device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[NL])
+{
+    p[0] = take_limb<true>(x, y);
+    if constexpr (NL > 1) {
+        p[1] = take_limb<false>(x, y);
+        p[2] = pack_bf16(x, y);
+    }
+}
+
+// Limbs per element: fp32 three, bf16 itself.
+template <typename T> struct Limbs;
+template <> struct Limbs<float> { static constexpr int N = 3; };
+template <> struct Limbs<bf16_t> { static constexpr int N = 1; };
+
+// Eight consecutive elements at any element-aligned address, as loaded (uintx4 pairs or one).
+struct __attribute__((packed, aligned(4))) Raw8F { unsigned v[8]; };
+struct __attribute__((packed, aligned(2))) Raw8H { unsigned v[4]; };
+__device__ __forceinline__ Raw8F load_raw8(const float *p) { return *reinterpret_cast<const Raw8F *>(p); }
+__device__ __forceinline__ Raw8H load_raw8(const bf16_t *p) { return *reinterpret_cast<const Raw8H *>(p); }
+__device__ __forceinline__ void zero_raw8(Raw8F &r, bool zero)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r.v[i] = zero ? 0u : r.v[i];
+}
+__device__ __forceinline__ void zero_raw8(Raw8H &r, bool zero)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = zero ? 0u : r.v[i];
+}
+// The granule moved down by sh elements (0 .. 7), zeros behind it: what a granule that ends behind its row becomes when the
+// last eight elements of the row were loaded in its place.
+__device__ __forceinline__ void shift_raw8(Raw8F &r, int sh)
+{
+#pragma unroll
+    for (int step = 4; step > 0; step >>= 1) {
+        const bool on = (sh & step) != 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r.v[i] = on ? (i + step < 8 ? r.v[i + step] : 0u) : r.v[i];
+    }
+}
+__device__ __forceinline__ void shift_raw8(Raw8H &r, int sh)
+{
+#pragma unroll
+    for (int step = 2; step > 0; step >>= 1) {
+        const bool on = (sh & (2 * step)) != 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.v[i] = on ? (i + step < 4 ? r.v[i + step] : 0u) : r.v[i];
+    }
+    const int bits = 16 * (sh & 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = __builtin_amdgcn_alignbit(i < 3 ? r.v[i + 1] : 0u, r.v[i], bits);
+}
+__device__ __forceinline__ void raw8_limbs(const Raw8F &r, uintx4 (&out)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned p[3];
+        split_pair<3>(__uint_as_float(r.v[2 * i]), __uint_as_float(r.v[2 * i + 1]), p);
+        out[0][i] = p[0]; out[1][i] = p[1]; out[2][i] = p[2];
+    }
+}
+__device__ __forceinline__ void raw8_limbs(const Raw8H &r, uintx4 (&out)[1])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[0][i] = r.v[i];
+}
+// Two neighbouring taps as limbs (zeros outside the chunk are passed in).
+__device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[3]) { split_pair<3>(a, b, p); }
+__device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[1])
+{
+    p[0] = (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);      // (widened bf16: exact)
+}
+
+// Four consecutive outputs at any element-aligned address.
+typedef float floatx4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned uintx2_u __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ void st4_any(float *p, float4 v)
+{
+    floatx4_u t = {v.x, v.y, v.z, v.w};
+    *reinterpret_cast<floatx4_u *>(p) = t;
+}
+__device__ __forceinline__ void st4_any(bf16_t *p, float4 v)
+{
+    uintx2_u t = {pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
+    *reinterpret_cast<uintx2_u *>(p) = t;
+}
+
+// a staged 32-position block: 64 bytes per limb + 16 (an odd number of 16-byte units)
+__host__ __device__ constexpr int band_block_bytes(int NL) { return 64 * NL + 16; }
+constexpr int kBandWaves = 4;
+constexpr int kBandThreads = 64 * kBandWaves;
+constexpr int kBandTapMargin = 48;           // zero taps in front of a staged chunk (and as many behind it)
+constexpr int kBandRedPitch = 36;            // floats per column of the output image
+// what a thread prefetches: granules of eight positions (fp32 8 registers each, bf16 4), pairs of taps
+constexpr int band_prefetch(int NL) { return NL == 3 ? 5 : 10; }
+constexpr int kBandTapPrefetch = 4;
+
+struct BandGeom {
+    int B, C, L, K;
+    int pad;            // effective pad of this correlation
+    int reverse;        // filter index reversed (input gradient)
+    int nb_log;         // log2 of the blocks of a row that are columns of a tile
+    int RW;             // rows per item = 32 >> nb_log
+    int PB;             // 32-position blocks of a row per item (a whole number of tiles)
+    int NP;             // pieces per row
+    unsigned np_magic;  // floor(2^32 / NP) + 1: item / NP == umulhi(item, np_magic) for NP > 1
+    int items;          // row groups x pieces of a channel
+    int F;              // taps per chunk
+    int pitch;          // bytes of one staged row
+    int TG;             // tile groups; the e of a chunk are split W / TG ways
+};
+// dwords of one of the two copies of a chunk's taps (copies 16 banks apart: the even and the odd lanes of a read)
+__host__ __device__ inline int band_tap_dwords(int F) { return ((F + 2 * kBandTapMargin) / 2 + 1 + 31) / 32 * 32 + 16; }
+// the taps lie behind the window and behind the output image, which shares the window's place
+__host__ __device__ inline unsigned band_tap_offset(int RW, int pitch)
+{
+    const unsigned stage = (unsigned)(RW * pitch), red = (unsigned)(kBandWaves * 32 * kBandRedPitch * 4);
+    return stage > red ? stage : red;
+}
+inline size_t band_lds_bytes(int NL, int RW, int pitch, int F)
+{
+    return band_tap_offset(RW, pitch) + (size_t)NL * 8 * band_tap_dwords(F);
+}
+
+// A lane's number, hidden from the compiler at each use: it would keep every address that follows from it in a register
+// for the whole kernel.
+__device__ __forceinline__ int band_hide(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+// waves per SIMD the kernel is compiled for
+constexpr int band_waves(int NL, int T) { return NL == 1 && T == 1 ? 4 : 3; }
+
+template <typename E, int T>
+__global__ __launch_bounds__(kBandThreads, band_waves(Limbs<E>::N, T)) void corr_band_kernel(
+    const E *__restrict__ in, const E *__restrict__ f, E *__restrict__ out, const BandGeom g)
+{
+    constexpr int NL = Limbs<E>::N;
+    constexpr int NPF = band_prefetch(NL);
+    constexpr int W = kBandWaves, THREADS = kBandThreads;
+    static_assert(T == 1 || T == 2 || (T == 4 && NL == 1), "register budget");
+    extern __shared__ __align__(16) unsigned char band_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NBk = 1 << g.nb_log;
+    const int c = blockIdx.x;
+    const int tg = wave % g.TG, ks = wave / g.TG, KS = W / g.TG;
+    const int NCH = (g.L + 15) >> 4, NB32 = (g.L + 31) >> 5;
+    constexpr int BS = band_block_bytes(NL);
+    const int TP = band_tap_dwords(g.F);
+    unsigned char *xs = band_smem;
+    unsigned *fs = reinterpret_cast<unsigned *>(band_smem + band_tap_offset(g.RW, g.pitch));   // limb l, copy p at (2 l + p) TP
+    const E *f_c = f + (size_t)c * (size_t)g.K;
+    const E *in_c = in + (size_t)c * (size_t)g.L;
+    const size_t CL = (size_t)g.C * (size_t)g.L;
+
+    // One stage of the walk: an item (RW rows x PB blocks; items y, 2 gy - 1 - y, 2 gy + y, ...: pieces of a causal filter
+    // cost what they lie from the start of the row, and this order evens them out) and a chunk of taps.
+    struct Stage {
+        int round, item, j0;            // item < 0: the walk has ended
+        int b0, p0;                     // first row, first block of the item
+        int e_lo, e_hi;                 // the e that hold a tap of the chunk and meet the row from some block of the piece
+        int wb0, n8;                    // first window block any tile of the piece reads, granules of eight positions per row
+        int inside;                     // every row of the item is in the batch and all of the window inside the rows
+    };
+    auto set_item = [&](Stage &s) {
+        const int gy = (int)gridDim.y, y = (int)blockIdx.y;
+        s.item = s.round * gy + ((s.round & 1) ? gy - 1 - y : y);
+        if (s.item >= g.items) { s.item = -1; return; }      // (only the last round is short)
+        const int rg = g.NP > 1 ? (int)__umulhi((unsigned)s.item, g.np_magic) : s.item;
+        s.b0 = rg * g.RW;
+        s.p0 = (s.item - rg * g.NP) * g.PB;
+    };
+    auto advance = [&](Stage &s, bool first) {
+        for (;;) {
+            if (first) {
+                first = false;
+            } else {
+                s.j0 += g.F;
+                if (s.j0 >= g.K) { s.j0 = 0; ++s.round; set_item(s); }
+            }
+            if (s.item < 0) return;
+            // (arithmetic shifts: floor division)
+            s.e_lo = max((s.j0 - g.pad) >> 4, -2 * (s.p0 + g.PB - 1));
+            s.e_hi = min((min(s.j0 + g.F, g.K) + 30 - g.pad) >> 4, NCH - 1 - 2 * s.p0);
+            if (s.e_lo > s.e_hi) continue;
+            s.wb0 = max(s.p0 + (s.e_lo >> 1), -(NBk - 1));
+            s.n8 = 4 * (min(s.p0 + g.PB - 1 + (s.e_hi >> 1), NB32 + NBk - 2) - s.wb0 + 1);
+            s.inside = s.wb0 >= 0 && 32 * s.wb0 + 8 * s.n8 <= g.L && s.b0 + g.RW <= g.B;
+            return;
+        }
+    };
+    // The window of a stage travels through registers: its loads are issued before the stage in front of it is multiplied.
+    // THREADS / RW neighbouring threads bring one row.
+    const int tpr_log = 3 + g.nb_log;                     // log2(THREADS / RW)
+    const int TPR = 1 << tpr_log;
+    decltype(load_raw8(in)) pre[NPF];
+    auto prefetch = [&](const Stage &s) {
+        const int tl = band_hide(tid), ld_row = tl >> tpr_log, ld_g = tl & (TPR - 1);
+        if (s.inside) {
+            const E *p = in_c + (size_t)(s.b0 + ld_row) * CL + (32 * s.wb0 + 8 * ld_g);
+            const E *last = p + 8 * (s.n8 - 1 - ld_g);                   // (granules past the window: its last one again)
+#pragma unroll
+            for (int i = 0; i < NPF; ++i)
+                if (i * TPR < s.n8) pre[i] = load_raw8(ld_g + i * TPR < s.n8 ? p + 8 * i * TPR : last);
+        } else {
+            // (rows past the batch, positions outside the row: loaded from inside, zeroed later)
+            const E *row = in_c + (size_t)min(s.b0 + ld_row, g.B - 1) * CL;
+            const int u0 = 32 * s.wb0 + 8 * ld_g;
+#pragma unroll
+            for (int i = 0; i < NPF; ++i)
+                if (i * TPR < s.n8) pre[i] = load_raw8(row + max(0, min(u0 + 8 * i * TPR, g.L - 8)));
+        }
+    };
+    // The taps of a chunk likewise, where there is more than one chunk.  Dword m of copy p: taps 2 m + p, 2 m + p + 1.
+    constexpr int NTF = kBandTapPrefetch;
+    E tap[NTF][3];
+    auto tap_triple = [&](int j0, int Fc, int m, E (&t3)[3]) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int jj = min(max(2 * m + i - kBandTapMargin, 0), Fc - 1);
+            t3[i] = f_c[g.reverse ? g.K - 1 - (j0 + jj) : j0 + jj];
+        }
+    };
+    auto store_triple = [&](int Fc, int m, const E (&t3)[3]) {
+        const int jj = 2 * m - kBandTapMargin;
+        float v[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = (jj + i >= 0 && jj + i < Fc) ? ld_elem(&t3[i]) : 0.f;
+        unsigned p[NL], q[NL];
+        pair_limbs(v[0], v[1], p);
+        pair_limbs(v[1], v[2], q);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            fs[2 * l * TP + m] = p[l];
+            fs[(2 * l + 1) * TP + m] = q[l];
+        }
+    };
+    const bool one_chunk = g.K <= g.F;
+    auto prefetch_taps = [&](const Stage &s) {
+        const int Fc = min(g.F, g.K - s.j0), tl = band_hide(tid);
+#pragma unroll
+        for (int i = 0; i < NTF; ++i)
+            if (THREADS * i < TP) tap_triple(s.j0, Fc, tl + THREADS * i, tap[i]);
+    };
+
+    floatx16 acc[T], low[NL == 3 ? T : 1];
+    Stage cur;
+    cur.round = 0; cur.j0 = 0;
+    set_item(cur);
+    if (cur.item < 0) return;
+    advance(cur, true);
+    prefetch(cur);
+    if (one_chunk) {
+        for (int m = tid; m < TP; m += THREADS) {
+            E t3[3];
+            tap_triple(0, g.K, m, t3);
+            store_triple(g.K, m, t3);
+        }
+    } else {
+        prefetch_taps(cur);
+    }
+    bool fresh = true;                                                   // first chunk of its item
+    while (cur.item >= 0) {
+        if (fresh) {
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    acc[t][i] = 0.f;
+                    if constexpr (NL == 3) low[t][i] = 0.f;
+                }
+        }
+        __syncthreads();                                                 // everyone is done with what LDS holds
+        if (!one_chunk) {
+            const int Fc = min(g.F, g.K - cur.j0), tl = band_hide(tid);
+#pragma unroll
+            for (int i = 0; i < NTF; ++i)
+                if (tl + THREADS * i < TP) store_triple(Fc, tl + THREADS * i, tap[i]);
+        }
+        {
+            const int tl = band_hide(tid), ld_row = tl >> tpr_log, ld_g = tl & (TPR - 1);
+            unsigned char *dst = xs + ld_row * g.pitch + (ld_g >> 2) * BS + (ld_g & 3) * 16;
+            const int dstep = (TPR >> 2) * BS;
+            if (!cur.inside) {
+                const int u0 = 32 * cur.wb0 + 8 * ld_g;
+                const bool no_row = cur.b0 + ld_row >= g.B;
+#pragma unroll
+                for (int i = 0; i < NPF; ++i) {
+                    const int u = u0 + 8 * i * TPR;
+                    if (i * TPR < cur.n8) {
+                        if (u + 8 > g.L) shift_raw8(pre[i], (u + 8 - g.L) & 7);
+                        zero_raw8(pre[i], no_row || u < 0 || u >= g.L);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NPF; ++i) {
+                if (ld_g + i * TPR < cur.n8) {
+                    uintx4 limbs[NL];
+                    raw8_limbs(pre[i], limbs);
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) *reinterpret_cast<uintx4 *>(dst + i * dstep + 64 * l) = limbs[l];
+                }
+            }
+        }
+        __syncthreads();
+        Stage nxt = cur;
+        advance(nxt, false);
+        if (nxt.item >= 0) {
+            prefetch(nxt);
+            if (!one_chunk) prefetch_taps(nxt);
+        }
+
+        const int ln_m = band_hide(lane), col = ln_m & 31, kg = ln_m >> 5;
+        // A: taps 16 e + 8 kg + v - r + pad, r = col: four dwords of the copy in which the first starts one.  B: the lane's column of tile t, block (m0 + blk + e / 2), half e % 2.
+        const int a0 = 8 * kg - col + g.pad - cur.j0 + kBandTapMargin;
+        const unsigned *a_base = fs + (a0 & 1) * TP + (a0 >> 1);
+        const unsigned char *b_base = xs + (col >> g.nb_log) * g.pitch + 16 * kg + ((col & (NBk - 1)) + cur.p0 - cur.wb0) * BS;
+        int rel[T], lo[T], hi[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            rel[t] = (tg + g.TG * t) << g.nb_log;
+            const int m0 = cur.p0 + rel[t];                              // first block of the tile
+            const bool any = m0 < NB32 && rel[t] < g.PB;                 // (otherwise a spare tile)
+            lo[t] = max(cur.e_lo, -2 * (m0 + NBk - 1));
+            hi[t] = any ? min(cur.e_hi, NCH - 1 - 2 * m0) : -(1 << 28);
+        }
+        // e = ea .. eb (those of this wave: cur.e_lo + ks modulo KS) for the tiles T0 .. T0 + N - 1.  The operands of the next
+        // tile are read while this one's are multiplied.
+        auto run = [&](auto t0c, auto nc, int ea, int eb) {
+            constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
+            ea += (cur.e_lo + ks - ea) & (KS - 1);
+            if (ea > eb) return;
+            const unsigned *ap = a_base + 8 * ea;
+            const unsigned char *bp[N];
+#pragma unroll
+            for (int t = 0; t < N; ++t) bp[t] = b_base + ((rel[T0 + t] + (ea >> 1)) * BS + (ea & 1) * 32);
+            uintx4 a[2][NL], b[2][NL];
+            auto read_a = [&](uintx4 (&to)[NL]) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) to[l][i] = ap[2 * l * TP + i];
+            };
+            auto read_b = [&](uintx4 (&to)[NL], int t) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(bp[t] + 64 * l);
+            };
+            auto step = [&](int e, bool more) {                          // (past the last e: the same addresses again)
+                ap += more ? 8 * KS : 0;
+                const int by = (KS & 1) ? ((e & 1) ? BS - 32 : 32) : (KS >> 1) * BS;
+#pragma unroll
+                for (int t = 0; t < N; ++t) bp[t] += more ? by : 0;
+            };
+            auto multiply = [&](int t, const uintx4 (&a)[NL], const uintx4 (&bb)[NL]) {
+                if constexpr (NL == 3) {
+                    // (the small products in an accumulator of their own: what rounds at the size of the sum is one
+                    // addition per e, not six)
+                    low[t] = mfma32x32x16(a[2], bb[0], low[t]);
+                    acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
+                    low[t] = mfma32x32x16(a[0], bb[2], low[t]);
+                    low[t] = mfma32x32x16(a[1], bb[1], low[t]);
+                    low[t] = mfma32x32x16(a[1], bb[0], low[t]);
+                    low[t] = mfma32x32x16(a[0], bb[1], low[t]);
+                } else {
+                    acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
+                }
+            };
+            read_a(a[0]);
+            read_b(b[0], 0);
+#pragma unroll 1
+            for (int e = ea; e <= eb;) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {                            // (two e per trip: two register sets)
+                    if (u == 0 || e <= eb) {
+                        const bool more = e + KS <= eb;
+#pragma unroll
+                        for (int t = 0; t < N; ++t) {
+                            const int k = u * N + t;
+                            if (t + 1 < N) {
+                                read_b(b[(k + 1) & 1], t + 1);
+                            } else {
+                                step(e, more);
+                                read_a(a[1 - u]);
+                                read_b(b[(k + 1) & 1], 0);
+                            }
+                            multiply(T0 + t, a[u], b[k & 1]);
+                        }
+                        e += KS;
+                    }
+                }
+            }
+        };
+        // The tiles lie in increasing order along the row, so lo and hi fall with t: those active at an e are the tiles a .. b
+        // with e in [lo[a], lo[a - 1]) and (hi[b + 1], hi[b]].
+        static_for<0, T>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            static_for<a, T>([&](auto bc) {
+                constexpr int b = decltype(bc)::value;
+                int ea = lo[a], eb = hi[b];
+                if constexpr (a > 0) eb = min(eb, lo[a - 1] - 1);
+                if constexpr (b + 1 < T) ea = max(ea, hi[b + 1] + 1);
+                run(ac, std::integral_constant<int, b - a + 1>{}, ea, eb);
+            });
+        });
+        fresh = nxt.item != cur.item;
+        if (fresh) {
+            // ---- tile t of every wave goes through LDS so that whole runs of a row are stored; where the e were split, the
+            // parts are added there in order.  A thread owns four positions of one column; a tile is 256 of them.
+            float *red = reinterpret_cast<float *>(band_smem);
+            const int ln = band_hide(lane);
+            const int col = ln & 31, kg = ln >> 5;
+            // lane (column, half kg) holds outputs 8 q + 4 kg + 0..3 in elements 4 q .. 4 q + 3
+            float *wr = red + wave * 32 * kBandRedPitch + col * kBandRedPitch + 4 * kg;
+            // A thread stores four positions of one column; the columns of eight neighbouring threads' groups, eight apart,
+            // lie a uniform distance apart (col8 of them: (8 col8 / NB) rows and (8 col8 % NB) blocks).
+            const int o_col = ln >> 3, o_pos = 4 * (ln & 7);
+            const int o_b = cur.b0 + (o_col >> g.nb_log), o_t = 32 * (cur.p0 + (o_col & (NBk - 1))) + o_pos;
+            E *o_base = out + (size_t)o_b * CL + (size_t)c * (size_t)g.L + o_t;
+            const bool whole = cur.b0 + g.RW <= g.B && 32 * (cur.p0 + g.PB) <= g.L;
+            auto store4 = [&](int tile, int col8, floatx4 v) {
+                const int db = (8 * col8) >> g.nb_log, dt = 32 * ((tile << g.nb_log) + ((8 * col8) & (NBk - 1)));
+                E *o = o_base + ((size_t)db * CL + (size_t)dt);
+                if (whole) {
+                    st4_any(o, make_float4(v[0], v[1], v[2], v[3]));
+                } else {
+                    const int pos = o_t + dt;
+                    if (o_b + db < g.B && pos < g.L) {                                 // (not a spare tile, column or position)
+                        if (pos + 3 < g.L) {
+                            st4_any(o, make_float4(v[0], v[1], v[2], v[3]));
+                        } else {
+                            st_elem(o, v[0]);
+                            if (pos + 1 < g.L) st_elem(o + 1, v[1]);
+                            if (pos + 2 < g.L) st_elem(o + 2, v[2]);
+                        }
+                    }
+                }
+            };
+            const float *r_base = red + o_col * kBandRedPitch + o_pos;
+            __syncthreads();                                             // everyone is done with the window
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if (t > 0 && KS > 1) __syncthreads();
+                if constexpr (NL == 3) acc[t] += low[t];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<floatx4 *>(wr + 8 * q) = floatx4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+                if (KS == 1) {
+                    // the wave's own tile
+                    wave_lds_fence();
+                    const int tile = tg + g.TG * t;
+                    if (cur.p0 + (tile << g.nb_log) < NB32 && (tile << g.nb_log) < g.PB) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            store4(tile, q, *reinterpret_cast<const floatx4 *>(r_base + (32 * wave + 8 * q) * kBandRedPitch));
+                    }
+                    wave_lds_fence();
+                } else {
+                    __syncthreads();
+                    // wave w stores columns 8 w .. 8 w + 7 of every tile
+                    for (int gq = 0; gq < g.TG; ++gq) {
+                        const float *r = r_base + (32 * gq + 8 * wave) * kBandRedPitch;
+                        floatx4 v = *reinterpret_cast<const floatx4 *>(r);
+                        for (int k = 1; k < KS; ++k) v += *reinterpret_cast<const floatx4 *>(r + k * g.TG * 32 * kBandRedPitch);
+                        const int tile = gq + g.TG * t;
+                        if (cur.p0 + (tile << g.nb_log) < NB32 && (tile << g.nb_log) < g.PB) store4(tile, wave, v);
+                    }
+                }
+            }
+        }
+        cur = nxt;
+    }
+}
+
+}  // namespace dwconv

@@ -71,10 +71,8 @@ constexpr int kMfmaMaxNDDw = 16;       // fp32 on long rows, K up to 226: four-w
 constexpr int kMfmaMaxNDDw2 = 32;      // dW in two passes over the block offsets (K up to 482), each into its own slices
 constexpr int kMfmaMaxNDDw3 = 48;      // fp32 dW in up to three passes (K up to 738)
 constexpr int kMfmaMaxNDDw4 = 64;      // bf16 dW in up to four passes (K up to 994): a pass is bound by memory there
-inline int mfma_max_nd(int /* either storage type */) { return kMfmaMaxNDDw; }                      // fwd, dX
-// fewest block offsets the long-filter forward / input-gradient kernel takes (from there to sixteen: whichever of
-// the two kernels wastes less on the row length)
-inline int longk_corr_min_nd(int dtype) { return (dtype == DWCONV_F32 ? kMfmaMaxNDWide : kMfmaMaxND) + 1; }
+// forward, input gradient on ordinary rows with the Toeplitz operands in registers (more: corr_band_kernel)
+inline int mfma_max_nd(int dtype) { return dtype == DWCONV_F32 ? 12 : 10; }
 // dW stage 1 (bf16 above six offsets: rows of whole 16-byte granules only)
 inline int mfma_max_nd_dw(const Shape &s)
 {
@@ -258,8 +256,8 @@ DwPlan plan_dw(const Shape &s);
 
 // Launch entry points of the per-path units.  A return value of -1 (fused backward only) means "does not apply".
 // Rows of 132 to 512 positions with long filters (RowsPlan::tall; units of their own: dwconv_launch_rowtall_*.hip).
-int launch_corr_rowtall_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
-int launch_corr_rowtall_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
+int launch_corr_band_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
+int launch_corr_band_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_dw_rowtall_f32(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p, hipStream_t st);
 int launch_dw_rowtall_bf16(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p, hipStream_t st);
 int launch_corr_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);

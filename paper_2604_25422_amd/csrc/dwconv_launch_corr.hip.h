@@ -73,6 +73,8 @@ int launch_corr_rowbatch_wide_t(dwconv::RowBatchGeom &rg, int nd, const void *in
 {
     auto go = [&](auto kernel) -> int { return launch_corr_rowbatch_kernel<T>(kernel, rg, 1, in, f, out, s, st); };
     if (rg.m <= 4) return nd == 7 ? go(dwconv::corr_rowbatch_kernel<T, 7, 1, 4, false>) : -1;
+    if constexpr (!std::is_same<T, float>::value) return -1;           // (bf16 rows of more than 64 positions: corr_band_kernel)
+    else
     switch (nd) {
     case 7: return go(dwconv::corr_rowbatch_kernel<T, 7, 1, 8, false>);
     case 8: return go(dwconv::corr_rowbatch_kernel<T, 8, 1, 8, false>);
@@ -170,10 +172,6 @@ int launch_corr_vrows_kernel(Kernel kernel, dwconv::CorrGeom g, const RowsPlan &
                        static_cast<const T *>(f), static_cast<T *>(out), g, rp.map);
     return launch_status();
 }
-// (fp32, seven to sixteen block offsets on virtual rows: a translation unit of its own, dwconv_launch_corr_rows_f32.hip)
-int launch_corr_vrows_wide_f32(const dwconv::CorrGeom &g, const RowsPlan &rp, int nd, const void *in, const void *f, void *out,
-                               const Shape &s, hipStream_t st);
-
 // Returns -1 when the shape or the pointers do not fit the matrix-core kernel.
 template <typename T>
 int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
@@ -183,11 +181,7 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     const RowsPlan rp = plan_rows(s);
     // (the sixteen-row kernels of short rows move granules with buffer loads and stores that need dword alignment only)
     if (rp.batch) return (aligned_to(in, 4) && aligned_to(out, 4)) ? launch_corr_rowbatch<T>(in, f, out, s, pad_eff, reverse, rp, st) : -1;
-    if (rp.tall) {
-        if (!aligned_to(in, 4) || !aligned_to(out, 4)) return -1;
-        if constexpr (std::is_same<T, float>::value) return launch_corr_rowtall_f32(in, f, out, s, pad_eff, reverse, st);
-        else return launch_corr_rowtall_bf16(in, f, out, s, pad_eff, reverse, st);
-    }
+    if (rp.tall) return -1;
     if (s.K < kMfmaMinK || nd < 2 || nd > mfma_max_nd(s.dtype) || s.L > kMfmaMaxL) return -1;
     // whole granules of four elements; otherwise only the kernels that load rows straight into LDS apply (see ragged_rows_ok)
     const bool granular = (s.L % 4) == 0 && aligned_to(in, 4 * sizeof(T)) && aligned_to(out, 4 * sizeof(T));
@@ -201,12 +195,6 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     // here; L25 K7 320 against 309 us)
     if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24))) return -1;
     if (!odd && !granular && !rows_direct_bf16 && !rows_direct_f32 && (!ragged_rows_ok(s, nd) || !aligned_to(in, 4) || !aligned_to(out, 4))) return -1;
-    // block offsets the long-filter kernel takes too (fp32 eleven to sixteen, bf16 seven to sixteen): only where rows
-    // fill their 1024-position segments to three quarters (shorter rows do less work on the long-filter kernel,
-    // which contracts in-row block pairs only)
-    if (!rp.on && nd >= longk_corr_min_nd(s.dtype) &&
-        4ll * s.L < 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen))
-        return -1;
     const long long rows = (long long)s.B * s.C;
     const int L_walk = odd ? s.L + 1 : s.L;             // (a shifted row may reach one position further)
     const long long segs_per_row = (L_walk + dwconv::kSegLen - 1) / dwconv::kSegLen;
@@ -357,7 +345,6 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
             case 6: return launch_rows(dwconv::corr_mfma_kernel<T, 6, true>);
             default: break;
             }
-            if constexpr (std::is_same<T, float>::value) return launch_corr_vrows_wide_f32(g, rp, nd, in, f, out, s, st);
             return -1;
         }
     }
@@ -389,12 +376,6 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
             case 8: return launch(dwconv::corr_mfma_bf16_kernel<8>, pi, pf, po);
             case 9: return launch(dwconv::corr_mfma_bf16_kernel<9>, pi, pf, po);
             case 10: return launch(dwconv::corr_mfma_bf16_kernel<10>, pi, pf, po);
-            case 11: return launch(dwconv::corr_mfma_bf16_kernel<11>, pi, pf, po);
-            case 12: return launch(dwconv::corr_mfma_bf16_kernel<12>, pi, pf, po);
-            case 13: return launch(dwconv::corr_mfma_bf16_kernel<13>, pi, pf, po);
-            case 14: return launch(dwconv::corr_mfma_bf16_kernel<14>, pi, pf, po);
-            case 15: return launch(dwconv::corr_mfma_bf16_kernel<15>, pi, pf, po);
-            case 16: return launch(dwconv::corr_mfma_bf16_kernel<16>, pi, pf, po);
             default: return -1;
             }
         }
@@ -435,13 +416,7 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
             switch (nd) {
             case 7: return launch(dwconv::corr_mfma_kernel<float, 7, false, true>, pi, pf, po);
             case 8: return launch(dwconv::corr_mfma_kernel<float, 8, false, true>, pi, pf, po);
-            case 9: return launch(dwconv::corr_mfma_kernel<float, 9, false, true>, pi, pf, po);
-            case 10: return launch(dwconv::corr_mfma_kernel<float, 10, false, true>, pi, pf, po);
-            case 11: return launch(dwconv::corr_mfma_kernel<float, 11, false, true>, pi, pf, po);
-            case 12: return launch(dwconv::corr_mfma_kernel<float, 12, false, true>, pi, pf, po);
-            case 13: return launch(dwconv::corr_mfma_kernel<float, 13, false, true>, pi, pf, po);
-            case 14: return launch(dwconv::corr_mfma_kernel<float, 14, false, true>, pi, pf, po);
-            default: return -1;                // (fifteen and sixteen offsets: no registers left for the element stores)
+            default: return -1;
             }
         }
         switch (nd) {
@@ -451,91 +426,49 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
         case 10: return launch(dwconv::corr_mfma_kernel<float, 10, false>, pi, pf, po);
         case 11: return launch(dwconv::corr_mfma_kernel<float, 11, false>, pi, pf, po);
         case 12: return launch(dwconv::corr_mfma_kernel<float, 12, false>, pi, pf, po);
-        case 13: return launch(dwconv::corr_mfma_kernel<float, 13, false>, pi, pf, po);
-        case 14: return launch(dwconv::corr_mfma_kernel<float, 14, false>, pi, pf, po);
-        case 15: return launch(dwconv::corr_mfma_kernel<float, 15, false>, pi, pf, po);
-        case 16: return launch(dwconv::corr_mfma_kernel<float, 16, false>, pi, pf, po);
         default: break;
         }
     }
     return -1;
 }
 
-// Filters too long for the register-resident Toeplitz form: whole rows and the whole filter in LDS.
-// Returns -1 when the shape or the pointers do not fit.
-template <typename T>
-int launch_corr_longk(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
+// Which filters of more than six block offsets go to corr_band_kernel (us, kernels it replaces there -> corr_band_kernel):
+//   fp32, ordinary rows of whole granules: from thirteen offsets (B32 C256 L4096: K = 160 101 / 107, 200 121 -> 103, 300 180 ->
+//     133, 1024 496 -> 296, 4096 1050 -> 712; the register-resident kernel keeps seven to twelve), from eleven where rows fill
+//     less than three quarters of their 1024-position segments; other lengths: from nine (L4097: K = 100 100 / 107, 200 220 ->
+//     126, 4097 3537 -> 954)
+//   bf16, rows of whole 16-byte granules: from eleven (B32 C256 L4096: K = 128 35 / 37, 226 50 -> 41, 4096 243 -> 148), from
+//     seven where rows fill less than three quarters of their segments (L512 K512 92 -> 48); other lengths and alignments:
+//     all (L4097: K = 100 119 -> 65, 4097 3213 -> 200)
+//   short rows with more than six offsets: virtual rows (fp32 L512 K100 91 -> 75, L160 81 -> 73) and rows of up to 512
+//     positions with filters of their own length (L256 K256 fp32 101 -> 76, bf16 105 -> 38), any alignment; rows of at most
+//     128 positions: bf16 above 64 (L128 K128 61 -> 35; fp32 L96 K96 48 / 59)
+inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const void *out)
 {
-    const int dmin = toeplitz_dmin(pad_eff), dmax = toeplitz_dmax(s.K, pad_eff);
-    if (dmax - dmin + 1 <= longk_corr_min_nd(s.dtype) - 1 || (s.L % 4) != 0) return -1;
-    const int NB = (s.L + 15) / 16;
-    if (!aligned_to(in, 4 * sizeof(T)) || !aligned_to(out, 4 * sizeof(T))) return -1;
-    if (s.K > dwconv::kLkMaxK || NB > dwconv::kLkMaxBlocks) {
-        // beyond what LDS holds whole: pieces of 4096 outputs, filter chunks of 4096 taps
-        dwconv::LongKTileGeom tg;
-        tg.B = s.B; tg.C = s.C; tg.L = s.L; tg.K = s.K; tg.pad = pad_eff; tg.reverse = reverse; tg.NB = NB;
-        tg.NP = (s.L + dwconv::kLkTilePiece - 1) / dwconv::kLkTilePiece;
-        tg.NCK = (s.K + dwconv::kLkTileChunk - 1) / dwconv::kLkTileChunk;
-        const long long gy = (((long long)s.B + 1) / 2) * tg.NP;
-        if (gy > 65535 || s.L > kMfmaMaxL) return -1;
-        if constexpr (sizeof(T) == 2) {
-            // bf16 storage: raw bf16 operands on the bf16 matrix instruction
-            const size_t lds = dwconv::longk_tiled_bf16_lds_bytes();
-            if (lds > kMaxLdsBytes || !allow_large_lds(dwconv::corr_longk_tiled_bf16_kernel<>)) return -1;
-            hipLaunchKernelGGL((dwconv::corr_longk_tiled_bf16_kernel<>), dim3((unsigned)s.C, (unsigned)gy),
-                               dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const bf16_t *>(in),
-                               static_cast<const bf16_t *>(f), static_cast<bf16_t *>(out), tg);
-            return launch_status();
-        } else {
-            const size_t lds = dwconv::longk_tiled_lds_bytes();
-            if (lds > kMaxLdsBytes || !allow_large_lds(dwconv::corr_longk_tiled_kernel<T>)) return -1;
-            hipLaunchKernelGGL((dwconv::corr_longk_tiled_kernel<T>), dim3((unsigned)s.C, (unsigned)gy),
-                               dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const T *>(in), static_cast<const T *>(f),
-                               static_cast<T *>(out), tg);
-            return launch_status();
-        }
+    const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
+    if (nd <= kMfmaMaxND) return false;
+    const RowsPlan rp = plan_rows(s);
+    if (rp.batch) {
+        int bd, bn;
+        rows_batch_offsets(s.L, s.K, pad_eff, &bd, &bn);
+        return s.dtype == DWCONV_BF16 && bn > kMfmaMaxND && s.L > 64;
     }
-    dwconv::LongKGeom g;
-    g.B = s.B; g.C = s.C; g.L = s.L; g.K = s.K;
-    g.pad = pad_eff; g.reverse = reverse; g.dmin = dmin; g.dmax = dmax;
-    g.NB = NB; g.NT = (NB + 15) / 16;
-    // rows per workgroup: about 32 (row pair, tile) items for its 16 waves, no more than the batch, and within half of
-    // the LDS of a compute unit, so that two workgroups share it and one stages its rows while the other computes
-    // (sixteen rows of 1024 positions in one resident workgroup measured slower than two rows in each of two)
-    auto lds_for = [&](int R) -> size_t {
-        return sizeof(T) == 2 ? dwconv::longk_corr_bf16_lds_bytes(s.K, NB, R) : dwconv::longk_corr_lds_bytes(s.K, NB, R);
-    };
-    int R = 2 * ((2 * dwconv::kLkWaves + g.NT - 1) / g.NT);
-    if (R > 2 * ((s.B + 1) / 2)) R = 2 * ((s.B + 1) / 2);
-    while (R > 2 && lds_for(R) > kMaxLdsBytes / 2) R -= 2;
-    g.R = R;
-    const long long row_groups = ((long long)s.B + R - 1) / R;
-    if (row_groups > 65535) return -1;
-    if constexpr (sizeof(T) == 2) {
-        // bf16 storage: raw rows and four shifted copies of the filter in LDS, bf16 matrix instruction
-        const size_t lds = lds_for(R);
-        if (lds > kMaxLdsBytes) return -1;
-        if (!allow_large_lds(dwconv::corr_longk_bf16_kernel<>)) return -1;
-        hipLaunchKernelGGL(dwconv::corr_longk_bf16_kernel<>, dim3((unsigned)s.C, (unsigned)row_groups),
-                           dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const bf16_t *>(in),
-                           static_cast<const bf16_t *>(f), static_cast<bf16_t *>(out), g);
-    } else {
-        const size_t lds = lds_for(R);
-        if (lds > kMaxLdsBytes) return -1;
-        if (!allow_large_lds(dwconv::corr_longk_kernel<T>)) return -1;
-        hipLaunchKernelGGL((dwconv::corr_longk_kernel<T>), dim3((unsigned)s.C, (unsigned)row_groups),
-                           dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const T *>(in), static_cast<const T *>(f),
-                           static_cast<T *>(out), g);
-    }
-    return launch_status();
+    if (rp.on || s.L <= 512) return true;
+    const bool filled = 4ll * s.L >= 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
+    if (s.dtype == DWCONV_F32) return nd >= ((s.L % 4) != 0 ? 9 : filled ? 13 : 11);
+    return (s.L % 8) != 0 || !aligned_to(in, 16) || !aligned_to(out, 16) || nd >= (filled ? 11 : 7);
 }
 
 template <typename T>
 int launch_corr(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
 {
-    int rc = launch_corr_mfma<T>(in, f, out, s, pad_eff, reverse, st);
-    if (rc >= 0) return rc;
-    rc = launch_corr_longk<T>(in, f, out, s, pad_eff, reverse, st);
+    int rc = -1;
+    if (corr_takes_band(s, pad_eff, in, out)) {
+        if constexpr (std::is_same<T, float>::value) rc = launch_corr_band_f32(in, f, out, s, pad_eff, reverse, st);
+        else rc = launch_corr_band_bf16(in, f, out, s, pad_eff, reverse, st);
+        if (rc >= 0) return rc;
+    }
+    rc = launch_corr_mfma<T>(in, f, out, s, pad_eff, reverse, st);
     if (rc >= 0) return rc;
     return launch_corr_valu<T>(in, f, out, s, pad_eff, reverse, st);
 }

@@ -1,4 +1,4 @@
-// Forward / input gradient, rows of at most 128 positions with seven to fifteen block offsets, bf16 storage.
+// Forward / input gradient, rows of at most 64 positions with seven block offsets, bf16 storage.
 #include "dwconv_launch_corr.hip.h"
 
 namespace dwhost {

@@ -1,19 +1,6 @@
-// Matrix-core kernels for filters whose length is of the order of the sequence (K up to 8192,
-// L up to 8192): the blocked-Toeplitz form of dwconv_mfma.hip.h with a long loop over block offsets.
-//
-//   Y[n][r] = sum_{d = dmin..dmax} sum_q Toep_d[r][q] X[n + d][q],   Toep_d[r][q] = w[16 d + q - r + pad]
-//
-// Here neither the Toeplitz operands (4 registers per offset, hundreds of offsets) nor the inputs fit
-// in registers, so a workgroup keeps the whole filter of its channel and whole rows in LDS:
-//   forward / input gradient:  grid (C, ceil(B/R)); a workgroup of 16 waves stages w[c,:] (with zero
-//       margins) and R rows x[b,c,:] (16-blocks padded to 24 floats, 15 zero blocks on both sides;
-//       R = 2 for rows of 8192, more for shorter rows so that the waves have about 32 (row pair, tile) items
-//       to share).  A wave owns items in alternating order (longk_item), which balances the
-//       triangular cost of a causal filter, and for each walks d over the offsets that touch the row:
-//       4 LDS dwords of Toeplitz operand, one 16-byte LDS read per row, 4 matrix instructions per row.
-//   weight gradient: see dw_longk_kernel below.
-// Sums are fp32; a chain never runs longer than 64 offsets (1024 terms) before it is folded into a
-// second accumulator.
+// Weight gradient (eq. (dk_def)) for filters whose length is of the order of the sequence (K up to 8192, L up to 8192):
+// the blocked form of dwconv_mfma.hip.h with hundreds of block offsets, split over the waves of a workgroup that keeps whole
+// rows in LDS.  (Forward and input gradient of such filters: dwconv_band.hip.h.)
 #pragma once
 #include "dwconv_common.hip.h"
 #include "dwconv_mfma.hip.h"
@@ -24,489 +11,6 @@ constexpr int kLkWaves = 16;            // waves per workgroup (1024 threads)
 constexpr int kLkRows = 2;              // rows staged together
 constexpr int kLkMaxBlocks = 512;       // 16-blocks per row: L <= 8192
 constexpr int kLkMaxK = 8192;
-constexpr int kLkMargin = 15;           // zero 16-blocks on both sides of a staged row
-constexpr int kLkWMargin = 48;          // zero taps on both sides of the staged filter
-constexpr int kLkFold = 64;             // offsets per inner accumulation chain
-
-struct LongKGeom {
-    int B, C, L, K;
-    int pad;        // effective pad of this correlation
-    int reverse;    // filter index reversed (input gradient)
-    int dmin, dmax; // block offsets that can hold a tap
-    int NB;         // 16-blocks per row, ceil(L / 16)
-    int NT;         // D tiles per row, ceil(NB / 16)
-    int R;          // rows staged per workgroup (even): R / 2 row pairs x NT tiles are the items its 16 waves share
-};
-
-__host__ __device__ inline int longk_filter_floats(int K) { return (K + 2 * kLkWMargin + 3) & ~3; }
-__host__ __device__ inline int longk_row_floats(int NB) { return (NB + 2 * kLkMargin) * kLdsBlockStride; }
-inline size_t longk_corr_lds_bytes(int K, int NB, int R)
-{
-    return sizeof(float) * ((size_t)longk_filter_floats(K) + (size_t)R * longk_row_floats(NB));
-}
-// Item number `round` of wave `wave`.  Under a causal pad tile t costs about t + 1, so the items (row pair rp, tile t)
-// are numbered dearest first, q = (NT - 1 - t) * RP + rp, and dealt to the 16 waves in rounds of 16, every other
-// round in reverse order: a wave (and with it a SIMD, which runs waves w, w + 4, ...) that gets a dear tile in one
-// round gets a cheap one in the next (one row pair of 32 tiles: tiles 31 - w and w).
-__device__ __forceinline__ int longk_item(int round, int wave)
-{
-    return round * kLkWaves + ((round & 1) ? kLkWaves - 1 - wave : wave);
-}
-
-// out[row, t] = sum_j in~[row, t + j - pad] * f_eff[c, j]
-template <typename T>
-__global__ __launch_bounds__(64 * kLkWaves) void corr_longk_kernel(const T *__restrict__ in, const T *__restrict__ f,
-                                                                    T *__restrict__ out, const LongKGeom g)
-{
-    extern __shared__ __align__(16) float lk_smem[];
-    float *fw = lk_smem;                                     // fw[kLkWMargin + j] = f_eff[j], zero outside [0, K)
-    float *xr = lk_smem + longk_filter_floats(g.K);
-    const int XR = longk_row_floats(g.NB);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i16 = lane & 15;
-    const int k4 = lane >> 4;
-    const int c = blockIdx.x;
-    const int b0 = blockIdx.y * g.R;
-
-    // ---- stage the filter and the rows
-    {
-        const T *f_c = f + (size_t)c * (size_t)g.K;
-        const int FW = longk_filter_floats(g.K);
-        for (int i = tid; i < FW; i += 64 * kLkWaves) {
-            const int j = i - kLkWMargin;
-            float v = 0.f;
-            if (j >= 0 && j < g.K) v = ld_elem(f_c + (g.reverse ? (g.K - 1 - j) : j));
-            fw[i] = v;
-        }
-        for (int rb = 0; rb < g.R; ++rb) {
-            float *xrow = xr + rb * XR;
-            const int b = b0 + rb;
-            // zero margins (16 useful floats of each of the 15 + 15 blocks)
-            for (int i = tid; i < 2 * kLkMargin * 16; i += 64 * kLkWaves) {
-                const int blk = i >> 4, q = i & 15;
-                const int lb = blk < kLkMargin ? blk : g.NB + blk;
-                xrow[lb * kLdsBlockStride + q] = 0.f;
-            }
-            const T *in_row = in + ((size_t)(b < g.B ? b : 0) * (size_t)g.C + (size_t)c) * (size_t)g.L;
-            for (int gi = tid; gi < g.NB * 4; gi += 64 * kLkWaves) {
-                const int u = 4 * gi;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (b < g.B && u + 3 < g.L) v = ld_elem4(in_row + u);
-                *reinterpret_cast<float4 *>(xrow + (kLkMargin + (gi >> 2)) * kLdsBlockStride + (gi & 3) * 4) = v;
-            }
-        }
-    }
-    __syncthreads();
-
-    // ---- items of this wave: (row pair, D tile), see longk_item
-    const int n_items = (g.R / 2) * g.NT;
-    {
-        for (int round = 0; round * kLkWaves < n_items; ++round) {
-            int item = longk_item(round, wave);
-            if (item >= n_items) continue;
-            // (a single round: cheapest first, wave w on tile w of one row pair of up to sixteen tiles; the other order
-            // measured 3 % slower on B32 C256 L4096 K4096)
-            if (n_items <= kLkWaves) item = n_items - 1 - item;
-            const int RP = g.R / 2;
-            const int t = g.NT - 1 - item / RP, rp = item % RP;
-            const int bq = b0 + 2 * rp;                     // first row of the pair
-            if (bq >= g.B) continue;
-            // offsets d for which some block 16 t + j + d of the tile lies inside the row
-            const int dlo = max(g.dmin, -(16 * t + 15));
-            const int dhi = min(g.dmax, g.NB - 1 - 16 * t);
-            floatx4 tot0 = floatx4{0.f, 0.f, 0.f, 0.f}, tot1 = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (dlo <= dhi) {
-                // A: lane (r = i16, k4) reads f_eff[16 d + 4 k4 + v - r + pad];  B: lane (j = i16, k4) reads X[16 t + j + d][4 k4 ..]
-                const float *ap = fw + kLkWMargin + 16 * dlo + 4 * k4 - i16 + g.pad;
-                const float *bp = xr + 2 * rp * XR + (kLkMargin + 16 * t + i16 + dlo) * kLdsBlockStride + 4 * k4;
-                for (int d0 = dlo; d0 <= dhi; d0 += kLkFold) {
-                    const int n = min(kLkFold, dhi - d0 + 1);
-                    floatx4 acc0 = floatx4{0.f, 0.f, 0.f, 0.f}, acc1 = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-                    for (int i = 0; i < n; ++i) {
-                        const float a0 = ap[0], a1 = ap[1], a2 = ap[2], a3 = ap[3];
-                        const float4 x0 = *reinterpret_cast<const float4 *>(bp);
-                        const float4 x1 = *reinterpret_cast<const float4 *>(bp + XR);
-                        acc0 = mfma16x16x4(a0, x0.x, acc0);
-                        acc1 = mfma16x16x4(a0, x1.x, acc1);
-                        acc0 = mfma16x16x4(a1, x0.y, acc0);
-                        acc1 = mfma16x16x4(a1, x1.y, acc1);
-                        acc0 = mfma16x16x4(a2, x0.z, acc0);
-                        acc1 = mfma16x16x4(a2, x1.z, acc1);
-                        acc0 = mfma16x16x4(a3, x0.w, acc0);
-                        acc1 = mfma16x16x4(a3, x1.w, acc1);
-                        ap += 16;
-                        bp += kLdsBlockStride;
-                    }
-                    tot0 += acc0;
-                    tot1 += acc1;
-                }
-            }
-            // lane (block j = i16, row group k4) owns outputs 16 j + 4 k4 + 0..3 of the tile
-            const int to = 256 * t + 16 * i16 + 4 * k4;
-            if (to + 3 < g.L) {
-                T *o0 = out + ((size_t)bq * (size_t)g.C + (size_t)c) * (size_t)g.L + to;
-                st_elem4(o0, make_float4(tot0[0], tot0[1], tot0[2], tot0[3]));
-                if (bq + 1 < g.B)
-                    st_elem4(o0 + (size_t)g.C * (size_t)g.L, make_float4(tot1[0], tot1[1], tot1[2], tot1[3]));
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Filters or rows beyond what LDS holds whole (K or L above 8192): the same kernel in tiles.
-// A workgroup owns one PIECE of 4096 outputs of a row pair and walks the filter in CHUNKS of 4096 taps.  For chunk ck
-// the operator restricted to taps [4096 ck, 4096 ck + 4096) is the operator of a 4096-tap filter with pad
-// pad - 4096 ck (any integer: the block offsets that can hold one of its taps follow from the same inequalities),
-// and its contribution to the piece needs the input window of 4096 + 4096 + 30 positions that those offsets reach:
-// both are staged (the filter chunk with zero margins, so that the taps of the neighbouring chunks inside its edge
-// blocks count as zeros here; the window with zeros outside the row), the sixteen waves add the chunk's
-// contribution to the accumulators of their tile (256 outputs x 2 rows), and the next chunk is staged.  A chunk whose
-// window misses the row is skipped, so a causal filter costs its triangle, not the square.
-constexpr int kLkTilePiece = 4096;                       // outputs per workgroup and row
-constexpr int kLkTileChunk = 4096;                       // taps staged at a time
-constexpr int kLkTileWinBlocks = kLkTilePiece / 16 + kLkTileChunk / 16 + 4;    // 16-blocks of a staged window (516)
-
-struct LongKTileGeom {
-    int B, C, L, K;
-    int pad;        // effective pad of this correlation
-    int reverse;    // filter index reversed (input gradient)
-    int NB;         // 16-blocks per row, ceil(L / 16)
-    int NP;         // pieces per row
-    int NCK;        // filter chunks
-};
-inline size_t longk_tiled_lds_bytes()
-{
-    return sizeof(float) * ((size_t)(kLkTileChunk + 2 * kLkWMargin) + (size_t)kLkRows * kLkTileWinBlocks * kLdsBlockStride);
-}
-
-template <typename T>
-__global__ __launch_bounds__(64 * kLkWaves) void corr_longk_tiled_kernel(const T *__restrict__ in, const T *__restrict__ f,
-                                                                          T *__restrict__ out, const LongKTileGeom g)
-{
-    extern __shared__ __align__(16) float lkt_smem[];
-    constexpr int FWT = kLkTileChunk + 2 * kLkWMargin;
-    constexpr int XR = kLkTileWinBlocks * kLdsBlockStride;
-    float *fw = lkt_smem;                                    // fw[kLkWMargin + jj] = tap 4096 ck + jj, zero outside the chunk
-    float *xr = lkt_smem + FWT;                              // two staged windows
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int t = __builtin_amdgcn_readfirstlane(tid >> 6);     // the wave's tile of the piece
-    const int i16 = lane & 15;
-    const int k4 = lane >> 4;
-    const int c = blockIdx.x;
-    const int a = g.NP - 1 - (int)(blockIdx.y % (unsigned)g.NP);     // piece (the dear ones of a causal filter first)
-    const int b0 = 2 * (int)(blockIdx.y / (unsigned)g.NP);
-    const int n0 = (kLkTilePiece / 16) * a + 16 * t;                 // row block of the tile's first output block
-    const T *f_c = f + (size_t)c * (size_t)g.K;
-
-    floatx4 tot0 = floatx4{0.f, 0.f, 0.f, 0.f}, tot1 = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int ck = 0; ck < g.NCK; ++ck) {
-        const int klen = min(kLkTileChunk, g.K - ck * kLkTileChunk);
-        const int padc = g.pad - ck * kLkTileChunk;
-        // block offsets that can hold a tap of the chunk (arithmetic shifts: floor division)
-        const int dminc = -((padc + 15) >> 4), dmaxc = (klen - padc + 14) >> 4;
-        const int wlo = (kLkTilePiece / 16) * a + dminc;             // row block of window block 0
-        const int nwb = kLkTilePiece / 16 + (dmaxc - dminc);         // window blocks
-        if (wlo + nwb - 1 < 0 || wlo >= g.NB) continue;              // the window misses the row (block-uniform)
-        __syncthreads();                                             // everyone is done with the previous chunk
-        for (int i = tid; i < FWT; i += 64 * kLkWaves) {
-            const int jj = i - kLkWMargin;
-            float v = 0.f;
-            if (jj >= 0 && jj < klen) {
-                const int j = ck * kLkTileChunk + jj;
-                v = ld_elem(f_c + (g.reverse ? (g.K - 1 - j) : j));
-            }
-            fw[i] = v;
-        }
-        for (int rb = 0; rb < kLkRows; ++rb) {
-            float *xrow = xr + rb * XR;
-            const int b = b0 + rb;
-            const T *in_row = in + ((size_t)(b < g.B ? b : 0) * (size_t)g.C + (size_t)c) * (size_t)g.L;
-            for (int gi = tid; gi < nwb * 4; gi += 64 * kLkWaves) {
-                const int m = wlo + (gi >> 2);
-                const int u = 16 * m + 4 * (gi & 3);
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (b < g.B && m >= 0 && u + 3 < g.L) v = ld_elem4(in_row + u);
-                *reinterpret_cast<float4 *>(xrow + (gi >> 2) * kLdsBlockStride + (gi & 3) * 4) = v;
-            }
-        }
-        __syncthreads();
-        // offsets for which some block n0 + j + d of the tile lies inside the row
-        const int dlo = max(dminc, -(n0 + 15));
-        const int dhi = min(dmaxc, g.NB - 1 - n0);
-        if (dlo <= dhi && b0 < g.B) {
-            // A: lane (r = i16, k4) reads chunk tap 16 d + 4 k4 + v - r + padc;  B: lane (j = i16, k4) reads window block 16 t + j + d - dminc
-            const float *ap = fw + kLkWMargin + 16 * dlo + 4 * k4 - i16 + padc;
-            const float *bp = xr + (16 * t + i16 + (dlo - dminc)) * kLdsBlockStride + 4 * k4;
-            for (int d0 = dlo; d0 <= dhi; d0 += kLkFold) {
-                const int n = min(kLkFold, dhi - d0 + 1);
-                floatx4 acc0 = floatx4{0.f, 0.f, 0.f, 0.f}, acc1 = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-                for (int i = 0; i < n; ++i) {
-                    const float a0 = ap[0], a1 = ap[1], a2 = ap[2], a3 = ap[3];
-                    const float4 x0 = *reinterpret_cast<const float4 *>(bp);
-                    const float4 x1 = *reinterpret_cast<const float4 *>(bp + XR);
-                    acc0 = mfma16x16x4(a0, x0.x, acc0);
-                    acc1 = mfma16x16x4(a0, x1.x, acc1);
-                    acc0 = mfma16x16x4(a1, x0.y, acc0);
-                    acc1 = mfma16x16x4(a1, x1.y, acc1);
-                    acc0 = mfma16x16x4(a2, x0.z, acc0);
-                    acc1 = mfma16x16x4(a2, x1.z, acc1);
-                    acc0 = mfma16x16x4(a3, x0.w, acc0);
-                    acc1 = mfma16x16x4(a3, x1.w, acc1);
-                    ap += 16;
-                    bp += kLdsBlockStride;
-                }
-                tot0 += acc0;
-                tot1 += acc1;
-            }
-        }
-    }
-    // lane (block j = i16, row group k4) owns outputs 16 j + 4 k4 + 0..3 of the tile
-    const int to = 16 * n0 + 16 * i16 + 4 * k4;
-    if (b0 < g.B && to + 3 < g.L) {
-        T *o0 = out + ((size_t)b0 * (size_t)g.C + (size_t)c) * (size_t)g.L + to;
-        st_elem4(o0, make_float4(tot0[0], tot0[1], tot0[2], tot0[3]));
-        if (b0 + 1 < g.B) st_elem4(o0 + (size_t)g.C * (size_t)g.L, make_float4(tot1[0], tot1[1], tot1[2], tot1[3]));
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// The same correlation for bf16 storage on the bf16 matrix instruction (v_mfma_f32_16x16x16_bf16): one
-// instruction covers a whole block offset of one row (products of two bf16 are exact in fp32, sums fp32, one
-// rounding at the store), so per offset a wave issues kLkRows instructions instead of 4 kLkRows.
-// LDS holds raw bf16:
-//   rows: 16-blocks of 32 bytes padded to 48 (as in corr_mfma_bf16_kernel), 15 zero blocks on both sides;
-//   filter: FOUR copies, copy s shifted by s taps (copy_s[i] = fw[i + s]), because lane (r, kg) needs the four
-//       consecutive taps fw[a .. a + 3], a = 16 d + 4 kg - r + pad (+ margin), as one aligned 8-byte read and
-//       a mod 4 depends on the lane only: it reads copy (a mod 4) at a - (a mod 4), and a grows by 16 per offset.
-//       The copies start 64 bytes apart modulo 256, which puts the sixteen r of a read on different banks.
-constexpr int kLkBf16CopyPad = 32;         // bf16 elements: makes the stride of the copies 64 bytes modulo 256
-__host__ __device__ constexpr int longk_bf16_copy_elems(int K)
-{
-    const int n = (K + 2 * kLkWMargin + 3) & ~3;                  // taps with margins, whole 8-byte granules
-    return (n + 127) / 128 * 128 + kLkBf16CopyPad;                // stride = 64 bytes mod 256
-}
-__host__ __device__ inline int longk_bf16_row_bytes(int NB) { return (NB + 2 * kLkMargin) * kBf16BlockBytes; }
-inline size_t longk_corr_bf16_lds_bytes(int K, int NB, int R)
-{
-    return (size_t)4 * longk_bf16_copy_elems(K) * 2 + (size_t)R * longk_bf16_row_bytes(NB);
-}
-
-template <int UNUSED = 0>   // (a template only so that the header can be included by several translation units)
-__global__ __launch_bounds__(64 * kLkWaves) void corr_longk_bf16_kernel(const bf16_t *__restrict__ in,
-                                                                         const bf16_t *__restrict__ f,
-                                                                         bf16_t *__restrict__ out, const LongKGeom g)
-{
-    extern __shared__ __align__(16) unsigned char lkb_smem[];
-    const int CE = longk_bf16_copy_elems(g.K);
-    uint16_t *fwc = reinterpret_cast<uint16_t *>(lkb_smem);      // copy s at fwc + s * CE
-    unsigned char *xr = lkb_smem + (size_t)4 * CE * 2;
-    const int XR = longk_bf16_row_bytes(g.NB);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i16 = lane & 15;
-    const int kg = lane >> 4;
-    const int c = blockIdx.x;
-    const int b0 = blockIdx.y * g.R;
-
-    // ---- stage the filter copies and the rows
-    {
-        const bf16_t *f_c = f + (size_t)c * (size_t)g.K;
-        const int FW = (g.K + 2 * kLkWMargin + 3) & ~3;
-        for (int i = tid; i < 4 * FW; i += 64 * kLkWaves) {
-            const int s = i / FW, e = i - s * FW;
-            const int j = e + s - kLkWMargin;
-            uint16_t v = 0;
-            if (j >= 0 && j < g.K) v = f_c[g.reverse ? (g.K - 1 - j) : j].bits;
-            fwc[s * CE + e] = v;
-        }
-        for (int rb = 0; rb < g.R; ++rb) {
-            unsigned char *xrow = xr + rb * XR;
-            const int b = b0 + rb;
-            // zero margins (the 32 useful bytes of each of the 15 + 15 blocks, 8 bytes at a time)
-            for (int i = tid; i < 2 * kLkMargin * 4; i += 64 * kLkWaves) {
-                const int blk = i >> 2, q = i & 3;
-                const int lb = blk < kLkMargin ? blk : g.NB + blk;
-                *reinterpret_cast<uint2 *>(xrow + lb * kBf16BlockBytes + 8 * q) = make_uint2(0u, 0u);
-            }
-            const bf16_t *in_row = in + ((size_t)(b < g.B ? b : 0) * (size_t)g.C + (size_t)c) * (size_t)g.L;
-            for (int gi = tid; gi < g.NB * 4; gi += 64 * kLkWaves) {
-                const int u = 4 * gi;
-                uint2 v = make_uint2(0u, 0u);
-                if (b < g.B && u + 3 < g.L) v = *reinterpret_cast<const uint2 *>(in_row + u);
-                *reinterpret_cast<uint2 *>(xrow + (kLkMargin + (gi >> 2)) * kBf16BlockBytes + (gi & 3) * 8) = v;
-            }
-        }
-    }
-    __syncthreads();
-
-    // this lane's filter copy: a = kLkWMargin + 16 d + 4 kg - i16 + pad, copy a & 3 read at a - (a & 3)
-    const int a0 = kLkWMargin + 4 * kg - i16 + g.pad;             // at d = 0; 16 d keeps a & 3
-    const int sh = a0 & 3;
-    const uint16_t *acopy = fwc + sh * CE + (a0 - sh);
-
-    // ---- items of this wave: (row pair, D tile), see longk_item
-    const int n_items = (g.R / 2) * g.NT;
-    {
-        for (int round = 0; round * kLkWaves < n_items; ++round) {
-            int item = longk_item(round, wave);
-            if (item >= n_items) continue;
-            // (a single round: cheapest first, wave w on tile w of one row pair of up to sixteen tiles; the other order
-            // measured 3 % slower on B32 C256 L4096 K4096)
-            if (n_items <= kLkWaves) item = n_items - 1 - item;
-            const int RP = g.R / 2;
-            const int t = g.NT - 1 - item / RP, rp = item % RP;
-            const int bq = b0 + 2 * rp;                     // first row of the pair
-            if (bq >= g.B) continue;
-            // offsets d for which some block 16 t + j + d of the tile lies inside the row
-            const int dlo = max(g.dmin, -(16 * t + 15));
-            const int dhi = min(g.dmax, g.NB - 1 - 16 * t);
-            floatx4 tot0 = floatx4{0.f, 0.f, 0.f, 0.f}, tot1 = floatx4{0.f, 0.f, 0.f, 0.f};
-            if (dlo <= dhi) {
-                // A: lane (r = i16, kg) reads taps 16 d + 4 kg + e - r + pad;  B: lane (j = i16, kg) reads X[16 t + j + d][4 kg ..]
-                const uint16_t *ap = acopy + 16 * dlo;
-                const unsigned char *bp = xr + 2 * rp * XR + (kLkMargin + 16 * t + i16 + dlo) * kBf16BlockBytes + 8 * kg;
-                for (int d0 = dlo; d0 <= dhi; d0 += kLkFold) {
-                    const int n = min(kLkFold, dhi - d0 + 1);
-                    floatx4 acc0 = floatx4{0.f, 0.f, 0.f, 0.f}, acc1 = floatx4{0.f, 0.f, 0.f, 0.f};
-                    // (one offset per trip, latency hidden by the four waves of a SIMD: four offsets per trip with all
-                    // twelve reads issued first measured 429 us instead of 224 us on B8 C256 L8192 K8192, two offsets
-                    // per trip on two register sets with the reads of one issued ahead of the other's instructions 266 us)
-#pragma unroll 1
-                    for (int i = 0; i < n; ++i) {
-                        const shortx4 a = *reinterpret_cast<const shortx4 *>(ap);
-                        const shortx4 x0 = *reinterpret_cast<const shortx4 *>(bp);
-                        const shortx4 x1 = *reinterpret_cast<const shortx4 *>(bp + XR);
-                        acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, x0, acc0, 0, 0, 0);
-                        acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, x1, acc1, 0, 0, 0);
-                        ap += 16;
-                        bp += kBf16BlockBytes;
-                    }
-                    tot0 += acc0;
-                    tot1 += acc1;
-                }
-            }
-            // lane (block j = i16, row group kg) owns outputs 16 j + 4 kg + 0..3 of the tile
-            const int to = 256 * t + 16 * i16 + 4 * kg;
-            if (to + 3 < g.L) {
-                bf16_t *o0 = out + ((size_t)bq * (size_t)g.C + (size_t)c) * (size_t)g.L + to;
-                st_elem4(o0, make_float4(tot0[0], tot0[1], tot0[2], tot0[3]));
-                if (bq + 1 < g.B)
-                    st_elem4(o0 + (size_t)g.C * (size_t)g.L, make_float4(tot1[0], tot1[1], tot1[2], tot1[3]));
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// bf16 storage beyond what LDS holds whole: the tiles of corr_longk_tiled_kernel (pieces of 4096 outputs of a row pair,
-// filter chunks of 4096 taps with pad - 4096 ck) on the operands of corr_longk_bf16_kernel (four shifted copies of the
-// filter chunk, raw bf16 window blocks of 48 bytes, one v_mfma_f32_16x16x16_bf16 per block offset and row).
-inline size_t longk_tiled_bf16_lds_bytes()
-{
-    return (size_t)4 * longk_bf16_copy_elems(kLkTileChunk) * 2 + (size_t)kLkRows * kLkTileWinBlocks * kBf16BlockBytes;
-}
-
-template <int UNUSED = 0>   // (a template only so that the header can be included by several translation units)
-__global__ __launch_bounds__(64 * kLkWaves) void corr_longk_tiled_bf16_kernel(const bf16_t *__restrict__ in,
-                                                                               const bf16_t *__restrict__ f,
-                                                                               bf16_t *__restrict__ out, const LongKTileGeom g)
-{
-    extern __shared__ __align__(16) unsigned char lktb_smem[];
-    constexpr int CE = longk_bf16_copy_elems(kLkTileChunk);
-    constexpr int FW = (kLkTileChunk + 2 * kLkWMargin + 3) & ~3;
-    constexpr int XR = kLkTileWinBlocks * kBf16BlockBytes;
-    uint16_t *fwc = reinterpret_cast<uint16_t *>(lktb_smem);     // copy s at fwc + s * CE: copy_s[e] = chunk tap e + s - margin
-    unsigned char *xr = lktb_smem + (size_t)4 * CE * 2;          // two staged windows
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int t = __builtin_amdgcn_readfirstlane(tid >> 6);      // the wave's tile of the piece
-    const int i16 = lane & 15;
-    const int kg = lane >> 4;
-    const int c = blockIdx.x;
-    const int a = g.NP - 1 - (int)(blockIdx.y % (unsigned)g.NP);     // piece (the dear ones of a causal filter first)
-    const int b0 = 2 * (int)(blockIdx.y / (unsigned)g.NP);
-    const int n0 = (kLkTilePiece / 16) * a + 16 * t;                 // row block of the tile's first output block
-    const bf16_t *f_c = f + (size_t)c * (size_t)g.K;
-
-    floatx4 tot0 = floatx4{0.f, 0.f, 0.f, 0.f}, tot1 = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int ck = 0; ck < g.NCK; ++ck) {
-        const int klen = min(kLkTileChunk, g.K - ck * kLkTileChunk);
-        const int padc = g.pad - ck * kLkTileChunk;
-        const int dminc = -((padc + 15) >> 4), dmaxc = (klen - padc + 14) >> 4;     // (arithmetic shifts: floor division)
-        const int wlo = (kLkTilePiece / 16) * a + dminc;             // row block of window block 0
-        const int nwb = kLkTilePiece / 16 + (dmaxc - dminc);         // window blocks
-        if (wlo + nwb - 1 < 0 || wlo >= g.NB) continue;              // the window misses the row (block-uniform)
-        __syncthreads();                                             // everyone is done with the previous chunk
-        for (int i = tid; i < 4 * FW; i += 64 * kLkWaves) {
-            const int s = i / FW, e = i - s * FW;
-            const int jj = e + s - kLkWMargin;
-            uint16_t v = 0;
-            if (jj >= 0 && jj < klen) {
-                const int j = ck * kLkTileChunk + jj;
-                v = f_c[g.reverse ? (g.K - 1 - j) : j].bits;
-            }
-            fwc[s * CE + e] = v;
-        }
-        for (int rb = 0; rb < kLkRows; ++rb) {
-            unsigned char *xrow = xr + rb * XR;
-            const int b = b0 + rb;
-            const bf16_t *in_row = in + ((size_t)(b < g.B ? b : 0) * (size_t)g.C + (size_t)c) * (size_t)g.L;
-            for (int gi = tid; gi < nwb * 4; gi += 64 * kLkWaves) {
-                const int m = wlo + (gi >> 2);
-                const int u = 16 * m + 4 * (gi & 3);
-                uint2 v = make_uint2(0u, 0u);
-                if (b < g.B && m >= 0 && u + 3 < g.L) v = *reinterpret_cast<const uint2 *>(in_row + u);
-                *reinterpret_cast<uint2 *>(xrow + (gi >> 2) * kBf16BlockBytes + (gi & 3) * 8) = v;
-            }
-        }
-        __syncthreads();
-        // offsets for which some block n0 + j + d of the tile lies inside the row
-        const int dlo = max(dminc, -(n0 + 15));
-        const int dhi = min(dmaxc, g.NB - 1 - n0);
-        if (dlo <= dhi && b0 < g.B) {
-            // A: lane (r = i16, kg) needs chunk taps 16 d + 4 kg + e - r + padc, e = 0..3: copy (a0 & 3) read at a0 - (a0 & 3),
-            // a0 = margin + 4 kg - r + padc (16 d keeps a0 & 3);  B: lane (j = i16, kg) reads window block 16 t + j + d - dminc
-            const int a0 = kLkWMargin + 4 * kg - i16 + padc;
-            const int sh = a0 & 3;
-            const uint16_t *ap = fwc + sh * CE + (a0 - sh) + 16 * dlo;
-            const unsigned char *bp = xr + (16 * t + i16 + (dlo - dminc)) * kBf16BlockBytes + 8 * kg;
-            for (int d0 = dlo; d0 <= dhi; d0 += kLkFold) {
-                const int n = min(kLkFold, dhi - d0 + 1);
-                floatx4 acc0 = floatx4{0.f, 0.f, 0.f, 0.f}, acc1 = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-                for (int i = 0; i < n; ++i) {
-                    const shortx4 av = *reinterpret_cast<const shortx4 *>(ap);
-                    const shortx4 x0 = *reinterpret_cast<const shortx4 *>(bp);
-                    const shortx4 x1 = *reinterpret_cast<const shortx4 *>(bp + XR);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, x0, acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, x1, acc1, 0, 0, 0);
-                    ap += 16;
-                    bp += kBf16BlockBytes;
-                }
-                tot0 += acc0;
-                tot1 += acc1;
-            }
-        }
-    }
-    // lane (block j = i16, row group kg) owns outputs 16 j + 4 kg + 0..3 of the tile
-    const int to = 16 * n0 + 16 * i16 + 4 * kg;
-    if (b0 < g.B && to + 3 < g.L) {
-        bf16_t *o0 = out + ((size_t)b0 * (size_t)g.C + (size_t)c) * (size_t)g.L + to;
-        st_elem4(o0, make_float4(tot0[0], tot0[1], tot0[2], tot0[3]));
-        if (b0 + 1 < g.B) st_elem4(o0 + (size_t)g.C * (size_t)g.L, make_float4(tot1[0], tot1[1], tot1[2], tot1[3]));
-    }
-}
 
 // ------------------------------------------------------------------------------------------------
 // Stage 1 of the weight gradient for long filters (eq. (dk_def)):
