@@ -95,8 +95,16 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
         return launch_status();
     };
     switch (T) {
-    case 1: return go(dwconv::corr_band_kernel<E, 1>);
-    case 2: return go(dwconv::corr_band_kernel<E, 2>);
+    case 1:
+        if constexpr (NL == 3) {
+            if (g.F < s.K) return go(dwconv::corr_band_kernel<E, 1, true>);
+        }
+        return go(dwconv::corr_band_kernel<E, 1>);
+    case 2:
+        if constexpr (NL == 3) {
+            if (g.F < s.K) return go(dwconv::corr_band_kernel<E, 2, true>);
+        }
+        return go(dwconv::corr_band_kernel<E, 2>);
     default:
         if constexpr (NL == 1) return go(dwconv::corr_band_kernel<E, 4>);
         else return -1;
