@@ -446,8 +446,9 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
 inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const void *out)
 {
     const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
-    if (nd <= kMfmaMaxND) return false;
     const RowsPlan rp = plan_rows(s);
+    if (rp.tall) return true;
+    if (nd <= kMfmaMaxND) return false;
     if (rp.batch) {
         int bd, bn;
         rows_batch_offsets(s.L, s.K, pad_eff, &bd, &bn);

@@ -192,6 +192,50 @@ def test_exact_bf16_tensors_on_different_halves(oracle_mod):
     _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "halves")
 
 
+# corr_band_kernel: rows of one and of several tiles and pieces, more and fewer columns than batch entries, filters in one
+# chunk and in several, longer than the row, tensors off every alignment
+@pytest.mark.parametrize("B,C,L,K,p,dtype,offset", [
+    (5, 2, 129, 129, 128, "f32", 0), (40, 2, 160, 100, 50, "f32", 0), (33, 3, 255, 300, 299, "f32", 1), (31, 2, 257, 140, 0, "f32", 0),
+    (7, 2, 512, 512, 0, "f32", 0), (1, 2, 1025, 201, 200, "f32", 3), (2, 3, 1056, 600, 300, "f32", 0), (2, 2, 300, 900, 400, "f32", 0),
+    (1, 1, 4096, 4096, 4095, "f32", 0), (3, 1, 4100, 6000, 5999, "f32", 2), (1, 2, 8192, 8192, 8191, "f32", 0), (9, 256, 1000, 170, 1, "f32", 0),
+    (33, 2, 65, 110, 109, "bf16", 0), (20, 2, 128, 128, 64, "bf16", 0), (40, 1, 120, 300, 100, "bf16", 0), (5, 3, 1000, 100, 3, "bf16", 1),
+    (1, 2, 4097, 4097, 2048, "bf16", 0), (2, 2, 2080, 513, 512, "bf16", 5), (1, 1, 20000, 9000, 8999, "bf16", 0), (64, 4, 512, 200, 7, "bf16", 0),
+])
+def test_exact_corr_band(oracle_mod, B, C, L, K, p, dtype, offset):
+    print(f"case exact corr_band {dtype} B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=21 + B + 3 * C + 5 * L, offset=offset, fused=False)
+
+
+# dw_band_kernel: one window of four to sixteen offsets and several, rows cut into virtual rows (fewer than five batch
+# entries), one, two and four groups of eight rows per stage, row ends inside a block, more slices than stages
+@pytest.mark.parametrize("B,C,L,K,p,dtype,offset", [
+    (70, 2, 132, 84, 0, "f32", 0), (35, 3, 131, 131, 65, "f32", 1), (17, 2, 192, 192, 191, "f32", 0), (1, 3, 1023, 150, 149, "f32", 0),
+    (2, 2, 1500, 300, 150, "f32", 2), (3, 2, 2048, 500, 0, "f32", 0), (4, 1, 4097, 700, 350, "f32", 3), (5, 1, 900, 2000, 1000, "f32", 0),
+    (9, 2, 1024, 1024, 1023, "f32", 0), (33, 260, 520, 160, 80, "f32", 0),
+    (70, 2, 116, 200, 100, "bf16", 0), (35, 3, 129, 84, 0, "bf16", 0), (18, 2, 201, 100, 99, "bf16", 1), (1, 3, 1024, 200, 199, "bf16", 0),
+    (2, 2, 1501, 300, 150, "bf16", 0), (4, 1, 4096, 530, 265, "bf16", 2), (6, 2, 1024, 128, 127, "bf16", 1), (5, 1, 900, 2000, 1000, "bf16", 0),
+    (9, 2, 2050, 1024, 1023, "bf16", 0),
+])
+def test_exact_dw_band(oracle_mod, B, C, L, K, p, dtype, offset):
+    print(f"case exact dw_band {dtype} B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=31 + B + 3 * C + 5 * L, offset=offset, fused=False)
+
+
+# ... and batches whose virtual row would be too long for 32-bit positions: rows of 129 to 512 positions go to the band kernels
+# with filters of any length (inputs in [-1, 1]: the weight gradient sums B L < 2^24 products)
+@pytest.mark.parametrize("B,K,p", [(12800, 66, 65), (15600, 16, 3)])
+def test_exact_band_huge_batch(oracle_mod, B, K, p):
+    L, tdt = 512, torch.float32
+    x, w, dy = small_ints((B, 1, L), 1, 1, tdt), small_ints((1, K), 2, 1, tdt), small_ints((B, 1, L), 3, 1, tdt)
+    xn, wn, dyn = as_f32_numpy(x), as_f32_numpy(w), as_f32_numpy(dy)
+    xd, wd, dyd = to_device(x), to_device(w), to_device(dy)
+    y, dx, dw = binding.dwconv_fwd(xd, wd, p), binding.dwconv_bwd_input(dyd, wd, p), binding.dwconv_bwd_weight(xd, dyd, K, p)
+    torch.cuda.synchronize()
+    _same("fwd", y, oracle_mod.fwd(xn, wn, p)[0], tdt, "huge batch")
+    _same("dx", dx, oracle_mod.bwd_input(dyn, wn, p)[0], tdt, "huge batch")
+    _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "huge batch")
+
+
 def _random_exact_shapes(n, seed):
     """Seeded shapes around every threshold of the dispatch (block-offset counts, row-length classes, channel counts
     that change the weight-gradient plan), each with a storage type and an element offset of the views."""
