@@ -103,15 +103,14 @@ RowsPlan plan_rows(const Shape &s)
         r.units = (s.B + dwconv::kRbRows - 1) / dwconv::kRbRows;
     }
     // Rows of nine to thirty-two blocks with more block offsets than the virtual-row kernels take (filters of the order
-    // of the row length): sixteen rows per tile with the filter window and the unit in LDS.
+    // of the row length), or a batch whose virtual row they cannot address: the band kernels, and weight-gradient slices that
+    // follow from units of four rows.  (bf16 up to twenty blocks: longer rows have the slices of long filters.)
     const int m = (s.L + 15) / 16;
-    // (bf16 up to twenty blocks: beyond, the long-filter kernels on the bf16 matrix instruction are faster - B1016 C128 L516
-    // K516 882 us per step there against 1389 us here at L = 512; fp32 2068 against 1373 us)
     // (rows that are not whole granules: they must start on a dword - any fp32 length, bf16 even lengths)
     const bool tall_rag = (s.L % 4) != 0 && nd > kMfmaMaxND && (s.dtype == DWCONV_F32 || (s.L % 2) == 0);      // (up to six offsets:
                                                                      // the kernels that load rows straight into LDS)
-    if (!batch && !vrows && ((s.L % 4) == 0 || tall_rag) && s.L > dwconv::kRbMaxL && m >= dwconv::kRtMinBlocks &&
-        m <= (s.dtype == DWCONV_F32 ? dwconv::kRtMaxBlocks : 20) &&
+    if (!batch && !vrows && ((s.L % 4) == 0 || tall_rag) && s.L > dwconv::kRbMaxL &&
+        m <= (s.dtype == DWCONV_F32 ? 32 : 20) &&
         (long long)dwconv::kRbRows * s.C * s.L * es < (1ll << 30)) {
         r.tall = true;
         r.units = (s.B + dwconv::kRbRows - 1) / dwconv::kRbRows;
@@ -136,102 +135,60 @@ int corr_entry(const void *in, const void *f, void *out, int B, int C, int L, in
 }
 
 // ------------------------------------------------------------------ weight gradient
-// Long filters: the assignment of block offsets to wave slots (dwconv::LongKDwTable), balanced by work.
-// Work of an offset d = the 64-position chunks in which it reaches the row; a group of n offsets runs n matrix
-// instructions over the union of its offsets' chunks.  Groups are cut greedily under a cap on size (9) and on
-// work; the cap is searched so that at most two groups per slot suffice and the busiest slot is as light as
-// possible; groups go to slots heaviest first, each to the least loaded slot that still has room.  The result
-// depends on (L, K, pad, slots) only and is cached.
-// Block offsets of the filter that have a block pair inside a row of ceil(L / 16) blocks (at least one).
-static void longk_dw_offsets(const Shape &s, int *dmin_out, int *dmax_out)
+// Which filters of more than six block offsets go to dw_band_kernel (us, kernels it replaces there -> dw_band_kernel):
+//   fp32, ordinary rows: from eleven offsets (B32 C256 L4096: K = 128 93 / 100, 160 114 -> 104, 300 185 -> 140, 4096 1142 -> 782;
+//     L4097 K4097 5288 -> 789); virtual rows from nine (L512: K = 100 89 / 98, 200 174 -> 106); rows of up to 512 positions that
+//     are neither: all (L256 K256 182 -> 103, L160 K100 108 -> 94)
+//   bf16, rows of whole 16-byte granules: from twelve (K = 128 35 / 39, 200 43 -> 40, 1024 186 -> 109), from seven where rows
+//     fill less than three quarters of their 1024-position segments (L256 K256 184 -> 39, L512 K100 41 / 41); other lengths: all
+//     (L4097 K100 309 -> 39)
+//   rows of at most 128 positions: bf16 above 112 (L128 K128 59 -> 40, L96 K96 42 / 53; fp32 L128 K128 66 / 92)
+static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
+{
+    const int nd = toeplitz_dmax(s.K, s.pad) - toeplitz_dmin(s.pad) + 1;
+    if (rp.tall) return true;
+    if (nd <= kMfmaMaxND) return false;
+    if (rp.batch) {
+        int bd, bn;
+        rows_batch_offsets(s.L, s.K, s.pad, &bd, &bn);
+        return s.dtype == DWCONV_BF16 && bn > kMfmaMaxND && s.L > 112;
+    }
+    if (rp.on) return nd >= 9;
+    if (s.dtype == DWCONV_F32) return nd >= 11 || s.L <= 512;
+    const bool filled = 4ll * s.L >= 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
+    return (s.L % 8) != 0 || nd >= (filled ? 12 : 7);
+}
+
+// Slices of dw_band_kernel on ordinary rows: about two workgroups per compute unit over channels, windows of offsets and
+// slices, a slice being two rows at least; two slices at least and a workspace of at most 64 MiB beyond that.  0: the slices
+// that the segments of the row give (times one per started sixteen offsets).  (More slices than stages: the surplus workgroups
+// write zeros.)
+static int dw_band_slices(const Shape &s, const RowsPlan &rp, int nd)
 {
     const int nb = (s.L + 15) / 16;
     int dmin = toeplitz_dmin(s.pad), dmax = toeplitz_dmax(s.K, s.pad);
     if (dmin < -(nb - 1)) dmin = -(nb - 1);
     if (dmax > nb - 1) dmax = nb - 1;
-    if (dmax < dmin) dmax = dmin;
-    *dmin_out = dmin;
-    *dmax_out = dmax;
-}
-
-std::shared_ptr<const dwconv::LongKDwTable> longk_dw_table(const Shape &s, int wgs, int *max_group)
-{
-    struct Entry { std::shared_ptr<const dwconv::LongKDwTable> table; int max_group; };
-    static std::mutex mu;
-    static std::map<std::array<int, 4>, Entry> cache;
-    const std::array<int, 4> key = {s.L, s.K, s.pad, wgs};
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) { *max_group = it->second.max_group; return it->second.table; }
-
-    // (only the block offsets that have a block pair inside a row: a filter longer than the row has offsets that reach nothing)
-    int dmin, dmax;
-    longk_dw_offsets(s, &dmin, &dmax);
-    const int NCH = (s.L + 63) / 64;
-    const int nslots = wgs * dwconv::kLkWaves;
-    auto fdiv = [](int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); };
-    auto ch_lo = [&](int d) { const int v = -fdiv(63 + 16 * d, 64); return v > 0 ? v : 0; };      // ceil((-63 - 16 d) / 64)
-    auto ch_hi = [&](int d) { const int v = fdiv(s.L - 1 - 16 * d, 64); return v < NCH - 1 ? v : NCH - 1; };
-    auto group_work = [&](int a, int n) {           // n offsets a .. a + n - 1
-        const int c = ch_hi(a) - ch_lo(a + n - 1) + 1;
-        return (long long)n * (c > 0 ? c : 0);
-    };
-    long long exact = 0;
-    for (int d = dmin; d <= dmax; ++d) exact += group_work(d, 1);
-    struct Group { int a, n; long long w; };
-    std::vector<Group> best_groups;
-    std::vector<int> best_slot;
-    long long best_max = -1;
-    for (int pct = 40; pct <= 400; pct += 4) {
-        const long long cap = exact * pct / (100LL * nslots) + 1;
-        std::vector<Group> groups;
-        for (int d = dmin; d <= dmax;) {
-            int n = 1;
-            while (d + n <= dmax && n < dwconv::kLkDwMaxGD && group_work(d, n + 1) <= cap) ++n;
-            groups.push_back({d, n, group_work(d, n)});
-            d += n;
-        }
-        if ((int)groups.size() > 2 * nslots || (int)groups.size() > dwconv::kLkDwMaxGroups) continue;
-        std::vector<int> order(groups.size());
-        for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return groups[x].w > groups[y].w; });
-        std::vector<long long> load(nslots, 0);
-        std::vector<int> count(nslots, 0), slot_of(groups.size(), 0);
-        for (int gi : order) {
-            int pick = -1;
-            for (int j = 0; j < nslots; ++j)
-                if (count[j] < 2 && (pick < 0 || load[j] < load[pick])) pick = j;
-            load[pick] += groups[gi].w;
-            ++count[pick];
-            slot_of[gi] = pick;
-        }
-        const long long mx = *std::max_element(load.begin(), load.end());
-        if (best_max < 0 || mx < best_max) { best_max = mx; best_groups = groups; best_slot = slot_of; }
+    if (rp.tall) {
+        // rows of nine to thirty-two blocks: windows of fifteen offsets, each with slices of sixteen rows at least
+        const long long nwin = (dmax - dmin + 1 + 14) / 15, units = (s.B + 3) / 4;
+        const long long su = (2LL * kComputeUnits + (long long)s.C * nwin - 1) / ((long long)s.C * nwin);
+        return (int)(std::min(su, (units + 3) / 4) * nwin);
     }
-    if (best_max < 0 || nslots > dwconv::kLkDwMaxSlots) {        // no assignment with two groups per slot
-        cache[key] = Entry{nullptr, 0};
-        *max_group = 0;
-        return nullptr;
+    if (nd <= mfma_max_nd_dw(s)) return 0;
+    if ((s.L % 4) == 0 && s.L <= 8192 && s.K <= 8192) {
+        const long long wgs = (dmax - dmin + 1 + 287) / 288;
+        long long rs = std::min((2LL * kComputeUnits + s.C * wgs - 1) / (s.C * wgs), std::min(128LL, (s.B + 1LL) / 2));
+        while (rs > 1 && 2 * rs * (long long)s.C * s.K * (long long)sizeof(float) > (64ll << 20)) --rs;
+        const long long bper = ((s.B + rs - 1) / rs + 1) / 2 * 2;
+        return (int)(2 * ((s.B + bper - 1) / bper));
     }
-    auto table = std::make_shared<dwconv::LongKDwTable>();
-    for (int i = 0; i < dwconv::kLkDwMaxGroups; ++i) { table->da[i] = 0; table->n[i] = 0; }
-    for (int j = 0; j < dwconv::kLkDwMaxSlots; ++j) table->g0[j] = table->g1[j] = dwconv::kLkDwNoGroup;
-    int mg = 1;
-    for (size_t i = 0; i < best_groups.size(); ++i) {
-        table->da[i] = (short)best_groups[i].a;
-        table->n[i] = (unsigned char)best_groups[i].n;
-        if (best_groups[i].n > mg) mg = best_groups[i].n;
-        const int j = best_slot[i];
-        if (table->g0[j] == dwconv::kLkDwNoGroup) table->g0[j] = (unsigned char)i;
-        else table->g1[j] = (unsigned char)i;
+    if ((s.L % (s.dtype == DWCONV_F32 ? 4 : 8)) == 0 && s.L >= kRaggedMinL) {
+        const long long items = (long long)s.B * ((s.L + kDwTT - 1) / kDwTT);
+        const long long sp = std::min((kTargetWaves / 4 + s.C - 1) / s.C, (items + 3) / 4);
+        return (int)(2 * std::max(sp, 1LL));
     }
-    static const int kGd[] = {1, 2, 3, 4, 6, 9};
-    int gd = 9;
-    for (int v : kGd)
-        if (v >= mg) { gd = v; break; }
-    cache[key] = Entry{table, gd};
-    *max_group = gd;
-    return table;
+    return 0;
 }
 
 // Depends on the shape only, so stage 1, stage 2 and the workspace query always agree.
@@ -292,14 +249,14 @@ DwPlan plan_dw(const Shape &s)
     p.segs_per_wave = (int)spw;
     p.items_per_slice = (int)per;
     p.S = (int)((items + per - 1) / per);
-    // seventeen to thirty-two block offsets: two launches of the register-resident kernel, each over half of
-    // the offsets and into its own slices (a launch writes zeros to the taps of the other half); stage 2 adds them
-    // (bf16: up to four launches over quarters of up to sixty-four offsets)
-    p.passes = (mfma_shape && nd > kMfmaMaxNDDw) ? (nd + kMfmaMaxNDDw - 1) / kMfmaMaxNDDw : 1;
-    if (p.passes > 1) {
-        p.single = false;
-        p.S *= p.passes;
+    p.band = dw_takes_band(s, p.rows);
+    if (p.band && !p.rows.on) {
+        const int slices = dw_band_slices(s, p.rows, nd);
+        if (slices > 0) { p.S = slices; p.single = false; }
+        else if (mfma_shape && nd > kMfmaMaxNDDw) { p.S *= (nd + kMfmaMaxNDDw - 1) / kMfmaMaxNDDw; p.single = false; }
     }
+    p.band_fits = (nd > kMfmaMaxND || p.rows.tall) && plan_dw_band(s, p.S, &p.bp);
+    p.band = p.band && p.band_fits;
     // the fused backward kernel of these shapes works on one channel per block: its own slice count
     p.S_fused = p.S;
     if (p.rows.batch && s.L <= dwconv::kRbBwdMaxL) {
@@ -317,80 +274,6 @@ DwPlan plan_dw(const Shape &s)
         const long long real_items = (long long)s.B * real_tiles;
         p.valu_tiles_per_row = (int)real_tiles;
         p.valu_items_per_slice = (int)((real_items + p.S - 1) / p.S);
-    }
-    // long filters: offsets are split over waves instead, partials land in exactly two slices
-    p.longk = false;
-    p.lk_wgs = p.lk_gd = 0;
-    p.lk_rs = 1; p.lk_bper = s.B;
-    const int NCH = (s.L + 63) / 64;
-    if (!p.rows.batch && nd > mfma_max_nd_dw(s) && s.K <= dwconv::kLkMaxK && (s.L % 4) == 0 && (s.L + 15) / 16 <= dwconv::kLkMaxBlocks &&
-        dwconv::longk_dw_lds_bytes(s.L, NCH) <= kMaxLdsBytes) {
-        const int per_wg = 2 * dwconv::kLkWaves * dwconv::kLkDwMaxGD;
-        int lk_dmin, lk_dmax;
-        longk_dw_offsets(s, &lk_dmin, &lk_dmax);
-        p.lk_wgs = (lk_dmax - lk_dmin + 1 + per_wg - 1) / per_wg;
-        p.lk_table = longk_dw_table(s, p.lk_wgs, &p.lk_gd);
-    }
-    p.manypass = false;
-    if (!p.rows.batch && !p.lk_table && nd > mfma_max_nd_dw(s) && (s.L % (s.dtype == DWCONV_F32 ? 4 : 8)) == 0 && s.L >= kRaggedMinL &&
-        s.L <= kMfmaMaxL && !p.rows.on) {
-        // filters (or rows) too long for the long-filter kernel's LDS: the register-resident kernel, sixteen block
-        // offsets per launch, every launch adding the taps it owns to one of two zero-filled sets of slices
-        p.manypass = true;
-        p.single = false;
-        p.wpb = dwconv::kWavesPerBlock;
-        p.passes = (nd + kMfmaMaxNDDw - 1) / kMfmaMaxNDDw;
-        long long sp = (kTargetWaves / p.wpb + s.C - 1) / s.C;       // workgroups per channel and launch
-        const long long all_items = (long long)s.B * (((long long)s.L + kDwTT - 1) / kDwTT);
-        if (sp > (all_items + p.wpb - 1) / p.wpb) sp = (all_items + p.wpb - 1) / p.wpb;
-        if (sp < 1) sp = 1;
-        p.S = (int)(2 * sp);
-        p.S_fused = p.S;
-        p.tiles_per_row = (int)(((long long)s.L + kDwTT - 1) / kDwTT);
-        p.valu_items_per_slice = (int)((all_items + p.S - 1) / p.S);
-        p.items_per_slice = p.valu_items_per_slice;
-    }
-    if (p.lk_table) {
-        p.longk = true;
-        // Workgroups: channels x groups of offsets.  Where that is fewer than two per compute unit (few channels, or rows
-        // so short that the offsets fit one workgroup) the batch is cut into slices too, each with its own two slices
-        // of partial sums (B78125 C1 L256 K700: one workgroup walked the whole batch, 112 ms; B128 C128 L4096 K4096: 128
-        // workgroups on 256 compute units).  At most 128, at least one pair of rows each, workspace at most 64 MiB.
-        long long rs = (2LL * kComputeUnits + (long long)s.C * p.lk_wgs - 1) / ((long long)s.C * p.lk_wgs);
-        if (rs > 128) rs = 128;
-        if (rs > (s.B + dwconv::kLkRows - 1) / dwconv::kLkRows) rs = (s.B + dwconv::kLkRows - 1) / dwconv::kLkRows;
-        while (rs > 1 && 2 * rs * (long long)s.C * s.K * (long long)sizeof(float) > (64ll << 20)) --rs;
-        if (rs < 1) rs = 1;
-        long long bper = ((s.B + rs - 1) / rs + dwconv::kLkRows - 1) / dwconv::kLkRows * dwconv::kLkRows;
-        rs = (s.B + bper - 1) / bper;
-        p.lk_rs = (int)rs;
-        p.lk_bper = (int)bper;
-        p.S = (int)(2 * rs);
-        p.S_fused = p.S;                                   // (no fused kernel for long filters: nothing needs more slices)
-        p.items_per_slice = (int)((items + p.S - 1) / p.S);       // the generic kernel, if it has to run, uses the same slices
-        p.valu_items_per_slice = (int)(((long long)s.B * p.valu_tiles_per_row + p.S - 1) / p.S);      // (of its own items: real rows)
-    }
-    p.tall_windows = 0;
-    if (p.rows.tall) {
-        // windows of fifteen relative block offsets (grid z), each with S / windows slices over units of four rows: about two
-        // workgroups per compute unit
-        int bd, bn;
-        rows_batch_offsets(s.L, s.K, s.pad, &bd, &bn);
-        const long long nwin = (bn + dwconv::kRtWindow - 1) / dwconv::kRtWindow;
-        const long long units = (s.B + 3) / 4;
-        long long su = (2LL * kComputeUnits + (long long)s.C * nwin - 1) / ((long long)s.C * nwin);
-        const long long su_max = (units + dwconv::kRtWaves - 1) / dwconv::kRtWaves;
-        if (su > su_max) su = su_max;
-        if (su > 4096) su = 4096;
-        if (su < 1) su = 1;
-        p.tall_windows = (int)nwin;
-        p.longk = false; p.lk_table = nullptr; p.manypass = false; p.single = false; p.passes = 1;
-        p.wpb = dwconv::kRtWaves;
-        p.S = (int)(su * nwin);
-        p.S_fused = p.S;
-        p.tiles_per_row = (int)units;
-        p.items_per_slice = (int)((units + su - 1) / su);
-        p.valu_items_per_slice = (int)(((long long)s.B * p.valu_tiles_per_row + p.S - 1) / p.S);
     }
     // the generic kernel on short rows: its items are the tiles of the virtual row of the channel
     p.valu_rows = plan_valu_rows(s);
@@ -507,12 +390,12 @@ int dwconv_bwd_weight(const void *x, const void *dy, void *dw, void *workspace, 
     if (rc != DWCONV_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *part = static_cast<float *>(workspace);
-    bool wrote_dw = false;
-    rc = (dtype == DWCONV_F32) ? launch_dw_partial_f32(x, dy, part, dw, &wrote_dw, s, p, st)
-                               : launch_dw_partial_bf16(x, dy, part, dw, &wrote_dw, s, p, st);
-    if (rc != DWCONV_OK || wrote_dw) return rc;
-    if (dtype == DWCONV_F32) return launch_dw_finalize<float>(part, dw, s, p, st);
-    return launch_dw_finalize<bf16_t>(part, dw, s, p, st);
+    DwPlan pf = p;
+    rc = (dtype == DWCONV_F32) ? launch_dw_partial_f32(x, dy, part, dw, &pf.S, s, p, st)
+                               : launch_dw_partial_bf16(x, dy, part, dw, &pf.S, s, p, st);
+    if (rc != DWCONV_OK || pf.S == 0) return rc;
+    if (dtype == DWCONV_F32) return launch_dw_finalize<float>(part, dw, s, pf, st);
+    return launch_dw_finalize<bf16_t>(part, dw, s, pf, st);
 }
 
 int dwconv_bwd_weight_noalloc(const void *x, const void *dy, void *dw, int B, int C, int L, int K, int pad_left,
@@ -578,7 +461,7 @@ int dwconv_bwd_is_fused(int B, int C, int L, int K, int pad_left, int dtype)
     const bool rows_fit = p.rows.on ? true      // (virtual rows; bf16: of even length, checked above)
                           : dtype == DWCONV_BF16 ? ((L % 8) == 0 || ((L % 2) == 0 && ((L % 4) != 0 ? ragged_rows_fused_ok(s, nd) : true)))
                                                  : ((L % 4) == 0 || ragged_rows_fused_ok(s, nd));
-    return (!p.longk && K >= kMfmaMinK && nd >= 2 && nd <= kMfmaMaxND && rows_fit && L <= kMfmaMaxL) ? 1 : 0;
+    return (K >= kMfmaMinK && nd >= 2 && nd <= kMfmaMaxND && rows_fit && L <= kMfmaMaxL) ? 1 : 0;
 }
 
 int dwconv_bwd_weight_single_pass(int B, int C, int L, int K, int pad_left, int dtype)
@@ -586,7 +469,7 @@ int dwconv_bwd_weight_single_pass(int B, int C, int L, int K, int pad_left, int 
     if (check_dw_shape(B, C, L, K, pad_left, dtype) != DWCONV_OK) return 0;
     const Shape s{B, C, L, K, pad_left, dtype};
     const DwPlan p = plan_dw(s);
-    return (p.single && p.S == 1 && !p.longk) ? 1 : 0;
+    return (p.single && p.S == 1) ? 1 : 0;
 }
 
 int dwconv_bwd_weight_slices(int B, int C, int L, int K, int pad_left, int dtype)

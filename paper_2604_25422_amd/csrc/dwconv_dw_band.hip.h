@@ -1,0 +1,400 @@
+// Stage 1 of the weight gradient (Sec. IV-A eq. (dk_def)) for filters of more than six 16-blocks, up to any length, on rows of
+// any length and alignment, on v_mfma_f32_32x32x16_bf16 in either storage type (fp32: three exact bf16 limbs per operand,
+// six of the nine limb products, see dwconv_band.hip.h).
+//
+//   G_d[q'][q] += X[m + d][q'] dY[m][q]      (32-blocks m, block offsets d),      dw[j] = sum over 32 d + q' - q + pad = j
+//
+// The sixteen entries of a contraction are eight rows of a channel at two neighbouring blocks: lane (q', half kg) holds element
+// q' of block m + d + kg of the eight rows, so LDS holds, per position, the eight rows side by side (16 bytes per limb), every
+// operand is one aligned 16-byte read whatever the offset, and staging transposes in registers: a thread brings four
+// positions of eight rows and writes four times eight rows.  Positions are permuted inside every 32 (pos ^ ((pos >> 3) & 3))
+// so that those writes fall on different banks.
+//
+// Workgroup (c, slice, window): 4 ND / KS offsets of one channel over every S-th stage; a stage is 8 RGN (virtual) rows x S32
+// blocks of dY and the blocks of x its offsets reach.  The waves split the offsets DG ways and the block pairs KS = 4 / DG
+// ways.  Few batch entries (fewer than five): rows are cut into nseg virtual rows of Lv positions, each with its own piece of
+// dY.
+// Several windows (more than twelve offsets in fp32, sixteen in bf16): a tap takes its products from two neighbouring
+// offsets, so a window shares its last offset with the next one and owns the taps that need no other window's offsets.
+//
+// What bounds it: at B8 C256 K = L = 8192 fp32 the matrix pipe (745 us where 206 G multiply-adds in six bf16 products take 520
+// at the 2.4 PFLOP/s a loop of nothing but this instruction reaches; the fp32 instruction it replaces 1100), bf16 the LDS reads (one
+// 16-byte read per lane and instruction: 232 us, before 250); with short rows the staging (B2048 C128 K = L = 256 fp32 206 us
+// of which two reads of memory are 104, before 366; bf16 L256 K256 39 us, before 184).  The reads of the next operand go
+// out ahead of each group of products, the loads of the next stage ahead of a stage's.  Error against 64 bits (fp32 long
+// filter): 2.4e-7, the fp32 instruction 9.4e-7.
+#pragma once
+#include "dwconv_band.hip.h"
+
+namespace dwconv {
+
+struct DwBandGeom {
+    int B, C, L, K, pad;
+    int dmin, nd;       // block offsets (of 32) that hold a tap and have a block pair inside a row
+    int ndw;            // offsets per window: ND (per wave) x DG
+    int DG;             // offset groups among the waves (KS = 4 / DG)
+    int nwin;           // window w: offsets from dmin + w (ndw - 1)
+    int nseg, Lv;       // virtual rows per row and their length (a multiple of 64; nseg == 1: the row)
+    int RGN;            // groups of eight virtual rows per stage
+    int S32;            // dY blocks per stage (even)
+    int nstep;          // stages along a virtual row
+    int stages;         // all stages
+    int rev;            // windows in falling order (the dear ones first)
+};
+constexpr int kDwBandThreads = 256;
+__host__ __device__ constexpr int dw_band_block_bytes(int NL) { return 32 * 16 * NL; }     // one 32-block of eight rows
+inline size_t dw_band_stage_bytes(int NL, int RGN, int S32, int ndw) { return (size_t)RGN * (size_t)(2 * S32 + ndw - 1) * dw_band_block_bytes(NL); }
+// One wave's diagonal image: 63 diagonals x 32 columns, pitch 34 (lane q writes diagonal c - q, so a pitch P puts the lanes
+// P - 1 floats apart: 33 left all of them on one bank, a third of the kernel's LDS cycles).
+constexpr int kDwBandDiagPitch = 34;
+constexpr int kDwBandDiag = 63 * kDwBandDiagPitch;
+inline size_t dw_band_lds_bytes(int NL, int RGN, int S32, int ndw, int ND)
+{
+    const size_t stage = dw_band_stage_bytes(NL, RGN, S32, ndw), ep = sizeof(float) * 4 * (size_t)(kDwBandDiag + 32 * ND + 32);
+    return stage > ep ? stage : ep;
+}
+
+// Four consecutive elements at any element-aligned address.
+struct __attribute__((packed, aligned(4))) Raw4F { unsigned v[4]; };
+struct __attribute__((packed, aligned(2))) Raw4H { unsigned v[2]; };
+__device__ __forceinline__ Raw4F load_raw4(const float *p) { return *reinterpret_cast<const Raw4F *>(p); }
+__device__ __forceinline__ Raw4H load_raw4(const bf16_t *p) { return *reinterpret_cast<const Raw4H *>(p); }
+// moved down by sh elements (0 .. 3), zeros behind; all zeros when zero
+__device__ __forceinline__ void fix_raw4(Raw4F &r, int sh, bool zero)
+{
+#pragma unroll
+    for (int step = 2; step > 0; step >>= 1) {
+        const bool on = (sh & step) != 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.v[i] = on ? (i + step < 4 ? r.v[i + step] : 0u) : r.v[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = zero ? 0u : r.v[i];
+}
+__device__ __forceinline__ void fix_raw4(Raw4H &r, int sh, bool zero)
+{
+    if (sh & 2) { r.v[0] = r.v[1]; r.v[1] = 0u; }
+    const int bits = 16 * (sh & 1);
+    r.v[0] = __builtin_amdgcn_alignbit(r.v[1], r.v[0], bits);
+    r.v[1] = r.v[1] >> bits;
+    r.v[0] = zero ? 0u : r.v[0];
+    r.v[1] = zero ? 0u : r.v[1];
+}
+__device__ __forceinline__ void zero_raw4(Raw4F &r, bool zero)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.v[i] = zero ? 0u : r.v[i];
+}
+__device__ __forceinline__ void zero_raw4(Raw4H &r, bool zero)
+{
+    r.v[0] = zero ? 0u : r.v[0];
+    r.v[1] = zero ? 0u : r.v[1];
+}
+// Eight rows x four positions -> per position the eight rows as limbs.
+__device__ __forceinline__ void transpose_limbs(const Raw4F (&r)[8], int pos, uintx4 (&out)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned p[3];
+        split_pair<3>(__uint_as_float(r[2 * i].v[pos]), __uint_as_float(r[2 * i + 1].v[pos]), p);
+        out[0][i] = p[0]; out[1][i] = p[1]; out[2][i] = p[2];
+    }
+}
+__device__ __forceinline__ void transpose_limbs(const Raw4H (&r)[8], int pos, uintx4 (&out)[1])
+{
+    const unsigned sel = (pos & 1) ? 0x07060302u : 0x05040100u;      // the upper or the lower halves of a pair of rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1].v[pos >> 1], r[2 * i].v[pos >> 1], sel);
+}
+
+template <typename E, int ND>
+__global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__restrict__ x, const E *__restrict__ dy,
+                                                                     float *__restrict__ part, E *__restrict__ dw_out,
+                                                                     const DwBandGeom g, int slices)
+{
+    constexpr int NL = Limbs<E>::N;
+    constexpr int PB = 16 * NL, BB = dw_band_block_bytes(NL);            // bytes of a position, of a block
+    extern __shared__ __align__(16) unsigned char dwb_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = blockIdx.x, sl = (int)blockIdx.y;
+    const int win = g.rev ? g.nwin - 1 - (int)blockIdx.z : (int)blockIdx.z;
+    const int NB32 = (g.L + 31) >> 5;
+    const int dlo = g.dmin + win * (g.ndw - 1), nd_here = min(g.ndw, g.nd - win * (g.ndw - 1));
+    const int KS = 4 / g.DG, dg = wave % g.DG, ks = wave / g.DG;
+    const int d0 = dlo + dg * ND, mine = min(ND, nd_here - dg * ND);     // this wave's offsets (mine <= 0: none)
+    const size_t CL = (size_t)g.C * (size_t)g.L;
+    const E *x_c = x + (size_t)c * (size_t)g.L, *dy_c = dy + (size_t)c * (size_t)g.L;
+    const int VR = g.B * g.nseg;
+
+    floatx16 acc[ND], low[NL == 3 ? ND : 1];
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            acc[i][k] = 0.f;
+            if constexpr (NL == 3) low[i][k] = 0.f;
+        }
+
+    // A stage: group vg of 8 RGN virtual rows, dY blocks yb0 .. yb0 + S32 - 1, x blocks xlo .. xlo + nx - 1.
+    struct Stage {
+        int st, vg, yb0, xlo, nx;
+    };
+    auto set_stage = [&](Stage &s) {
+        s.vg = s.st / g.nstep;
+        s.yb0 = (s.st - s.vg * g.nstep) * g.S32;
+        s.xlo = s.yb0 + dlo;
+        int xhi = s.xlo + g.S32 + g.ndw - 2;
+        if (g.nseg == 1) {
+            // (a block of zeros on both sides of the row: the other half of a pair that is half inside)
+            s.xlo = max(s.xlo, -1);
+            xhi = min(xhi, NB32);
+        }
+        s.nx = xhi - s.xlo + 1;
+    };
+    // the next stage in which some offset of the window meets a row (nx <= 0: none does); st >= stages: the end
+    auto advance = [&](Stage &s) {
+        do {
+            s.st += (int)gridDim.y;
+            if (s.st >= g.stages) return;
+            set_stage(s);
+        } while (s.nx <= 0);
+    };
+    // Staging: 64 WPR threads bring one group of eight rows, one item of four positions of x and one of dY each (the plan
+    // keeps a stage that small); the rows of an item are wave-uniform, so a load is a scalar base and a lane offset.  The
+    // items of a stage are loaded while the stage before it is multiplied.
+    const int WPR = 4 / g.RGN;
+    const int rg_ld = wave / WPR, it_ld = tid & (64 * WPR - 1);
+    decltype(load_raw4(x)) raw_x[8], raw_y[8];
+    auto row_of = [&](int vr, int &off) -> size_t {                      // element offset of (virtual) row vr; off: its first position
+        vr = min(vr, VR - 1);
+        const int b = g.nseg == 1 ? vr : vr / g.nseg;
+        off = g.nseg == 1 ? 0 : (vr - b * g.nseg) * g.Lv;
+        return (size_t)b * CL;
+    };
+    auto load_items = [&](const Stage &s) {
+        const int it = band_hide(it_ld), vr0 = (s.vg * g.RGN + rg_ld) * 8;
+        // (positions outside the row are loaded from inside it and put right below)
+        int ux = 32 * s.xlo + min(4 * it, 32 * s.nx - 4), uy = 32 * s.yb0 + min(4 * it, 32 * g.S32 - 4);
+        if (g.nseg == 1) {
+            ux = max(0, min(ux, g.L - 4));
+            uy = min(uy, g.L - 4);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const size_t row = (size_t)min(vr0 + r, VR - 1) * CL;
+                raw_x[r] = load_raw4(x_c + row + ux);
+                raw_y[r] = load_raw4(dy_c + row + uy);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                int off;
+                const size_t row = row_of(vr0 + r, off);
+                raw_x[r] = load_raw4(x_c + row + max(0, min(ux + off, g.L - 4)));
+                raw_y[r] = load_raw4(dy_c + row + max(0, min(uy + off, g.L - 4)));
+            }
+        }
+    };
+    // Rows past the batch, positions outside the row, positions of dY that belong to the next virtual row: zeros; a group of
+    // four that ends behind its row was loaded from further left.  u: the first position of the item in its virtual row.
+    auto put_right = [&](decltype(raw_x) &raw, int vr0, int u, int end) __attribute__((always_inline)) {
+        if (g.nseg == 1) {
+            const bool zero = u < 0 || u >= g.L;
+            const int over = u + 4 - g.L;
+            if ((g.L & 3) != 0 && __builtin_amdgcn_ballot_w64(!zero && over > 0) != 0) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) fix_raw4(raw[r], !zero && over > 0 ? over : 0, zero);
+            } else if (__builtin_amdgcn_ballot_w64(zero) != 0) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) zero_raw4(raw[r], zero);
+            }
+            if (vr0 + 8 > VR) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (vr0 + r >= VR) zero_raw4(raw[r], true);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                int off;
+                (void)row_of(vr0 + r, off);
+                const int v = u + off;
+                fix_raw4(raw[r], v + 4 > g.L && v < g.L ? (v + 4 - g.L) & 3 : 0, vr0 + r >= VR || v < 0 || v >= g.L || u >= end);
+            }
+        }
+    };
+    auto store_items = [&](const Stage &s) {
+        const int it = band_hide(it_ld), vr0 = (s.vg * g.RGN + rg_ld) * 8;
+        unsigned char *base = dwb_smem + rg_ld * ((s.nx + g.S32) * BB);
+        put_right(raw_x, vr0, 32 * s.xlo + 4 * it, 1 << 30);
+        put_right(raw_y, vr0, 32 * s.yb0 + 4 * it, g.Lv);
+        auto put = [&](const decltype(raw_x) &raw, unsigned char *dst) {
+            const int q = (4 * it) & 31, sw = (q >> 3) & 3;
+            dst += ((4 * it) & ~31) * PB;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uintx4 limbs[NL];
+                transpose_limbs(raw, j, limbs);
+#pragma unroll
+                for (int l = 0; l < NL; ++l) *reinterpret_cast<uintx4 *>(dst + ((q + j) ^ sw) * PB + 16 * l) = limbs[l];
+            }
+        };
+        if (4 * it < 32 * s.nx) put(raw_x, base);
+        if (4 * it < 32 * g.S32) put(raw_y, base + s.nx * BB);
+    };
+
+    Stage cur;
+    cur.st = sl - (int)gridDim.y;
+    cur.nx = 0;
+    advance(cur);
+    if (cur.st < g.stages) load_items(cur);
+    while (cur.st < g.stages) {
+        const int yb0 = cur.yb0, xlo = cur.xlo, nx = cur.nx;
+        const int rg_bytes = (nx + g.S32) * BB;                          // one group of eight rows: x blocks, dY blocks
+        __syncthreads();                                                 // everyone is done with the stage before
+        store_items(cur);
+        __syncthreads();
+        advance(cur);
+        if (cur.st < g.stages) load_items(cur);
+
+        int plo[ND], phi[ND];                                            // block pairs p (blocks yb0 + 2 p, + 1) per offset
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+            const int d = d0 + i;
+            plo[i] = 0;
+            phi[i] = g.S32 / 2 - 1;
+            if (g.nseg == 1) {
+                plo[i] = max(0, (-yb0 - d) >> 1);                        // ceil((-yb0 - d - 1) / 2)
+                phi[i] = min(min(g.S32, NB32 - yb0 + 1) / 2 - 1, (NB32 - 1 - yb0 - d) >> 1);
+            }
+            if (i >= mine) phi[i] = -(1 << 28);
+        }
+        const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
+        const int lane_off = (q ^ ((q >> 3) & 3)) * PB + kg * BB;
+        // pairs p = pa .. pb (those of this wave) for the offsets I0 .. I0 + N - 1
+        auto run = [&](auto i0c, auto nc, const unsigned char *xw, const unsigned char *yw, int pa, int pb) {
+            constexpr int I0 = decltype(i0c)::value, N = decltype(nc)::value;
+            pa += (ks - pa) & (KS - 1);
+            if (pa > pb) return;
+            const unsigned char *yp = yw + 2 * pa * BB, *xp = xw + (2 * pa + I0) * BB;
+            uintx4 y[2][NL], xv[2][NL];
+            auto read_y = [&](uintx4 (&to)[NL]) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(yp + 16 * l);
+            };
+            auto read_x = [&](uintx4 (&to)[NL], int i) {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(xp + i * BB + 16 * l);
+            };
+            auto multiply = [&](int i, const uintx4 (&a)[NL], const uintx4 (&b)[NL]) {
+                if constexpr (NL == 3) {
+                    low[i] = mfma32x32x16(a[2], b[0], low[i]);
+                    acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+                    low[i] = mfma32x32x16(a[0], b[2], low[i]);
+                    low[i] = mfma32x32x16(a[1], b[1], low[i]);
+                    low[i] = mfma32x32x16(a[1], b[0], low[i]);
+                    low[i] = mfma32x32x16(a[0], b[1], low[i]);
+                } else {
+                    acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+                }
+            };
+            read_y(y[0]);
+            read_x(xv[0], 0);
+#pragma unroll 1
+            for (int p = pa; p <= pb;) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (u == 0 || p <= pb) {
+                        const int by = p + KS <= pb ? 2 * KS * BB : 0;   // (past the last pair: the same addresses again)
+#pragma unroll
+                        for (int i = 0; i < N; ++i) {
+                            const int k = u * N + i;
+                            if (i + 1 < N) {
+                                read_x(xv[(k + 1) & 1], i + 1);
+                            } else {
+                                yp += by;
+                                xp += by;
+                                read_y(y[1 - u]);
+                                read_x(xv[(k + 1) & 1], 0);
+                            }
+                            multiply(I0 + i, xv[k & 1], y[u]);
+                        }
+                        p += KS;
+                    }
+                }
+            }
+        };
+        for (int rg = 0; rg < g.RGN; ++rg) {
+            const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + d0 - xlo) * BB;
+            const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
+            // the bounds fall with the offset: those active at a pair are the offsets a .. b with p in [plo[a], plo[a - 1]) and
+            // (phi[b + 1], phi[b]]
+            static_for<0, ND>([&](auto ac) {
+                constexpr int a = decltype(ac)::value;
+                static_for<a, ND>([&](auto bc) {
+                    constexpr int b = decltype(bc)::value;
+                    int pa = plo[a], pb = phi[b];
+                    if constexpr (a > 0) pb = min(pb, plo[a - 1] - 1);
+                    if constexpr (b + 1 < ND) pa = max(pa, phi[b + 1] + 1);
+                    run(ac, std::integral_constant<int, b - a + 1>{}, xw, yw, pa, pb);
+                });
+            });
+        }
+    }
+
+    // ---- diagonal sums: every wave those of its offsets (tap 32 i + e, e = q' - q + 31, of offset d0 + i), then the waves'
+    // tap rows added in wave order
+    __syncthreads();
+    float *img = reinterpret_cast<float *>(dwb_smem) + wave * kDwBandDiag;
+    float *taps = reinterpret_cast<float *>(dwb_smem) + 4 * kDwBandDiag;
+    constexpr int TW = 32 * ND + 32;
+    float *tap = taps + wave * TW;
+    for (int i = lane; i < TW; i += 64) tap[i] = 0.f;
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+        // lane (column q, half kg) holds rows q' = 8 (k / 4) + 4 kg + k % 4 in element k
+        const int q = lane & 31, kg = lane >> 5;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            float v = acc[i][k];
+            if constexpr (NL == 3) v += low[i][k];
+            img[(8 * (k >> 2) + 4 * kg + (k & 3) - q + 31) * kDwBandDiagPitch + q] = v;
+        }
+        wave_lds_fence();
+        if (lane < 63) {
+            const int q_lo = max(0, 31 - lane), q_hi = min(31, 62 - lane);
+            float sum = 0.f;
+            for (int qq = q_lo; qq <= q_hi; ++qq) sum += img[lane * kDwBandDiagPitch + qq];
+            tap[32 * i + lane] += sum;
+        }
+        wave_lds_fence();
+    }
+    __syncthreads();
+    // tap T = 0 .. 32 nd_here + 30 of the window is j = 32 dlo - 31 + pad + T; it owns lags j - pad in [32 dlo, 32 dhi), the first
+    // and the last window whatever lies beyond (taps no offset reaches are zero)
+    const int jw = 32 * dlo - 31 + g.pad;
+    const int j_lo = win == 0 ? 0 : 32 * dlo + g.pad, j_hi = win + 1 == g.nwin ? g.K : min(g.K, 32 * (dlo + nd_here - 1) + g.pad);
+    float *dst = part + ((size_t)sl * (size_t)g.C + (size_t)c) * (size_t)g.K;
+    for (int j = max(0, j_lo) + tid; j < j_hi; j += kDwBandThreads) {
+        const int t = j - jw;
+        float sum = 0.f;
+        if (t >= 0 && t < 32 * nd_here + 31) {
+            // wave (dg, ks) owns taps 32 ND dg .. 32 ND dg + 32 ND + 30
+            for (int w = 0; w < 4; ++w) {
+                const int tt = t - 32 * ND * (w % g.DG);
+                if (tt >= 0 && tt < 32 * ND + 31) sum += taps[w * TW + tt];
+            }
+        }
+        if (dw_out) {
+            st_elem(dw_out + (size_t)c * (size_t)g.K + (size_t)j, sum);
+        } else {
+            dst[j] = sum;
+            // (slices beyond those of this launch are part of the workspace's layout: zeros)
+            for (int o = sl + (int)gridDim.y; o < slices; o += (int)gridDim.y)
+                part[((size_t)o * (size_t)g.C + (size_t)c) * (size_t)g.K + (size_t)j] = 0.f;
+        }
+    }
+}
+
+}  // namespace dwconv

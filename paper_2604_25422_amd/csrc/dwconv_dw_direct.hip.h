@@ -118,25 +118,18 @@ constexpr int dw_direct_wave_floats(int ND)
     const int stage = 5 * 256 + kSegLen, gf = ND * 256, diag = ((16 * ND + 15) * 17 + 3) / 4 * 4;
     return stage > gf ? (stage > diag ? stage : diag) : (gf > diag ? gf : diag);
 }
-// Taps a wave hands to the block-level sum: all of them fit 16 ND when the offsets cover the whole filter; a launch over
-// part of the offsets (nine and more, see the j0 / j1 arguments of the kernel) owns up to 16 ND + 15 taps.
-constexpr int dw_direct_row_floats(int ND) { return 16 * ND + (ND >= 9 ? 16 : 0); }
+// Taps a wave hands to the block-level sum: all of them fit 16 ND.
+constexpr int dw_direct_row_floats(int ND) { return 16 * ND; }
 constexpr size_t dw_direct_lds_bytes(int ND, int W) { return (size_t)W * (size_t)(dw_direct_wave_floats(ND) + dw_direct_row_floats(ND)) * sizeof(float); }
 
 // W waves per block.  dw_out == nullptr: the block's sums go to slice blockIdx.y of part; otherwise (one
 // block per channel, gridDim.y == 1) they are the weight gradient itself and go to dw_out.
 // ROWS: short rows, the wave walks the virtual row of its channel (see RowsMap); B is then 1 and segs_per_row the
 // number of segments of the virtual row.
-// [j0, j1): the taps this launch owns, at most dw_direct_row_floats(ND) of them (0, K unless the block offsets of the
-// filter are split over several launches); the other taps of its slices are written as zeros, or, with own_only set,
-// left alone (filters with hundreds of block offsets: dozens of launches share two zero-filled sets of slices).
-// seg0: the first 1024-position segment of every row this launch walks (segs_per_row of them): a launch over offsets
-// far from lag 0 skips the segments whose x window lies outside the row.
 template <int ND, int W, bool ROWS>
 __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_direct_kernel(
     const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, float *__restrict__ dw_out,
-    int B, int C, int L, int K, int pad, int dmin, int segs_per_row, const RowsMap rm, int j0, int j1, int seg0,
-    int own_only)
+    int B, int C, int L, int K, int pad, int dmin, int segs_per_row, const RowsMap rm)
 {
     constexpr int XW = kSegLen + 16 * ND;          // staged x window (floats)
     constexpr int NGX = XW / 4;                    // its 16-byte granules: 4 full loads and a tail
@@ -196,11 +189,10 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_direct_k
                 // batches are walked from the last to the first: the input-gradient call that usually runs just
                 // before this one walks them upwards, so its last rows of dY are still in the last-level cache
                 const size_t row = ((size_t)(B - 1 - pb) * (size_t)C + (size_t)c) * (size_t)L;
-                const int t0 = (seg0 + pseg) * kSegLen;
+                const int t0 = pseg * kSegLen;
                 const int u0 = 4 * (t0 + 16 * dmin);
                 x_shift = u0 < 0 ? u0 : 0;
-                // (a window that starts past the end of the row - possible when dmin > 0, the second of two passes
-                // over the block offsets - gets an empty resource: every load returns zero)
+                // (a window that starts past the end of the row gets an empty resource: every load returns zero)
                 rx = row_tail_resource(x + row, L, u0 > 0 ? min(u0, 4 * L) : 0);
                 rg = row_tail_resource(dy + row, L, 4 * t0);
             }
@@ -260,7 +252,7 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_direct_k
             // beyond them, so only the first 4 lr chunks can add anything, lr = 1..3 the 256-position regions that hold
             // positions of the row; they need the loads up to x_lr (x0 g0 x1 g1 ... in issue order, the nine loads of this
             // segment being the last nine issued).  Then all nine loads of the next segment go out in the usual order.
-            const int left = L - (seg0 + seg) * kSegLen;
+            const int left = L - seg * kSegLen;
             if (left <= 3 * 256) {
                 const int lr = left <= 256 ? 1 : (left <= 512 ? 2 : 3);
                 if (lr == 1) wait_vmcnt_at_most<6>();
@@ -345,14 +337,12 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_direct_k
 
     // ---- per-wave diagonal sums, then the waves of the block in wave order
     static_assert(WREG >= ((16 * ND + 15) * 17 + 3) / 4 * 4, "diagonal image fits the wave's region");
-    dw_wave_diagonal_sums<ND>(G, s_mem[wave], s_dw[wave], lane, j0, j1, pad, dmin);
+    dw_wave_diagonal_sums<ND>(G, s_mem[wave], s_dw[wave], lane, K, pad, dmin);
     __syncthreads();
-    for (int j = own_only ? j0 + tid : tid; j < (own_only ? j1 : K); j += 64 * W) {
+    for (int j = tid; j < K; j += 64 * W) {
         float sum = 0.f;
-        if (j >= j0 && j < j1) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) sum += s_dw[w][j - j0];
-        }
+        for (int w = 0; w < W; ++w) sum += s_dw[w][j];
         if (dw_out) dw_out[(size_t)c * (size_t)K + (size_t)j] = sum;
         else part[((size_t)blockIdx.y * (size_t)C + (size_t)c) * (size_t)K + (size_t)j] = sum;
     }

@@ -17,11 +17,10 @@
 
 #include "dwconv_common.hip.h"
 #include "dwconv_dw_direct.hip.h"
-#include "dwconv_longk.hip.h"
 #include "dwconv_mfma.hip.h"
 #include "dwconv_rowbatch.hip.h"
-#include "dwconv_rowtall.hip.h"
 #include "dwconv_corr_direct.hip.h"
+#include "dwconv_dw_band.hip.h"
 
 namespace dwhost {
 
@@ -67,17 +66,16 @@ constexpr int kMfmaMinK = 1;      // (one and two taps ran 2.4x slower on the ve
                                   // against 133 us at three taps)
 constexpr int kMfmaMaxND = 6;          // fused backward, bf16, short rows
 constexpr int kMfmaMaxNDWide = 10;     // fp32 on long rows, K up to 130: whole-channel workgroups for dW still possible
-constexpr int kMfmaMaxNDDw = 16;       // fp32 on long rows, K up to 226: four-wave dW workgroups, two correlate waves per SIMD
-constexpr int kMfmaMaxNDDw2 = 32;      // dW in two passes over the block offsets (K up to 482), each into its own slices
-constexpr int kMfmaMaxNDDw3 = 48;      // fp32 dW in up to three passes (K up to 738)
-constexpr int kMfmaMaxNDDw4 = 64;      // bf16 dW in up to four passes (K up to 994): a pass is bound by memory there
+constexpr int kMfmaMaxNDDw = 16;       // virtual rows, and the unit in which dW slices of longer filters grow
+constexpr int kMfmaMaxNDDw3 = 48;      // fp32 dW slices: as many per segment group as started sixteen offsets up to here
+constexpr int kMfmaMaxNDDw4 = 64;      // ... bf16
 // forward, input gradient on ordinary rows with the Toeplitz operands in registers (more: corr_band_kernel)
 inline int mfma_max_nd(int dtype) { return dtype == DWCONV_F32 ? 12 : 10; }
-// dW stage 1 (bf16 above six offsets: rows of whole 16-byte granules only)
+// Block offsets up to which the slices of dW follow from the segments of the rows (beyond: dw_band_slices).  The number of
+// slices is part of the workspace's layout, whichever kernel fills them.
 inline int mfma_max_nd_dw(const Shape &s)
 {
     if (s.dtype == DWCONV_F32 || (s.L % 8) == 0) {
-        // two passes only where rows fill their 1024-position segments to three quarters (else the long-filter kernel)
         const long long padded = ((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen;
         return 4ll * s.L >= 3 * padded ? (s.dtype == DWCONV_F32 ? kMfmaMaxNDDw3 : kMfmaMaxNDDw4) : kMfmaMaxNDDw;
     }
@@ -87,16 +85,16 @@ inline int mfma_max_nd_dw(const Shape &s)
 // element-aligned; bf16: even lengths that are not multiples of eight).  The kernels that bring rows straight into
 // LDS take them when every row starts on a dword: their loads are range-checked per dword, so a granule that
 // straddles the end of its row is completed with zeros, and the last outputs of a row are stored by element.  Two to
-// six block offsets; fp32 also the register-staged forward / input-gradient kernel of seven to sixteen offsets (row
-// resources, the same range check) and the weight-gradient kernel in every number of launches; rows long enough that
+// six block offsets; fp32 also the register-staged forward / input-gradient kernel of seven and eight offsets (row
+// resources, the same range check) and the weight-gradient kernel of up to ten; rows long enough that
 // 1024-position segments are not mostly padding (the kernels skip what lies past the end of a row, the fused one does not).
 // Short rows of such lengths with up to six block offsets are walked as virtual rows instead (plan_rows): there the granule in
 // which a row ends is completed with zeros in LDS by the lane that loaded it.
-constexpr int kRaggedMinL = 768;           // the fused backward kernel on such rows (it contracts whole segments), many-launch dW
+constexpr int kRaggedMinL = 768;           // the fused backward kernel on such rows (it contracts whole segments)
 constexpr int kRaggedRowsMinL = 129;       // forward / input gradient / weight gradient (they skip the quarters or regions past
                                            // the end of a row): B4096 C128 L202 K48 798 us per step against 1343 us on the
                                            // generic kernels; the fused kernel took 1279 us for the backward half alone
-constexpr int kRaggedMaxNDF32 = 48;        // (fp32 weight gradient in up to three launches of sixteen offsets)
+constexpr int kRaggedMaxNDF32 = 48;        // (fp32: the offsets up to which dW slices follow from the segments)
 inline bool ragged_rows_ok(const Shape &s, int nd)
 {
     return s.K >= kMfmaMinK && nd >= 2 && nd <= (s.dtype == DWCONV_F32 ? kRaggedMaxNDF32 : kMfmaMaxND) && s.L >= kRaggedRowsMinL &&
@@ -119,8 +117,8 @@ constexpr int kMfmaMaxL = 1 << 27;      // byte offsets inside a row stay below 
 struct RowsPlan {
     bool on;
     bool batch;             // rows of at most 128 positions: sixteen rows of a channel per matrix tile instead
-    bool tall;              // rows of 132 to 512 positions with more block offsets than the virtual-row kernels take: sixteen
-                            // rows per tile with filter and unit in LDS (dwconv_rowtall.hip.h); `on` stays false
+    bool tall;              // rows of 132 to 512 positions with more block offsets than the virtual-row kernels take: the
+                            // band kernels; `on` stays false
     int units;              // batch: groups of sixteen rows per channel
     int nvs;                // 1024-position segments of the virtual row
     dwconv::RowsMap map;
@@ -226,17 +224,21 @@ bool allow_large_lds(Kernel kernel)
 
 enum DwKernel { DW_VALU_K8, DW_VALU_K32, DW_VALU_K64, DW_VALU_K256 };
 
+// Stage 1 on dw_band_kernel (filters of more than six block offsets).
+struct DwBandPlan {
+    dwconv::DwBandGeom g;
+    int ND;                // offsets per wave (the kernel is compiled per number)
+    int S;                 // slices it uses: at most those of the workspace
+    size_t lds;
+};
+bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p);
+
 struct DwPlan {
+    bool band;             // dw_band_kernel (dw_takes_band)
+    bool band_fits;        // it can run: where the kernel of the plan does not take the tensors (bf16 bases off a 16-byte granule)
+    DwBandPlan bp;
     DwKernel kernel;
-    bool longk;            // shape fits the long-filter matrix-core kernel (two zero-filled slices)
-    int lk_wgs, lk_gd;     // its workgroups per channel, largest group of offsets (accumulators per group)
-    int tall_windows;      // rows.tall: windows of fifteen relative block offsets (grid z), S / tall_windows slices each
-    int lk_rs, lk_bper;    // its batch slices (each with two slices of partial sums of its own) and batch entries per slice
-    std::shared_ptr<const dwconv::LongKDwTable> lk_table;   // which offsets every wave slot owns
-    int S;                 // partial slices per coefficient (all passes together)
-    int passes;            // launches of the stage-1 kernel, each over part of the block offsets into S / passes slices
-    bool manypass;         // filters beyond the long-filter kernel's LDS: `passes` launches of sixteen offsets into TWO
-                           // zero-filled sets of S / 2 slices (even launches the first set, odd launches the second)
+    int S;                 // partial slices per coefficient
     RowsPlan rows;         // short rows: stage 1 walks the virtual row of a channel
     int wpb;               // waves per block of the matrix-core stage-1 kernels
     int dw_nc;             // short rows, sixteen-row units: channels per block of the stage-1 kernel (1 or 2)
@@ -255,17 +257,16 @@ constexpr int kDwThreads = 256;
 DwPlan plan_dw(const Shape &s);
 
 // Launch entry points of the per-path units.  A return value of -1 (fused backward only) means "does not apply".
-// Rows of 132 to 512 positions with long filters (RowsPlan::tall; units of their own: dwconv_launch_rowtall_*.hip).
 int launch_corr_band_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_band_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
-int launch_dw_rowtall_f32(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p, hipStream_t st);
-int launch_dw_rowtall_bf16(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p, hipStream_t st);
 int launch_corr_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
-int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, bool *wrote_dw, const Shape &s,
+int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,
                           const DwPlan &p, hipStream_t st);
-int launch_dw_partial_bf16(const void *x, const void *dy, float *part, void *dw_out, bool *wrote_dw, const Shape &s,
+int launch_dw_partial_bf16(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,
                            const DwPlan &p, hipStream_t st);
+int launch_dw_band_f32(const void *x, const void *dy, float *part, void *dw_out, const DwBandPlan &p, int slices, hipStream_t st);
+int launch_dw_band_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwBandPlan &p, int slices, hipStream_t st);
 // (fp32, seven to sixteen block offsets; returns -1 when it does not apply)
 int launch_dw_partial_wide_f32(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                                int dmin, int nd, hipStream_t st);

@@ -119,9 +119,8 @@ int launch_bwd_fused(const void *dy, const void *x, const void *w, void *dx, flo
                      const Shape &s, const DwPlan &p, hipStream_t st)
 {
     *wrote_dw = false;
-    if (p.longk) return -1;
+    if (p.band) return -1;                                   // (two launches)
     if (p.rows.batch) return launch_bwd_rowbatch<T>(dy, x, w, dx, part, dw_out, wrote_dw, s, p, st);
-    if (p.rows.tall) return -1;                              // (two launches)
     // bf16 virtual rows: rows of even length (they start on a dword), pitch of whole 16-byte granules (otherwise the two
     // separate kernels)
     if (s.dtype == DWCONV_BF16 && p.rows.on &&

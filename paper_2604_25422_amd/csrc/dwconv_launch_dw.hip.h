@@ -100,15 +100,13 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
             if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
             hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                                static_cast<const float *>(x), static_cast<const float *>(dy), part,
-                               static_cast<float *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map, 0,
-                               s.K, 0, 0);
+                               static_cast<float *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map);
         } else {
             auto kernel = dwconv::dw_partial_direct_kernel<ND, W, false>;
             if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
             hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                                static_cast<const float *>(x), static_cast<const float *>(dy), part,
-                               static_cast<float *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map,
-                               0, s.K, 0, 0);
+                               static_cast<float *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map);
         }
     } else if (bf16_odd_rows(s, x, dy)) {
         // bf16 rows that do not all start on a dword: the same kernels on rows shifted to the dword in which they start
@@ -122,8 +120,7 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
             auto go = [&](auto kernel, int B, int segs) {
                 hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                                    static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
-                                   static_cast<bf16_t *>(dw_out), B, s.C, s.L, s.K, s.pad, dmin, segs, 0, s.K, 0, 0,
-                                   p.rows.map, aligned_to(x, 4) ? 0 : 1);
+                                   static_cast<bf16_t *>(dw_out), B, s.C, s.L, s.K, s.pad, dmin, segs, p.rows.map, aligned_to(x, 4) ? 0 : 1);
             };
             if (p.rows.on) go(dwconv::dw_partial_bf16_kernel<ND, W, true, true>, 1, p.tiles_per_row);
             // (a shifted row may reach one position into a segment more)
@@ -138,8 +135,7 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
         if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
         hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                            static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
-                           static_cast<bf16_t *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, 0, s.K, 0, 0,
-                           p.rows.map, 0);
+                           static_cast<bf16_t *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, p.rows.map, 0);
     } else if (p.rows.on) {
         // bf16 short rows (longer than 64 positions): the virtual row of a channel, widened to fp32 through registers
         auto kernel = dwconv::dw_partial_mfma_kernel<T, ND, W, true>;
@@ -157,8 +153,7 @@ int launch_dw_partial_mfma_ndw(const void *x, const void *dy, float *part, void 
         if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
         hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                            static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(dy), part,
-                           static_cast<bf16_t *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, 0, s.K, 0, 0,
-                           dwconv::RowsMap{0, 0, 0, 0, 0u, 0u}, 0);
+                           static_cast<bf16_t *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin, p.tiles_per_row, dwconv::RowsMap{0, 0, 0, 0, 0u, 0u}, 0);
     } else {
         auto kernel = dwconv::dw_partial_mfma_kernel<T, ND, W, false>;
         constexpr size_t lds = dwconv::dw_mfma_lds_bytes(ND, W);
@@ -193,19 +188,6 @@ int launch_dw_partial_mfma(const void *x, const void *dy, float *part, void *dw_
     const int nd = dmax - dmin + 1;
     // (rows of at most 128 positions: the sixteen-row kernel needs rows that start on a dword, nothing more)
     if (p.rows.batch) return (aligned_to(x, 4) && aligned_to(dy, 4)) ? launch_dw_rowbatch<T>(x, dy, part, dw_out, s, p, st) : -1;
-    if (p.rows.tall) {
-        if (!aligned_to(x, 4) || !aligned_to(dy, 4)) return -1;
-        if constexpr (std::is_same<T, float>::value) return launch_dw_rowtall_f32(x, dy, part, s, p, st);
-        else return launch_dw_rowtall_bf16(x, dy, part, s, p, st);
-    }
-    if (p.manypass) {
-        if constexpr (std::is_same<T, float>::value) {
-            if (!aligned_to(x, 16) || !aligned_to(dy, 16)) return -1;
-            return launch_dw_partial_wide_f32(x, dy, part, nullptr, s, p, dmin, nd, st);
-        } else {
-            return launch_dw_partial_wide_bf16(x, dy, part, nullptr, s, p, dmin, nd, st);
-        }
-    }
     if (s.K < kMfmaMinK || nd < 2 || nd > mfma_max_nd_dw(s) || s.L > kMfmaMaxL) return -1;
     // whole granules of four elements; otherwise only the kernels that load rows straight into LDS apply (see ragged_rows_ok)
     const bool granular = (s.L % 4) == 0 && aligned_to(x, 4 * sizeof(T)) && aligned_to(dy, 4 * sizeof(T));
@@ -232,74 +214,25 @@ int launch_dw_partial_mfma(const void *x, const void *dy, float *part, void *dw_
     }
 }
 
-template <typename T, int GD>
-int launch_dw_longk_gd(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p,
-                       const dwconv::LongKDwGeom &g, hipStream_t st)
-{
-    // all slices start at zero: a group stores only the taps it owns
-    auto fill = [&]() {
-        const size_t n = (size_t)p.S * (size_t)s.C * (size_t)s.K;
-        size_t fill_blocks = (n + 256 * 8 - 1) / (256 * 8);
-        if (fill_blocks > 65536) fill_blocks = 65536;
-        hipLaunchKernelGGL(dwconv::fill_zero_kernel<>, dim3((unsigned)fill_blocks), dim3(256), 0, st, part, n);
-    };
-    if constexpr (sizeof(T) == 2) {
-        // bf16 storage: raw rows in LDS, bf16 matrix instruction
-        const size_t lds = dwconv::longk_dw_bf16_lds_bytes(s.L);
-        if (lds > kMaxLdsBytes || !allow_large_lds(dwconv::dw_longk_bf16_kernel<GD>)) return -1;
-        fill();
-        hipLaunchKernelGGL((dwconv::dw_longk_bf16_kernel<GD>), dim3((unsigned)s.C, (unsigned)p.lk_wgs, (unsigned)p.lk_rs),
-                           dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const bf16_t *>(x),
-                           static_cast<const bf16_t *>(dy), part, g, *p.lk_table);
-    } else {
-        const size_t lds = dwconv::longk_dw_lds_bytes(s.L, g.NCH);
-        if (lds > kMaxLdsBytes || !allow_large_lds(dwconv::dw_longk_kernel<T, GD>)) return -1;
-        fill();
-        hipLaunchKernelGGL((dwconv::dw_longk_kernel<T, GD>), dim3((unsigned)s.C, (unsigned)p.lk_wgs, (unsigned)p.lk_rs),
-                           dim3(64 * dwconv::kLkWaves), lds, st, static_cast<const T *>(x), static_cast<const T *>(dy),
-                           part, g, *p.lk_table);
-    }
-    return launch_status();
-}
-
-// Returns -1 when the pointers do not fit the long-filter matrix-core kernel.
 template <typename T>
-int launch_dw_partial_longk(const void *x, const void *dy, float *part, const Shape &s, const DwPlan &p, hipStream_t st)
-{
-    if (!aligned_to(x, 4 * sizeof(T)) || !aligned_to(dy, 4 * sizeof(T))) return -1;
-    dwconv::LongKDwGeom g;
-    g.B = s.B; g.C = s.C; g.L = s.L; g.K = s.K; g.pad = s.pad;
-    g.dmin = toeplitz_dmin(s.pad); g.dmax = toeplitz_dmax(s.K, s.pad);
-    g.NCH = (s.L + 63) / 64;
-    g.bper = p.lk_bper;
-    if (p.S != 2 * p.lk_rs) return -1;
-    switch (p.lk_gd) {
-    case 1: return launch_dw_longk_gd<T, 1>(x, dy, part, s, p, g, st);
-    case 2: return launch_dw_longk_gd<T, 2>(x, dy, part, s, p, g, st);
-    case 3: return launch_dw_longk_gd<T, 3>(x, dy, part, s, p, g, st);
-    case 4: return launch_dw_longk_gd<T, 4>(x, dy, part, s, p, g, st);
-    case 6: return launch_dw_longk_gd<T, 6>(x, dy, part, s, p, g, st);
-    default: return launch_dw_longk_gd<T, 9>(x, dy, part, s, p, g, st);
-    }
-}
-
-template <typename T>
-int launch_dw_partial(const void *x, const void *dy, float *part, void *dw_out, bool *wrote_dw, const Shape &s,
+int launch_dw_partial(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,
                       const DwPlan &p, hipStream_t st)
 {
-    // dw_out: where a single-slice matrix-core launch may put the gradient itself (nullptr: always write part);
-    // *wrote_dw tells the caller whether it did.
-    if (wrote_dw) *wrote_dw = false;
-    if (p.longk) {
-        const int rc = launch_dw_partial_longk<T>(x, dy, part, s, p, st);
-        if (rc >= 0) return rc;
-    }
+    // dw_out: where a single-slice matrix-core launch may put the gradient itself (nullptr: always write part, all p.S slices);
+    // *slices tells the caller how many slices of part hold the sums (0: dw_out holds the gradient).
     void *direct = (p.single && p.S == 1) ? dw_out : nullptr;
-    const int rc = launch_dw_partial_mfma<T>(x, dy, part, direct, s, p, st);
-    if (rc >= 0) {
-        if (wrote_dw && direct && rc == DWCONV_OK) *wrote_dw = true;
-        return rc;
+    int rc = p.band ? -1 : launch_dw_partial_mfma<T>(x, dy, part, direct, s, p, st);
+    if (slices) *slices = direct ? 0 : p.S;
+    if (rc < 0 && p.band_fits) {
+        // (a caller that takes the gradient needs no more slices than the launch uses)
+        const int used = dw_out ? p.bp.S : p.S;
+        direct = p.bp.S == 1 ? dw_out : nullptr;
+        if (slices) *slices = direct ? 0 : used;
+        if constexpr (std::is_same<T, float>::value) rc = launch_dw_band_f32(x, dy, part, direct, p.bp, used, st);
+        else rc = launch_dw_band_bf16(x, dy, part, direct, p.bp, used, st);
     }
+    if (rc >= 0) return rc;
+    if (slices) *slices = p.S;
     switch (p.kernel) {
     case DW_VALU_K8: launch_dw_partial_valu<T, 8>(x, dy, part, s, p, st); break;
     case DW_VALU_K32: launch_dw_partial_valu<T, 32>(x, dy, part, s, p, st); break;

@@ -3,10 +3,10 @@
 
 namespace dwhost {
 
-int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, bool *wrote_dw, const Shape &s,
+int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,
                           const DwPlan &p, hipStream_t st)
 {
-    return launch_dw_partial<float>(x, dy, part, dw_out, wrote_dw, s, p, st);
+    return launch_dw_partial<float>(x, dy, part, dw_out, slices, s, p, st);
 }
 
 }  // namespace dwhost

@@ -23,8 +23,15 @@ int launch_dw_wide_multi_f32(int nd, const void *x, const void *dy, float *part,
     case 8: return launch_multi_nd<8>(x, dy, part, dw_out, s, p, dmin, st);
     case 9: return launch_multi_nd<9>(x, dy, part, dw_out, s, p, dmin, st);
     case 10: return launch_multi_nd<10>(x, dy, part, dw_out, s, p, dmin, st);
-    default: return -1;        // (eleven to sixteen offsets: four-wave workgroups only, the plan never asks for more)
+    default: return -1;
     }
+}
+
+int launch_dw_partial_wide_f32(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
+                               int dmin, int nd, hipStream_t st)
+{
+    if (p.wpb == 4) return launch_dw_wide_w4_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
+    return p.rows.on ? -1 : launch_dw_wide_multi_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
 }
 
 }  // namespace dwhost
