@@ -29,20 +29,13 @@
 namespace dwconv {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// Two fp32 values -> one dword of two bf16, rounded to nearest even.
-__device__ __forceinline__ unsigned pack_bf16(float x, float y)
-{
-    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{x, y}), bf16x2));
-}
 // The next limbs of a pair: what is left of it afterwards goes back to x, y.  CLAMP (first limb): the rounding must not
 // turn a finite value into infinity; the excess of a value beyond the largest bf16 (infinity and NaN among them) stays
 // in the second limb.

@@ -20,6 +20,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float v)
     return u >> 16;
 }
 
+// Two fp32 values -> one dword of two bf16, rounded to nearest even (one instruction).
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack_bf16(float x, float y)
+{
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{x, y}), bf16x2));
+}
+
 __device__ __forceinline__ float ld_elem(const float *p) { return *p; }
 __device__ __forceinline__ float ld_elem(const bf16_t *p) { return bf16_bits_to_f32(p->bits); }
 __device__ __forceinline__ void st_elem(float *p, float v) { *p = v; }
@@ -45,15 +53,15 @@ __device__ __forceinline__ void st_elem4_stream(float *p, float4 v)
 __device__ __forceinline__ void st_elem4(bf16_t *p, float4 v)
 {
     uint2 u;
-    u.x = f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
-    u.y = f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16);
+    u.x = pack_bf16(v.x, v.y);
+    u.y = pack_bf16(v.z, v.w);
     *reinterpret_cast<uint2 *>(p) = u;
 }
 __device__ __forceinline__ void st_elem4_stream(bf16_t *p, float4 v)
 {
     nt_uintx2 u;
-    u[0] = f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
-    u[1] = f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16);
+    u[0] = pack_bf16(v.x, v.y);
+    u[1] = pack_bf16(v.z, v.w);
     __builtin_nontemporal_store(u, reinterpret_cast<nt_uintx2 *>(p));
 }
 

@@ -87,7 +87,7 @@ int launch_bwd_rowbatch(const void *dy, const void *x, const void *w, void *dx, 
     };
     const int m = (s.L + 15) / 16;              // the kernel is compiled per (block offsets, 16-blocks of a row)
     auto launch_m = [&](auto k1, auto k2, auto k3, int ndv) -> int {
-        const size_t lds_rb = dwconv::rb_bwd_lds_bytes(s.L, ndv);
+        const size_t lds_rb = dwconv::rb_bwd_lds_bytes(s.L, ndv, (int)sizeof(T));
         return m == 1 ? launch_rb(k1, lds_rb) : m == 2 ? launch_rb(k2, lds_rb) : launch_rb(k3, lds_rb);
     };
     int rc = -1;

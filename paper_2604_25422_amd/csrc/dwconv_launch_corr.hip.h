@@ -51,8 +51,9 @@ int launch_corr_rowbatch_kernel(Kernel kernel, dwconv::RowBatchGeom &rg, int nc,
                                 const Shape &s, hipStream_t st)
 {
     // one resident round of waves: J per channel group, each walking units j, j + J, ...
+    // (bf16: as many as its registers allow - a wave has half the bytes in flight)
     const long long groups = s.C / nc;
-    const long long resident = corr_wave_slots(kernel, 64 * dwconv::kRbCorrWaves);
+    const long long resident = sizeof(T) == 2 ? resident_waves(kernel, 64 * dwconv::kRbCorrWaves) : corr_wave_slots(kernel, 64 * dwconv::kRbCorrWaves);
     long long J = resident / groups;
     if (J < 1) J = 1;
     if (J > rg.n_units) J = rg.n_units;
@@ -61,7 +62,7 @@ int launch_corr_rowbatch_kernel(Kernel kernel, dwconv::RowBatchGeom &rg, int nc,
     const long long blocks = (groups * J + dwconv::kRbCorrWaves - 1) / dwconv::kRbCorrWaves;
     if (blocks > 0x1fffffffLL) return -1;
     rg.J = (int)J;
-    const size_t lds = (size_t)dwconv::kRbCorrWaves * dwconv::rb_corr_wave_floats(s.L, nc) * sizeof(float);
+    const size_t lds = (size_t)dwconv::kRbCorrWaves * dwconv::rb_corr_wave_bytes(s.L, nc, (int)sizeof(T));
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(64 * dwconv::kRbCorrWaves), lds, st,
                        static_cast<const T *>(in), static_cast<const T *>(f), static_cast<T *>(out), rg);
     return launch_status();

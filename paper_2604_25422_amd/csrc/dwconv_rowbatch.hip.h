@@ -1,5 +1,10 @@
-// Short rows on the matrix cores, sixteen rows at a time (L <= 128; fp32, or bf16 storage widened to fp32 on the way
-// into LDS: fp32 matrix instructions and sums either way, one rounding at the store).  Rows are moved in granules of
+// Short rows on the matrix cores, sixteen rows at a time (L <= 128).  fp32: fp32 matrix instructions; bf16: the forward, input-
+// gradient and fused backward kernels on the bf16 matrix instruction (a sixteenth of the matrix time, half the LDS), the
+// separate weight-gradient kernel on rows widened to fp32; fp32 sums either way, one rounding at the store.
+// B16384 C128 L48 K48, widened to fp32 -> here: forward 129 -> 79 us, backward 223 -> 184 us, with the rows of four channels
+// moved as one piece (bwd_rowbatch_kernel) 109 us; fp32 backward, by that alone, 253 -> 232 us.  Now bound by memory (402 MB
+// at 5.1 TB/s are 78 us forward, 117 us backward for what does not come from the last-level cache).
+// Rows are moved in granules of
 // four elements; a row that is not whole granules (L % 4 != 0, one channel per wave) ends in a granule whose last
 // elements belong to the next row: they are replaced by zeros on the way into LDS, and on the way out only the
 // elements of the row are stored.  Rows need to start on a dword only (buffer loads; bf16: even L).
@@ -98,12 +103,81 @@ __device__ __forceinline__ void rb_store_granule(T *p, float4 v, int rem)
     }
 }
 
+// What the forward / input-gradient contraction works on in LDS: fp32 rows as they are (four instructions of four positions per
+// pair of blocks), bf16 rows as raw bf16 (one instruction of sixteen; half the LDS, no conversion on the way in).  Q: four
+// neighbouring elements of the image; Taps: a lane's four of a Toeplitz block.
+template <typename T> struct RbImage;
+template <> struct RbImage<float> {
+    typedef float E;
+    typedef float4 Q;
+    struct Taps { float v[4]; };
+    static __device__ __forceinline__ Q zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
+    static __device__ __forceinline__ Q granule(uintx4 raw, int rem) { return rb_granule<float>(raw, rem); }
+    static __device__ __forceinline__ Q tile(floatx4 a) { return make_float4(a[0], a[1], a[2], a[3]); }
+    static __device__ __forceinline__ void store(float *p, Q v, int rem) { rb_store_granule(p, v, rem); }
+    static __device__ __forceinline__ void set(Taps &t, int v, const float *f, int j, bool ok)
+    {
+        const float a = f[j];
+        t.v[v] = ok ? a : 0.f;
+    }
+    static __device__ __forceinline__ floatx4 contract(const Taps &t, Q q, floatx4 a)
+    {
+        a = mfma16x16x4(t.v[0], q.x, a);
+        a = mfma16x16x4(t.v[1], q.y, a);
+        a = mfma16x16x4(t.v[2], q.z, a);
+        return mfma16x16x4(t.v[3], q.w, a);
+    }
+};
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+// Sixteen lanes read sixteen times four bf16, lane i those at its own address p; it receives element i % 4 ... of four lanes:
+// the transposed 4 x 16 matrix whose row r lanes 4 r .. 4 r + 3 read.
+__device__ __forceinline__ shortx4 rb_read_transposed(const unsigned short *p)
+{
+    typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+    return __builtin_bit_cast(shortx4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)p));
+}
+template <> struct RbImage<bf16_t> {
+    typedef unsigned short E;
+    typedef uintx2 Q;
+    typedef shortx4 Taps;
+    static __device__ __forceinline__ Q zero() { return uintx2{0u, 0u}; }
+    static __device__ __forceinline__ Q granule(uintx2 raw, int rem)
+    {
+        if (rem) {
+            if (rem == 1) raw[0] &= 0xffffu;
+            raw[1] = rem == 3 ? raw[1] & 0xffffu : 0u;
+        }
+        return raw;
+    }
+    static __device__ __forceinline__ Q tile(floatx4 a) { return uintx2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])}; }
+    static __device__ __forceinline__ void store(bf16_t *p, Q v, int rem)
+    {
+        if (!rem) {
+            __builtin_nontemporal_store(v, reinterpret_cast<uintx2 *>(p));
+        } else {
+            unsigned short *o = reinterpret_cast<unsigned short *>(p);
+            o[0] = (unsigned short)v[0];
+            if (rem > 1) o[1] = (unsigned short)(v[0] >> 16);
+            if (rem > 2) o[2] = (unsigned short)v[1];
+        }
+    }
+    static __device__ __forceinline__ void set(Taps &t, int v, const bf16_t *f, int j, bool ok)
+    {
+        const short a = (short)f[j].bits;
+        t[v] = ok ? a : (short)0;
+    }
+    static __device__ __forceinline__ floatx4 contract(const Taps &t, Q q, floatx4 a)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(t, __builtin_bit_cast(shortx4, q), a, 0, 0, 0);
+    }
+};
+
 // LDS image of a unit in the correlate kernel, one per wave: row r of the unit at float r * pitch; inside it the
 // NC channels the wave owns, each rounded up to whole 16-blocks (the floats between the end of a row and the end
-// of its last block stay zero).  The pitch is 4 modulo 8 floats, so the 16-byte operand reads and tile writes of
+// of its last block stay zero).  The pitch is 16 bytes modulo 32, so the operand reads and tile writes of
 // sixteen rows spread over the banks.  The outputs of a unit replace its inputs in the same image.
-__host__ __device__ constexpr int rb_corr_pitch(int L, int NC) { return NC * ((L + 15) / 16 * 16) + 4; }
-__host__ __device__ constexpr int rb_corr_wave_floats(int L, int NC) { return kRbRows * rb_corr_pitch(L, NC); }
+__host__ __device__ constexpr int rb_corr_pitch(int L, int NC, int ES) { return NC * ((L + 15) / 16 * 16) + 16 / ES; }      // elements
+__host__ __device__ constexpr size_t rb_corr_wave_bytes(int L, int NC, int ES) { return (size_t)kRbRows * rb_corr_pitch(L, NC, ES) * ES; }
 constexpr int kRbCorrWaves = 4;   // waves per block: neighbouring channels, whose rows share cache lines
 
 // out[b, c, t] = sum_j in~[b, c, t + j - pad] * f_eff[c, j].
@@ -119,7 +193,10 @@ template <typename T, int ND, int NC, int MB, bool RAG>
 __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || ND > 6) ? 3 : kMfmaWavesPerSimd)) void corr_rowbatch_kernel(
     const T *__restrict__ in, const T *__restrict__ f, T *__restrict__ out, const RowBatchGeom g)
 {
-    constexpr int ES = (int)sizeof(T);          // bf16 storage is widened on the way into LDS; fp32 arithmetic
+    constexpr int ES = (int)sizeof(T);
+    typedef RbImage<T> Im;
+    typedef typename Im::E E;
+    typedef typename Im::Q Q;
     // MB: 16-blocks per row the kernel is compiled for (two channels per wave: 3, the register budget)
     static_assert(MB >= 1 && MB <= kRbMaxBlocks && (NC == 1 || MB <= 3) && (NC == 1 || !RAG), "row blocks");
     constexpr int NLD = NC * MB;                 // 16 rows * NC * 4 MB granules over 64 lanes
@@ -129,8 +206,8 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
     const int i16 = lane & 15;      // A: output position r;  B/D: row of the unit
     const int k4 = lane >> 4;       // contraction sub-index;  D: position group
     const int Lc = 16 * g.m;
-    const int Lo = NC * Lc + 4;
-    float *sw = dyn_lds + wave * (kRbRows * Lo);
+    const int Lo = NC * Lc + 16 / ES;
+    E *sw = reinterpret_cast<E *>(dyn_lds) + wave * (kRbRows * Lo);
 
     const int Cg = g.C / NC;                    // channel groups
     const int id = (int)blockIdx.x * kRbCorrWaves + wave;
@@ -153,7 +230,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
         img[i] = gi < NG ? (r * Lo + h * Lc + 4 * (cg - h * Lg)) | (RAG && cg == Lg - 1 ? (g.L & 3) : 0) : 0;
     }
     for (int i = lane; i < kRbRows * Lo / 4; i += 64)
-        *reinterpret_cast<float4 *>(sw + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<Q *>(sw + 4 * i) = Im::zero();
     wave_lds_fence();
 
     typename Raw4<T>::type pre[NLD];
@@ -172,7 +249,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
         for (int i = 0; i < NLD; ++i)
             if (i < nld && lane + 64 * i < NG) {
                 const int rem = RAG ? (img[i] & 3) : 0;
-                *reinterpret_cast<float4 *>(sw + (img[i] - rem)) = rb_granule<T>(pre[i], rem);
+                *reinterpret_cast<Q *>(sw + (img[i] - rem)) = Im::granule(pre[i], rem);
             }
     };
     prefetch(unit);
@@ -180,7 +257,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
     wave_lds_fence();
 
     // Toeplitz operands: A[h][d][v] (lane (r, k)) = f_eff[c0 + h][16 (dmin + d) + 4k + v - r + pad]
-    float A[NC][ND][4];
+    typename Im::Taps A[NC][ND];
 #pragma unroll
     for (int h = 0; h < NC; ++h) {
         const T *f_c = f + (size_t)(c0 + h) * (size_t)g.K;
@@ -191,11 +268,10 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
                 const int j = 16 * (g.dmin + d) + 4 * k4 + v - i16 + g.pad;
                 const bool ok = j >= 0 && j < g.K;
                 const int jc = ok ? (g.reverse ? (g.K - 1 - j) : j) : 0;
-                const float a = ld_elem(f_c + jc);
-                A[h][d][v] = ok ? a : 0.f;
+                Im::set(A[h][d], v, f_c, jc, ok);
             }
     }
-    float *sp = sw + i16 * Lo + 4 * k4;
+    E *sp = sw + i16 * Lo + 4 * k4;
 
     for (;;) {
         const int unit_n = unit + g.J;
@@ -214,11 +290,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
                     for (int d = 0; d < ND; ++d) {
                         const int mi = mo + g.dmin + d;
                         if (mi >= 0 && mi < g.m) {
-                            const float4 cur = *reinterpret_cast<const float4 *>(sp + h * Lc + 16 * mi);
-                            a4 = mfma16x16x4(A[h][d][0], cur.x, a4);
-                            a4 = mfma16x16x4(A[h][d][1], cur.y, a4);
-                            a4 = mfma16x16x4(A[h][d][2], cur.z, a4);
-                            a4 = mfma16x16x4(A[h][d][3], cur.w, a4);
+                            a4 = Im::contract(A[h][d], *reinterpret_cast<const Q *>(sp + h * Lc + 16 * mi), a4);
                         }
                     }
                 }
@@ -228,7 +300,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
 #pragma unroll
             for (int mo = 0; mo < MB; ++mo)
                 if (mo < g.m && 16 * mo + 4 * k4 < g.L)
-                    *reinterpret_cast<float4 *>(sp + h * Lc + 16 * mo) = make_float4(acc[mo][0], acc[mo][1], acc[mo][2], acc[mo][3]);
+                    *reinterpret_cast<Q *>(sp + h * Lc + 16 * mo) = Im::tile(acc[mo]);
         }
         wave_lds_fence();
         // every lane swaps its granules of the image: outputs out (stored as whole rows), inputs of the next unit in
@@ -243,9 +315,9 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
             for (int i = 0; i < NLD; ++i)
                 if (i < nld && lane + 64 * i < NG) {
                     const int rem = RAG ? (img[i] & 3) : 0;
-                    const float4 ov = *reinterpret_cast<const float4 *>(sw + (img[i] - rem));
-                    if (more) *reinterpret_cast<float4 *>(sw + (img[i] - rem)) = rb_granule<T>(pre[i], rem);
-                    if (gl_off[i] < lim) rb_store_granule(out_u + gl_off[i] / ES, ov, rem);
+                    const Q ov = *reinterpret_cast<const Q *>(sw + (img[i] - rem));
+                    if (more) *reinterpret_cast<Q *>(sw + (img[i] - rem)) = Im::granule(pre[i], rem);
+                    if (gl_off[i] < lim) Im::store(out_u + gl_off[i] / ES, ov, rem);
                 }
         }
         wave_lds_fence();
@@ -448,26 +520,28 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_rowbatch_kernel(
 
 // Fused backward for short rows: dx = correlate(dY, reversed w, pad' = K - 1 - pad) and stage 1 of the weight
 // gradient from ONE pass over dY (units of sixteen rows of one channel).  grid = (ceil(C / 4), S): the four waves
-// of a block own four neighbouring channels (their rows share cache lines) and slice blockIdx.y of the units,
-// walked from the last batch to the first; every wave writes its own slice of part (or dw itself when S == 1), so
-// there is no workgroup barrier.  Per unit a wave holds two LDS images: dY (row pitch
+// of a block own four neighbouring channels and slice blockIdx.y of the units, walked from the last batch to the first;
+// every wave writes its own slice of part (or dw itself when S == 1).  Memory is moved by the whole block, rows of the four
+// channels as one piece (four rows of 48 bf16 are three cache lines where a wave's own rows end inside lines), two
+// barriers per unit.  Per unit a wave holds two LDS images: dY (row pitch
 // 16 m + 4 floats, the layout of corr_rowbatch_kernel: 16-byte operand reads for dx, the tiles of dx replace dY in
 // place) and x (pitch rb_dw_pitch).  Order per unit: prefetch of the next unit's dY and x rows into registers;
 // G_d += x * dY; D tiles of dx from the dY image with the arithmetic of corr_rowbatch_kernel (same instruction
 // order per output, so dx is bit-identical to the separate call); the tiles replace dY; every lane swaps its
 // granules (dx out as whole rows, next dY in) and drains the next x rows.
 constexpr int kRbBwdMaxL = 48;
-__host__ __device__ constexpr int rb_bwd_dy_pitch(int L) { return (L + 15) / 16 * 16 + 4; }
-__host__ __device__ constexpr int rb_bwd_wave_floats(int L, int ND)
+__host__ __device__ constexpr int rb_bwd_dy_pitch(int L, int ES) { return (L + 15) / 16 * 16 + 16 / ES; }      // elements
+__host__ __device__ constexpr int rb_bwd_x_pitch(int L, int ES) { return ES == 2 ? rb_bwd_dy_pitch(L, ES) : rb_dw_pitch(L, 1); }
+__host__ __device__ constexpr int rb_bwd_wave_floats(int L, int ND, int ES)
 {
-    const int stage = kRbRows * (rb_bwd_dy_pitch(L) + rb_dw_pitch(L, 1));
+    const int stage = kRbRows * (rb_bwd_dy_pitch(L, ES) + rb_bwd_x_pitch(L, ES)) * ES / 4;
     const int diag = ((16 * ND + 15) * 17 + 3) / 4 * 4;
     return stage > diag ? stage : diag;
 }
 constexpr int kRbBwdWaves = 4;
-__host__ __device__ constexpr size_t rb_bwd_lds_bytes(int L, int ND)
+__host__ __device__ constexpr size_t rb_bwd_lds_bytes(int L, int ND, int ES)
 {
-    return (size_t)kRbBwdWaves * (size_t)(rb_bwd_wave_floats(L, ND) + rb_tap_floats(ND)) * sizeof(float);
+    return (size_t)kRbBwdWaves * (size_t)(rb_bwd_wave_floats(L, ND, ES) + rb_tap_floats(ND)) * sizeof(float);
 }
 
 // RAG: rows that are not whole granules (the masks and element stores of the partial granule cost registers this
@@ -478,52 +552,60 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
     float *__restrict__ part, T *__restrict__ dw_out, int B, int C, int L, int K, int pad, int dmin, int n_units)
 {
     constexpr int ES = (int)sizeof(T);
+    typedef RbImage<T> Im;
+    typedef typename Im::E E;
+    typedef typename Im::Q Q;
     // rows of at most kRbBwdMaxL positions (register budget: two prefetched tensors, Toeplitz operands, accumulators)
     static_assert(M >= 1 && 16 * M <= kRbBwdMaxL, "rows of M 16-blocks");
-    constexpr int NLD = (kRbRows * 4 * M + 63) / 64;
+    constexpr int THREADS = 64 * kRbBwdWaves;
+    constexpr int NLD = (kRbRows * kRbBwdWaves * 4 * M + THREADS - 1) / THREADS;
     constexpr int MB = M;
     constexpr int NR = 2 * M - 1;                             // relative block offsets of the weight gradient
     extern __shared__ __align__(16) float dyn_lds[];
-    const int wreg = rb_bwd_wave_floats(L, ND);
+    const int wreg = rb_bwd_wave_floats(L, ND, ES);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, k4 = lane >> 4;
-    const int c = kRbBwdWaves * (int)blockIdx.x + wave;
-    if (c >= C) return;                                       // (no workgroup barrier below)
+    const int c0 = kRbBwdWaves * (int)blockIdx.x;
+    const int nch = C - c0 < kRbBwdWaves ? C - c0 : kRbBwdWaves;      // (a wave without a channel works on zeros)
+    const int c = c0 + wave < C ? c0 + wave : C - 1;
     float *s_wave = dyn_lds + wave * wreg;
     float *s_dw = dyn_lds + kRbBwdWaves * wreg + wave * rb_tap_floats(ND);
     constexpr int m = M;
-    const int Ld = 16 * m + 4;                                // pitch of the dY image
-    const int Lp = rb_dw_pitch(L, 1);                         // pitch of the x image
-    float *sd = s_wave, *sx = s_wave + kRbRows * Ld;
+    const int Ld = 16 * m + 16 / ES;                            // pitch of the dY image
+    const int Lp = rb_bwd_x_pitch(L, ES);                         // pitch of the x image
+    E *sd = reinterpret_cast<E *>(s_wave), *sx = sd + kRbRows * Ld;
     // input-gradient geometry: pad' = K - 1 - pad, offsets -(dmin + ND - 1) .. -dmin
     const int padx = K - 1 - pad;
     const int dminx = -(dmin + ND - 1);
 
     const int CL = C * L;
     const int Lg = (L + 3) >> 2;                              // (the last granule partial when L % 4 != 0)
-    const int NG = kRbRows * Lg;
-    const int nld = (NG + 63) >> 6;
-    int gl_off[NLD], img_d[NLD], img_x[NLD];                  // img_d: float index (a multiple of 4) + elements of a partial granule
+    const int NG = kRbRows * nch * Lg;
+    const int nld = (NG + THREADS - 1) / THREADS;
+    int gl_off[NLD], img_d[NLD], img_x[NLD];                  // img_d: element index (a multiple of 4) + elements of a partial granule
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-        const int gi = lane + 64 * i;
-        const int r = gi / Lg, cg = gi - r * Lg;
-        gl_off[i] = gi < NG ? ES * (r * CL + 4 * cg) : kOutOfRow;
-        img_d[i] = gi < NG ? (r * Ld + 4 * cg) | (RAG && cg == Lg - 1 ? (L & 3) : 0) : 0;
-        img_x[i] = gi < NG ? r * Lp + 4 * cg : 0;
+        const int gi = tid + THREADS * i;
+        const int r = gi / (nch * Lg), rest = gi - r * (nch * Lg);
+        const int h = rest / Lg, cg = rest - h * Lg;
+        const int image = h * (wreg * 4 / ES);
+        gl_off[i] = gi < NG ? ES * (r * CL + h * L + 4 * cg) : kOutOfRow;
+        img_d[i] = gi < NG ? (image + r * Ld + 4 * cg) | (RAG && cg == Lg - 1 ? (L & 3) : 0) : 0;
+        img_x[i] = gi < NG ? image + kRbRows * Ld + r * Lp + 4 * cg : 0;
     }
+    E *images = reinterpret_cast<E *>(dyn_lds);
     for (int i = lane; i < kRbRows * (Ld + Lp) / 4; i += 64)
-        *reinterpret_cast<float4 *>(s_wave + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
-    wave_lds_fence();
+        *reinterpret_cast<Q *>(sd + 4 * i) = Im::zero();
+    __syncthreads();
 
     floatx4 G[NR];
 #pragma unroll
     for (int e = 0; e < NR; ++e) G[e] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int dmax = dmin + ND - 1;
     // Toeplitz operands of the input gradient: A[d][v] (lane (r, k)) = w[K - 1 - (16 (dminx + d) + 4k + v - r + padx)]
-    float A[ND][4];
+    typename Im::Taps A[ND];
     {
         const T *f_c = w + (size_t)c * (size_t)K;
 #pragma unroll
@@ -532,8 +614,7 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
             for (int v = 0; v < 4; ++v) {
                 const int j = 16 * (dminx + d) + 4 * k4 + v - i16 + padx;
                 const bool ok = j >= 0 && j < K;
-                const float a = ld_elem(f_c + (ok ? K - 1 - j : 0));
-                A[d][v] = ok ? a : 0.f;
+                Im::set(A[d], v, f_c, ok ? K - 1 - j : 0, ok);
             }
     }
 
@@ -543,9 +624,9 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
     auto prefetch = [&](int u) {
         const int b0 = kRbRows * (n_units - 1 - u);
         const int nr = B - b0 < kRbRows ? B - b0 : kRbRows;
-        const size_t first = ((size_t)b0 * (size_t)C + (size_t)c) * (size_t)L;
-        const uintx4 rd = rb_unit_resource(dy + first, nr, CL, L);
-        const uintx4 rx = rb_unit_resource(x + first, nr, CL, L);
+        const size_t first = ((size_t)b0 * (size_t)C + (size_t)c0) * (size_t)L;
+        const uintx4 rd = rb_unit_resource(dy + first, nr, CL, nch * L);
+        const uintx4 rx = rb_unit_resource(x + first, nr, CL, nch * L);
 #pragma unroll
         for (int i = 0; i < NLD; ++i)
             if (i < nld) {
@@ -560,35 +641,54 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
         release_after_wait(px);
 #pragma unroll
         for (int i = 0; i < NLD; ++i)
-            if (i < nld && lane + 64 * i < NG) {
+            if (i < nld && tid + THREADS * i < NG) {
                 const int rem = RAG ? (img_d[i] & 3) : 0;
-                *reinterpret_cast<float4 *>(sd + (img_d[i] - rem)) = rb_granule<T>(pd[i], rem);
-                *reinterpret_cast<float4 *>(sx + img_x[i]) = rb_granule<T>(px[i], rem);
+                *reinterpret_cast<Q *>(images + (img_d[i] - rem)) = Im::granule(pd[i], rem);
+                *reinterpret_cast<Q *>(images + img_x[i]) = Im::granule(px[i], rem);
             }
-        wave_lds_fence();
+        __syncthreads();
     }
-    float *sp = sd + i16 * Ld + 4 * k4;
+    E *sp = sd + i16 * Ld + 4 * k4;
     while (unit < n_units) {
         const int unit_n = unit + stride;
         const bool more = unit_n < n_units;
         if (more) prefetch(unit_n);
-        // weight gradient: four rows per instruction, accumulators by relative block offset (see dw_rowbatch_kernel)
-        static_for<0, kRbRows / 4>([&](auto gc) {
-            constexpr int g4 = decltype(gc)::value;
-            const float *xrow = sx + (4 * g4 + k4) * Lp + i16;
-            const float *grow = sd + (4 * g4 + k4) * Ld + i16;
-            float xa[M], gb[M];
+        // weight gradient, accumulators by relative block offset (see dw_rowbatch_kernel)
+        if constexpr (ES == 2) {
+            // all sixteen rows in one instruction: lane (q, k) takes rows 4 k .. 4 k + 3 of position 16 b + q, which the
+            // transposing read hands it when lane i of the sixteen reads four positions 4 (i % 4) of row 4 k + i / 4
+            const E *xr = sx + (4 * k4 + (i16 >> 2)) * Lp + 4 * (i16 & 3);
+            const E *gr = sd + (4 * k4 + (i16 >> 2)) * Ld + 4 * (i16 & 3);
+            shortx4 xa[M], gb[M];
             static_for<0, M>([&](auto bc) {
                 constexpr int b = decltype(bc)::value;
-                xa[b] = xrow[16 * b];
-                gb[b] = grow[16 * b];
+                xa[b] = rb_read_transposed(xr + 16 * b);
+                gb[b] = rb_read_transposed(gr + 16 * b);
             });
             static_for<0, M * M>([&](auto pc) {
                 constexpr int mo = decltype(pc)::value / M, mi = decltype(pc)::value % M;
                 constexpr int rel = mi - mo;
-                if (rel >= dmin && rel <= dmax) G[rel + M - 1] = mfma16x16x4(xa[mi], gb[mo], G[rel + M - 1]);
+                if (rel >= dmin && rel <= dmax)
+                    G[rel + M - 1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xa[mi], gb[mo], G[rel + M - 1], 0, 0, 0);
             });
-        });
+        } else {
+            static_for<0, kRbRows / 4>([&](auto gc) {
+                constexpr int g4 = decltype(gc)::value;
+                const E *xrow = sx + (4 * g4 + k4) * Lp + i16;
+                const E *grow = sd + (4 * g4 + k4) * Ld + i16;
+                float xa[M], gb[M];
+                static_for<0, M>([&](auto bc) {
+                    constexpr int b = decltype(bc)::value;
+                    xa[b] = xrow[16 * b];
+                    gb[b] = grow[16 * b];
+                });
+                static_for<0, M * M>([&](auto pc) {
+                    constexpr int mo = decltype(pc)::value / M, mi = decltype(pc)::value % M;
+                    constexpr int rel = mi - mo;
+                    if (rel >= dmin && rel <= dmax) G[rel + M - 1] = mfma16x16x4(xa[mi], gb[mo], G[rel + M - 1]);
+                });
+            });
+        }
         // input gradient: lane (row i16, position group k4) owns outputs 16 mo + 4 k4 + 0..3 of block mo
         floatx4 acc[MB];
 #pragma unroll
@@ -599,11 +699,7 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
                 for (int d = 0; d < ND; ++d) {
                     const int mi = mo + dminx + d;
                     if (mi >= 0 && mi < m) {
-                        const float4 cur = *reinterpret_cast<const float4 *>(sp + 16 * mi);
-                        a4 = mfma16x16x4(A[d][0], cur.x, a4);
-                        a4 = mfma16x16x4(A[d][1], cur.y, a4);
-                        a4 = mfma16x16x4(A[d][2], cur.z, a4);
-                        a4 = mfma16x16x4(A[d][3], cur.w, a4);
+                        a4 = Im::contract(A[d], *reinterpret_cast<const Q *>(sp + 16 * mi), a4);
                     }
                 }
             }
@@ -613,8 +709,8 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
 #pragma unroll
         for (int mo = 0; mo < MB; ++mo)
             if (mo < m && 16 * mo + 4 * k4 < L)
-                *reinterpret_cast<float4 *>(sp + 16 * mo) = make_float4(acc[mo][0], acc[mo][1], acc[mo][2], acc[mo][3]);
-        wave_lds_fence();
+                *reinterpret_cast<Q *>(sp + 16 * mo) = Im::tile(acc[mo]);
+        __syncthreads();                                      // (every wave's tiles stand in its image)
         wait_untracked_loads();
         release_after_wait(pd);
         release_after_wait(px);
@@ -622,26 +718,27 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
             const int b0 = kRbRows * (n_units - 1 - unit);
             const int nr = B - b0 < kRbRows ? B - b0 : kRbRows;
             const int lim = ES * nr * CL;
-            T *dx_u = dx + ((size_t)b0 * (size_t)C + (size_t)c) * (size_t)L;
+            T *dx_u = dx + ((size_t)b0 * (size_t)C + (size_t)c0) * (size_t)L;
 #pragma unroll
             for (int i = 0; i < NLD; ++i)
-                if (i < nld && lane + 64 * i < NG) {
+                if (i < nld && tid + THREADS * i < NG) {
                     const int rem = RAG ? (img_d[i] & 3) : 0;
-                    const float4 ov = *reinterpret_cast<const float4 *>(sd + (img_d[i] - rem));
+                    const Q ov = *reinterpret_cast<const Q *>(images + (img_d[i] - rem));
                     if (more) {
-                        *reinterpret_cast<float4 *>(sd + (img_d[i] - rem)) = rb_granule<T>(pd[i], rem);
-                        *reinterpret_cast<float4 *>(sx + img_x[i]) = rb_granule<T>(px[i], rem);
+                        *reinterpret_cast<Q *>(images + (img_d[i] - rem)) = Im::granule(pd[i], rem);
+                        *reinterpret_cast<Q *>(images + img_x[i]) = Im::granule(px[i], rem);
                     }
-                    if (gl_off[i] < lim) rb_store_granule(dx_u + gl_off[i] / ES, ov, rem);
+                    if (gl_off[i] < lim) Im::store(dx_u + gl_off[i] / ES, ov, rem);
                 }
         }
-        wave_lds_fence();
+        __syncthreads();
         unit = unit_n;
     }
 
     // ---- diagonal sums of this wave's accumulators: its slice of the partial sums
     rb_diagonal_sums<NR>(G, M, s_wave, s_dw, lane, K, pad, dmin, ND);
     wave_lds_fence();
+    if (wave >= nch) return;
     const int j0 = rb_tap_j0(pad, dmin), j1 = rb_tap_j1(K, pad, dmin, ND);      // (the other taps of a longer filter are zero)
     for (int j = lane; j < K; j += 64) {
         const size_t o = (size_t)c * (size_t)K + (size_t)j;

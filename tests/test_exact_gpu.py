@@ -236,6 +236,18 @@ def test_exact_band_huge_batch(oracle_mod, B, K, p):
     _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "huge batch")
 
 
+# bf16, sixteen rows per tile: one to eight blocks per row, two to six block offsets, one and two channels per wave, row ends inside
+# a granule of four, units that the batch does not fill, filters longer than the row
+@pytest.mark.parametrize("offset", [0, 2])
+@pytest.mark.parametrize("B,C,L,K,p", [
+    (16, 2, 48, 48, 24), (17, 6, 48, 33, 32), (33, 4, 16, 2, 1), (40, 5, 14, 14, 13), (31, 8, 30, 20, 0), (15, 4, 44, 64, 32), (100, 12, 48, 66, 65),
+    (70, 7, 46, 48, 47), (50, 4, 6, 5, 2), (16, 4, 32, 31, 15), (65, 3, 60, 16, 8), (90, 4, 62, 40, 39), (20, 2, 64, 90, 45), (18, 3, 50, 300, 150),
+])
+def test_exact_bf16_sixteen_rows(oracle_mod, B, C, L, K, p, offset):
+    print(f"case exact bf16 sixteen rows B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, "bf16", seed=41 + B + 3 * C + 5 * L, offset=offset)
+
+
 def _random_exact_shapes(n, seed):
     """Seeded shapes around every threshold of the dispatch (block-offset counts, row-length classes, channel counts
     that change the weight-gradient plan), each with a storage type and an element offset of the views."""
