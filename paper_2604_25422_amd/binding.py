@@ -84,11 +84,13 @@ def _check(status: int):
         raise DwconvError(status, status_string(status))
 
 
+_DTYPE_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is not None:
+        return code
     raise TypeError(f"unsupported dtype {t.dtype}: float32 or bfloat16 storage only")
 
 
@@ -96,7 +98,7 @@ def _on_current_device(t: torch.Tensor, name: str):
     """The library enqueues on the current stream of the current device: every tensor must live there."""
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
-    if t.device.index != torch.cuda.current_device():
+    if t.get_device() != torch._C._cuda_getDevice():
         raise ValueError(f"{name} is on {t.device}, the current device is cuda:{torch.cuda.current_device()}")
 
 
@@ -119,7 +121,9 @@ def _dev2(t: torch.Tensor, name: str, C: int, K: int | None = None, dtype=None):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device, on which every tensor of a call lives (a GPU tensor exists, so the
+    runtime is up).  The raw queries: a Stream object per call costs what the rest of a small call's checks do."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def dwconv_fwd(x: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tensor | None = None) -> torch.Tensor:
@@ -129,7 +133,7 @@ def dwconv_fwd(x: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tenso
     if w.dtype != x.dtype:
         raise TypeError("x and w must share a dtype")
     y = torch.empty_like(x) if out is None else _dev3(out, "out")
-    if y.shape != x.shape or y.dtype != x.dtype:
+    if out is not None and (y.shape != x.shape or y.dtype != x.dtype):
         raise ValueError("out must match x")
     _check(lib().dwconv_fwd(x.data_ptr(), w.data_ptr(), y.data_ptr(), B, C, L, K, int(pad_left), _dtype_code(x), _stream()))
     return y
@@ -142,7 +146,7 @@ def dwconv_bwd_input(dy: torch.Tensor, w: torch.Tensor, pad_left: int, out: torc
     if w.dtype != dy.dtype:
         raise TypeError("dy and w must share a dtype")
     dx = torch.empty_like(dy) if out is None else _dev3(out, "out")
-    if dx.shape != dy.shape or dx.dtype != dy.dtype:
+    if out is not None and (dx.shape != dy.shape or dx.dtype != dy.dtype):
         raise ValueError("out must match dy")
     _check(lib().dwconv_bwd_input(dy.data_ptr(), w.data_ptr(), dx.data_ptr(), B, C, L, K, int(pad_left), _dtype_code(dy), _stream()))
     return dx
@@ -217,7 +221,7 @@ def dwconv_bwd(dy, x, w, pad_left: int, workspace=None, out_dx=None, out_dw=None
     wd = _dev2(w, "w", C, K, x.dtype)
     dx = torch.empty_like(dy) if out_dx is None else _dev3(out_dx, "out_dx")
     dw = torch.empty((C, K), dtype=x.dtype, device=x.device) if out_dw is None else _dev2(out_dw, "out_dw", C, K, x.dtype)
-    if dx.shape != dy.shape or dx.dtype != dy.dtype:
+    if out_dx is not None and (dx.shape != dy.shape or dx.dtype != dy.dtype):
         raise ValueError("out_dx must be shaped and typed like dy")
     _check(lib().dwconv_bwd(dy.data_ptr(), x.data_ptr(), wd.data_ptr(), dx.data_ptr(), dw.data_ptr(),
                             workspace.data_ptr(), nbytes, B, C, L, K, int(pad_left), _dtype_code(x), _stream()))
