@@ -172,7 +172,10 @@ int launch_corr_vrows_kernel(Kernel kernel, dwconv::CorrGeom g, const RowsPlan &
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, static_cast<const T *>(in),
                        static_cast<const T *>(f), static_cast<T *>(out), g, rp.map);
     return launch_status();
-}
+}// (fp32, seven to twelve block offsets on virtual rows: a translation unit of its own, dwconv_launch_corr_rows_f32.hip)
+int launch_corr_vrows_wide_f32(const dwconv::CorrGeom &g, const RowsPlan &rp, int nd, const void *in, const void *f, void *out,
+                               const Shape &s, hipStream_t st);
+
 // Returns -1 when the shape or the pointers do not fit the matrix-core kernel.
 template <typename T>
 int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
@@ -346,6 +349,7 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
             case 6: return launch_rows(dwconv::corr_mfma_kernel<T, 6, true>);
             default: break;
             }
+            if constexpr (std::is_same<T, float>::value) return launch_corr_vrows_wide_f32(g, rp, nd, in, f, out, s, st);
             return -1;
         }
     }
@@ -443,7 +447,9 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
 //     all (L4097: K = 100 119 -> 65, 4097 3213 -> 200)
 //   short rows with more than six offsets: virtual rows (fp32 L512 K100 91 -> 75, L160 81 -> 73) and rows of up to 512
 //     positions with filters of their own length (L256 K256 fp32 101 -> 76, bf16 105 -> 38), any alignment; rows of at most
-//     128 positions: bf16 above 64 (L128 K128 61 -> 35; fp32 L96 K96 48 / 59)
+//     128 positions: bf16 above 64 (L128 K128 61 -> 35; fp32 L96 K96 48 / 59).  Virtual rows of more than 512 positions (fp32)
+//     keep the register-resident kernel up to twelve offsets: their blocks do not fill the tiles of an item (B200 C32 L700 K80
+//     15.4 / 18.6)
 inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const void *out)
 {
     const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
@@ -455,7 +461,8 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
         rows_batch_offsets(s.L, s.K, pad_eff, &bd, &bn);
         return s.dtype == DWCONV_BF16 && bn > kMfmaMaxND && s.L > 64;
     }
-    if (rp.on || s.L <= 512) return true;
+    if (s.L <= 512) return true;
+    if (rp.on) return nd > 12 || !aligned_to(in, 16) || !aligned_to(out, 16);
     const bool filled = 4ll * s.L >= 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
     if (s.dtype == DWCONV_F32) return nd >= ((s.L % 4) != 0 ? 9 : filled ? 13 : 11);
     return (s.L % 8) != 0 || !aligned_to(in, 16) || !aligned_to(out, 16) || nd >= (filled ? 11 : 7);
