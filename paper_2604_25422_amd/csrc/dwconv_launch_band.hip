@@ -46,7 +46,7 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
         if (g.PB > row_tiles * NBk) g.PB = row_tiles * NBk;
         const int whole = nb32 + 2 * (NBk - 1);
         for (int F = s.K < 32768 ? (s.K + 1) & ~1 : 32768;; F = (F - 1) / 32 * 32) {
-            if (F <= 64 || (whole_filter && F < s.K)) return false;
+            if (F < s.K && (F <= 64 || whole_filter)) return false;       // (a chunk is 65 taps at least; a shorter filter is one chunk)
             g.F = F;
             int wb = g.PB + (F + 46) / 32 + 2;
             if (wb > whole) wb = whole;

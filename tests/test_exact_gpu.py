@@ -236,6 +236,31 @@ def test_exact_band_huge_batch(oracle_mod, B, K, p):
     _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "huge batch")
 
 
+# ... whichever length the filter has: which kernels a call launches, by the profiler's record of it (a result alone cannot show
+# that a call fell back to the vector ALU)
+def _kernels(call):
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "dwconv::" in e.name]
+
+
+@pytest.mark.parametrize("B,L,K,p,dtype", [(47300, 364, 19, 9, "f32"), (16000, 512, 64, 63, "f32"), (35000, 364, 2, 0, "f32"),
+                                           (46000, 304, 7, 3, "bf16"), (42000, 320, 66, 10, "bf16")])
+def test_band_kernel_takes_short_filters_of_huge_batches(oracle_mod, B, L, K, p, dtype):
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    print(f"case huge batch {dtype} B{B} L{L} K{K} p{p}", flush=True)
+    x, w = small_ints((B, 1, L), 1, LIM, tdt), small_ints((1, K), 2, LIM, tdt)
+    xd, wd = to_device(x), to_device(w)
+    out = {}
+    names = _kernels(lambda: out.update(y=binding.dwconv_fwd(xd, wd, p), dx=binding.dwconv_bwd_input(xd, wd, p)))
+    xn, wn = as_f32_numpy(x), as_f32_numpy(w)
+    _same("fwd", out["y"], oracle_mod.fwd(xn, wn, p)[0], tdt, "huge batch")
+    _same("dx", out["dx"], oracle_mod.bwd_input(xn, wn, p)[0], tdt, "huge batch")
+    assert len(names) == 2 and all("corr_band_kernel" in n for n in names), names
+
+
 # bf16, sixteen rows per tile: one to eight blocks per row, two to six block offsets, one and two channels per wave, row ends inside
 # a granule of four, units that the batch does not fill, filters longer than the row
 @pytest.mark.parametrize("offset", [0, 2])
