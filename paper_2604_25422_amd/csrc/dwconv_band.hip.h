@@ -36,27 +36,30 @@ __device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The next limbs of a pair: what is left of it afterwards goes back to x, y.  CLAMP (first limb): the rounding must not
-// turn a finite value into infinity; the excess of a value beyond the largest bf16 (infinity and NaN among them) stays
-// in the second limb.
-template <bool CLAMP>
+// The next limbs of a pair: what is left of it afterwards goes back to x, y.
 __device__ __forceinline__ unsigned take_limb(float &x, float &y)
 {
-    constexpr float kMaxBf16 = 0x1.fep127f;
-    const unsigned p = CLAMP ? pack_bf16(__builtin_amdgcn_fmed3f(x, -kMaxBf16, kMaxBf16), __builtin_amdgcn_fmed3f(y, -kMaxBf16, kMaxBf16))
-                             : pack_bf16(x, y);
+    const unsigned p = pack_bf16(x, y);
     x -= __uint_as_float(p << 16);
     y -= __uint_as_float(p & 0xffff0000u);
     return p;
 }
-template <int NL>
-__device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[NL])
+// The three limbs of HALF of x and of y.  Rounding may take a first limb (and a product of two) up to 2^-8 past its value: with
+// halves that never turns a finite operand, or a product inside the range of a float, into infinity.
+__device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[3])
 {
-    p[0] = take_limb<true>(x, y);
-    if constexpr (NL > 1) {
-        p[1] = take_limb<false>(x, y);
-        p[2] = pack_bf16(x, y);
-    }
+    x *= 0.5f;
+    y *= 0.5f;
+    p[0] = take_limb(x, y);
+    p[1] = take_limb(x, y);
+    p[2] = pack_bf16(x, y);
+}
+// The sum of products whose operands were halves: big holds the products of first limbs, small the others.  Where big is not
+// finite it is what the definition gives (the first limb of an infinity is that infinity), and small - infinities of either
+// sign, or the NaN that is left of an infinity behind its first limb - says nothing.
+__device__ __forceinline__ float limb_sum(float big, float small)
+{
+    return 4.f * (__builtin_isfinite(big) ? big + small : big);
 }
 
 // Limbs per element: fp32 three, bf16 itself.
@@ -107,7 +110,7 @@ __device__ __forceinline__ void raw8_limbs(const Raw8F &r, uintx4 (&out)[3])
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         unsigned p[3];
-        split_pair<3>(__uint_as_float(r.v[2 * i]), __uint_as_float(r.v[2 * i + 1]), p);
+        split_pair(__uint_as_float(r.v[2 * i]), __uint_as_float(r.v[2 * i + 1]), p);
         out[0][i] = p[0]; out[1][i] = p[1]; out[2][i] = p[2];
     }
 }
@@ -117,7 +120,7 @@ __device__ __forceinline__ void raw8_limbs(const Raw8H &r, uintx4 (&out)[1])
     for (int i = 0; i < 4; ++i) out[0][i] = r.v[i];
 }
 // Two neighbouring taps as limbs (zeros outside the chunk are passed in).
-__device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[3]) { split_pair<3>(a, b, p); }
+__device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[3]) { split_pair(a, b, p); }
 __device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[1])
 {
     p[0] = (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);      // (widened bf16: exact)
@@ -465,9 +468,11 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
         if constexpr (FOLD) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
-                total[t] += acc[t] + low[t];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[t][i] = low[t][i] = 0.f;
+                for (int i = 0; i < 16; ++i) {
+                    total[t][i] += limb_sum(acc[t][i], low[t][i]);
+                    acc[t][i] = low[t][i] = 0.f;
+                }
             }
         }
         fresh = nxt.item != cur.item;
@@ -508,8 +513,12 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 if (t > 0 && KS > 1) __syncthreads();
-                if constexpr (FOLD) acc[t] = total[t];
-                else if constexpr (NL == 3) acc[t] += low[t];
+                if constexpr (FOLD) {
+                    acc[t] = total[t];
+                } else if constexpr (NL == 3) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[t][i] = limb_sum(acc[t][i], low[t][i]);
+                }
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     *reinterpret_cast<floatx4 *>(wr + 8 * q) = floatx4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};

@@ -96,7 +96,7 @@ __device__ __forceinline__ void transpose_limbs(const Raw4F (&r)[8], int pos, ui
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         unsigned p[3];
-        split_pair<3>(__uint_as_float(r[2 * i].v[pos]), __uint_as_float(r[2 * i + 1].v[pos]), p);
+        split_pair(__uint_as_float(r[2 * i].v[pos]), __uint_as_float(r[2 * i + 1].v[pos]), p);
         out[0][i] = p[0]; out[1][i] = p[1]; out[2][i] = p[2];
     }
 }
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             float v = acc[i][k];
-            if constexpr (NL == 3) v += low[i][k];
+            if constexpr (NL == 3) v = limb_sum(v, low[i][k]);
             img[(8 * (k >> 2) + 4 * kg + (k & 3) - q + 31) * kDwBandDiagPitch + q] = v;
         }
         wave_lds_fence();

@@ -116,3 +116,63 @@ def test_non_finite_inputs_stay_where_the_contract_says(B, C, L, K, p, dtype, ba
             assert torch.equal(g0[other], dirty[other]), f"{name}: another channel changed"
             jl, jh = max(jlo, 0), min(jhi, K - 1)
             assert not torch.isfinite(dirty[c0, jl:jh + 1]).any(), f"{name}: coefficients [{jl}, {jh}] must not be finite"
+
+
+# fp32 operands at the top of their range on the kernels that work on limbs of them (filters of more than six block offsets):
+# every output is one product, so it must be what the definition gives - infinite exactly where the product is, never NaN, the
+# product itself otherwise, up to the last float, also where the rounding of a first limb goes past it.
+# (one chunk of taps and several, one tile per wave and two; windows of offsets and rows cut into virtual rows for dW)
+BIG = [(2, 3, 2048, 300, 299), (6, 3, 256, 256, 100), (40, 2, 160, 100, 50), (1, 1, 8192, 8192, 4000), (9, 2, 1024, 700, 0)]
+TOP = 2.0 ** 100 * (1 + 2.0 ** -8 + 2.0 ** -9)         # first limb above it, second limb negative
+PAIRS = [(TOP, 2.0 ** 100), (-TOP, 2.0 ** 100), (TOP, TOP), (2.0 ** 63 * (2 - 2.0 ** -8), 2.0 ** 63 * (2 - 2.0 ** -8)),
+         (2.0 ** 64, 2.0 ** 64 * (1 - 2.0 ** -24)), (3.4028234663852886e38, 1.0), (1.0, -3.4028234663852886e38), (3.4028234663852886e38, 2.0)]
+
+
+@pytest.mark.parametrize("B,C,L,K,p", BIG)
+def test_products_at_the_top_of_the_range(B, C, L, K, p):
+    u, j = L // 2, p + 20 if p + 20 < K else p - 20
+    for a, b in PAIRS:
+        print(f"case top of the range B{B} C{C} L{L} K{K} p{p}: {a!r} x {b!r}", flush=True)
+        x = torch.zeros(B, C, L); x[:, :, u] = a
+        w = torch.zeros(C, K); w[:, j] = b
+        dy = torch.zeros(B, C, L); dy[0, :, u + 3] = b                          # one pair per coefficient
+        exp = (torch.tensor([a], dtype=torch.float32).double() * torch.tensor([b], dtype=torch.float32).double()).float()[0]
+        want_y = torch.zeros(B, C, L); want_y[:, :, u - j + p] = exp             # y[t] takes x[t + j - p]
+        want_dx = torch.zeros(B, C, L); want_dx[:, :, u + j - p] = exp
+        want_dw = torch.zeros(C, K)
+        if 0 <= p - 3 < K:
+            want_dw[:, p - 3] = exp                                              # dw[j] takes dy[u + 3] x[u + 3 + j - p]
+        y = binding.dwconv_fwd(x.cuda(), w.cuda(), p).cpu()
+        dx = binding.dwconv_bwd_input(x.cuda(), w.cuda(), p).cpu()
+        dw = binding.dwconv_bwd_weight(x.cuda(), dy.cuda(), K, p).cpu()
+        for name, got, want in (("fwd", y, want_y), ("dx", dx, want_dx), ("dw", dw, want_dw)):
+            assert not torch.isnan(got).any(), f"{name}: a NaN from finite inputs"
+            assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got.sign(), want.sign()), name
+            # (three limbs per operand, the products of the small ones left out: 2^-24 of the product, and roundings of the sums)
+            fin = torch.isfinite(want)
+            err = ((got[fin].double() - want[fin].double()).abs() / want[fin].double().abs().clamp_min(1e-30)).max()
+            assert float(err) <= 2.0 ** -22, (name, float(err))
+
+
+# An infinity among operands of one sign: the outputs it enters are that infinity (all taps in one chunk; the zero taps that fill up a
+# chunk make the outputs at its edges NaN)
+@pytest.mark.parametrize("B,C,L,K,p", BIG[:3])
+def test_infinity_on_the_limb_kernels(B, C, L, K, p):
+    g = torch.Generator(device="cpu"); g.manual_seed(5)
+    u = L // 2
+    x = torch.rand(B, C, L, generator=g); x[B - 1, 1, u] = float("inf")
+    w = torch.rand(C, K, generator=g) + 0.5
+    y = binding.dwconv_fwd(x.cuda(), w.cuda(), p).cpu()
+    lo, hi = max(u + p - K + 1, 0), min(u + p, L - 1)
+    assert (y[B - 1, 1, lo:hi + 1] == float("inf")).all()
+    assert torch.isfinite(y[:, [0] + list(range(2, C))]).all()
+    dy = torch.rand(B, C, L, generator=g) + 0.5
+    dw = binding.dwconv_bwd_weight(x.cuda(), dy.cuda(), K, p).cpu()
+    jlo, jhi = max(u + p - L + 1, 0), min(u + p, K - 1)
+    assert (dw[1, jlo:jhi + 1] == float("inf")).all()
+    x[B - 1, 1, u] = 1.0
+    w[1, K // 2] = float("-inf")
+    x += 0.5
+    y = binding.dwconv_fwd(x.cuda(), w.cuda(), p).cpu()
+    t0, t1 = max(p - K // 2, 0), min(L - 1 + p - K // 2, L - 1)
+    assert (y[:, 1, t0:t1 + 1] == float("-inf")).all()
