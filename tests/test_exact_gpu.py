@@ -236,6 +236,67 @@ def test_exact_band_huge_batch(oracle_mod, B, K, p):
     _same("dw", dw, oracle_mod.bwd_weight(xn, dyn, K, p)[0], tdt, "huge batch")
 
 
+# fp32 values that need all 24 bits, on the kernels that work on bf16 limbs of them (integers in [-3, 3] are one limb, and the
+# products of the other two are lost in the tolerance of random data).  Every output is one product:
+#   a value times one: all three limbs of the value against the first of the other operand, either way round - bit for bit;
+#   odd 12-bit times odd 12-bit integers: exact in 24 bits, and the product of the two second limbs is 2^-16 of it
+FULL = [
+    (5, 2, 129, 129, 128), (40, 2, 160, 100, 50), (31, 2, 257, 140, 0), (7, 2, 512, 512, 0), (1, 2, 1025, 201, 200), (2, 3, 1056, 600, 300),
+    (1, 1, 4096, 4096, 4095), (3, 1, 4100, 6000, 5999), (1, 2, 8192, 8192, 4096), (9, 256, 1000, 230, 1), (2, 2, 300, 900, 400),
+    (70, 2, 132, 84, 0), (17, 2, 192, 192, 191), (3, 2, 2048, 500, 0), (33, 260, 520, 160, 80),
+]
+
+
+def _values(shape, seed, kind):
+    g = torch.Generator(device="cpu"); g.manual_seed(seed)
+    if kind == "12 bits":
+        v = 2049 + 2 * torch.randint(0, 1024, shape, generator=g)
+    else:                                                # all 24 bits, exponents 2^-20 to 2^20
+        v = ((1 << 23) + torch.randint(0, 1 << 23, shape, generator=g)).double() * 2.0 ** torch.randint(-43, -2, shape, generator=g).double()
+    return (v * (2 * torch.randint(0, 2, shape, generator=g) - 1)).float()
+
+
+@pytest.mark.parametrize("B,C,L,K,p", FULL)
+def test_exact_fp32_needs_every_limb(B, C, L, K, p):
+    print(f"case every limb B{B} C{C} L{L} K{K} p{p}", flush=True)
+    u, j = L // 3, min(p + 17, K - 1) if K - 1 - p > p else max(p - 17, 0)
+    for kind in ("24 bits", "12 bits"):
+        one = 1.0 if kind == "24 bits" else 3271.0
+        x, w, dy = _values((B, C, L), 1, kind), _values((C, K), 2, kind), _values((B, C, L), 3, kind)
+        delta_w = torch.zeros(C, K); delta_w[:, j] = one
+        delta_x = torch.zeros(B, C, L); delta_x[:, :, u] = one
+        delta_1 = torch.zeros(B, C, L); delta_1[B // 2, :, u] = one
+
+        def shifted(v, o):                               # v[t + o], zeros outside the row
+            out = torch.zeros_like(v)
+            a, b = max(0, -o), min(L, L - o)
+            if a < b:
+                out[..., a:b] = v[..., a + o:b + o]
+            return out
+
+        def taps(v, sign):                               # [B, C, K]: v at u + sign (j - p) for every tap j, zeros outside the row
+            at = u + sign * (torch.arange(K) - p)
+            return torch.where((at >= 0) & (at < L), v[..., at.clamp(0, L - 1)], torch.zeros(()))
+
+        def rows_of(v, sign):                            # [C, L]: w at tap p + sign (t - u) for every position t
+            at = p + sign * (torch.arange(L) - u)
+            return torch.where((at >= 0) & (at < K), v[..., at.clamp(0, K - 1)], torch.zeros(()))
+
+        dev = lambda t: t.cuda()                         # noqa: E731
+        cases = [
+            ("fwd, dense x", binding.dwconv_fwd(dev(x), dev(delta_w), p), one * shifted(x, j - p)),
+            ("fwd, dense w", binding.dwconv_fwd(dev(delta_x), dev(w), p), one * rows_of(w, -1).expand(B, C, L)),
+            ("dx, dense dy", binding.dwconv_bwd_input(dev(dy), dev(delta_w), p), one * shifted(dy, p - j)),
+            ("dx, dense w", binding.dwconv_bwd_input(dev(delta_x), dev(w), p), one * rows_of(w, 1).expand(B, C, L)),
+            ("dw, dense x", binding.dwconv_bwd_weight(dev(x), dev(delta_1), K, p), one * taps(x[B // 2], 1)),
+            ("dw, dense dy", binding.dwconv_bwd_weight(dev(delta_1), dev(dy), K, p), one * taps(dy[B // 2], -1)),
+        ]
+        torch.cuda.synchronize()
+        for name, got, want in cases:
+            got = got.cpu()
+            assert torch.equal(got, want), f"{kind} {name}: {int((got != want).sum())} of {want.numel()} values differ"
+
+
 # ... whichever length the filter has: which kernels a call launches, by the profiler's record of it (a result alone cannot show
 # that a call fell back to the vector ALU)
 def _kernels(call):
