@@ -34,6 +34,7 @@ struct DwBandGeom {
     int ndw;            // offsets per window: ND (per wave) x DG
     int DG;             // offset groups among the waves (KS = 4 / DG)
     int nwin;           // window w: offsets from dmin + w (ndw - 1)
+    int win0;           // the launch's first (in its order)
     int nseg, Lv;       // virtual rows per row and their length (a multiple of 64; nseg == 1: the row)
     int RGN;            // groups of eight virtual rows per stage
     int S32;            // dY blocks per stage (even)
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = blockIdx.x, sl = (int)blockIdx.y;
-    const int win = g.rev ? g.nwin - 1 - (int)blockIdx.z : (int)blockIdx.z;
+    const int wz = g.win0 + (int)blockIdx.z, win = g.rev ? g.nwin - 1 - wz : wz;
     const int NB32 = (g.L + 31) >> 5;
     const int dlo = g.dmin + win * (g.ndw - 1), nd_here = min(g.ndw, g.nd - win * (g.ndw - 1));
     const int KS = 4 / g.DG, dg = wave % g.DG, ks = wave / g.DG;

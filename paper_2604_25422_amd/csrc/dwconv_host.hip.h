@@ -110,6 +110,7 @@ inline bool bf16_odd_rows(const Shape &s, const void *a, const void *b)
 }
 inline bool ragged_rows_fused_ok(const Shape &s, int nd) { return ragged_rows_ok(s, nd) && s.L >= kRaggedMinL; }
 constexpr int kComputeUnits = 256;     // MI355X
+constexpr int kMaxGridChannels = 0xffffffffu / 256;     // workgroups of 256 threads along one dimension of a grid
 constexpr int kMfmaMaxL = 1 << 27;      // byte offsets inside a row stay below the out-of-row marker of the buffer loads
 
 // Short rows (see dwconv::RowsMap): whether the matrix-core kernels should walk the virtual row of a channel, and

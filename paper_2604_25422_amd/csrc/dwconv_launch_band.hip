@@ -90,8 +90,13 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
     }
     auto go = [&](auto kernel) -> int {
         if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)gy), dim3(dwconv::kBandThreads), lds, st,
-                           static_cast<const E *>(in), static_cast<const E *>(f), static_cast<E *>(out), g);
+        // (a grid dimension holds fewer than 2^32 threads: further channels in launches of their own)
+        for (int c0 = 0; c0 < s.C; c0 += kMaxGridChannels) {
+            const int n = s.C - c0 < kMaxGridChannels ? s.C - c0 : kMaxGridChannels;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)gy), dim3(dwconv::kBandThreads), lds, st,
+                               static_cast<const E *>(in) + (size_t)c0 * (size_t)s.L, static_cast<const E *>(f) + (size_t)c0 * (size_t)s.K,
+                               static_cast<E *>(out) + (size_t)c0 * (size_t)s.L, g);
+        }
         return launch_status();
     };
     switch (T) {

@@ -176,3 +176,43 @@ def test_infinity_on_the_limb_kernels(B, C, L, K, p):
     y = binding.dwconv_fwd(x.cuda(), w.cuda(), p).cpu()
     t0, t1 = max(p - K // 2, 0), min(L - 1 + p - K // 2, L - 1)
     assert (y[:, 1, t0:t1 + 1] == float("-inf")).all()
+
+
+# More channels than a grid dimension holds workgroups of 256 threads (2^24), and more windows of block offsets than its third
+# dimension holds (65535): the band kernels launch what is beyond separately.
+def test_band_kernels_with_2_to_the_24_channels():
+    B, C, L, K, p = 1, (1 << 24) + 3, 9, 97, 40
+    tdt = torch.bfloat16
+    x = _device_ints((B, C, L), 71, 2, tdt).view(B, C, L)
+    dy = _device_ints((B, C, L), 72, 2, tdt).view(B, C, L)
+    w = _device_ints((1, C, K), 73, 2, tdt)[0]
+    y = binding.dwconv_fwd(x, w, p)
+    dx = binding.dwconv_bwd_input(dy, w, p)
+    dw = binding.dwconv_bwd_weight(x, dy, K, p)
+    torch.cuda.synchronize()
+    sel = torch.tensor([0, 1, 5_000_000, (1 << 24) - 257, (1 << 24) - 2, (1 << 24) - 1, 1 << 24, C - 1], device="cuda")
+    xs, ds, ws = x[0, sel].double().cpu(), dy[0, sel].double().cpu(), w[sel].double().cpu()
+    want_y, want_dx, want_dw = torch.zeros_like(xs), torch.zeros_like(xs), torch.zeros_like(ws)
+    for t in range(L):
+        for u in range(L):
+            j = u - t + p                                    # y[t] takes x[u] w[j]
+            want_y[:, t] += xs[:, u] * ws[:, j]
+            want_dx[:, u] += ds[:, t] * ws[:, j]
+            want_dw[:, j] += ds[:, t] * xs[:, u]
+    for name, got, want in (("fwd", y[0, sel], want_y), ("dx", dx[0, sel], want_dx), ("dw", dw[sel], want_dw)):
+        assert torch.equal(got.cpu(), want.to(tdt)), name
+
+
+def test_weight_gradient_with_more_than_65535_windows():
+    B, C, K = 1, 1, 23_100_001
+    L, p = K, K - 1
+    x = _device_ints((B, C, L), 81, 3, torch.float32)
+    dy = torch.zeros(B, C, L, device="cuda")
+    u = L - 5
+    dy[0, 0, u] = 1.0                                        # dw[j] = x[u + j - p]
+    want = torch.zeros(C, K, device="cuda")
+    want[0, p - u:] = x[0, 0, :u + K - p]
+    dw = binding.dwconv_bwd_weight(x, dy, K, p)             # (a workspace of 87 GB that this call does not touch)
+    torch.cuda.synchronize()
+    assert torch.equal(dw, want)
+    torch.cuda.empty_cache()
