@@ -94,11 +94,17 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}: float32 or bfloat16 storage only")
 
 
+# The raw queries of the current device and its current stream: a Stream object per call costs what the rest of a small call's
+# checks do.  Where a PyTorch does not have them, the public ones.
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda dev: torch.cuda.current_stream(dev).cuda_stream)
+
+
 def _on_current_device(t: torch.Tensor, name: str):
     """The library enqueues on the current stream of the current device: every tensor must live there."""
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
-    if t.get_device() != torch._C._cuda_getDevice():
+    if t.get_device() != _current_device():
         raise ValueError(f"{name} is on {t.device}, the current device is cuda:{torch.cuda.current_device()}")
 
 
@@ -122,8 +128,8 @@ def _dev2(t: torch.Tensor, name: str, C: int, K: int | None = None, dtype=None):
 
 def _stream():
     """The current stream of the current device, on which every tensor of a call lives (a GPU tensor exists, so the
-    runtime is up).  The raw queries: a Stream object per call costs what the rest of a small call's checks do."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    runtime is up)."""
+    return _raw_stream(_current_device())
 
 
 def dwconv_fwd(x: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tensor | None = None) -> torch.Tensor:

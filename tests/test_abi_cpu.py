@@ -174,6 +174,22 @@ def test_binding_refuses_cpu_tensors():
         binding.dwconv_bwd_weight(x, x, 3, 1)
 
 
+def test_binding_does_without_the_private_queries(monkeypatch):
+    """The current device and stream come from torch's raw queries where it has them and from the public ones elsewhere."""
+    import importlib.util
+    import types
+    import torch
+    from paper_2604_25422_amd import binding
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev: types.SimpleNamespace(cuda_stream=4096 + dev))
+    spec = importlib.util.spec_from_file_location("paper_2604_25422_amd._binding_public", binding.__file__)
+    public = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(public)
+    assert public._current_device() == 3 and public._stream() == 4099
+
+
 def test_workloads_are_seeded_and_shaped():
     import torch
     from paper_2604_25422_amd import workloads
