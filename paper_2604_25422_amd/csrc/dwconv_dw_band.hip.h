@@ -45,9 +45,10 @@ struct DwBandGeom {
 constexpr int kDwBandThreads = 256;
 __host__ __device__ constexpr int dw_band_block_bytes(int NL) { return 32 * 16 * NL; }     // one 32-block of eight rows
 inline size_t dw_band_stage_bytes(int NL, int RGN, int S32, int ndw) { return (size_t)RGN * (size_t)(2 * S32 + ndw - 1) * dw_band_block_bytes(NL); }
-// One wave's diagonal image: 63 diagonals x 32 columns, pitch 34 (lane q writes diagonal c - q, so a pitch P puts the lanes
-// P - 1 floats apart: 33 left all of them on one bank, a third of the kernel's LDS cycles).
-constexpr int kDwBandDiagPitch = 34;
+// One wave's diagonal image: 63 diagonals x 32 columns, pitch 36 (lane q writes diagonal c - q, so a pitch P puts the lanes
+// P - 1 floats apart: an even P spreads them over the banks; a lane's diagonal is eight 16-byte reads, sixteen lanes' on
+// different banks).
+constexpr int kDwBandDiagPitch = 36;
 constexpr int kDwBandDiag = 63 * kDwBandDiagPitch;
 inline size_t dw_band_lds_bytes(int NL, int RGN, int S32, int ndw, int ND)
 {
@@ -351,6 +352,9 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     constexpr int TW = 32 * ND + 32;
     float *tap = taps + wave * TW;
     for (int i = lane; i < TW; i += 64) tap[i] = 0.f;
+    // (the cells a diagonal has no entry in stay zero: a sum is 32 columns whatever its length.  A loop over the columns it
+    // has, one LDS round trip after the other, took 5 us of a call: B1 C257 L480 K105 bf16 11.7 us)
+    for (int i = lane; i < kDwBandDiag / 4; i += 64) *reinterpret_cast<floatx4 *>(img + 4 * i) = floatx4{0.f, 0.f, 0.f, 0.f};
     wave_lds_fence();
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
@@ -364,9 +368,12 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         }
         wave_lds_fence();
         if (lane < 63) {
-            const int q_lo = max(0, 31 - lane), q_hi = min(31, 62 - lane);
+            floatx4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const floatx4 *>(img + lane * kDwBandDiagPitch + 4 * j);
             float sum = 0.f;
-            for (int qq = q_lo; qq <= q_hi; ++qq) sum += img[lane * kDwBandDiagPitch + qq];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum = (((sum + v[j][0]) + v[j][1]) + v[j][2]) + v[j][3];
             tap[32 * i + lane] += sum;
         }
         wave_lds_fence();
