@@ -32,13 +32,17 @@ struct DwBandGeom {
     int B, C, L, K, pad;
     int dmin, nd;       // block offsets (of 32) that hold a tap and have a block pair inside a row
     int ndw;            // offsets per window: ND (per wave) x DG
-    int DG;             // offset groups among the waves (KS = 4 / DG)
+    int dg_log;         // log2 of the offset groups among the waves (DG; KS = 4 / DG).  (Powers of two as their logarithms, other
+                        // divisors with the reciprocals they need: a division by a number of run time is some 200 cycles, and
+                        // a small call is a few thousand)
     int nwin;           // window w: offsets from dmin + w (ndw - 1)
     int win0;           // the launch's first (in its order)
     int nseg, Lv;       // virtual rows per row and their length (a multiple of 64; nseg == 1: the row)
-    int RGN;            // groups of eight virtual rows per stage
+    unsigned seg_magic; // floor(2^16 / nseg) + 1: v / nseg == v * seg_magic >> 16 for the at most eight virtual rows there are
+    int rg_log;         // log2 of the groups of eight virtual rows per stage (RGN)
     int S32;            // dY blocks per stage (even)
     int nstep;          // stages along a virtual row
+    unsigned step_magic;// floor(2^32 / nstep) + 1: st / nstep == umulhi(st, step_magic); 0: too many stages for that
     int stages;         // all stages
     int rev;            // windows in falling order (the dear ones first)
 };
@@ -123,11 +127,14 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int wz = g.win0 + (int)blockIdx.z, win = g.rev ? g.nwin - 1 - wz : wz;
     const int NB32 = (g.L + 31) >> 5;
     const int dlo = g.dmin + win * (g.ndw - 1), nd_here = min(g.ndw, g.nd - win * (g.ndw - 1));
-    const int KS = 4 / g.DG, dg = wave % g.DG, ks = wave / g.DG;
+    const int DG = 1 << g.dg_log, KS = 4 >> g.dg_log, dg = wave & (DG - 1), ks = wave >> g.dg_log;
+    const int RGN = 1 << g.rg_log;
     const int d0 = dlo + dg * ND, mine = min(ND, nd_here - dg * ND);     // this wave's offsets (mine <= 0: none)
     const size_t CL = (size_t)g.C * (size_t)g.L;
     const E *x_c = x + (size_t)c * (size_t)g.L, *dy_c = dy + (size_t)c * (size_t)g.L;
     const int VR = g.B * g.nseg;
+    const int NBV = g.nseg == 1 ? NB32 : g.Lv >> 5;                      // blocks of a virtual row
+    const int seg_blocks = (g.nseg - 1) * NBV;
 
     floatx16 acc[ND], low[NL == 3 ? ND : 1];
 #pragma unroll
@@ -143,15 +150,14 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         int st, vg, yb0, xlo, nx;
     };
     auto set_stage = [&](Stage &s) {
-        s.vg = s.st / g.nstep;
+        s.vg = g.nstep == 1 ? s.st : g.step_magic ? (int)__umulhi((unsigned)s.st, g.step_magic) : s.st / g.nstep;
         s.yb0 = (s.st - s.vg * g.nstep) * g.S32;
         s.xlo = s.yb0 + dlo;
         int xhi = s.xlo + g.S32 + g.ndw - 2;
-        if (g.nseg == 1) {
-            // (a block of zeros on both sides of the row: the other half of a pair that is half inside)
-            s.xlo = max(s.xlo, -1);
-            xhi = min(xhi, NB32);
-        }
+        // (a block of zeros on both sides of the row: the other half of a pair that is half inside.  Blocks count from the start
+        // of each virtual row, of which the last starts seg_blocks into its row)
+        s.xlo = max(s.xlo, -1 - seg_blocks);
+        xhi = min(xhi, NB32);
         s.nx = xhi - s.xlo + 1;
     };
     // the next stage in which some offset of the window meets a row (nx <= 0: none does); st >= stages: the end
@@ -165,17 +171,17 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     // Staging: 64 WPR threads bring one group of eight rows, one item of four positions of x and one of dY each (the plan
     // keeps a stage that small); the rows of an item are wave-uniform, so a load is a scalar base and a lane offset.  The
     // items of a stage are loaded while the stage before it is multiplied.
-    const int WPR = 4 / g.RGN;
-    const int rg_ld = wave / WPR, it_ld = tid & (64 * WPR - 1);
+    const int WPR = 4 >> g.rg_log;
+    const int rg_ld = wave >> (2 - g.rg_log), it_ld = tid & (64 * WPR - 1);
     decltype(load_raw4(x)) raw_x[8], raw_y[8];
     auto row_of = [&](int vr, int &off) -> size_t {                      // element offset of (virtual) row vr; off: its first position
         vr = min(vr, VR - 1);
-        const int b = g.nseg == 1 ? vr : vr / g.nseg;
+        const int b = g.nseg == 1 ? vr : (int)(((unsigned)vr * g.seg_magic) >> 16);
         off = g.nseg == 1 ? 0 : (vr - b * g.nseg) * g.Lv;
         return (size_t)b * CL;
     };
     auto load_items = [&](const Stage &s) {
-        const int it = band_hide(it_ld), vr0 = (s.vg * g.RGN + rg_ld) * 8;
+        const int it = band_hide(it_ld), vr0 = ((s.vg << g.rg_log) + rg_ld) * 8;
         // (positions outside the row are loaded from inside it and put right below)
         int ux = 32 * s.xlo + min(4 * it, 32 * s.nx - 4), uy = 32 * s.yb0 + min(4 * it, 32 * g.S32 - 4);
         if (g.nseg == 1) {
@@ -221,12 +227,14 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
                 int off;
                 (void)row_of(vr0 + r, off);
                 const int v = u + off;
-                fix_raw4(raw[r], v + 4 > g.L && v < g.L ? (v + 4 - g.L) & 3 : 0, vr0 + r >= VR || v < 0 || v >= g.L || u >= end);
+                const bool zero = vr0 + r >= VR || v < 0 || v >= g.L || u >= end;
+                if (__builtin_amdgcn_ballot_w64(zero || v + 4 > g.L) != 0)
+                    fix_raw4(raw[r], v + 4 > g.L && v < g.L ? (v + 4 - g.L) & 3 : 0, zero);
             }
         }
     };
     auto store_items = [&](const Stage &s) {
-        const int it = band_hide(it_ld), vr0 = (s.vg * g.RGN + rg_ld) * 8;
+        const int it = band_hide(it_ld), vr0 = ((s.vg << g.rg_log) + rg_ld) * 8;
         unsigned char *base = dwb_smem + rg_ld * ((s.nx + g.S32) * BB);
         put_right(raw_x, vr0, 32 * s.xlo + 4 * it, 1 << 30);
         put_right(raw_y, vr0, 32 * s.yb0 + 4 * it, g.Lv);
@@ -263,12 +271,9 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
 #pragma unroll
         for (int i = 0; i < ND; ++i) {
             const int d = d0 + i;
-            plo[i] = 0;
-            phi[i] = g.S32 / 2 - 1;
-            if (g.nseg == 1) {
-                plo[i] = max(0, (-yb0 - d) >> 1);                        // ceil((-yb0 - d - 1) / 2)
-                phi[i] = min(min(g.S32, NB32 - yb0 + 1) / 2 - 1, (NB32 - 1 - yb0 - d) >> 1);
-            }
+            // (the pairs that meet the row from some virtual row)
+            plo[i] = max(0, (-yb0 - d - seg_blocks) >> 1);               // ceil((-yb0 - d - 1 - seg_blocks) / 2)
+            phi[i] = min(min(g.S32, NBV - yb0 + 1) / 2 - 1, (NB32 - 1 - yb0 - d) >> 1);
             if (i >= mine) phi[i] = -(1 << 28);
         }
         const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
@@ -326,7 +331,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
                 }
             }
         };
-        for (int rg = 0; rg < g.RGN; ++rg) {
+        for (int rg = 0; rg < RGN; ++rg) {
             const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + d0 - xlo) * BB;
             const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
             // the bounds fall with the offset: those active at a pair are the offsets a .. b with p in [plo[a], plo[a - 1]) and
@@ -371,10 +376,10 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             floatx4 v[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const floatx4 *>(img + lane * kDwBandDiagPitch + 4 * j);
-            float sum = 0.f;
+            floatx4 sum = v[0];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) sum = (((sum + v[j][0]) + v[j][1]) + v[j][2]) + v[j][3];
-            tap[32 * i + lane] += sum;
+            for (int j = 1; j < 8; ++j) sum += v[j];
+            tap[32 * i + lane] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
         }
         wave_lds_fence();
     }
@@ -390,7 +395,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         if (t >= 0 && t < 32 * nd_here + 31) {
             // wave (dg, ks) owns taps 32 ND dg .. 32 ND dg + 32 ND + 30
             for (int w = 0; w < 4; ++w) {
-                const int tt = t - 32 * ND * (w % g.DG);
+                const int tt = t - 32 * ND * (w & (DG - 1));
                 if (tt >= 0 && tt < 32 * ND + 31) sum += taps[w * TW + tt];
             }
         }

@@ -32,13 +32,13 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
         const int most = NL == 3 ? 12 : 16;
         const int nwin = g.nd <= most ? 1 : (g.nd - 1 + most - 2) / (most - 1);
         const int per = nwin == 1 ? g.nd : (g.nd - 1 + nwin - 1) / nwin + 1;
-        if (per <= 3) { p->ND = per; g.DG = 1; }
-        else if (per <= 4) { p->ND = 2; g.DG = 2; }
-        else if (per <= 6) { p->ND = 3; g.DG = 2; }
-        else if (per <= 8) { p->ND = 2; g.DG = 4; }
-        else if (per <= 12) { p->ND = 3; g.DG = 4; }
-        else { p->ND = 4; g.DG = 4; }
-        g.ndw = p->ND * g.DG;
+        if (per <= 3) { p->ND = per; g.dg_log = 0; }
+        else if (per <= 4) { p->ND = 2; g.dg_log = 1; }
+        else if (per <= 6) { p->ND = 3; g.dg_log = 1; }
+        else if (per <= 8) { p->ND = 2; g.dg_log = 2; }
+        else if (per <= 12) { p->ND = 3; g.dg_log = 2; }
+        else { p->ND = 4; g.dg_log = 2; }
+        g.ndw = p->ND << g.dg_log;
         g.nwin = g.nd <= g.ndw ? 1 : (g.nd - 1 + g.ndw - 2) / (g.ndw - 1);
     }
     // fewer than eight rows: several virtual rows per row
@@ -50,6 +50,7 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
         g.nseg = (s.L + g.Lv - 1) / g.Lv;
         if (g.nseg == 1) g.Lv = 1 << 30;
     }
+    g.seg_magic = 65536u / (unsigned)g.nseg + 1u;
     const int nbv = g.nseg > 1 ? g.Lv / 32 : nb32;
     const int BB = dwconv::dw_band_block_bytes(NL);
     const int blocks = (int)(kMaxLdsBytes / 2) / BB;                   // of a stage: two workgroups per compute unit
@@ -60,12 +61,13 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     g.nstep = (nbv + g.S32 - 1) / g.S32;
     g.S32 = ((nbv + g.nstep - 1) / g.nstep + 1) / 2 * 2;
     const long long VR = (long long)s.B * g.nseg;
-    g.RGN = 1;
-    while (g.nstep == 1 && g.RGN < 4 && (long long)g.RGN * 16 <= VR && 2 * g.RGN * (g.S32 + x_blocks(g.S32)) <= blocks &&
-           2 * g.RGN * x_blocks(g.S32) <= 32 && 2 * g.RGN * g.S32 <= 32) g.RGN *= 2;
-    const long long groups = (VR + 8 * g.RGN - 1) / (8 * g.RGN);
+    g.rg_log = 0;
+    while (g.nstep == 1 && g.rg_log < 2 && (16ll << g.rg_log) <= VR && (2 << g.rg_log) * (g.S32 + x_blocks(g.S32)) <= blocks &&
+           (2 << g.rg_log) * x_blocks(g.S32) <= 32 && (2 << g.rg_log) * g.S32 <= 32) ++g.rg_log;
+    const long long groups = (VR + (8 << g.rg_log) - 1) / (8 << g.rg_log);
     if (groups * g.nstep > 0x3fffffff || VR > 0x3fffffff) return false;
     g.stages = (int)(groups * g.nstep);
+    g.step_magic = (long long)g.stages * g.nstep < (1ll << 32) ? (unsigned)((1ull << 32) / (unsigned)g.nstep) + 1u : 0u;
     g.rev = s.pad >= s.K / 2 ? 1 : 0;
     // slices that are used: about two rounds of two workgroups per compute unit (a workgroup's start and its diagonal sums do
     // not shrink with its stages: B8 C256 K = L = 8192 with one slice 745 us, two 837 us; bf16 232 / 286), partial sums of at
@@ -74,7 +76,7 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     S = std::min(S, (16ll << 20) / ((long long)s.C * s.K * 4));
     S = std::min(S, (long long)std::min(g.stages, slices));
     p->S = S < 1 ? 1 : (int)S;
-    p->lds = dwconv::dw_band_lds_bytes(NL, g.RGN, g.S32, x_blocks(g.S32) - g.S32 + 1, p->ND);
+    p->lds = dwconv::dw_band_lds_bytes(NL, 1 << g.rg_log, g.S32, x_blocks(g.S32) - g.S32 + 1, p->ND);
     return true;
 }
 

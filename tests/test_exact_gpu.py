@@ -221,6 +221,15 @@ def test_exact_dw_band(oracle_mod, B, C, L, K, p, dtype, offset):
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=31 + B + 3 * C + 5 * L, offset=offset, fused=False)
 
 
+# ... rows cut into virtual rows with filters as long as the row: block pairs and stages outside the row from every virtual row
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,C,L,K,p", [(1, 2, 1100, 1100, 0), (3, 2, 1500, 1500, 1499), (4, 1, 700, 700, 350), (2, 2, 2060, 2500, 2499), (4, 2, 1030, 1400, 20),
+                                       (1, 1, 5000, 5000, 4999), (3, 3, 2049, 1100, 1099)])
+def test_exact_dw_band_few_rows(oracle_mod, B, C, L, K, p, dtype):
+    print(f"case exact dw_band few rows {dtype} B{B} C{C} L{L} K{K} p{p}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=37 + B + 3 * C + 5 * L, fused=False)
+
+
 # ... and batches whose virtual row would be too long for 32-bit positions: rows of 129 to 512 positions go to the band kernels
 # with filters of any length (inputs in [-1, 1]: the weight gradient sums B L < 2^24 products)
 @pytest.mark.parametrize("B,K,p", [(12800, 66, 65), (15600, 16, 3)])
