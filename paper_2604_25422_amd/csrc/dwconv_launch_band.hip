@@ -36,11 +36,11 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
             // matrix pipe and LDS: more tiles per tap operand and shorter sums (fp32 K = L = 8192 633 us, 818 us with TG = 4)
             T = s.K <= 512 ? 2 : TMAX;
             g.TG = T == 2 && s.K <= 512 ? 4 : 2;
-            // fewer tiles per item where there would be less than two workgroups per compute unit
-            while (T * g.TG > 1 && (T * g.TG / 2 >= row_tiles || s.C * row_groups * ((row_tiles + T * g.TG - 1) / (T * g.TG)) < 2 * kComputeUnits)) {
-                if (T > 1) T /= 2;
-                else g.TG /= 2;
-            }
+        }
+        // fewer tiles per item where there would be less than two workgroups per compute unit
+        while (T * g.TG > 1 && (T * g.TG / 2 >= row_tiles || s.C * row_groups * ((row_tiles + T * g.TG - 1) / (T * g.TG)) < 2 * kComputeUnits)) {
+            if (T > 1) T /= 2;
+            else g.TG /= 2;
         }
         g.PB = T * g.TG * NBk;
         if (g.PB > row_tiles * NBk) g.PB = row_tiles * NBk;
