@@ -134,13 +134,24 @@ int corr_entry(const void *in, const void *f, void *out, int B, int C, int L, in
 }
 
 // ------------------------------------------------------------------ weight gradient
-// Which filters of more than six block offsets go to dw_band_kernel (us, kernels it replaces there -> dw_band_kernel):
-//   fp32, ordinary rows: from eleven offsets (B32 C256 L4096: K = 128 93 / 100, 160 114 -> 104, 300 185 -> 140, 4096 1142 -> 782;
-//     L4097 K4097 5288 -> 789); virtual rows from nine (L512: K = 100 89 / 98, 200 174 -> 106); rows of up to 512 positions that
-//     are neither: all (L256 K256 182 -> 103, L160 K100 108 -> 94)
-//   bf16, rows of whole 16-byte granules: from twelve (K = 128 35 / 39, 200 43 -> 40, 1024 186 -> 109), from seven where rows
-//     fill less than three quarters of their 1024-position segments (L256 K256 184 -> 39, L512 K100 41 / 41); other lengths: all
-//     (L4097 K100 309 -> 39)
+// Which filters of more than six block offsets go to dw_band_kernel (us, the register-resident kernels -> dw_band_kernel; K
+// causal).  Up to sixteen offsets the register-resident kernels walk 1024-position segments, a wave each, and are the faster
+// ones while there are few of them or the batch fills the groups of eight rows that dw_band_kernel contracts badly; it has more
+// to do once per workgroup (a stage of eight rows, diagonal sums of 32 x 32 products).
+//   fp32, ordinary rows: with 64 segments per channel from eleven offsets (B32 C256 L4096: K = 160 98 -> 91, 226 137 -> 126; B40 C16
+//     L2048 K160 14.1 -> 12.1), with 16 of them and 4096 in all from fourteen (B16 C768 L1024: K = 160 39.6 / 44.0, 200 50.5 -> 47.2;
+//     B49 C4 L816 K200, 196 in all: 11.3 / 16.0), never below 1024 in all (B250 C2 L883 K144 9.9 / 14.4) or with less than three quarters of
+//     the groups of eight (B9 C64 L9016 K160 26 / 37; B13 C31 L9568 24 / 24)
+//   fp32, virtual rows: from eleven offsets (B5 C768 L272: K = 118 10.2 / 15.2, 160 15.9 -> 13.6; B256 C128 L400: K = 118 44 / 48,
+//     135 55 -> 50) and 1024 segments (B373 C5 L352 K160, 765: 10.3 / 11.8)
+//   bf16, rows of whole 16-byte granules that fill their 1024-position segments to three quarters: from twelve offsets with 1024
+//     segments, 32 of them per channel or 16 and 4096 in all (B16 C768 L1024 K176 17.4 -> 15.9, B32 C256 L4096 K200 38 -> 33; B8 C256
+//     L1024 K176 6.4 / 7.1, B1 C128 L16000 K179 8.7 / 12.9)
+//   bf16, other rows of whole granules: from seven offsets with 17 segments per channel (B20 C64 L400 K100 8.7 -> 8.5, B500 C16 L256
+//     K100 18.5 -> 9.4; B16 C256 L600 K100 6.9 / 7.8), from eleven with more than 1024 in all (B5 C256 L640 K160 5.8 -> 5.5;
+//     B1 C257 L1464 K160 6.2 / 7.6)
+//   all with more than sixteen offsets (fp32 B32 C256 L4096 K300 185 -> 140, 4096 1142 -> 782), all bf16 rows of other lengths (L4097
+//     K100 309 -> 39), all rows of up to 512 positions that are neither virtual nor below 129 (L256 K256 fp32 182 -> 100)
 //   rows of at most 128 positions: bf16 above 112 (L128 K128 59 -> 40, L96 K96 42 / 53; fp32 L128 K128 66 / 92)
 static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
 {
@@ -152,10 +163,14 @@ static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
         rows_batch_offsets(s.L, s.K, s.pad, &bd, &bn);
         return s.dtype == DWCONV_BF16 && bn > kMfmaMaxND && s.L > 112;
     }
-    if (rp.on) return nd >= 9;
-    if (s.dtype == DWCONV_F32) return nd >= 11 || s.L <= 512;
-    const bool filled = 4ll * s.L >= 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
-    return (s.L % 8) != 0 || nd >= (filled ? 12 : 7);
+    if (rp.on) return nd >= 11 && (long long)rp.nvs * s.C >= 1024;
+    if (nd > kMfmaMaxNDDw || s.L <= 512 * (s.dtype == DWCONV_F32) || (s.dtype == DWCONV_BF16 && (s.L % 8) != 0)) return true;
+    const long long segs_per_row = ((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen, segs = s.B * segs_per_row;
+    const bool many = segs >= 16 && segs * s.C >= 4096;
+    if (s.dtype == DWCONV_F32)
+        return segs * s.C >= 1024 && nd >= (segs >= 64 ? 11 : many ? 14 : kMfmaMaxNDDw + 1) && 4ll * s.B >= 3 * ((s.B + 7ll) / 8 * 8);
+    if (4ll * s.L >= 3 * segs_per_row * dwconv::kSegLen) return nd >= 12 && segs * s.C >= 1024 && (segs >= 32 || many);
+    return segs > 16 || (nd >= 11 && segs * s.C > 1024);
 }
 
 // Slices of dw_band_kernel on ordinary rows: about two workgroups per compute unit over channels, windows of offsets and

@@ -1,5 +1,5 @@
-// Weight-gradient stage-1 kernels, bf16 storage, seven to eleven block offsets (more: dw_band_kernel, see dw_takes_band) on
-// rows of whole 16-byte granules that fill their segments (a unit of its own, like the fp32 one).
+// Weight-gradient stage-1 kernels, bf16 storage, seven to sixteen block offsets on rows of whole 16-byte granules (a unit of its
+// own, like the fp32 one; which of them go to dw_band_kernel instead: dw_takes_band).
 #include "dwconv_host.hip.h"
 #include "dwconv_dw_bf16.hip.h"
 
@@ -32,6 +32,11 @@ int launch_dw_partial_wide_bf16(const void *x, const void *dy, float *part, void
     case 9: return launch_wide_nd<9>(x, dy, part, dw_out, s, p, dmin, st);
     case 10: return launch_wide_nd<10>(x, dy, part, dw_out, s, p, dmin, st);
     case 11: return launch_wide_nd<11>(x, dy, part, dw_out, s, p, dmin, st);
+    case 12: return launch_wide_nd<12>(x, dy, part, dw_out, s, p, dmin, st);
+    case 13: return launch_wide_nd<13>(x, dy, part, dw_out, s, p, dmin, st);
+    case 14: return launch_wide_nd<14>(x, dy, part, dw_out, s, p, dmin, st);
+    case 15: return launch_wide_nd<15>(x, dy, part, dw_out, s, p, dmin, st);
+    case 16: return launch_wide_nd<16>(x, dy, part, dw_out, s, p, dmin, st);
     default: return -1;
     }
 }

@@ -30,8 +30,9 @@ int launch_dw_wide_multi_f32(int nd, const void *x, const void *dy, float *part,
 int launch_dw_partial_wide_f32(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                                int dmin, int nd, hipStream_t st)
 {
+    if (p.rows.on) return launch_dw_wide_rows_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
     if (p.wpb == 4) return launch_dw_wide_w4_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
-    return p.rows.on ? -1 : launch_dw_wide_multi_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
+    return launch_dw_wide_multi_f32(nd, x, dy, part, dw_out, s, p, dmin, st);
 }
 
 }  // namespace dwhost

@@ -1,11 +1,11 @@
-// Shared by the translation units of the fp32 weight-gradient kernels with seven to ten block offsets (the largest fully
+// Shared by the translation units of the fp32 weight-gradient kernels with seven to sixteen block offsets (the largest fully
 // unrolled kernels of the library: split over several units so that they compile side by side).
 #pragma once
 #include "dwconv_host.hip.h"
 
 namespace dwhost {
 
-// fp32, seven to ten block offsets (K up to 130): the LDS-direct kernel on ordinary rows.
+// fp32, seven to sixteen block offsets (K up to 226): the LDS-direct kernel on ordinary rows.
 template <int ND, int W>
 int launch_dw_partial_wide_ndw(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                                int dmin, hipStream_t st)
@@ -27,6 +27,8 @@ int launch_dw_partial_wide_ndw(const void *x, const void *dy, float *part, void 
 // waves.
 int launch_dw_wide_w4_f32(int nd, const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                           int dmin, hipStream_t st);
+int launch_dw_wide_rows_f32(int nd, const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
+                            int dmin, hipStream_t st);
 int launch_dw_wide_multi_f32(int nd, const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                              int dmin, hipStream_t st);
 
