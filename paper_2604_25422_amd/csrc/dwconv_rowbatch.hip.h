@@ -114,7 +114,7 @@ template <> struct RbImage<float> {
     static __device__ __forceinline__ Q zero() { return make_float4(0.f, 0.f, 0.f, 0.f); }
     static __device__ __forceinline__ Q granule(uintx4 raw, int rem) { return rb_granule<float>(raw, rem); }
     static __device__ __forceinline__ Q tile(floatx4 a) { return make_float4(a[0], a[1], a[2], a[3]); }
-    static __device__ __forceinline__ void store(float *p, Q v, int rem) { rb_store_granule(p, v, rem); }
+    static __device__ __forceinline__ void store(float *p, Q v, int rem, bool /* pieces of whole sectors */) { rb_store_granule(p, v, rem); }
     static __device__ __forceinline__ void set(Taps &t, int v, const float *f, int j, bool ok)
     {
         const float a = f[j];
@@ -129,6 +129,13 @@ template <> struct RbImage<float> {
     }
 };
 typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef unsigned uintx2_a __attribute__((ext_vector_type(2), aligned(4)));
+// A wave stores its bf16 outputs past the caches only where what it has of a batch entry is whole 64-byte sectors, two at least: the
+// parts of a sector that different waves stream out reach memory one by one (forward, streamed / not: B407671 C5 L16 K16
+// 71 / 40 us, B47453 C64 L12 K12 63 / 37, B20000 C33 L48 K48 33 / 25, B100000 C32 L16 K16 40.5 / 38.3; whole sectors B16384 C128 L48
+// K48 71 / 87).  (The fused backward kernel, whose block moves four channels as one piece, streams always: B20000 C64 L36 K16
+// 58 / 63 us.)
+__host__ __device__ constexpr bool rb_whole_sectors(int bytes) { return bytes >= 128 && bytes % 64 == 0; }
 // Sixteen lanes read sixteen times four bf16, lane i those at its own address p; it receives element i % 4 ... of four lanes:
 // the transposed 4 x 16 matrix whose row r lanes 4 r .. 4 r + 3 read.
 __device__ __forceinline__ shortx4 rb_read_transposed(const unsigned short *p)
@@ -150,10 +157,12 @@ template <> struct RbImage<bf16_t> {
         return raw;
     }
     static __device__ __forceinline__ Q tile(floatx4 a) { return uintx2{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3])}; }
-    static __device__ __forceinline__ void store(bf16_t *p, Q v, int rem)
+    static __device__ __forceinline__ void store(bf16_t *p, Q v, int rem, bool sectors)
     {
-        if (!rem) {
+        if (!rem && sectors) {
             __builtin_nontemporal_store(v, reinterpret_cast<uintx2 *>(p));
+        } else if (!rem) {
+            *reinterpret_cast<uintx2_a *>(p) = v;
         } else {
             unsigned short *o = reinterpret_cast<unsigned short *>(p);
             o[0] = (unsigned short)v[0];
@@ -208,6 +217,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
     const int Lc = 16 * g.m;
     const int Lo = NC * Lc + 16 / ES;
     E *sw = reinterpret_cast<E *>(dyn_lds) + wave * (kRbRows * Lo);
+    const bool sectors = rb_whole_sectors(NC * g.L * ES);
 
     const int Cg = g.C / NC;                    // channel groups
     const int id = (int)blockIdx.x * kRbCorrWaves + wave;
@@ -317,7 +327,7 @@ __global__ __launch_bounds__(64 * kRbCorrWaves, (ND > 9 ? 2 : (MB > 4 || RAG || 
                     const int rem = RAG ? (img[i] & 3) : 0;
                     const Q ov = *reinterpret_cast<const Q *>(sw + (img[i] - rem));
                     if (more) *reinterpret_cast<Q *>(sw + (img[i] - rem)) = Im::granule(pre[i], rem);
-                    if (gl_off[i] < lim) Im::store(out_u + gl_off[i] / ES, ov, rem);
+                    if (gl_off[i] < lim) Im::store(out_u + gl_off[i] / ES, ov, rem, sectors);
                 }
         }
         wave_lds_fence();
@@ -728,7 +738,7 @@ __global__ __launch_bounds__(64 * kRbBwdWaves, (RAG ? 3 : kMfmaWavesPerSimd)) vo
                         *reinterpret_cast<Q *>(images + (img_d[i] - rem)) = Im::granule(pd[i], rem);
                         *reinterpret_cast<Q *>(images + img_x[i]) = Im::granule(px[i], rem);
                     }
-                    if (gl_off[i] < lim) Im::store(dx_u + gl_off[i] / ES, ov, rem);
+                    if (gl_off[i] < lim) Im::store(dx_u + gl_off[i] / ES, ov, rem, true);
                 }
         }
         __syncthreads();
