@@ -69,8 +69,9 @@ constexpr int kMfmaMaxNDWide = 10;     // fp32 on long rows, K up to 130: whole-
 constexpr int kMfmaMaxNDDw = 16;       // virtual rows, and the unit in which dW slices of longer filters grow
 constexpr int kMfmaMaxNDDw3 = 48;      // fp32 dW slices: as many per segment group as started sixteen offsets up to here
 constexpr int kMfmaMaxNDDw4 = 64;      // ... bf16
-// forward, input gradient on ordinary rows with the Toeplitz operands in registers (more: corr_band_kernel)
-inline int mfma_max_nd(int dtype) { return dtype == DWCONV_F32 ? 12 : 10; }
+// forward, input gradient on ordinary rows with the Toeplitz operands in registers (more: corr_band_kernel; fp32 thirteen and
+// fourteen on rows that are not whole granules only)
+inline int mfma_max_nd(int dtype) { return dtype == DWCONV_F32 ? 14 : 10; }
 // Block offsets up to which the slices of dW follow from the segments of the rows (beyond: dw_band_slices).  The number of
 // slices is part of the workspace's layout, whichever kernel fills them.
 inline int mfma_max_nd_dw(const Shape &s)
@@ -85,8 +86,8 @@ inline int mfma_max_nd_dw(const Shape &s)
 // element-aligned; bf16: even lengths that are not multiples of eight).  The kernels that bring rows straight into
 // LDS take them when every row starts on a dword: their loads are range-checked per dword, so a granule that
 // straddles the end of its row is completed with zeros, and the last outputs of a row are stored by element.  Two to
-// six block offsets; fp32 also the register-staged forward / input-gradient kernel of seven and eight offsets (row
-// resources, the same range check) and the weight-gradient kernel of up to ten; rows long enough that
+// six block offsets; fp32 also the register-staged forward / input-gradient kernel of seven to fourteen offsets (row
+// resources, the same range check) and the weight-gradient kernel of up to sixteen; rows long enough that
 // 1024-position segments are not mostly padding (the kernels skip what lies past the end of a row, the fused one does not).
 // Short rows of such lengths with up to six block offsets are walked as virtual rows instead (plan_rows): there the granule in
 // which a row ends is completed with zeros in LDS by the lane that loaded it.

@@ -196,8 +196,12 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     const bool rows_direct_f32 = sizeof(T) == 4 && rp.on && nd <= kMfmaMaxND;
     const bool odd = bf16_odd_rows(s, in, out);
     // (rows of a dozen positions are all gap as virtual rows: B50000 C128 L9 K9 fwd 249 us on the vector-ALU kernel, 323 us
-    // here; L25 K7 320 against 309 us)
-    if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24))) return -1;
+    // here; L25 K7 320 against 309 us.  Calls of up to 1024 segments are a wait for memory each, and the vector-ALU kernel waits
+    // once less: it keeps them while its arithmetic is short - B2175 C1 L41 K16 3.6 / 4.8 us, B200 C64 L47 K31 4.6 / 4.8, K64 5.3 -> 5.0,
+    // B100 C256 L61, 1792 segments, K31 6.2 -> 5.7; ordinary rows B232 C2 L1989 K7 3.9 / 4.3, K48 4.7 -> 4.2)
+    const long long odd_segs = rp.on ? (long long)rp.nvs * s.C : (long long)s.B * s.C * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen);
+    const bool odd_small = odd_segs <= 1024 && odd_segs * s.K <= (rp.on ? 32768 : 16384);
+    if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24) || odd_small)) return -1;
     if (!odd && !granular && !rows_direct_bf16 && !rows_direct_f32 && (!ragged_rows_ok(s, nd) || !aligned_to(in, 4) || !aligned_to(out, 4))) return -1;
     const long long rows = (long long)s.B * s.C;
     const int L_walk = odd ? s.L + 1 : s.L;             // (a shifted row may reach one position further)
@@ -421,6 +425,12 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
             switch (nd) {
             case 7: return launch(dwconv::corr_mfma_kernel<float, 7, false, true>, pi, pf, po);
             case 8: return launch(dwconv::corr_mfma_kernel<float, 8, false, true>, pi, pf, po);
+            case 9: return launch(dwconv::corr_mfma_kernel<float, 9, false, true>, pi, pf, po);
+            case 10: return launch(dwconv::corr_mfma_kernel<float, 10, false, true>, pi, pf, po);
+            case 11: return launch(dwconv::corr_mfma_kernel<float, 11, false, true>, pi, pf, po);
+            case 12: return launch(dwconv::corr_mfma_kernel<float, 12, false, true>, pi, pf, po);
+            case 13: return launch(dwconv::corr_mfma_kernel<float, 13, false, true>, pi, pf, po);
+            case 14: return launch(dwconv::corr_mfma_kernel<float, 14, false, true>, pi, pf, po);
             default: return -1;
             }
         }
@@ -437,19 +447,23 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     return -1;
 }
 
-// Which filters of more than six block offsets go to corr_band_kernel (us, kernels it replaces there -> corr_band_kernel):
-//   fp32, ordinary rows of whole granules: from thirteen offsets (B32 C256 L4096: K = 160 101 / 107, 200 121 -> 103, 300 180 ->
-//     133, 1024 496 -> 296, 4096 1050 -> 712; the register-resident kernel keeps seven to twelve), from eleven where rows fill
-//     less than three quarters of their 1024-position segments; other lengths: from nine (L4097: K = 100 100 / 107, 200 220 ->
-//     126, 4097 3537 -> 954)
+// Which filters of more than six block offsets go to corr_band_kernel (us, kernels it replaces there -> corr_band_kernel).  Small
+// calls keep the register-resident kernels further up: a wave each for their segments, against workgroups that stage taps and
+// window and add up four waves' parts.
+//   fp32, ordinary rows of whole granules: from thirteen offsets (B32 C256 L4096: K = 160 87 / 107, 200 111 -> 89, 300 180 ->
+//     133, 1024 496 -> 296, 4096 1050 -> 712), from eleven where rows fill less than three quarters of their 1024-position segments
+//   fp32, other lengths: from nine (B32 C256 L4097: K = 128 156 -> 88, 200 223 -> 108, 4097 3537 -> 954; B64 C64 L1501, 8192 segments in
+//     all: K = 160 38 -> 23), nine and ten from 10240 segments on (B2107 C1 L3979 K128, 8428: 26 / 30), eleven to fourteen from 4096 on
+//     (B160 C5 L4809 K200, 4000: 18.9 / 21.9; B13 C257 L999 K160, 3341: 15.5 / 20.5)
 //   bf16, rows of whole 16-byte granules: from eleven (B32 C256 L4096: K = 128 35 / 37, 226 50 -> 41, 4096 243 -> 148), from
-//     seven where rows fill less than three quarters of their segments (L512 K512 92 -> 48); other lengths and alignments:
-//     all (L4097: K = 100 119 -> 65, 4097 3213 -> 200)
-//   short rows with more than six offsets: virtual rows (fp32 L512 K100 91 -> 75, L160 81 -> 73) and rows of up to 512
-//     positions with filters of their own length (L256 K256 fp32 101 -> 76, bf16 105 -> 38), any alignment; rows of at most
-//     128 positions: bf16 above 64 (L128 K128 61 -> 35; fp32 L96 K96 48 / 59).  Virtual rows of more than 512 positions (fp32)
-//     keep the register-resident kernel up to twelve offsets: their blocks do not fill the tiles of an item (B200 C32 L700 K80
-//     15.4 / 18.6)
+//     seven where rows fill less than three quarters of their segments and there are more than 1024 (L512 K512 92 -> 48); other
+//     lengths and alignments: all (L4097: K = 100 119 -> 65, 4097 3213 -> 200)
+//   short rows with more than six offsets: fp32 virtual rows of up to 512 positions with more than 4096 segments up to eight offsets
+//     (B1000 C128 L160 K84 50 -> 44; B20 C256 L400, 2304: 9.6 / 10.5), 1024 up to twelve (B64 C256 L512 K100 25 -> 22; B41 C47 L240
+//     K130, 564: 6.4 / 9.3), all beyond; rows of up to 512 positions with filters of their own length (L256 K256 fp32 101 -> 76, bf16
+//     105 -> 38), any alignment; rows of at most 128 positions: bf16 above 64 (L128 K128 61 -> 35; fp32 L96 K96 48 / 59).  Virtual rows of
+//     more than 512 positions (fp32) keep the register-resident kernel up to twelve offsets: their blocks do not fill the tiles
+//     of an item (B200 C32 L700 K80 15.4 / 18.6)
 inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const void *out)
 {
     const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
@@ -461,11 +475,14 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
         rows_batch_offsets(s.L, s.K, pad_eff, &bd, &bn);
         return s.dtype == DWCONV_BF16 && bn > kMfmaMaxND && s.L > 64;
     }
+    const bool granules = aligned_to(in, 16) && aligned_to(out, 16);
+    if (rp.on) return nd > 12 || !granules || (s.L <= 512 && (long long)rp.nvs * s.C > (nd <= 8 ? 4096 : 1024));
     if (s.L <= 512) return true;
-    if (rp.on) return nd > 12 || !aligned_to(in, 16) || !aligned_to(out, 16);
-    const bool filled = 4ll * s.L >= 3ll * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
-    if (s.dtype == DWCONV_F32) return nd >= ((s.L % 4) != 0 ? 9 : filled ? 13 : 11);
-    return (s.L % 8) != 0 || !aligned_to(in, 16) || !aligned_to(out, 16) || nd >= (filled ? 11 : 7);
+    const long long segs_per_row = ((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen, segs = (long long)s.B * s.C * segs_per_row;
+    const bool filled = 4ll * s.L >= 3 * segs_per_row * dwconv::kSegLen;
+    if (s.dtype == DWCONV_F32 && (s.L % 4) != 0) return nd >= (segs > 10240 ? 9 : segs >= 4096 ? 11 : 15);
+    if (s.dtype == DWCONV_F32) return nd >= (filled ? 13 : 11);
+    return (s.L % 8) != 0 || !granules || nd >= (filled || segs <= 1024 ? 11 : 7);
 }
 
 template <typename T>
