@@ -1,6 +1,7 @@
 // Launchers of the forward / input-gradient kernels for long filters (dwconv_band.hip.h), both storage types.
 #include "dwconv_band.hip.h"
 #include "dwconv_host.hip.h"
+#include <algorithm>
 
 namespace dwhost {
 
@@ -37,13 +38,20 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
             T = s.K <= 512 ? 2 : TMAX;
             g.TG = T == 2 && s.K <= 512 ? 4 : 2;
         }
-        // fewer tiles per item where there would be less than two workgroups per compute unit
-        while (T * g.TG > 1 && (T * g.TG / 2 >= row_tiles || s.C * row_groups * ((row_tiles + T * g.TG - 1) / (T * g.TG)) < 2 * kComputeUnits)) {
+        // fewer tiles per item where there would be less than two workgroups per compute unit (one for items of two tiles:
+        // B1 C64 L13934 K226 fp32 7.0 us with two, 8.6 with one; B1 C130 L3148 K130 bf16 4.9 / 5.5)
+        while (T * g.TG > 1 && (T * g.TG / 2 >= row_tiles || s.C * row_groups * ((row_tiles + T * g.TG - 1) / (T * g.TG)) <
+                                                                 (T * g.TG > 2 ? 2 : 1) * kComputeUnits)) {
             if (T > 1) T /= 2;
             else g.TG /= 2;
         }
-        g.PB = T * g.TG * NBk;
-        if (g.PB > row_tiles * NBk) g.PB = row_tiles * NBk;
+        // rows a little longer than one item: pieces of equal length instead of a second one of a tile or two (fp32 B16 C256
+        // L2100 K400 53 -> 44 us), bf16 also of half the tiles (B8 C512 L2300: K = 200 20.1 -> 17.5, 1000 35 -> 29)
+        const int rest = nb32 - T * g.TG * NBk;
+        const bool two = nb32 > 32 && rest > 0 && rest <= 2 * NBk;
+        if (two && NL == 1 && rest > 2 && T * g.TG == 8) T /= 2;
+        const int pieces = (row_tiles + T * g.TG - 1) / (T * g.TG);
+        g.PB = (two ? (row_tiles + pieces - 1) / pieces : std::min(T * g.TG, row_tiles)) * NBk;
         const int whole = nb32 + 2 * (NBk - 1);
         for (int F = s.K < 32768 ? (s.K + 1) & ~1 : 32768;; F = (F - 1) / 32 * 32) {
             if (F < s.K && (F <= 64 || whole_filter)) return false;       // (a chunk is 65 taps at least; a shorter filter is one chunk)

@@ -206,6 +206,15 @@ def test_exact_corr_band(oracle_mod, B, C, L, K, p, dtype, offset):
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=21 + B + 3 * C + 5 * L, offset=offset, fused=False)
 
 
+# ... rows a little longer than the eight tiles of an item (pieces of equal length, bf16 of four tiles), items of one, two and four tiles
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,C,L,K,p", [(9, 40, 2052, 300, 299), (9, 40, 2300, 250, 125), (16, 40, 2560, 1100, 0), (8, 70, 2120, 240, 239), (3, 64, 2304, 2304, 2303),
+                                       (5, 130, 1100, 300, 0), (2, 33, 900, 260, 130), (1, 260, 4100, 230, 229)])
+def test_exact_corr_band_pieces(oracle_mod, B, C, L, K, p, dtype):
+    print(f"case exact corr_band pieces {dtype} B{B} C{C} L{L} K{K} p{p}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=23 + B + 3 * C + 5 * L, fused=False, two_stage=False)
+
+
 # dw_band_kernel: one window of four to sixteen offsets and several, rows cut into virtual rows (fewer than five batch
 # entries), one, two and four groups of eight rows per stage, row ends inside a block, more slices than stages
 @pytest.mark.parametrize("B,C,L,K,p,dtype,offset", [
