@@ -454,7 +454,8 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
 //     133, 1024 496 -> 296, 4096 1050 -> 712), from eleven where rows fill less than three quarters of their 1024-position segments
 //   fp32, other lengths: from nine (B32 C256 L4097: K = 128 156 -> 88, 200 223 -> 108, 4097 3537 -> 954; B64 C64 L1501, 8192 segments in
 //     all: K = 160 38 -> 23), nine and ten from 10240 segments on (B2107 C1 L3979 K128, 8428: 26 / 30), eleven to fourteen from 4096 on
-//     (B160 C5 L4809 K200, 4000: 18.9 / 21.9; B13 C257 L999 K160, 3341: 15.5 / 20.5)
+//     (B160 C5 L4809 K200, 4000: 18.9 / 21.9; B13 C257 L999 K160, 3341: 15.5 / 20.5) or where rows fill less than three quarters of
+//     their segments (B1 C33 L1221 K192 7.6 -> 5.1)
 //   bf16, rows of whole 16-byte granules: from eleven (B32 C256 L4096: K = 128 35 / 37, 226 50 -> 41, 4096 243 -> 148), from
 //     seven where rows fill less than three quarters of their segments and there are more than 1024 (L512 K512 92 -> 48); other
 //     lengths and alignments: all (L4097: K = 100 119 -> 65, 4097 3213 -> 200)
@@ -480,7 +481,7 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
     if (s.L <= 512) return true;
     const long long segs_per_row = ((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen, segs = (long long)s.B * s.C * segs_per_row;
     const bool filled = 4ll * s.L >= 3 * segs_per_row * dwconv::kSegLen;
-    if (s.dtype == DWCONV_F32 && (s.L % 4) != 0) return nd >= (segs > 10240 ? 9 : segs >= 4096 ? 11 : 15);
+    if (s.dtype == DWCONV_F32 && (s.L % 4) != 0) return nd >= (segs > 10240 ? 9 : segs >= 4096 || !filled ? 11 : 15);
     if (s.dtype == DWCONV_F32) return nd >= (filled ? 13 : 11);
     return (s.L % 8) != 0 || !granules || nd >= (filled || segs <= 1024 ? 11 : 7);
 }

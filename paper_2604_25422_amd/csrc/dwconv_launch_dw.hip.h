@@ -197,7 +197,9 @@ int launch_dw_partial_mfma(const void *x, const void *dy, float *part, void *dw_
     const bool rows_direct_f32 = sizeof(T) == 4 && p.rows.on && nd <= kMfmaMaxND;
     const bool rows_direct = (rows_direct_bf16 || rows_direct_f32) && aligned_to(x, 4) && aligned_to(dy, 4);
     if (bf16_odd_rows(s, x, dy)) {
-        if (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, x, dy, p.rows)) return -1;
+        // (rows of one to three positions are all gap as virtual rows: B61773 C32 L1 K2 21 us on the vector-ALU kernel, 32 us here;
+        // with one tap there are no gaps: B30000 C64 L1 K1 2457 -> 27 us)
+        if (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, x, dy, p.rows) || (p.rows.on && s.L < 4 && s.K > 1)) return -1;
     } else if (!granular && !rows_direct && (!ragged_rows_ok(s, nd) || p.rows.on || !aligned_to(x, 4) || !aligned_to(dy, 4))) return -1;
     if constexpr (std::is_same<T, float>::value) {
         if (nd > kMfmaMaxND) return launch_dw_partial_wide_f32(x, dy, part, dw_out, s, p, dmin, nd, st);
