@@ -17,7 +17,11 @@
  *     w, dw are dense row-major [C, K] (Sec. IV-A, last paragraph).  No strides.
  *   - dtype is the STORAGE type of every tensor of the call (DWCONV_F32 as in
  *     the paper, or DWCONV_BF16).  Products and sums are always fp32; bf16
- *     outputs are rounded to nearest-even once, at the final store.
+ *     outputs are rounded to nearest-even once, at the final store.  (fp32
+ *     filters of more than about 66 taps may run as products of three bf16
+ *     limbs per operand, which differ from the fp32 products by at most 2^-24
+ *     of them; operands below 2^-125 then count as multiples of 2^-148, and
+ *     results below 2^-126 are multiples of 2^-147.)
  *   - Padding: the output length is L.  x~ is x extended by zeros; pad_left in
  *     [0, K-1] zeros are implied on the left and K-1-pad_left on the right.
  *     pad_left = K/2 is the paper's p (eq. (padding_width)), pad_left = K-1 is

@@ -9,8 +9,10 @@
 // consecutive taps, B (lane col, half kg) eight consecutive positions.
 //
 // fp32 storage on the bf16 instruction: every operand is the exact sum of three bf16 limbs (24 = 8 + 8 + 8 significant bits,
-// rounded to nearest, so a limb is at most 2^-9 of the one before it); products of limbs are exact in fp32, sums fp32.
-// Six of the nine limb products are kept; the three left out are below 2^-25 of the product, half an fp32 rounding.
+// rounded to nearest, so a limb is at most 2^-8 of the one before it); products of limbs are exact in fp32, sums fp32.
+// Six of the nine limb products are kept; the three left out are together at most 2^-24 of the product, the unit roundoff
+// of fp32.  The limbs are kept scaled to the size of the operand, with an accumulator for each scale of their products
+// (split_pair, limb_sum).
 // The instruction does sixteen times the fp32 one's products a cycle, so six of them are 2.7 times cheaper (an fp32
 // matrix kernel is bound by the matrix pipe from about seven block offsets on).
 //
@@ -36,30 +38,29 @@ __device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c)
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// The next limbs of a pair: what is left of it afterwards goes back to x, y.
-__device__ __forceinline__ unsigned take_limb(float &x, float &y)
-{
-    const unsigned p = pack_bf16(x, y);
-    x -= __uint_as_float(p << 16);
-    y -= __uint_as_float(p & 0xffff0000u);
-    return p;
-}
-// The three limbs of HALF of x and of y.  Rounding may take a first limb (and a product of two) up to 2^-8 past its value: with
-// halves that never turns a finite operand, or a product inside the range of a float, into infinity.
+// The three limbs of HALF of x and of y, the second times 2^8 and the third times 2^16: they are then all of the size of the
+// operand, so every fp32 value from 2^-125 on keeps its bits, and the smaller ones theirs but the last, 2^-149 (unscaled, the third
+// limb of a value below 2^-110 would lie below the smallest bf16: values around 2^-125 had an error of one per cent.  B8 C256
+// K = L = 8192 step 2094 us unscaled, 2108 us; B2048 C128 L256 K256 524, 538).  Halves, because rounding may take a first limb (and a product of two) up to 2^-8 past its value: no finite
+// operand, and no product inside the range of a float, turns into infinity.
 __device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[3])
 {
-    x *= 0.5f;
-    y *= 0.5f;
-    p[0] = take_limb(x, y);
-    p[1] = take_limb(x, y);
+    p[0] = pack_bf16(0.5f * x, 0.5f * y);
+    x = 128.f * __builtin_fmaf(-2.f, __uint_as_float(p[0] << 16), x);
+    y = 128.f * __builtin_fmaf(-2.f, __uint_as_float(p[0] & 0xffff0000u), y);
+    p[1] = pack_bf16(x, y);
+    x = 256.f * (x - __uint_as_float(p[1] << 16));
+    y = 256.f * (y - __uint_as_float(p[1] & 0xffff0000u));
     p[2] = pack_bf16(x, y);
 }
-// The sum of products whose operands were halves: big holds the products of first limbs, small the others.  Where big is not
-// finite it is what the definition gives (the first limb of an infinity is that infinity), and small - infinities of either
-// sign, or the NaN that is left of an infinity behind its first limb - says nothing.
-__device__ __forceinline__ float limb_sum(float big, float small)
+// The sum of products whose operands were halves: big holds the products of first limbs, mid those of a first and a second limb
+// (times 2^8), low the others (times 2^16).  Where big is not finite it is what the definition gives (the first limb of an
+// infinity is that infinity), and the small products - infinities of either sign, or the NaN that is left of an infinity behind its
+// first limb - say nothing; nor do they where the sum of their absolute values exceeds the range of a float.
+__device__ __forceinline__ float limb_sum(float big, float mid, float low)
 {
-    return 4.f * (__builtin_isfinite(big) ? big + small : big);
+    const float sum = __builtin_fmaf(__builtin_fmaf(low, 0x1p-8f, mid), 0x1p-8f, big);
+    return 4.f * (__builtin_isfinite(sum) ? sum : big);
 }
 
 // Limbs per element: fp32 three, bf16 itself.
@@ -147,7 +148,9 @@ constexpr int kBandThreads = 64 * kBandWaves;
 constexpr int kBandTapMargin = 48;           // zero taps in front of a staged chunk (and as many behind it)
 constexpr int kBandRedPitch = 36;            // floats per column of the output image
 // what a thread prefetches: granules of eight positions (fp32 8 registers each, bf16 4), pairs of taps
+// (fp32, two tiles per wave, at most four granules: 167 registers, three waves per SIMD instead of two)
 constexpr int band_prefetch(int NL) { return NL == 3 ? 5 : 10; }
+constexpr int kBandPrefetchF32Few = 4;
 constexpr int kBandTapPrefetch = 4;
 
 struct BandGeom {
@@ -185,18 +188,17 @@ __device__ __forceinline__ int band_hide(int v)
     return v;
 }
 // waves per SIMD the kernel is compiled for
-constexpr int band_waves(int NL, int T) { return NL == 1 && T == 1 ? 4 : 3; }
+constexpr int band_waves(int NL, int T, int NPF) { return NL == 3 && T == 2 ? (NPF <= kBandPrefetchF32Few ? 3 : 2) : NL == 1 && T == 1 ? 4 : 3; }
 
 //
 // FOLD (fp32, filters in several chunks): the sums of a chunk are added to totals of their own behind it, so that no chain of
 // additions is longer than the e of one chunk (B8 C256 K = L = 8192: error against 64 bits 1.7e-7 and 645 us, without 3.2e-7
 // and 634 us; the fp32 instruction it replaced 5.6e-7 and 1007 us).
-template <typename E, int T, bool FOLD = false>
-__global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)) void corr_band_kernel(
+template <typename E, int T, bool FOLD = false, int NPF = band_prefetch(Limbs<E>::N)>
+__global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T, NPF)) void corr_band_kernel(
     const E *__restrict__ in, const E *__restrict__ f, E *__restrict__ out, const BandGeom g)
 {
     constexpr int NL = Limbs<E>::N;
-    constexpr int NPF = band_prefetch(NL);
     constexpr int W = kBandWaves, THREADS = kBandThreads;
     static_assert(T == 1 || T == 2 || (T == 4 && NL == 1), "register budget");
     extern __shared__ __align__(16) unsigned char band_smem[];
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
             fs[(2 * l + 1) * TP + m] = q[l];
         }
     };
-    const bool one_chunk = g.K <= g.F;
+    const bool one_chunk = (NL == 3 && !FOLD) || g.K <= g.F;             // (fp32 in several chunks: FOLD)
     auto prefetch_taps = [&](const Stage &s) {
         const int Fc = min(g.F, g.K - s.j0), tl = band_hide(tid);
 #pragma unroll
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
             if (THREADS * i < TP) tap_triple(s.j0, Fc, tl + THREADS * i, tap[i]);
     };
 
-    floatx16 acc[T], low[NL == 3 ? T : 1], total[FOLD ? T : 1];
+    floatx16 acc[T], mid[NL == 3 ? T : 1], low[NL == 3 ? T : 1], total[FOLD ? T : 1];
     Stage cur;
     cur.round = 0; cur.j0 = 0;
     set_item(cur);
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
                     acc[t][i] = 0.f;
-                    if constexpr (NL == 3) low[t][i] = 0.f;
+                    if constexpr (NL == 3) mid[t][i] = low[t][i] = 0.f;
                     if constexpr (FOLD) total[t][i] = 0.f;
                 }
         }
@@ -416,14 +418,13 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
             };
             auto multiply = [&](int t, const uintx4 (&a)[NL], const uintx4 (&bb)[NL]) {
                 if constexpr (NL == 3) {
-                    // (the small products in an accumulator of their own: what rounds at the size of the sum is one
-                    // addition per e, not six)
+                    // (an accumulator for each scale: what rounds at the size of the sum is one addition per e, not six)
                     low[t] = mfma32x32x16(a[2], bb[0], low[t]);
                     acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
+                    mid[t] = mfma32x32x16(a[1], bb[0], mid[t]);
                     low[t] = mfma32x32x16(a[0], bb[2], low[t]);
+                    mid[t] = mfma32x32x16(a[0], bb[1], mid[t]);
                     low[t] = mfma32x32x16(a[1], bb[1], low[t]);
-                    low[t] = mfma32x32x16(a[1], bb[0], low[t]);
-                    low[t] = mfma32x32x16(a[0], bb[1], low[t]);
                 } else {
                     acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
                 }
@@ -439,6 +440,30 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
 #pragma unroll
                         for (int t = 0; t < N; ++t) {
                             const int k = u * N + t;
+                            if constexpr (NL == 3 && T == 2 && NPF <= kBandPrefetchF32Few) {
+                                // (one set of registers for A: each limb is read again behind its last product)
+                                uintx4 (&av)[NL] = a[0];
+                                const uintx4 (&bb)[NL] = b[k & 1];
+                                const int t1 = T0 + t;
+                                const bool last = t + 1 == N;
+                                if (last) step(e, more);
+                                read_b(b[(k + 1) & 1], last ? 0 : t + 1);
+                                auto next = [&](int l) {
+                                    if (last)
+#pragma unroll
+                                        for (int i = 0; i < 4; ++i) av[l][i] = ap[2 * l * TP + i];
+                                };
+                                low[t1] = mfma32x32x16(av[2], bb[0], low[t1]);
+                                next(2);
+                                low[t1] = mfma32x32x16(av[1], bb[1], low[t1]);
+                                mid[t1] = mfma32x32x16(av[1], bb[0], mid[t1]);
+                                next(1);
+                                acc[t1] = mfma32x32x16(av[0], bb[0], acc[t1]);
+                                mid[t1] = mfma32x32x16(av[0], bb[1], mid[t1]);
+                                low[t1] = mfma32x32x16(av[0], bb[2], low[t1]);
+                                next(0);
+                                continue;
+                            }
                             if (t + 1 < N) {
                                 read_b(b[(k + 1) & 1], t + 1);
                             } else {
@@ -470,8 +495,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
             for (int t = 0; t < T; ++t) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    total[t][i] += limb_sum(acc[t][i], low[t][i]);
-                    acc[t][i] = low[t][i] = 0.f;
+                    total[t][i] += limb_sum(acc[t][i], mid[t][i], low[t][i]);
+                    acc[t][i] = mid[t][i] = low[t][i] = 0.f;
                 }
             }
         }
@@ -517,7 +542,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T)
                     acc[t] = total[t];
                 } else if constexpr (NL == 3) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[t][i] = limb_sum(acc[t][i], low[t][i]);
+                    for (int i = 0; i < 16; ++i) acc[t][i] = limb_sum(acc[t][i], mid[t][i], low[t][i]);
                 }
 #pragma unroll
                 for (int q = 0; q < 4; ++q)

@@ -17,10 +17,10 @@
 // Several windows (more than twelve offsets in fp32, sixteen in bf16): a tap takes its products from two neighbouring
 // offsets, so a window shares its last offset with the next one and owns the taps that need no other window's offsets.
 //
-// What bounds it: at B8 C256 K = L = 8192 fp32 the matrix pipe (745 us where 206 G multiply-adds in six bf16 products take 520
+// What bounds it: at B8 C256 K = L = 8192 fp32 the matrix pipe (793 us where 206 G multiply-adds in six bf16 products take 520
 // at the 2.4 PFLOP/s a loop of nothing but this instruction reaches; the fp32 instruction it replaces 1100), bf16 the LDS reads (one
-// 16-byte read per lane and instruction: 232 us, before 250); with short rows the staging (B2048 C128 K = L = 256 fp32 206 us
-// of which two reads of memory are 104, before 366; bf16 L256 K256 39 us, before 184).  The reads of the next operand go
+// 16-byte read per lane and instruction: 185 us, before 250); with short rows the staging (B2048 C128 K = L = 256 fp32 207 us
+// of which two reads of memory are 104, before 366; bf16 B512 C256 L256 K256 39 us, before 184).  The reads of the next operand go
 // out ahead of each group of products, the loads of the next stage ahead of a stage's.  Error against 64 bits (fp32 long
 // filter): 2.4e-7, the fp32 instruction 9.4e-7.
 #pragma once
@@ -136,13 +136,13 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int NBV = g.nseg == 1 ? NB32 : g.Lv >> 5;                      // blocks of a virtual row
     const int seg_blocks = (g.nseg - 1) * NBV;
 
-    floatx16 acc[ND], low[NL == 3 ? ND : 1];
+    floatx16 acc[ND], mid[NL == 3 ? ND : 1], low[NL == 3 ? ND : 1];
 #pragma unroll
     for (int i = 0; i < ND; ++i)
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             acc[i][k] = 0.f;
-            if constexpr (NL == 3) low[i][k] = 0.f;
+            if constexpr (NL == 3) mid[i][k] = low[i][k] = 0.f;
         }
 
     // A stage: group vg of 8 RGN virtual rows, dY blocks yb0 .. yb0 + S32 - 1, x blocks xlo .. xlo + nx - 1.
@@ -297,10 +297,10 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
                 if constexpr (NL == 3) {
                     low[i] = mfma32x32x16(a[2], b[0], low[i]);
                     acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+                    mid[i] = mfma32x32x16(a[1], b[0], mid[i]);
                     low[i] = mfma32x32x16(a[0], b[2], low[i]);
+                    mid[i] = mfma32x32x16(a[0], b[1], mid[i]);
                     low[i] = mfma32x32x16(a[1], b[1], low[i]);
-                    low[i] = mfma32x32x16(a[1], b[0], low[i]);
-                    low[i] = mfma32x32x16(a[0], b[1], low[i]);
                 } else {
                     acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
                 }
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             float v = acc[i][k];
-            if constexpr (NL == 3) v = limb_sum(v, low[i][k]);
+            if constexpr (NL == 3) v = limb_sum(v, mid[i][k], low[i][k]);
             img[(8 * (k >> 2) + 4 * kg + (k & 3) - q + 31) * kDwBandDiagPitch + q] = v;
         }
         wave_lds_fence();

@@ -15,7 +15,7 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
     g.B = s.B; g.C = s.C; g.L = s.L; g.K = s.K; g.pad = pad_eff; g.reverse = reverse;
     if (s.L < 8 || s.L > kMfmaMaxL) return -1;
     constexpr int TMAX = NL == 3 ? 2 : 4;
-    int T = 1, NBk = 1;
+    int T = 1, NBk = 1, window_blocks = 0;
     long long row_groups = 1;
     // Geometry with columns of 2^nb_log blocks; false when window and taps do not fit (half the LDS of a compute unit, the
     // prefetch registers).  whole_filter: only with all taps in one chunk.
@@ -34,7 +34,9 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
         } else {
             // eight tiles per item.  Filters of up to 512 taps are bound by memory: every wave its own tiles, nothing to add
             // up afterwards (bf16 B32 C256 L4096, TG = 4 / 2: K = 226 41 / 49 us, K = 300 46 / 51 us); longer ones by the
-            // matrix pipe and LDS: more tiles per tap operand and shorter sums (fp32 K = L = 8192 633 us, 818 us with TG = 4)
+            // matrix pipe and LDS: more tiles per tap operand and shorter sums (fp32 K = L = 8192 633 us, 818 us with TG = 4).
+            // Two tiles per wave in fp32 too, though one would leave room for a third workgroup (two / one: L4096 K200 104 / 108 us,
+            // K300 125 / 128, K500 182 / 196; B100 C256 L700 K400 100 / 129; short rows B2048 C128 L256 K256 178 / 200)
             T = s.K <= 512 ? 2 : TMAX;
             g.TG = T == 2 && s.K <= 512 ? 4 : 2;
         }
@@ -65,8 +67,10 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
             g.pitch = 16 * units;
             if (g.RW * wb * 4 <= dwconv::band_prefetch(NL) * dwconv::kBandThreads &&
                 (F >= s.K || dwconv::band_tap_dwords(F) <= dwconv::kBandTapPrefetch * dwconv::kBandThreads) &&
-                dwconv::band_lds_bytes(NL, g.RW, g.pitch, F) <= kMaxLdsBytes / 2)
+                dwconv::band_lds_bytes(NL, g.RW, g.pitch, F) <= kMaxLdsBytes / 2) {
+                window_blocks = wb;
                 return true;
+            }
         }
     };
     // Columns of a tile: few blocks of many batch entries for short rows (every column is then at the same distance from the
@@ -84,9 +88,13 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
     if (row_groups * g.NP * g.NP > 0xffffffffll || row_groups * g.NP > 0x3fffffff) return -1;
     g.items = (int)(row_groups * g.NP);
     const size_t lds = dwconv::band_lds_bytes(NL, g.RW, g.pitch, g.F);
+    // fp32, two tiles per wave: a third workgroup per compute unit where window and prefetch are small enough for it (two / three:
+    // B2048 C128 L160 K160 117 / 104 us, B16 C256 L2100 K400 48.4 / 42.5, B1000 C128 L224 K100 70 / 65)
+    const bool few = NL == 3 && T == 2 && g.F >= s.K && 3 * lds <= kMaxLdsBytes &&
+                     g.RW * window_blocks * 4 <= dwconv::kBandPrefetchF32Few * dwconv::kBandThreads;
     // workgroups per channel: whole rounds of the resident ones, items spread evenly; a workgroup's start (its taps, a
     // first window that nothing hides) counts as half an item
-    const int by_lds = (int)(kMaxLdsBytes / lds), by_regs = dwconv::band_waves(NL, T);
+    const int by_lds = (int)(kMaxLdsBytes / lds), by_regs = dwconv::band_waves(NL, T, few ? dwconv::kBandPrefetchF32Few : dwconv::band_prefetch(NL));
     const long long slots = (long long)kComputeUnits * (by_lds < by_regs ? by_lds : by_regs);
     int gy = 1;
     double best = 0.0;
@@ -116,6 +124,7 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
     case 2:
         if constexpr (NL == 3) {
             if (g.F < s.K) return go(dwconv::corr_band_kernel<E, 2, true>);
+            if (few) return go(dwconv::corr_band_kernel<E, 2, false, dwconv::kBandPrefetchF32Few>);
         }
         return go(dwconv::corr_band_kernel<E, 2>);
     default:

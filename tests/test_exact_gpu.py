@@ -257,7 +257,9 @@ def test_exact_band_huge_batch(oracle_mod, B, K, p):
 # fp32 values that need all 24 bits, on the kernels that work on bf16 limbs of them (integers in [-3, 3] are one limb, and the
 # products of the other two are lost in the tolerance of random data).  Every output is one product:
 #   a value times one: all three limbs of the value against the first of the other operand, either way round - bit for bit;
-#   odd 12-bit times odd 12-bit integers: exact in 24 bits, and the product of the two second limbs is 2^-16 of it
+#   odd 12-bit times odd 12-bit integers: exact in 24 bits, and the product of the two second limbs is 2^-16 of it;
+#   values at the bottom of the range, denormal ones among them, times 2^60 - bit for bit: the lower limbs of such a value are below
+#   the smallest bf16 unless they are scaled (multiples of 2^-148: the limbs are those of half of a value)
 FULL = [
     (5, 2, 129, 129, 128), (40, 2, 160, 100, 50), (31, 2, 257, 140, 0), (7, 2, 512, 512, 0), (1, 2, 1025, 201, 200), (2, 3, 1056, 600, 300),
     (1, 1, 4096, 4096, 4095), (3, 1, 4100, 6000, 5999), (1, 2, 8192, 8192, 4096), (9, 256, 1000, 230, 1), (2, 2, 300, 900, 400),
@@ -269,6 +271,9 @@ def _values(shape, seed, kind):
     g = torch.Generator(device="cpu"); g.manual_seed(seed)
     if kind == "12 bits":
         v = 2049 + 2 * torch.randint(0, 1024, shape, generator=g)
+    elif kind == "bottom":                               # multiples of 2^-148 up to 2^-107, of 1 to 24 bits
+        v = (((1 << 23) + torch.randint(0, 1 << 23, shape, generator=g)) >> torch.randint(0, 24, shape, generator=g)).double()
+        v = v * 2.0 ** (-148 + torch.randint(0, 17, shape, generator=g)).double()
     else:                                                # all 24 bits, exponents 2^-20 to 2^20
         v = ((1 << 23) + torch.randint(0, 1 << 23, shape, generator=g)).double() * 2.0 ** torch.randint(-43, -2, shape, generator=g).double()
     return (v * (2 * torch.randint(0, 2, shape, generator=g) - 1)).float()
@@ -278,8 +283,8 @@ def _values(shape, seed, kind):
 def test_exact_fp32_needs_every_limb(B, C, L, K, p):
     print(f"case every limb B{B} C{C} L{L} K{K} p{p}", flush=True)
     u, j = L // 3, min(p + 17, K - 1) if K - 1 - p > p else max(p - 17, 0)
-    for kind in ("24 bits", "12 bits"):
-        one = 1.0 if kind == "24 bits" else 3271.0
+    for kind in ("24 bits", "12 bits", "bottom"):
+        one = {"24 bits": 1.0, "12 bits": 3271.0, "bottom": 2.0 ** 60}[kind]
         x, w, dy = _values((B, C, L), 1, kind), _values((C, K), 2, kind), _values((B, C, L), 3, kind)
         delta_w = torch.zeros(C, K); delta_w[:, j] = one
         delta_x = torch.zeros(B, C, L); delta_x[:, :, u] = one
