@@ -14,8 +14,9 @@
 // would otherwise fall on the same LDS banks.  The permutation is applied on the memory side of the loads.
 // Loads of a segment in issue order: x0 g0 x1 g1 xt (x_h, g_h: elements [512 h, 512 h + 512) of the x window and
 // of the dY tile; xt: 128 elements of x tail, two per lane; a second such load above eight block offsets).
-// Needs L % 8 == 0 and 16-byte aligned tensors.  Up to sixteen block offsets fit 128 registers; above six the
-// diagonal image of the accumulators (18 KB of LDS per wave at sixteen) is what limits the waves per compute unit.
+// Rows that start on a dword (even lengths, 4-byte aligned tensors; other rows and tensors: ODD) up to six block offsets, rows of
+// whole 16-byte granules up to sixteen.  Those fit 128 registers; above six the diagonal image of the accumulators (18 KB of LDS
+// per wave at sixteen) is what limits the waves per compute unit.
 #pragma once
 #include "dwconv_bwd_fused.hip.h"
 
@@ -28,14 +29,14 @@ constexpr int dw_bf16_wave_floats(int ND)
     const int stage = (dw_bf16_win_x(ND) + kSegLen) / 2, diag = ((16 * ND + 15) * 17 + 3) / 4 * 4;
     return stage > diag ? stage : diag;
 }
-// taps a wave hands to the block-level sum (see dw_direct_row_floats: a launch over part of the offsets owns up to 16 ND + 15)
-constexpr int dw_bf16_row_floats(int ND) { return 16 * ND + (ND >= 9 ? 16 : 0); }
+// taps a wave hands to the block-level sum: all of them fit 16 ND
+constexpr int dw_bf16_row_floats(int ND) { return 16 * ND; }
 constexpr size_t dw_bf16_lds_bytes(int ND, int W) { return (size_t)W * (size_t)(dw_bf16_wave_floats(ND) + dw_bf16_row_floats(ND)) * sizeof(float); }
 
 // position of logical 16-block nb inside the staged windows
 __host__ __device__ constexpr int bf16_block_pos(int nb) { return (nb & ~3) | ((nb & 3) ^ ((nb >> 2) & 3)); }
 
-// ROWS: short rows, the wave walks the virtual row of its channel (see RowsMap; pitch a multiple of 8 and row length a
+// ROWS: short rows, the wave walks the virtual row of its channel (see RowsMap; pitch a multiple of 8 and
 // row length even: a 16-byte granule lies in one row or in one gap, or holds the last two, four or six elements of a row, in
 // which case the rest of it is cleared in LDS once it has landed: rows_granule8_byte_offset); B is then 1 and segs_per_row the number of segments of the
 // virtual row.  Every lane translates the position of its granule on the memory side of the loads.
@@ -143,8 +144,8 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void dw_partial_bf16_ker
                 rx = row_tail_resource(x + (row - (size_t)s_next), len, u0 > 0 ? min(u0, 2 * len) : 0);
                 rg = row_tail_resource(dy + (row - (size_t)s_next), len, 2 * t0);
             } else {
-            // (a window that starts past the end of the row - the second of two launches - gets an empty resource)
-            rx = row_tail_resource(x + row, L, u0 > 0 ? min(u0, 2 * L) : 0);
+            // (dmin <= 0: a window starts before the end of the row)
+            rx = row_tail_resource(x + row, L, u0 > 0 ? u0 : 0);
             rg = row_tail_resource(dy + row, L, 2 * t0);
             }
         } else {
