@@ -40,9 +40,10 @@ __device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c)
 
 // The three limbs of HALF of x and of y, the second times 2^8 and the third times 2^16: they are then all of the size of the
 // operand, so every fp32 value from 2^-125 on keeps its bits, and the smaller ones theirs but the last, 2^-149 (unscaled, the third
-// limb of a value below 2^-110 would lie below the smallest bf16: values around 2^-125 had an error of one per cent.  B8 C256
-// K = L = 8192 step 2094 us unscaled, 2108 us; B2048 C128 L256 K256 524, 538).  Halves, because rounding may take a first limb (and a product of two) up to 2^-8 past its value: no finite
-// operand, and no product inside the range of a float, turns into infinity.
+// limb of a value below 2^-110 would lie below the smallest bf16: values around 2^-125 had an error of one per cent; the scaled
+// ones and their third accumulator cost 1 % of a step of B2048 C128 L256 K256, 512 -> 520 us).  Halves, because
+// rounding may take a first limb (and a product of two) up to 2^-8 past its value: no finite operand, and no product inside the
+// range of a float, turns into infinity.
 __device__ __forceinline__ void split_pair(float x, float y, unsigned (&p)[3])
 {
     p[0] = pack_bf16(0.5f * x, 0.5f * y);
@@ -148,7 +149,7 @@ constexpr int kBandThreads = 64 * kBandWaves;
 constexpr int kBandTapMargin = 48;           // zero taps in front of a staged chunk (and as many behind it)
 constexpr int kBandRedPitch = 36;            // floats per column of the output image
 // what a thread prefetches: granules of eight positions (fp32 8 registers each, bf16 4), pairs of taps
-// (fp32, two tiles per wave, at most four granules: 167 registers, three waves per SIMD instead of two)
+// (fp32, two tiles per wave: with at most four granules 167 registers, three waves per SIMD instead of two)
 constexpr int band_prefetch(int NL) { return NL == 3 ? 5 : 10; }
 constexpr int kBandPrefetchF32Few = 4;
 constexpr int kBandTapPrefetch = 4;
@@ -399,12 +400,13 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
             const unsigned char *bp[N];
 #pragma unroll
             for (int t = 0; t < N; ++t) bp[t] = b_base + ((rel[T0 + t] + (ea >> 1)) * BS + (ea & 1) * 32);
-            uintx4 a[2][NL], b[2][NL];
-            auto read_a = [&](uintx4 (&to)[NL]) {
+            // (two register sets for A and B; fp32 one for A, whose limbs are each read again behind their last product: a dozen
+            // registers less, and 1 % of B8 C256 K = L = 8192)
+            constexpr int SETS = NL == 3 ? 1 : 2;
+            uintx4 a[SETS][NL], b[2][NL];
+            auto read_limb = [&](uintx4 (&to)[NL], int l) {
 #pragma unroll
-                for (int l = 0; l < NL; ++l)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) to[l][i] = ap[2 * l * TP + i];
+                for (int i = 0; i < 4; ++i) to[l][i] = ap[2 * l * TP + i];
             };
             auto read_b = [&](uintx4 (&to)[NL], int t) {
 #pragma unroll
@@ -416,20 +418,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
 #pragma unroll
                 for (int t = 0; t < N; ++t) bp[t] += more ? by : 0;
             };
-            auto multiply = [&](int t, const uintx4 (&a)[NL], const uintx4 (&bb)[NL]) {
-                if constexpr (NL == 3) {
-                    // (an accumulator for each scale: what rounds at the size of the sum is one addition per e, not six)
-                    low[t] = mfma32x32x16(a[2], bb[0], low[t]);
-                    acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
-                    mid[t] = mfma32x32x16(a[1], bb[0], mid[t]);
-                    low[t] = mfma32x32x16(a[0], bb[2], low[t]);
-                    mid[t] = mfma32x32x16(a[0], bb[1], mid[t]);
-                    low[t] = mfma32x32x16(a[1], bb[1], low[t]);
-                } else {
-                    acc[t] = mfma32x32x16(a[0], bb[0], acc[t]);
-                }
-            };
-            read_a(a[0]);
+#pragma unroll
+            for (int l = 0; l < NL; ++l) read_limb(a[0], l);
             read_b(b[0], 0);
 #pragma unroll 1
             for (int e = ea; e <= eb;) {
@@ -439,39 +429,28 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                         const bool more = e + KS <= eb;
 #pragma unroll
                         for (int t = 0; t < N; ++t) {
-                            const int k = u * N + t;
-                            if constexpr (NL == 3 && T == 2 && NPF <= kBandPrefetchF32Few) {
-                                // (one set of registers for A: each limb is read again behind its last product)
+                            const int k = u * N + t, tt = T0 + t;
+                            const bool last = t + 1 == N;
+                            const uintx4 (&bb)[NL] = b[k & 1];
+                            if (last) step(e, more);
+                            if constexpr (NL == 3) {
                                 uintx4 (&av)[NL] = a[0];
-                                const uintx4 (&bb)[NL] = b[k & 1];
-                                const int t1 = T0 + t;
-                                const bool last = t + 1 == N;
-                                if (last) step(e, more);
                                 read_b(b[(k + 1) & 1], last ? 0 : t + 1);
-                                auto next = [&](int l) {
-                                    if (last)
-#pragma unroll
-                                        for (int i = 0; i < 4; ++i) av[l][i] = ap[2 * l * TP + i];
-                                };
-                                low[t1] = mfma32x32x16(av[2], bb[0], low[t1]);
-                                next(2);
-                                low[t1] = mfma32x32x16(av[1], bb[1], low[t1]);
-                                mid[t1] = mfma32x32x16(av[1], bb[0], mid[t1]);
-                                next(1);
-                                acc[t1] = mfma32x32x16(av[0], bb[0], acc[t1]);
-                                mid[t1] = mfma32x32x16(av[0], bb[1], mid[t1]);
-                                low[t1] = mfma32x32x16(av[0], bb[2], low[t1]);
-                                next(0);
-                                continue;
-                            }
-                            if (t + 1 < N) {
-                                read_b(b[(k + 1) & 1], t + 1);
+                                // (an accumulator for each scale: what rounds at the size of the sum is one addition per e, not six)
+                                low[tt] = mfma32x32x16(av[2], bb[0], low[tt]);
+                                if (last) read_limb(av, 2);
+                                low[tt] = mfma32x32x16(av[1], bb[1], low[tt]);
+                                mid[tt] = mfma32x32x16(av[1], bb[0], mid[tt]);
+                                if (last) read_limb(av, 1);
+                                acc[tt] = mfma32x32x16(av[0], bb[0], acc[tt]);
+                                mid[tt] = mfma32x32x16(av[0], bb[1], mid[tt]);
+                                low[tt] = mfma32x32x16(av[0], bb[2], low[tt]);
+                                if (last) read_limb(av, 0);
                             } else {
-                                step(e, more);
-                                read_a(a[1 - u]);
-                                read_b(b[(k + 1) & 1], 0);
+                                if (last) read_limb(a[1 - u], 0);
+                                read_b(b[(k + 1) & 1], last ? 0 : t + 1);
+                                acc[tt] = mfma32x32x16(a[u][0], bb[0], acc[tt]);
                             }
-                            multiply(T0 + t, a[u], b[k & 1]);
                         }
                         e += KS;
                     }

@@ -90,7 +90,7 @@ CLASSES = [
     (6, 10, 5000, 40, 11), (2, 4, 1024, 3, 1),
     # seven to sixteen block offsets
     (3, 5, 2064, 100, 99), (5, 2, 3072, 128, 127), (2, 3, 1032, 226, 100), (3, 4, 2064, 160, 159), (7, 2, 1024, 161, 80),
-    # weight gradient in two, three and four launches over the block offsets
+    # seventeen to sixty-three block offsets: band kernels, weight gradient in several windows of offsets
     (3, 4, 1024, 256, 255), (2, 2, 3000, 482, 481), (2, 3, 2048, 700, 350), (3, 2, 1024, 994, 993),
     # long filters: rows and filter in LDS
     (3, 2, 256, 200, 100), (2, 3, 512, 512, 511), (2, 1, 1000, 2500, 1200), (1, 2, 4096, 4096, 4095), (21, 2, 1024, 600, 599),
@@ -102,14 +102,14 @@ CLASSES = [
     # ... and of 4 n + 2 positions from 129 (bf16: two or six elements of the last granule belong to the row, the last
     # group of four outputs of a row is stored by element)
     (300, 12, 198, 31, 15), (64, 2, 506, 64, 63), (50, 3, 134, 16, 15), (21, 3, 774, 7, 3), (40, 5, 202, 48, 24), (33, 2, 130, 66, 0),
-    # ... and of odd lengths (fp32: one to three floats of the last granule belong to the row; bf16: the vector-ALU kernels)
+    # ... and of odd lengths (fp32: one to three floats of the last granule belong to the row; bf16: rows shifted to the dword they start in)
     (300, 12, 199, 31, 15), (64, 2, 507, 64, 63), (50, 3, 133, 16, 15), (21, 3, 773, 7, 3), (40, 5, 201, 48, 24), (33, 2, 129, 66, 0),
     (17, 4, 365, 48, 47),
     # ... bf16 rows of 64 to 128 positions of even length
     (90, 3, 98, 48, 24), (70, 4, 126, 31, 15), (130, 2, 66, 16, 15), (40, 5, 70, 7, 3),
     # longer short rows (virtual rows) with seven to sixteen block offsets
     (20, 3, 256, 100, 99), (9, 2, 384, 160, 80), (6, 4, 512, 226, 0), (12, 256, 200, 130, 129), (7, 3, 640, 200, 100),
-    # rows of nine to thirty-two blocks with filters of the order of the row length: sixteen rows per tile, filter in LDS
+    # rows of nine to thirty-two blocks with filters of the order of the row length: band kernels, whole rows per item
     (20, 3, 256, 256, 255), (9, 2, 512, 512, 256), (33, 4, 160, 160, 80), (5, 3, 384, 700, 350), (18, 2, 144, 1000, 999),
     (7, 256, 192, 192, 191), (4, 2, 512, 2048, 1024), (70, 5, 132, 300, 0), (3, 2, 500, 500, 499),
     # ... rows that are not whole granules of four
@@ -123,11 +123,11 @@ CLASSES = [
     # 768 positions; bf16: even lengths), ragged last segments, rows that end one, two and three positions into a granule
     (2, 3, 2050, 64, 63), (3, 5, 4097, 31, 15), (2, 4, 1026, 7, 3), (3, 2, 1027, 66, 0), (5, 3, 769, 16, 15), (2, 2, 3075, 48, 24),
     (4, 256, 2049, 64, 63), (3, 2, 1030, 33, 16), (2, 3, 5001, 20, 19),
-    # ... with seven to sixteen block offsets (fp32: register-staged forward, weight gradient in one to three launches)
+    # ... with seven and more block offsets (fp32: register-staged forward or band kernel)
     (2, 3, 2050, 128, 127), (3, 2, 1027, 160, 80), (2, 2, 4098, 226, 100), (1, 3, 3001, 100, 99), (2, 2, 2050, 482, 481),
     (2, 2, 1026, 700, 350), (2, 256, 1025, 130, 129),
-    # filters or rows beyond what LDS holds whole: forward / input gradient in pieces of 4096 outputs and chunks of 4096
-    # taps, the fp32 weight gradient in dozens of launches of sixteen block offsets
+    # filters or rows beyond what LDS holds whole: forward / input gradient in pieces of rows and chunks of taps, the weight
+    # gradient in windows of block offsets
     (1, 2, 9000, 300, 299), (1, 1, 16384, 16384, 16383), (2, 1, 12000, 9000, 4000), (1, 2, 20000, 8192, 100),
     (3, 1, 8200, 8200, 0), (1, 2, 9000, 900, 899), (2, 2, 8196, 2000, 1000),
     # one workgroup per channel: the weight gradient as a single kernel
@@ -213,6 +213,14 @@ def test_exact_corr_band(oracle_mod, B, C, L, K, p, dtype, offset):
 def test_exact_corr_band_pieces(oracle_mod, B, C, L, K, p, dtype):
     print(f"case exact corr_band pieces {dtype} B{B} C{C} L{L} K{K} p{p}", flush=True)
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=23 + B + 3 * C + 5 * L, fused=False, two_stage=False)
+
+
+# ... fp32, two tiles per wave with a third workgroup per compute unit (windows of two and a half to four granules per thread):
+# batches that are not whole items, spare tiles, pieces of equal length
+@pytest.mark.parametrize("B,C,L,K,p", [(66, 256, 160, 160, 80), (70, 256, 192, 100, 99), (65, 260, 224, 110, 0), (8, 130, 2100, 200, 199), (9, 300, 700, 230, 30)])
+def test_exact_corr_band_third_workgroup(oracle_mod, B, C, L, K, p):
+    print(f"case exact corr_band third workgroup B{B} C{C} L{L} K{K} p{p}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, "f32", seed=25 + B + 3 * C + 5 * L, fused=False, two_stage=False)
 
 
 # dw_band_kernel: one window of four to sixteen offsets and several, rows cut into virtual rows (fewer than five batch
@@ -399,10 +407,10 @@ SEVERAL_UNITS = [
     (400, 256, 196, 48, 24),       # ... rows of 8 n + 4 positions (bf16: the last granule of a row is half gap)
     (600, 256, 100, 33, 16),       # ... from 64 positions on bf16 storage
     (400, 256, 198, 48, 24),       # ... rows of 4 n + 2 positions
-    (400, 256, 199, 48, 24),       # ... rows of odd length (fp32 virtual rows; bf16 on the vector-ALU kernels)
+    (400, 256, 199, 48, 24),       # ... rows of odd length (bf16: shifted to the dword they start in)
     (700, 256, 98, 48, 24),        # ... bf16 rows below 129 positions of even length
     (40, 256, 1027, 160, 80),      # ordinary rows that are not whole granules, eleven block offsets
-    (300, 256, 256, 256, 255),     # rows of sixteen blocks, filter in LDS
+    (300, 256, 256, 256, 255),     # rows of sixteen blocks, band kernels
 ]
 
 
