@@ -170,7 +170,9 @@ DWCONV_API int dwconv_bwd_weight_slices(int B, int C, int L, int K, int pad_left
 
 /*
  * 1 when, for this shape and 16-byte aligned tensors, dwconv_bwd_weight runs as a single kernel
- * (one workgroup per channel, S = 1, no second stage); 0 otherwise or on bad arguments.
+ * because one workgroup reduces a whole channel (S = 1, no second stage); 0 otherwise or on bad arguments.  (Where
+ * it is 0, S > 1 and filters are long, dwconv_bwd_weight may still need no second stage and leave the workspace alone;
+ * dwconv_bwd_weight_partial always writes all S slices.)
  */
 DWCONV_API int dwconv_bwd_weight_single_pass(int B, int C, int L, int K, int pad_left, int dtype);
 

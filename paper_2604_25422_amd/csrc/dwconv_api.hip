@@ -173,10 +173,12 @@ static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
     return segs > 16 || (nd >= 11 && segs * s.C > 1024);
 }
 
-// Slices of dw_band_kernel on ordinary rows: about two workgroups per compute unit over channels, windows of offsets and
-// slices, a slice being two rows at least; two slices at least and a workspace of at most 64 MiB beyond that.  0: the slices
-// that the segments of the row give (times one per started sixteen offsets).  (More slices than stages: the surplus workgroups
-// write zeros.)
+// Slices of the workspace for the filters of dw_band_kernel.  Callers keep workspaces and read slices by these numbers
+// (dwconv_bwd_weight_slices), so they stay what they have been although the kernel mostly uses fewer (DwBandPlan::S, chosen from
+// the channels, windows and stages there are): a call that takes the gradient sums only those used, dwconv_bwd_weight_partial
+// writes zeros to the rest.  About two workgroups per compute unit over channels, windows of offsets and slices, a slice being
+// two rows at least; two slices at least and a workspace of at most 64 MiB beyond that.  0: the slices that the segments of the
+// row give (times one per started sixteen offsets).
 static int dw_band_slices(const Shape &s, const RowsPlan &rp, int nd)
 {
     const int nb = (s.L + 15) / 16;

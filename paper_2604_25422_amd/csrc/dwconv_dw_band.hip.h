@@ -17,10 +17,13 @@
 // Several windows (more than twelve offsets in fp32, sixteen in bf16): a tap takes its products from two neighbouring
 // offsets, so a window shares its last offset with the next one and owns the taps that need no other window's offsets.
 //
-// What bounds it: at B8 C256 K = L = 8192 fp32 the matrix pipe (793 us where 206 G multiply-adds in six bf16 products take 520
-// at the 2.4 PFLOP/s a loop of nothing but this instruction reaches; the fp32 instruction it replaces 1100), bf16 the LDS reads (one
-// 16-byte read per lane and instruction: 185 us, before 250); with short rows the staging (B2048 C128 K = L = 256 fp32 207 us
-// of which two reads of memory are 104, before 366; bf16 B512 C256 L256 K256 39 us, before 184).  The reads of the next operand go
+// What bounds it (counters: share of a launch's cycles in which the unit is busy).  B8 C256 K = L = 8192 fp32: matrix pipe 54 %,
+// vector ALU (splitting and transposing every stage once per window) 41 %, under a lowered clock: 793 us where 206 G multiply-adds
+// in six bf16 products take 520 at the 2.4 PFLOP/s a loop of nothing but this instruction reaches; the fp32 instruction it replaces
+// 1100.  bf16: LDS 59 % (one 16-byte read per lane and instruction), vector ALU 37 %, matrix pipe 30 %: 201 us, before 250.  Short
+// rows, B2048 C128 K = L = 256 fp32: vector ALU 42 %, matrix pipe 27 %, 206 us of which two reads of memory are 104, before 366
+// (bf16 B512 C256 L256 K256 51 us, before 184): one stage in LDS at a time, so that these only overlap across the two workgroups of a
+// compute unit, and causal filters give the waves unequal numbers of block pairs.  The reads of the next operand go
 // out ahead of each group of products, the loads of the next stage ahead of a stage's.  Error against 64 bits (fp32 long
 // filter): 2.4e-7, the fp32 instruction 9.4e-7.
 #pragma once

@@ -66,7 +66,7 @@ constexpr int kMfmaMinK = 1;      // (one and two taps ran 2.4x slower on the ve
                                   // against 133 us at three taps)
 constexpr int kMfmaMaxND = 6;          // fused backward, bf16, short rows
 constexpr int kMfmaMaxNDWide = 10;     // fp32 on long rows, K up to 130: whole-channel workgroups for dW still possible
-constexpr int kMfmaMaxNDDw = 16;       // virtual rows, and the unit in which dW slices of longer filters grow
+constexpr int kMfmaMaxNDDw = 16;       // register-resident weight gradient, and the unit in which dW slices of longer filters grow
 constexpr int kMfmaMaxNDDw3 = 48;      // fp32 dW slices: as many per segment group as started sixteen offsets up to here
 constexpr int kMfmaMaxNDDw4 = 64;      // ... bf16
 // forward, input gradient on ordinary rows with the Toeplitz operands in registers (more: corr_band_kernel; fp32 thirteen and

@@ -134,7 +134,7 @@ def test_single_pass_query(lib):
     assert f(128, 768, 1024, 32, 31, 1) == 1
     assert f(40, 64, 1024, 16, 15, 0) == 0           # channels do not fill the chip
     assert f(4, 64, 1024, 16, 15, 0) == 1            # ... but at most four segments per wave: launch-bound, one kernel
-    assert f(8, 256, 8192, 8192, 8191, 0) == 0       # long filter: two zero-filled slices
+    assert f(8, 256, 8192, 8192, 8191, 0) == 0       # long filter: a workspace of two slices
     assert f(1, 256, 1024, 16, 15, 0) == 1           # a single segment per channel: one kernel as well
     assert f(32, 256, 4098, 64, 63, 0) == 1          # row length not a multiple of 4: rows still start on a dword
     assert f(32, 256, 4098, 128, 127, 0) == 0        # ... but only up to six block offsets
@@ -144,20 +144,20 @@ def test_single_pass_query(lib):
     assert lib.dwconv_bwd_is_fused(4, 8, 500, 64, 63, 0) == 1 and lib.dwconv_bwd_is_fused(4, 8, 502, 64, 63, 0) == 1
     assert lib.dwconv_bwd_is_fused(4, 8, 503, 64, 63, 0) == 1 and lib.dwconv_bwd_is_fused(4, 8, 503, 64, 63, 1) == 0
     assert lib.dwconv_bwd_is_fused(4, 8, 502, 128, 127, 0) == 0      # ... up to six block offsets
-    # seventeen to thirty-two block offsets: two launches over halves of the offsets, each into its own slices,
-    # so an even number of slices and never one kernel - also for small problems, in either storage type
+    # seventeen and more block offsets: the workspace has as many slices per segment group as started sixteen offsets, of which
+    # dw_band_kernel may need fewer; never the answer "one kernel" - also for small problems, in either storage type
     S226, S256 = lib.dwconv_bwd_weight_slices(32, 256, 4096, 226, 225, 0), lib.dwconv_bwd_weight_slices(32, 256, 4096, 256, 255, 0)
     assert S256 == 2 * S226 and f(32, 256, 4096, 256, 255, 0) == 0
     assert f(2, 4, 1024, 300, 150, 0) == 0 and lib.dwconv_bwd_weight_slices(2, 4, 1024, 300, 150, 0) == 2
     assert lib.dwconv_bwd_weight_slices(32, 256, 4096, 256, 255, 1) == S256
-    # bf16: up to four launches (up to 64 offsets), fp32 up to three (48); beyond, the long-filter kernel: two slices per
-    # batch slice (one batch slice where channels x offset groups already fill the chip, as on the benchmark shape)
+    # ... bf16 up to 64 offsets, fp32 up to 48; beyond, two slices per batch slice (one batch slice where channels x offset
+    # groups already fill the chip, as on the benchmark shape)
     assert lib.dwconv_bwd_weight_slices(32, 256, 4096, 994, 993, 1) == 2 * S256
     assert lib.dwconv_bwd_weight_slices(32, 256, 4096, 994, 993, 0) == 4
     assert lib.dwconv_bwd_weight_slices(8, 256, 8192, 8192, 8191, 0) == 2
     assert lib.dwconv_bwd_weight_slices(1000, 1, 1024, 2000, 1000, 0) == 250    # one channel: 125 batch slices of eight rows
     assert 2 * lib.dwconv_bwd_weight_slices(32, 256, 4096, 600, 599, 0) == 3 * S256
-    # ... but not for rows that fill less than three quarters of their segments (long-filter kernel: two slices per batch slice)
+    # ... but not for rows that fill less than three quarters of their segments (two slices per batch slice)
     assert lib.dwconv_bwd_weight_slices(64, 256, 640, 300, 150, 0) == 4 and f(64, 256, 640, 300, 150, 0) == 0
     assert f(0, 256, 4096, 64, 63, 0) == 0           # bad shape
 

@@ -28,26 +28,25 @@ SMALL = [
     (1, 2, 40, 100, 99), (1, 2, 40, 100, 50), (2, 2, 130, 260, 129),
     (2, 3, 600, 64, 63), (1, 2, 4100, 64, 32), (2, 2, 1500, 300, 299), (1, 1, 3000, 700, 350),
     (1, 2, 1100, 1030, 1029),
-    # long-filter matrix-core kernels: odd batch (row pairing), paper-style and anti-causal pads, every group size
+    # long filters on the band kernels: odd batches, paper-style and anti-causal pads
     (3, 2, 256, 200, 100), (2, 3, 512, 512, 511), (1, 2, 2048, 1500, 700), (2, 2, 1024, 130, 129),
     (1, 1, 1024, 90, 0), (3, 1, 640, 640, 320), (1, 2, 4096, 4096, 4095), (2, 1, 1000, 2500, 1200),
     (1, 1, 8192, 300, 299), (1, 2, 72, 67, 66),
     # seven to ten block offsets (fp32 register-resident class up to K = 130): every count, ragged rows, several rows per wave
     (3, 5, 2060, 100, 99), (2, 3, 1028, 112, 50), (5, 2, 3072, 128, 127), (2, 2, 1100, 130, 0), (9, 4, 1024, 97, 96),
-    # eleven to sixteen block offsets: register-resident kernels (fwd/dX: rows that fill three quarters of their
-    # 1024-position segments, the long-filter kernel otherwise); every count, ragged rows, several segments per wave
+    # eleven to sixteen block offsets: register-resident and band kernels on either side of their rules; every count, ragged
+    # rows, several segments per wave
     (3, 4, 2060, 160, 159), (2, 3, 1028, 226, 100), (5, 2, 3072, 200, 0), (2, 2, 1100, 180, 90),
     (7, 2, 1024, 161, 80), (3, 3, 1024, 176, 175), (2, 5, 800, 190, 95), (4, 2, 3000, 215, 214), (2, 3, 2048, 226, 225),
     (2, 2, 4092, 226, 0), (70, 32, 1024, 170, 169),
-    # seventeen to thirty-two block offsets: the weight gradient in two passes over the offsets (second pass with
-    # windows that start past the end of the row when pad is small), fwd/dX on the long-filter kernel
+    # seventeen to thirty-two block offsets: the band kernels (dW: windows that start past the end of the row when pad is small)
     (3, 4, 1024, 256, 255), (2, 3, 2048, 300, 150), (2, 2, 3000, 482, 481), (5, 2, 1024, 400, 0), (4, 2, 4092, 350, 100),
     (70, 32, 1024, 260, 259), (1, 1, 800, 480, 0),
     # long filters on short rows: many rows per workgroup, batches that are not whole groups of them
     (21, 2, 1024, 600, 599), (11, 2, 2048, 900, 450), (37, 1, 512, 700, 0),
-    # thirty-three to forty-eight block offsets: the weight gradient in three passes
+    # thirty-three to forty-eight block offsets: the weight gradient in several windows of offsets
     (2, 3, 2048, 700, 350), (2, 2, 3000, 513, 0), (40, 8, 1024, 530, 529), (3, 2, 1024, 738, 737),
-    # filters or rows beyond 8192: tiled long-filter forward / input gradient, many-launch weight gradient
+    # filters or rows beyond 8192: taps in chunks (forward / input gradient), many windows of offsets (weight gradient)
     (1, 2, 9000, 300, 299), (1, 1, 16384, 16384, 16383), (2, 1, 12000, 9000, 4000), (3, 1, 8200, 8200, 0),
     (1, 2, 9000, 900, 899), (1, 1, 32768, 20000, 19999),
     # matrix-core kernels at row lengths that are multiples of 4 but not of 8, 16 or 64
@@ -113,13 +112,13 @@ def test_small_shapes_f32(oracle_mod, B, C, L, K, p):
                                                    (2, 3, 512, 512, 511), (3, 1, 640, 640, 320), (1, 2, 4096, 4096, 4095),
                                                    (2, 1, 1000, 2500, 1200), (1, 1, 8192, 300, 299), (3, 2, 1024, 1024, 0),
                                                    (5, 2, 4100, 700, 350), (3, 3, 260, 513, 17), (1, 1, 8192, 8192, 8191),
-                                                   # bf16 weight gradient in two passes over seventeen to thirty-two offsets
+                                                   # bf16 weight gradient, seventeen to thirty-two offsets
                                                    (3, 4, 1024, 256, 255), (2, 3, 2048, 300, 150), (2, 2, 3000, 482, 481),
                                                    (5, 2, 1024, 400, 0), (70, 32, 1024, 260, 259), (1, 1, 8192, 300, 299),
                                                    # long filters on short rows: many rows per workgroup, batches that
                                                    # are not whole groups of them
                                                    (21, 2, 1024, 600, 599), (11, 2, 2048, 900, 450), (37, 1, 512, 700, 0),
-                                                   # bf16 weight gradient in three and four passes (33 to 64 offsets)
+                                                   # ... 33 to 64 offsets
                                                    (2, 3, 2048, 700, 350), (3, 2, 1024, 994, 993), (2, 2, 3000, 513, 0),
                                                    (40, 8, 1024, 530, 529)])
 def test_small_shapes_bf16(oracle_mod, B, C, L, K, p):
