@@ -432,9 +432,9 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                             const int k = u * N + t, tt = T0 + t;
                             const bool last = t + 1 == N;
                             const uintx4 (&bb)[NL] = b[k & 1];
-                            if (last) step(e, more);
                             if constexpr (NL == 3) {
                                 uintx4 (&av)[NL] = a[0];
+                                if (last) step(e, more);
                                 read_b(b[(k + 1) & 1], last ? 0 : t + 1);
                                 // (an accumulator for each scale: what rounds at the size of the sum is one addition per e, not six)
                                 low[tt] = mfma32x32x16(av[2], bb[0], low[tt]);
@@ -447,8 +447,13 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                                 low[tt] = mfma32x32x16(av[0], bb[2], low[tt]);
                                 if (last) read_limb(av, 0);
                             } else {
-                                if (last) read_limb(a[1 - u], 0);
-                                read_b(b[(k + 1) & 1], last ? 0 : t + 1);
+                                if (t + 1 < N) {
+                                    read_b(b[(k + 1) & 1], t + 1);
+                                } else {
+                                    step(e, more);
+                                    read_limb(a[1 - u], 0);
+                                    read_b(b[(k + 1) & 1], 0);
+                                }
                                 acc[tt] = mfma32x32x16(a[u][0], bb[0], acc[tt]);
                             }
                         }
