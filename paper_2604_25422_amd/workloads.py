@@ -1,7 +1,7 @@
 """Seeded synthetic inputs for the depthwise-convolution hot path.
 
 This module holds no arithmetic of the operator itself: it only draws the
-tensors that both the HIP library and the CPU checker are fed.  The shapes are
+tensors that both the HIP library and the CPU oracle are fed.  The shapes are
 the five benchmark configurations of this build (index 1 is the headline
 training-step shape) plus, as index 5, the shape of the paper's own measurements
 (Sec. V: B = 16384, H = 128, L = 48, K = 48, pad K/2); seeded random tensors stand in for the S4ConvD
