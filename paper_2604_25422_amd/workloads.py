@@ -2,7 +2,7 @@
 
 This module holds no arithmetic of the operator itself: it only draws the
 tensors that both the HIP library and the CPU oracle are fed.  The shapes are
-the five benchmark configurations of this build (index 1 is the headline
+the five benchmark configurations (index 1 is the headline
 training-step shape) plus, as index 5, the shape of the paper's own measurements
 (Sec. V: B = 16384, H = 128, L = 48, K = 48, pad K/2); seeded random tensors stand in for the S4ConvD
 activations of the paper's ASHRAE GEPIII workload (Sec. III-A..C), whose
