@@ -173,6 +173,29 @@ static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
     return segs > 16 || (nd >= 11 && segs * s.C > 1024);
 }
 
+// Which of dw_band_kernel's filters go to dw_toep_kernel: by the products of 32 x 32 x 16 that either would form.  dw_toep_kernel
+// stages less per product but its tiles are 1024 lags wide: lags beyond the filter, and positions that only the far lags of a tile
+// have lost, are multiplied all the same.  dw_band_kernel has groups of eight rows to fill (fewer batch entries: virtual rows, whose
+// stages are small), and a stage of its own for every twelve (bf16 sixteen) offsets of 32.  us, dw_band_kernel -> dw_toep_kernel,
+// with the ratio of the products:
+//   fp32, five batch entries and more: B8 C256 L8192 K8192 (1.12) 778 -> 628, B17 C736 L889 K889 (1.06) 188 -> 126, B49 C32 L3184
+//     K3184 (1.20) 171 / 176, B97 C96 L1856 K1856 (1.56) 248 / 279, B284 C103 L768 K768 (1.70) 212 / 303
+//   bf16: B8 C256 L8192 K8192 (1.12) 201 -> 127, B12 C355 L1832 K1832 (1.28) 54 -> 37, B7 C128 L4367 K4367 (1.36) 55 -> 37, B275 C83
+//     L880 K880 (1.49) 52 / 66, B53 C264 L784 K784 (1.60) 36 / 46
+//   fewer batch entries, fp32: B4 C71 L912 K912 (1.92) 11.1 / 12.0, B1 C365 L5675 K5675 (1.19) 215 -> 73, B4 C672 L1080 K1080 (1.84) 64 -> 52, B1 C396 L1104 K1104 (2.15)
+//     35 -> 14, B3 C64 L7667 K163 (4.7) 14 / 24; bf16: B3 C320 L3968 K3968 (0.96) 83 -> 28, B2 C384 L1150 K1150 (2.59) 17.1 -> 7.7
+static bool dw_takes_toep(const Shape &s, const DwPlan &p)
+{
+    const double lo = std::min(s.pad, s.L - 1), hi = std::min(s.K - 1 - s.pad, s.L - 1);           // lags -lo .. hi
+    const double pairs = (lo + hi + 1) * s.L - (lo * (lo + 1) + hi * (hi + 1)) / 2;
+    const int nseg = p.bp.g.nseg;
+    const double groups = (double)(((long long)s.B * nseg + 7) / 8);
+    // (two blocks at a time: half a product lost per offset of 32 at the end of the row, and the offsets at both ends of the filter)
+    const double band = groups * (8.0 * pairs / nseg / (1024 * 16) + 0.75 * ((lo + hi + 1) / 32 + 2));
+    const double most = s.dtype == DWCONV_F32 ? (nseg > 2 ? 2.2 : nseg > 1 ? 1.85 : 1.15) : (nseg > 1 ? 2.6 : 1.42);
+    return p.tp.work <= most * band;
+}
+
 // Slices of the workspace for the filters of dw_band_kernel.  Callers keep workspaces and read slices by these numbers
 // (dwconv_bwd_weight_slices), so they stay what they have been although the kernel mostly uses fewer (DwBandPlan::S, chosen from
 // the channels, windows and stages there are): a call that takes the gradient sums only those used, dwconv_bwd_weight_partial
@@ -273,6 +296,7 @@ DwPlan plan_dw(const Shape &s)
     }
     p.band_fits = (nd > kMfmaMaxND || p.rows.tall) && plan_dw_band(s, p.S, &p.bp);
     p.band = p.band && p.band_fits;
+    p.toep = p.band && plan_dw_toep(s, p.S, &p.tp) && dw_takes_toep(s, p);
     // the fused backward kernel of these shapes works on one channel per block: its own slice count
     p.S_fused = p.S;
     if (p.rows.batch && s.L <= dwconv::kRbBwdMaxL) {

@@ -21,6 +21,7 @@
 #include "dwconv_rowbatch.hip.h"
 #include "dwconv_corr_direct.hip.h"
 #include "dwconv_dw_band.hip.h"
+#include "dwconv_dw_toep.hip.h"
 
 namespace dwhost {
 
@@ -235,10 +236,22 @@ struct DwBandPlan {
 };
 bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p);
 
+// Stage 1 on dw_toep_kernel (filters of hundreds of taps and more).
+struct DwToepPlan {
+    dwconv::DwToepGeom g;
+    int T;                 // tiles of 1024 lags per workgroup (the kernel is compiled per number)
+    int S;                 // slices it uses: at most those of the workspace
+    double work;           // products of 32 x 32 x 16 of a channel
+    size_t lds;
+};
+bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p);
+
 struct DwPlan {
     bool band;             // dw_band_kernel (dw_takes_band)
     bool band_fits;        // it can run: where the kernel of the plan does not take the tensors (bf16 bases off a 16-byte granule)
     DwBandPlan bp;
+    bool toep;             // dw_toep_kernel in its place (dw_takes_toep)
+    DwToepPlan tp;
     DwKernel kernel;
     int S;                 // partial slices per coefficient
     RowsPlan rows;         // short rows: stage 1 walks the virtual row of a channel
@@ -269,6 +282,8 @@ int launch_dw_partial_bf16(const void *x, const void *dy, float *part, void *dw_
                            const DwPlan &p, hipStream_t st);
 int launch_dw_band_f32(const void *x, const void *dy, float *part, void *dw_out, const DwBandPlan &p, int slices, hipStream_t st);
 int launch_dw_band_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwBandPlan &p, int slices, hipStream_t st);
+int launch_dw_toep_f32(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st);
+int launch_dw_toep_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st);
 // (fp32, seven to sixteen block offsets; returns -1 when it does not apply)
 int launch_dw_partial_wide_f32(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                                int dmin, int nd, hipStream_t st);

@@ -227,11 +227,16 @@ int launch_dw_partial(const void *x, const void *dy, float *part, void *dw_out, 
     if (slices) *slices = direct ? 0 : p.S;
     if (rc < 0 && p.band_fits) {
         // (a caller that takes the gradient needs no more slices than the launch uses)
-        const int used = dw_out ? p.bp.S : p.S;
-        direct = p.bp.S == 1 ? dw_out : nullptr;
+        const int mine = p.toep ? p.tp.S : p.bp.S, used = dw_out ? mine : p.S;
+        direct = mine == 1 ? dw_out : nullptr;
         if (slices) *slices = direct ? 0 : used;
-        if constexpr (std::is_same<T, float>::value) rc = launch_dw_band_f32(x, dy, part, direct, p.bp, used, st);
-        else rc = launch_dw_band_bf16(x, dy, part, direct, p.bp, used, st);
+        if (p.toep) {
+            if constexpr (std::is_same<T, float>::value) rc = launch_dw_toep_f32(x, dy, part, direct, p.tp, used, st);
+            else rc = launch_dw_toep_bf16(x, dy, part, direct, p.tp, used, st);
+        } else {
+            if constexpr (std::is_same<T, float>::value) rc = launch_dw_band_f32(x, dy, part, direct, p.bp, used, st);
+            else rc = launch_dw_band_bf16(x, dy, part, direct, p.bp, used, st);
+        }
     }
     if (rc >= 0) return rc;
     if (slices) *slices = p.S;

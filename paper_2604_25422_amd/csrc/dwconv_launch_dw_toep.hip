@@ -1,0 +1,97 @@
+// Stage 1 of the weight gradient for filters of hundreds of taps and more (dwconv_dw_toep.hip.h), both storage types: the plan
+// and the launchers.
+#include "dwconv_dw_toep.hip.h"
+#include "dwconv_host.hip.h"
+#include <algorithm>
+
+namespace dwhost {
+
+// Depends on the shape only.  False: no geometry (rows of fewer than eight positions, more pieces than a grid holds).
+// slices: those of the workspace, at least as many as the plan uses.
+bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
+{
+    if (s.L < 8 || s.L > kMfmaMaxL) return false;
+    dwconv::DwToepGeom &g = p->g;
+    const int NL = s.dtype == DWCONV_F32 ? 3 : 1;
+    g.B = s.B; g.C = s.C; g.L = s.L; g.K = s.K; g.pad = s.pad;
+    const long long first = std::max(-(long long)s.pad, -(long long)(s.L - 1)), last = std::min((long long)s.K - 1 - s.pad, (long long)s.L - 1);
+    g.blk0 = (int)(first >> 5);
+    g.shift = (int)(first & 31);
+    g.nblk = (int)((last - first) >> 5) + 1;
+    const int tiles = (g.nblk + 31) / 32;
+    // tiles per workgroup: as many as registers hold while there are three workgroups per compute unit (bf16 B8 C256 K = L = 8192,
+    // 512 workgroups of four tiles 140 us, 1024 of two 125, 2048 of one 152; fp32 there 1024 of two 618, 2048 of one 658)
+    p->T = NL == 3 ? 2 : 4;
+    while (p->T > 1 && (p->T / 2 >= tiles || (long long)s.C * ((tiles + p->T - 1) / p->T) < 3 * kComputeUnits)) p->T /= 2;
+    g.npiece = (tiles + p->T - 1) / p->T;
+    if (g.npiece > 65535) return false;
+    // chunks of equal length, as few as fit half the LDS of a compute unit (a third where registers allow a third workgroup)
+    const size_t budget = kMaxLdsBytes / (size_t)dwconv::toep_waves(NL, p->T);
+    const int whole = (s.L + 31) / 32 + 64;                               // blocks of X that any tile can reach
+    for (int n = 1;; ++n) {
+        g.F = (int)((((long long)s.L + n - 1) / n + 31) / 32 * 32);
+        const int blocks = std::min(dwconv::toep_blocks(p->T, g.F), whole);
+        p->lds = dwconv::dw_toep_lds_bytes(NL, blocks, g.F);
+        g.tap_off = (int)dwconv::dw_toep_tap_offset(NL, blocks);
+        if (4 * blocks <= dwconv::kToepX * dwconv::kToepThreads && g.F <= 8 * dwconv::kToepY * dwconv::kToepThreads && p->lds <= budget) break;
+    }
+    // products of 32 x 32 x 16 of a batch entry: in all, and of the piece that has most
+    double most = 0.0;
+    p->work = 0.0;
+    for (int i = 0; i < g.npiece; ++i) {
+        double piece = 0.0;
+        for (int t = i * p->T; t < std::min(tiles, (i + 1) * p->T); ++t) {
+            const long long o0 = first + 1024ll * t, from = std::max(0ll, -(o0 + 1023)), to = std::min((long long)s.L, s.L - o0);
+            piece += std::max(0ll, to - from + 30) / 16 + 1;
+        }
+        p->work += piece;
+        most = std::max(most, piece);
+    }
+    // slices: three workgroups per compute unit and none with more than its share, as far as the batch and the workspace go, where
+    // that is worth a second launch (fp32 B11 C64 L4135 K4135 139 us in one slice)
+    const long long wgs = (long long)s.C * g.npiece, slots = 3ll * kComputeUnits;
+    const long long stages = (long long)s.B * (((long long)s.L + g.F - 1) / g.F);
+    const double us = 1.2 * stages + most * s.B * (NL == 3 ? 6 : 1) * 32.0 / 4 / 2000.0;      // (of a workgroup that has its SIMDs to itself)
+    long long S = 1;
+    if (us > 10.0) S = std::min((long long)(us / 4.0), std::max((slots + wgs - 1) / wgs, (long long)(most * slots / (p->work * s.C) + 0.5)));
+    S = std::max(1ll, std::min(S, (long long)std::min(s.B, slices)));
+    g.rows = (int)((s.B + S - 1) / S);
+    p->S = (s.B + g.rows - 1) / g.rows;
+    p->work *= s.B;
+    return true;
+}
+
+template <typename E>
+static int launch_dw_toep(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
+{
+    auto go = [&](auto kernel) -> int {
+        if (p.lds > 64 * 1024 && !allow_large_lds(kernel)) return DWCONV_ERR_LAUNCH;
+        // (a grid dimension holds fewer than 2^32 threads: further channels in launches of their own)
+        for (int c0 = 0; c0 < p.g.C; c0 += kMaxGridChannels) {
+            const int n = p.g.C - c0 < kMaxGridChannels ? p.g.C - c0 : kMaxGridChannels;
+            const size_t row = (size_t)c0 * (size_t)p.g.L, taps = (size_t)c0 * (size_t)p.g.K;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.S, (unsigned)p.g.npiece), dim3(dwconv::kToepThreads), p.lds, st,
+                               static_cast<const E *>(x) + row, static_cast<const E *>(dy) + row, part + taps,
+                               dw_out ? static_cast<E *>(dw_out) + taps : nullptr, p.g, slices);
+        }
+        return launch_status();
+    };
+    switch (p.T) {
+    case 1: return go(dwconv::dw_toep_kernel<E, 1>);
+    case 2: return go(dwconv::dw_toep_kernel<E, 2>);
+    default:
+        if constexpr (std::is_same<E, float>::value) return DWCONV_ERR_LAUNCH;       // (never planned)
+        else return go(dwconv::dw_toep_kernel<E, 4>);
+    }
+}
+
+int launch_dw_toep_f32(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
+{
+    return launch_dw_toep<float>(x, dy, part, dw_out, p, slices, st);
+}
+int launch_dw_toep_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
+{
+    return launch_dw_toep<bf16_t>(x, dy, part, dw_out, p, slices, st);
+}
+
+}  // namespace dwhost

@@ -247,6 +247,25 @@ def test_exact_dw_band_few_rows(oracle_mod, B, C, L, K, p, dtype):
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=37 + B + 3 * C + 5 * L, fused=False)
 
 
+# dw_toep_kernel: one, two and several tiles of 1024 lags (and one lag more), first lags at every place of a block and a granule, rows
+# that end inside a granule, filters longer than the row on either side, one and several chunks of a row, several slices (with a
+# rest of batch entries), tensors off every alignment
+TOEP = [
+    (1, 3, 1024, 1024, 1023, "f32", 0), (1, 2, 1025, 1025, 512, "f32", 1), (2, 2, 1031, 2100, 1031, "f32", 0), (3, 2, 1100, 1040, 0, "f32", 3),
+    (1, 2, 2048, 2049, 2031, "f32", 0), (1, 300, 2049, 2050, 2049, "f32", 0), (1, 2, 5003, 9000, 8000, "f32", 2), (4, 2, 1066, 5000, 17, "f32", 0),
+    (8, 33, 4101, 4101, 4100, "f32", 0), (17, 10, 889, 889, 444, "f32", 1), (1, 800, 513, 513, 250, "f32", 0), (6, 130, 4100, 4100, 2050, "f32", 0),
+    (1, 2, 8, 20, 9, "bf16", 0), (1, 3, 1024, 1024, 1023, "bf16", 1), (2, 2, 1031, 2100, 1030, "bf16", 0), (1, 900, 1025, 1025, 1007, "bf16", 0),
+    (1, 2, 5003, 9000, 8000, "bf16", 0), (9, 40, 2304, 2304, 2303, "bf16", 3), (7, 5, 4367, 4367, 4366, "bf16", 0), (12, 2, 1832, 1832, 0, "bf16", 0),
+    (1, 800, 4097, 4097, 4096, "bf16", 0), (3, 2, 8200, 8200, 4095, "bf16", 5),
+]
+
+
+@pytest.mark.parametrize("B,C,L,K,p,dtype,offset", TOEP)
+def test_exact_dw_toep(oracle_mod, B, C, L, K, p, dtype, offset):
+    print(f"case exact dw_toep {dtype} B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=43 + B + 3 * C + 5 * L, offset=offset, fused=False)
+
+
 # ... and batches whose virtual row would be too long for 32-bit positions: rows of 129 to 512 positions go to the band kernels
 # with filters of any length (inputs in [-1, 1]: the weight gradient sums B L < 2^24 products)
 @pytest.mark.parametrize("B,K,p", [(12800, 66, 65), (15600, 16, 3)])
@@ -336,6 +355,13 @@ def _kernels(call):
         call()
         torch.cuda.synchronize()
     return [e.name for e in prof.events() if "dwconv::" in e.name]
+
+
+@pytest.mark.parametrize("B,C,L,K,p,dtype,offset", [TOEP[0], TOEP[7], TOEP[9], TOEP[11], TOEP[13], TOEP[17], TOEP[19]])
+def test_dw_toep_takes_long_filters(B, C, L, K, p, dtype, offset):
+    x = torch.zeros(B, C, L, device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    names = _kernels(lambda: binding.dwconv_bwd_weight(x, x, K, p))
+    assert "dw_toep_kernel" in names[0] and len(names) <= 2, names
 
 
 @pytest.mark.parametrize("B,L,K,p,dtype", [(47300, 364, 19, 9, "f32"), (16000, 512, 64, 63, "f32"), (35000, 364, 2, 0, "f32"),
