@@ -121,6 +121,21 @@ __device__ __forceinline__ void raw8_limbs(const Raw8H &r, uintx4 (&out)[1])
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[0][i] = r.v[i];
 }
+// The granule back to front.
+__device__ __forceinline__ void reverse_raw8(Raw8F &r)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { const unsigned t = r.v[i]; r.v[i] = r.v[7 - i]; r.v[7 - i] = t; }
+}
+__device__ __forceinline__ void reverse_raw8(Raw8H &r)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const unsigned t = r.v[i];
+        r.v[i] = __builtin_amdgcn_alignbit(r.v[3 - i], r.v[3 - i], 16);
+        r.v[3 - i] = __builtin_amdgcn_alignbit(t, t, 16);
+    }
+}
 // Two neighbouring taps as limbs (zeros outside the chunk are passed in).
 __device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[3]) { split_pair(a, b, p); }
 __device__ __forceinline__ void pair_limbs(float a, float b, unsigned (&p)[1])
@@ -275,18 +290,25 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                 if (i * TPR < s.n8) pre[i] = load_raw8(row + max(0, min(u0 + 8 * i * TPR, g.L - 8)));
         }
     };
-    // The taps of a chunk likewise, where there is more than one chunk.  Dword m of copy p: taps 2 m + p, 2 m + p + 1.
+    // The taps of a chunk, likewise where there is more than one chunk.  Dword m of copy 0: taps 2 m, 2 m + 1 behind the margin; of copy 1:
+    // 2 m + 1, 2 m + 2 for an odd pad, 2 m - 1, 2 m for an even one.  (The even lanes of a tap read take one copy, the odd ones the
+    // other, and either way both the same dwords, 16 of 32 banks apart; with the first form for all pads they met in a bank on the even
+    // ones: a third of the LDS cycles were conflicts, dx of bf16 B8 C256 K = L = 8192 129 -> 124 us.  Kernels of fewer tiles than there
+    // can be have the small calls: a few more instructions ahead of the first product are 0.2 us of 7 there, and LDS is not what they
+    // wait for)
+    constexpr bool LONG = FOLD || T == (NL == 3 ? 2 : 4);
+    const int odd_pad = LONG ? g.pad & 1 : 1;
+    // ... dword by dword: the shortest way to the first product.  NTF of them per thread and chunk travel through registers (bf16)
     constexpr int NTF = kBandTapPrefetch;
-    E tap[NTF][3];
     auto tap_triple = [&](int j0, int Fc, int m, E (&t3)[3]) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            const int jj = min(max(2 * m + i - kBandTapMargin, 0), Fc - 1);
+            const int jj = min(max(2 * m + i + odd_pad - 1 - kBandTapMargin, 0), Fc - 1);
             t3[i] = f_c[g.reverse ? g.K - 1 - (j0 + jj) : j0 + jj];
         }
     };
     auto store_triple = [&](int Fc, int m, const E (&t3)[3]) {
-        const int jj = 2 * m - kBandTapMargin;
+        const int jj = 2 * m + odd_pad - 1 - kBandTapMargin;
         float v[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) v[i] = (jj + i >= 0 && jj + i < Fc) ? ld_elem(&t3[i]) : 0.f;
@@ -295,16 +317,59 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
         pair_limbs(v[1], v[2], q);
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-            fs[2 * l * TP + m] = p[l];
-            fs[(2 * l + 1) * TP + m] = q[l];
+            fs[(2 * l + 1 - odd_pad) * TP + m] = p[l];
+            fs[(2 * l + odd_pad) * TP + m] = q[l];
+        }
+    };
+    // ... and by granules of eight, a tenth of the loads: filters of a thousand taps and more in one chunk, and every chunk of several
+    // in fp32 (a granule of a thread in registers).  On shorter filters a thread's chain of instructions is what counts: 0.5 us of 6.
+    typedef decltype(load_raw8(in)) Raw;
+    const int n_taps8 = g.F / 8 + 1;                                     // (the last takes over what is left)
+    auto load_taps = [&](int j0, int gi, Raw &raw, E &next) {
+        // (from inside the filter: what lies outside the chunk is put right below)
+        const int j = min(j0 + 8 * gi, g.K - 8), n = min(max(j0 + 8 * gi + (odd_pad ? 8 : -1), 0), g.K - 1);
+        raw = load_raw8(f_c + (g.reverse ? g.K - 8 - j : j));
+        next = f_c[g.reverse ? g.K - 1 - n : n];
+    };
+    auto store_taps = [&](int j0, int gi, Raw &raw, const E &next) {
+        const int Fc = min(g.F, g.K - j0), over = j0 + 8 * gi - (g.K - 8);
+        if (g.reverse) reverse_raw8(raw);
+        if (over > 0) shift_raw8(raw, over & 7);
+        zero_raw8(raw, 8 * gi >= Fc);
+        const float v = (odd_pad ? 8 * gi + 8 < Fc : gi > 0 && 8 * gi <= Fc) ? ld_elem(&next) : 0.f;
+        uintx4 limbs[NL];
+        unsigned side[NL];
+        raw8_limbs(raw, limbs);
+        pair_limbs(v, v, side);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            unsigned *to = fs + 2 * l * TP + kBandTapMargin / 2 + 4 * gi;
+            uintx4 odd;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                odd[k] = odd_pad ? __builtin_amdgcn_alignbit(k < 3 ? limbs[l][k + 1] : side[l], limbs[l][k], 16)
+                                 : __builtin_amdgcn_alignbit(limbs[l][k], k > 0 ? limbs[l][k - 1] : side[l], 16);
+            *reinterpret_cast<uintx4 *>(to) = limbs[l];
+            *reinterpret_cast<uintx4 *>(to + TP) = odd;
+            if (gi == 0) {
+                to[-1] = 0u;
+                to[TP - 1] = odd_pad ? limbs[l][0] << 16 : 0u;
+            }
         }
     };
     const bool one_chunk = (NL == 3 && !FOLD) || g.K <= g.F;             // (fp32 in several chunks: FOLD)
+    Raw tap8;
+    E beside8, tap[FOLD ? 1 : NTF][3];
     auto prefetch_taps = [&](const Stage &s) {
-        const int Fc = min(g.F, g.K - s.j0), tl = band_hide(tid);
+        const int tl = band_hide(tid);
+        if constexpr (FOLD) {
+            load_taps(s.j0, min(tl, n_taps8 - 1), tap8, beside8);
+        } else {
+            const int Fc = min(g.F, g.K - s.j0);
 #pragma unroll
-        for (int i = 0; i < NTF; ++i)
-            if (THREADS * i < TP) tap_triple(s.j0, Fc, tl + THREADS * i, tap[i]);
+            for (int i = 0; i < NTF; ++i)
+                if (THREADS * i < TP) tap_triple(s.j0, Fc, tl + THREADS * i, tap[i]);
+        }
     };
 
     floatx16 acc[T], mid[NL == 3 ? T : 1], low[NL == 3 ? T : 1], total[FOLD ? T : 1];
@@ -314,14 +379,36 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     if (cur.item < 0) return;
     advance(cur, true);
     prefetch(cur);
-    if (one_chunk) {
+    // (K >= 1024: bf16 B1 C224 L5952 K5952 20.0 -> 17.1 us; in the kernels of fewer tiles the code alone, not run, took the registers of
+    // their stages: bf16 B1579 C472 L112 K108 111 -> 125 us)
+    const bool granules = FOLD || (LONG && one_chunk && g.K >= 1024);
+    if (granules) {
+        // (what lies in front of the taps and behind them stays zero)
+        for (int m = tid; m < TP; m += THREADS)
+            if (m < kBandTapMargin / 2 - 1 || m >= kBandTapMargin / 2 + 4 * n_taps8)
+#pragma unroll
+                for (int l = 0; l < 2 * NL; ++l) fs[l * TP + m] = 0u;
+    }
+    if (!one_chunk) {
+        prefetch_taps(cur);
+    } else if (granules) {
+        // (not unrolled: what a launch runs through it first fetches from memory)
+        Raw ahead;
+        E ahead_beside;
+        if (tid < n_taps8) load_taps(0, tid, ahead, ahead_beside);
+#pragma unroll 1
+        for (int gi = tid; gi < n_taps8; gi += THREADS) {
+            Raw raw = ahead;
+            const E beside = ahead_beside;
+            if (gi + THREADS < n_taps8) load_taps(0, gi + THREADS, ahead, ahead_beside);
+            store_taps(0, gi, raw, beside);
+        }
+    } else {
         for (int m = tid; m < TP; m += THREADS) {
             E t3[3];
             tap_triple(0, g.K, m, t3);
             store_triple(g.K, m, t3);
         }
-    } else {
-        prefetch_taps(cur);
     }
     bool fresh = true;                                                   // first chunk of its item
     while (cur.item >= 0) {
@@ -337,10 +424,15 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
         }
         __syncthreads();                                                 // everyone is done with what LDS holds
         if (!one_chunk) {
-            const int Fc = min(g.F, g.K - cur.j0), tl = band_hide(tid);
+            const int tl = band_hide(tid);
+            if constexpr (FOLD) {
+                if (tl < n_taps8) store_taps(cur.j0, tl, tap8, beside8);
+            } else {
+                const int Fc = min(g.F, g.K - cur.j0);
 #pragma unroll
-            for (int i = 0; i < NTF; ++i)
-                if (tl + THREADS * i < TP) store_triple(Fc, tl + THREADS * i, tap[i]);
+                for (int i = 0; i < NTF; ++i)
+                    if (tl + THREADS * i < TP) store_triple(Fc, tl + THREADS * i, tap[i]);
+            }
         }
         {
             const int tl = band_hide(tid), ld_row = tl >> tpr_log, ld_g = tl & (TPR - 1);
@@ -379,7 +471,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
         const int ln_m = band_hide(lane), col = ln_m & 31, kg = ln_m >> 5;
         // A: taps 16 e + 8 kg + v - r + pad, r = col: four dwords of the copy in which the first starts one.  B: the lane's column of tile t, block (m0 + blk + e / 2), half e % 2.
         const int a0 = 8 * kg - col + g.pad - cur.j0 + kBandTapMargin;
-        const unsigned *a_base = fs + (a0 & 1) * TP + (a0 >> 1);
+        const unsigned *a_base = fs + (a0 & 1) * TP + ((a0 + 1 - odd_pad) >> 1);
         const unsigned char *b_base = xs + (col >> g.nb_log) * g.pitch + 16 * kg + ((col & (NBk - 1)) + cur.p0 - cur.wb0) * BS;
         int rel[T], lo[T], hi[T];
 #pragma unroll
