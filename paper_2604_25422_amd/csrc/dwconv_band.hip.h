@@ -182,6 +182,9 @@ struct BandGeom {
     int F;              // taps per chunk
     int pitch;          // bytes of one staged row
     int TG;             // tile groups; the e of a chunk are split W / TG ways
+    int fold;           // TG - 1 (TG is a power of two): every other round of tiles over the groups goes back to front (causal filters: the
+                        // work grows or falls along the row); otherwise 0
+    int tile0;          // the first tile of the first round: negative where there are spare tiles and the work grows
 };
 // dwords of one of the two copies of a chunk's taps (copies 16 banks apart: the even and the odd lanes of a read)
 __host__ __device__ inline int band_tap_dwords(int F) { return ((F + 2 * kBandTapMargin) / 2 + 1 + 31) / 32 * 32 + 16; }
@@ -223,6 +226,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     const int NBk = 1 << g.nb_log;
     const int c = blockIdx.x;
     const int tg = wave % g.TG, ks = wave / g.TG, KS = W / g.TG;
+    auto tile_of = [&](int group, int t) { return g.tile0 + g.TG * t + ((t & 1) ? group ^ g.fold : group); };
     const int NCH = (g.L + 15) >> 4, NB32 = (g.L + 31) >> 5;
     constexpr int BS = band_block_bytes(NL);
     const int TP = band_tap_dwords(g.F);
@@ -476,9 +480,9 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
         int rel[T], lo[T], hi[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            rel[t] = (tg + g.TG * t) << g.nb_log;
+            rel[t] = tile_of(tg, t) << g.nb_log;
             const int m0 = cur.p0 + rel[t];                              // first block of the tile
-            const bool any = m0 < NB32 && rel[t] < g.PB;                 // (otherwise a spare tile)
+            const bool any = m0 < NB32 && (unsigned)rel[t] < (unsigned)g.PB;     // (otherwise a spare tile)
             lo[t] = max(cur.e_lo, -2 * (m0 + NBk - 1));
             hi[t] = any ? min(cur.e_hi, NCH - 1 - 2 * m0) : -(1 << 28);
         }
@@ -626,8 +630,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                 if (KS == 1) {
                     // the wave's own tile
                     wave_lds_fence();
-                    const int tile = tg + g.TG * t;
-                    if (cur.p0 + (tile << g.nb_log) < NB32 && (tile << g.nb_log) < g.PB) {
+                    const int tile = tile_of(tg, t);
+                    if (cur.p0 + (tile << g.nb_log) < NB32 && (unsigned)(tile << g.nb_log) < (unsigned)g.PB) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
                             store4(tile, q, *reinterpret_cast<const floatx4 *>(r_base + (32 * wave + 8 * q) * kBandRedPitch));
@@ -640,8 +644,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                         const float *r = r_base + (32 * gq + 8 * wave) * kBandRedPitch;
                         floatx4 v = *reinterpret_cast<const floatx4 *>(r);
                         for (int k = 1; k < KS; ++k) v += *reinterpret_cast<const floatx4 *>(r + k * g.TG * 32 * kBandRedPitch);
-                        const int tile = gq + g.TG * t;
-                        if (cur.p0 + (tile << g.nb_log) < NB32 && (tile << g.nb_log) < g.PB) store4(tile, wave, v);
+                        const int tile = tile_of(gq, t);
+                        if (cur.p0 + (tile << g.nb_log) < NB32 && (unsigned)(tile << g.nb_log) < (unsigned)g.PB) store4(tile, wave, v);
                     }
                 }
             }

@@ -84,6 +84,13 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
     for (int nb = nb_min < 4 && nb32 > 32 ? 4 : nb_min; nb <= 5 && !ok; ++nb) ok = fit(nb, false);
     if (!ok) return -1;
     g.NP = (nb32 + g.PB - 1) / g.PB;
+    // Tiles q, 2 TG - 1 - q, ... for wave group q where the work of a tile falls along the row, the same from the end of the row where it
+    // grows (spare tiles are where there is little to do); q, TG + q, ... where it is largest in the middle, or an item is not the
+    // whole row and its tiles differ little (fp32 B19 C303 L1356 K1356 causal forward 85 us, 91 the other way).  Causal, forward and
+    // input gradient, us: fp32 B2048 C128 L256 K256 169 -> 163, 164 -> 157, B186 C69 L736 K736 61 -> 57, 59 -> 54, B1 C583 L3040 K3040
+    // 47 -> 42, 47 -> 42
+    g.fold = g.NP == 1 && (4ll * pad_eff < s.K || 4ll * (s.K - 1 - pad_eff) < s.K) ? g.TG - 1 : 0;
+    g.tile0 = g.fold && 2 * pad_eff > s.K ? (g.PB >> g.nb_log) - T * g.TG : 0;
     g.np_magic = g.NP > 1 ? (unsigned)((1ull << 32) / (unsigned)g.NP) + 1u : 0u;
     if (row_groups * g.NP * g.NP > 0xffffffffll || row_groups * g.NP > 0x3fffffff) return -1;
     g.items = (int)(row_groups * g.NP);
