@@ -17,15 +17,14 @@
 // Several windows (more than twelve offsets in fp32, sixteen in bf16): a tap takes its products from two neighbouring
 // offsets, so a window shares its last offset with the next one and owns the taps that need no other window's offsets.
 //
-// What bounds it (counters: share of a launch's cycles in which the unit is busy).  B8 C256 K = L = 8192 fp32: matrix pipe 54 %,
-// vector ALU (splitting and transposing every stage once per window) 41 %, under a lowered clock: 793 us where 206 G multiply-adds
-// in six bf16 products take 520 at the 2.4 PFLOP/s a loop of nothing but this instruction reaches; the fp32 instruction it replaces
-// 1100.  bf16: LDS 59 % (one 16-byte read per lane and instruction), vector ALU 37 %, matrix pipe 30 %: 201 us, before 250.  Short
-// rows, B2048 C128 K = L = 256 fp32: vector ALU 42 %, matrix pipe 27 %, 206 us of which two reads of memory are 104, before 366
-// (bf16 B512 C256 L256 K256 51 us, before 184): one stage in LDS at a time, so that these only overlap across the two workgroups of a
-// compute unit, and causal filters give the waves unequal numbers of block pairs.  The reads of the next operand go
-// out ahead of each group of products, the loads of the next stage ahead of a stage's.  Error against 64 bits (fp32 long
-// filter): 2.4e-7, the fp32 instruction 9.4e-7.
+// Filters of a thousand taps and more mostly go to dw_toep_kernel (dwconv_dw_toep.hip.h).
+//
+// What bounds it (counters: share of a launch's cycles in which the unit is busy).  Short rows, B2048 C128 K = L = 256 fp32: matrix pipe
+// 44 %, vector ALU 39 % (splitting and transposing), 150-166 us of which two reads of memory are 104 (204-210 before the waves of a
+// group shared its items and the offsets were dealt, 27 % and 42 %; 366 on the fp32 instruction): one stage in LDS at a time, so that
+// these only overlap across the two workgroups of a compute unit.  The reads of the next operand go out ahead of each group of
+// products, the loads of the next stage ahead of a stage's.  Error against 64 bits: fp32 B8 C256 K = L = 8192 2.4e-7, the fp32
+// instruction 9.4e-7.
 #pragma once
 #include "dwconv_band.hip.h"
 
@@ -48,6 +47,7 @@ struct DwBandGeom {
     unsigned step_magic;// floor(2^32 / nstep) + 1: st / nstep == umulhi(st, step_magic); 0: too many stages for that
     int stages;         // all stages
     int rev;            // windows in falling order (the dear ones first)
+    int fold;           // DG - 1: a wave's second offset (and fourth) counts from the other end of the groups; otherwise 0
 };
 constexpr int kDwBandThreads = 256;
 __host__ __device__ constexpr int dw_band_block_bytes(int NL) { return 32 * 16 * NL; }     // one 32-block of eight rows
@@ -59,7 +59,7 @@ constexpr int kDwBandDiagPitch = 36;
 constexpr int kDwBandDiag = 63 * kDwBandDiagPitch;
 inline size_t dw_band_lds_bytes(int NL, int RGN, int S32, int ndw, int ND)
 {
-    const size_t stage = dw_band_stage_bytes(NL, RGN, S32, ndw), ep = sizeof(float) * 4 * (size_t)(kDwBandDiag + 32 * ND + 32);
+    const size_t stage = dw_band_stage_bytes(NL, RGN, S32, ndw), ep = sizeof(float) * 4 * (size_t)(kDwBandDiag + 64 * ND);
     return stage > ep ? stage : ep;
 }
 
@@ -116,7 +116,7 @@ __device__ __forceinline__ void transpose_limbs(const Raw4H (&r)[8], int pos, ui
     for (int i = 0; i < 4; ++i) out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1].v[pos >> 1], r[2 * i].v[pos >> 1], sel);
 }
 
-template <typename E, int ND>
+template <typename E, int ND, int DG, bool SPLIT>
 __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__restrict__ x, const E *__restrict__ dy,
                                                                      float *__restrict__ part, E *__restrict__ dw_out,
                                                                      const DwBandGeom g, int slices)
@@ -130,9 +130,18 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int wz = g.win0 + (int)blockIdx.z, win = g.rev ? g.nwin - 1 - wz : wz;
     const int NB32 = (g.L + 31) >> 5;
     const int dlo = g.dmin + win * (g.ndw - 1), nd_here = min(g.ndw, g.nd - win * (g.ndw - 1));
-    const int DG = 1 << g.dg_log, KS = 4 >> g.dg_log, dg = wave & (DG - 1), ks = wave >> g.dg_log;
+    constexpr int KS = 4 / DG;
+    const int dg = wave & (DG - 1), ks = wave / DG;
     const int RGN = 1 << g.rg_log;
-    const int d0 = dlo + dg * ND, mine = min(ND, nd_here - dg * ND);     // this wave's offsets (mine <= 0: none)
+    // This wave's offsets: one of every DG.  (A range of them left the waves with unequal work where the pairs fall with the distance
+    // from lag 0; causal filters: the rounds over the groups alternate in direction, so that each wave has near and far ones, and
+    // start from the near end, so that the places of the last window that have no offset are far ones.  bf16, both tensors by every
+    // thread: a range, whose pairs are nearly the same ones: B3220 C123 L144 K144 75 us, 79 dealt)
+    constexpr bool DEALT = SPLIT || NL == 3;
+    const int spare = DEALT && g.fold && g.rev ? g.ndw - nd_here : 0, swing = DEALT ? (dg ^ g.fold) - dg : 0;
+    constexpr int STEP = DEALT ? DG : 1;
+    const int off0 = (DEALT ? dg : dg * ND) - spare;                     // the i-th: off0 + STEP i, + swing in odd rounds
+    auto offset_of = [&](int i) { return off0 + STEP * i + ((i & 1) ? swing : 0); };
     const size_t CL = (size_t)g.C * (size_t)g.L;
     const E *x_c = x + (size_t)c * (size_t)g.L, *dy_c = dy + (size_t)c * (size_t)g.L;
     const int VR = g.B * g.nseg;
@@ -175,8 +184,12 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     // keeps a stage that small); the rows of an item are wave-uniform, so a load is a scalar base and a lane offset.  The
     // items of a stage are loaded while the stage before it is multiplied.
     const int WPR = 4 >> g.rg_log;
-    const int rg_ld = wave >> (2 - g.rg_log), it_ld = tid & (64 * WPR - 1);
-    decltype(load_raw4(x)) raw_x[8], raw_y[8];
+    const int rg_ld = wave >> (2 - g.rg_log), it_ld = tid & ((SPLIT ? 32 : 64) * WPR - 1);
+    // SPLIT: where a stage is a whole row and either tensor is half a group's items (rows of up to 256 positions in two groups, 512 in one), one
+    // half of the waves brings x and the other dY, one item per thread, and the blocks of zeros beside the row are written once.  (Both
+    // tensors by every thread: two items for the first of two waves, and an eighth of one, zeros, for the second)
+    const bool y_wave = SPLIT && (wave & (WPR - 1)) >= WPR / 2;
+    decltype(load_raw4(x)) raw_x[8], raw_y[SPLIT ? 1 : 8];
     auto row_of = [&](int vr, int &off) -> size_t {                      // element offset of (virtual) row vr; off: its first position
         vr = min(vr, VR - 1);
         const int b = g.nseg == 1 ? vr : (int)(((unsigned)vr * g.seg_magic) >> 16);
@@ -186,30 +199,42 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     auto load_items = [&](const Stage &s) {
         const int it = band_hide(it_ld), vr0 = ((s.vg << g.rg_log) + rg_ld) * 8;
         // (positions outside the row are loaded from inside it and put right below)
-        int ux = 32 * s.xlo + min(4 * it, 32 * s.nx - 4), uy = 32 * s.yb0 + min(4 * it, 32 * g.S32 - 4);
-        if (g.nseg == 1) {
-            ux = max(0, min(ux, g.L - 4));
-            uy = min(uy, g.L - 4);
+        if constexpr (SPLIT) {
+            const E *p = (y_wave ? dy_c : x_c) + min(4 * it, g.L - 4);
+            if (vr0 + 8 <= VR) {
+                p += (size_t)vr0 * CL;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const size_t row = (size_t)min(vr0 + r, VR - 1) * CL;
-                raw_x[r] = load_raw4(x_c + row + ux);
-                raw_y[r] = load_raw4(dy_c + row + uy);
+                for (int r = 0; r < 8; ++r) raw_x[r] = load_raw4(p + r * CL);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) raw_x[r] = load_raw4(p + (size_t)min(vr0 + r, VR - 1) * CL);
             }
         } else {
+            int ux = 32 * s.xlo + min(4 * it, 32 * s.nx - 4), uy = 32 * s.yb0 + min(4 * it, 32 * g.S32 - 4);
+            if (g.nseg == 1) {
+                ux = max(0, min(ux, g.L - 4));
+                uy = min(uy, g.L - 4);
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                int off;
-                const size_t row = row_of(vr0 + r, off);
-                raw_x[r] = load_raw4(x_c + row + max(0, min(ux + off, g.L - 4)));
-                raw_y[r] = load_raw4(dy_c + row + max(0, min(uy + off, g.L - 4)));
+                for (int r = 0; r < 8; ++r) {
+                    const size_t row = (size_t)min(vr0 + r, VR - 1) * CL;
+                    raw_x[r] = load_raw4(x_c + row + ux);
+                    raw_y[r] = load_raw4(dy_c + row + uy);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    int off;
+                    const size_t row = row_of(vr0 + r, off);
+                    raw_x[r] = load_raw4(x_c + row + max(0, min(ux + off, g.L - 4)));
+                    raw_y[r] = load_raw4(dy_c + row + max(0, min(uy + off, g.L - 4)));
+                }
             }
         }
     };
     // Rows past the batch, positions outside the row, positions of dY that belong to the next virtual row: zeros; a group of
     // four that ends behind its row was loaded from further left.  u: the first position of the item in its virtual row.
     auto put_right = [&](decltype(raw_x) &raw, int vr0, int u, int end) __attribute__((always_inline)) {
-        if (g.nseg == 1) {
+        if (SPLIT || g.nseg == 1) {
             const bool zero = u < 0 || u >= g.L;
             const int over = u + 4 - g.L;
             if ((g.L & 3) != 0 && __builtin_amdgcn_ballot_w64(!zero && over > 0) != 0) {
@@ -239,9 +264,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     auto store_items = [&](const Stage &s) {
         const int it = band_hide(it_ld), vr0 = ((s.vg << g.rg_log) + rg_ld) * 8;
         unsigned char *base = dwb_smem + rg_ld * ((s.nx + g.S32) * BB);
-        put_right(raw_x, vr0, 32 * s.xlo + 4 * it, 1 << 30);
-        put_right(raw_y, vr0, 32 * s.yb0 + 4 * it, g.Lv);
-        auto put = [&](const decltype(raw_x) &raw, unsigned char *dst) {
+        auto put = [&](const decltype(raw_x) &raw, unsigned char *dst) __attribute__((always_inline)) {
             const int q = (4 * it) & 31, sw = (q >> 3) & 3;
             dst += ((4 * it) & ~31) * PB;
 #pragma unroll
@@ -252,15 +275,35 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
                 for (int l = 0; l < NL; ++l) *reinterpret_cast<uintx4 *>(dst + ((q + j) ^ sw) * PB + 16 * l) = limbs[l];
             }
         };
-        if (4 * it < 32 * s.nx) put(raw_x, base);
-        if (4 * it < 32 * g.S32) put(raw_y, base + s.nx * BB);
+        if constexpr (SPLIT) {
+            // (the window of x may start behind the row's first block or end before its last)
+            put_right(raw_x, vr0, 4 * it, 1 << 30);
+            const int blk = it >> 3, to = y_wave ? s.nx + blk : blk - s.xlo;
+            if (blk < (y_wave ? g.S32 : NB32) && to >= 0 && (y_wave || to < s.nx)) put(raw_x, base + (to - blk) * BB);
+        } else {
+            put_right(raw_x, vr0, 32 * s.xlo + 4 * it, 1 << 30);
+            put_right(raw_y, vr0, 32 * s.yb0 + 4 * it, g.Lv);
+            if (4 * it < 32 * s.nx) put(raw_x, base);
+            if (4 * it < 32 * g.S32) put(raw_y, base + s.nx * BB);
+        }
     };
 
     Stage cur;
     cur.st = sl - (int)gridDim.y;
     cur.nx = 0;
     advance(cur);
-    if (cur.st < g.stages) load_items(cur);
+    if (cur.st < g.stages) {
+        load_items(cur);
+        if constexpr (SPLIT) {
+            // (x blocks -1 and NB32; one stage is like the other)
+            for (int rg = 0; rg < RGN; ++rg)
+                for (int i = tid; i < 2 * (BB / 16); i += kDwBandThreads) {
+                    const int at = (i < BB / 16 ? -1 : NB32) - cur.xlo;
+                    if (at >= 0 && at < cur.nx)
+                        *reinterpret_cast<uintx4 *>(dwb_smem + rg * ((cur.nx + g.S32) * BB) + at * BB + 16 * (i < BB / 16 ? i : i - BB / 16)) = uintx4{0u, 0u, 0u, 0u};
+                }
+        }
+    }
     while (cur.st < g.stages) {
         const int yb0 = cur.yb0, xlo = cur.xlo, nx = cur.nx;
         const int rg_bytes = (nx + g.S32) * BB;                          // one group of eight rows: x blocks, dY blocks
@@ -273,11 +316,11 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         int plo[ND], phi[ND];                                            // block pairs p (blocks yb0 + 2 p, + 1) per offset
 #pragma unroll
         for (int i = 0; i < ND; ++i) {
-            const int d = d0 + i;
+            const int d = dlo + offset_of(i);
             // (the pairs that meet the row from some virtual row)
             plo[i] = max(0, (-yb0 - d - seg_blocks) >> 1);               // ceil((-yb0 - d - 1 - seg_blocks) / 2)
             phi[i] = min(min(g.S32, NBV - yb0 + 1) / 2 - 1, (NB32 - 1 - yb0 - d) >> 1);
-            if (i >= mine) phi[i] = -(1 << 28);
+            if ((unsigned)offset_of(i) >= (unsigned)nd_here) phi[i] = -(1 << 28);
         }
         const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
         const int lane_off = (q ^ ((q >> 3) & 3)) * PB + kg * BB;
@@ -286,7 +329,9 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             constexpr int I0 = decltype(i0c)::value, N = decltype(nc)::value;
             pa += (ks - pa) & (KS - 1);
             if (pa > pb) return;
-            const unsigned char *yp = yw + 2 * pa * BB, *xp = xw + (2 * pa + I0) * BB;
+            const unsigned char *yp = yw + 2 * pa * BB, *xp[2];                      // (of the even and the odd rounds over the groups)
+            xp[0] = xw + (2 * pa + off0) * BB;
+            xp[1] = xp[0] + swing * BB;
             uintx4 y[2][NL], xv[2][NL];
             auto read_y = [&](uintx4 (&to)[NL]) {
 #pragma unroll
@@ -294,7 +339,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             };
             auto read_x = [&](uintx4 (&to)[NL], int i) {
 #pragma unroll
-                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(xp + i * BB + 16 * l);
+                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(xp[DEALT ? (I0 + i) & 1 : 0] + (I0 + i) * STEP * BB + 16 * l);
             };
             auto multiply = [&](int i, const uintx4 (&a)[NL], const uintx4 (&b)[NL]) {
                 if constexpr (NL == 3) {
@@ -323,7 +368,8 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
                                 read_x(xv[(k + 1) & 1], i + 1);
                             } else {
                                 yp += by;
-                                xp += by;
+                                xp[0] += by;
+                                if constexpr (DEALT) xp[1] += by;
                                 read_y(y[1 - u]);
                                 read_x(xv[(k + 1) & 1], 0);
                             }
@@ -335,7 +381,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             }
         };
         for (int rg = 0; rg < RGN; ++rg) {
-            const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + d0 - xlo) * BB;
+            const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + dlo - xlo) * BB;
             const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
             // the bounds fall with the offset: those active at a pair are the offsets a .. b with p in [plo[a], plo[a - 1]) and
             // (phi[b + 1], phi[b]]
@@ -352,14 +398,13 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         }
     }
 
-    // ---- diagonal sums: every wave those of its offsets (tap 32 i + e, e = q' - q + 31, of offset d0 + i), then the waves'
-    // tap rows added in wave order
+    // ---- diagonal sums: every wave those of its offsets (e = q' - q + 31 of each), then the two offsets a tap belongs to and the
+    // waves' parts of each added in order
     __syncthreads();
     float *img = reinterpret_cast<float *>(dwb_smem) + wave * kDwBandDiag;
     float *taps = reinterpret_cast<float *>(dwb_smem) + 4 * kDwBandDiag;
-    constexpr int TW = 32 * ND + 32;
+    constexpr int TW = 64 * ND;
     float *tap = taps + wave * TW;
-    for (int i = lane; i < TW; i += 64) tap[i] = 0.f;
     // (the cells a diagonal has no entry in stay zero: a sum is 32 columns whatever its length.  A loop over the columns it
     // has, one LDS round trip after the other, took 5 us of a call: B1 C257 L480 K105 bf16 11.7 us)
     for (int i = lane; i < kDwBandDiag / 4; i += 64) *reinterpret_cast<floatx4 *>(img + 4 * i) = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -382,7 +427,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             floatx4 sum = v[0];
 #pragma unroll
             for (int j = 1; j < 8; ++j) sum += v[j];
-            tap[32 * i + lane] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            tap[64 * i + lane] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
         }
         wave_lds_fence();
     }
@@ -396,10 +441,15 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         const int t = j - jw;
         float sum = 0.f;
         if (t >= 0 && t < 32 * nd_here + 31) {
-            // wave (dg, ks) owns taps 32 ND dg .. 32 ND dg + 32 ND + 30
-            for (int w = 0; w < 4; ++w) {
-                const int tt = t - 32 * ND * (w & (DG - 1));
-                if (tt >= 0 && tt < 32 * ND + 31) sum += taps[w * TW + tt];
+            // diagonal t % 32 of offset t / 32 and t % 32 + 32 of the one before it; waves (dg, 0), (dg, 1) .. have an offset
+#pragma unroll
+            for (int h = 1; h >= 0; --h) {
+                const int o = (t >> 5) - h, e = (t & 31) + 32 * h;
+                if (o >= 0 && o < nd_here && e < 63) {
+                    const int at_o = o + spare, i = DEALT ? at_o / DG : at_o % ND, r = DEALT ? at_o & (DG - 1) : at_o / ND;
+                    const int at = (DEALT && (i & 1) ? r ^ g.fold : r) * TW + 64 * i + e;
+                    for (int w = 0; w < KS; ++w) sum += taps[w * DG * TW + at];
+                }
             }
         }
         if (dw_out) {

@@ -231,6 +231,7 @@ enum DwKernel { DW_VALU_K8, DW_VALU_K32, DW_VALU_K64, DW_VALU_K256 };
 struct DwBandPlan {
     dwconv::DwBandGeom g;
     int ND;                // offsets per wave (the kernel is compiled per number)
+    bool split;            // one half of the waves of a group of rows brings x, the other dY
     int S;                 // slices it uses: at most those of the workspace
     size_t lds;
 };

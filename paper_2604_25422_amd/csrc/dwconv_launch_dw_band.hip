@@ -64,11 +64,13 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     g.rg_log = 0;
     while (g.nstep == 1 && g.rg_log < 2 && (16ll << g.rg_log) <= VR && (2 << g.rg_log) * (g.S32 + x_blocks(g.S32)) <= blocks &&
            (2 << g.rg_log) * x_blocks(g.S32) <= 32 && (2 << g.rg_log) * g.S32 <= 32) ++g.rg_log;
+    p->split = g.nseg == 1 && g.nstep == 1 && g.rg_log < 2 && 8 * nb32 <= 32 * (4 >> g.rg_log) && 8 * g.S32 <= 32 * (4 >> g.rg_log);
     const long long groups = (VR + (8 << g.rg_log) - 1) / (8 << g.rg_log);
     if (groups * g.nstep > 0x3fffffff || VR > 0x3fffffff) return false;
     g.stages = (int)(groups * g.nstep);
     g.step_magic = (long long)g.stages * g.nstep < (1ll << 32) ? (unsigned)((1ull << 32) / (unsigned)g.nstep) + 1u : 0u;
     g.rev = s.pad >= s.K / 2 ? 1 : 0;
+    g.fold = 4ll * s.pad < s.K || 4ll * (s.K - 1 - s.pad) < s.K ? (1 << g.dg_log) - 1 : 0;
     // slices that are used: about two rounds of two workgroups per compute unit (a workgroup's start and its diagonal sums do
     // not shrink with its stages: B8 C256 K = L = 8192 with one slice 745 us, two 837 us; bf16 232 / 286), partial sums of at
     // most 16 MiB
@@ -99,13 +101,25 @@ static int launch_dw_band(const void *x, const void *dy, float *part, void *dw_o
         }
         return launch_status();
     };
-    switch (p.ND) {
-    case 1: return go(dwconv::dw_band_kernel<E, 1>);
-    case 2: return go(dwconv::dw_band_kernel<E, 2>);
-    case 3: return go(dwconv::dw_band_kernel<E, 3>);
+    auto form = [&](auto nd, auto dg) -> int {
+        constexpr int ND = decltype(nd)::value, DG = decltype(dg)::value;
+        return p.split ? go(dwconv::dw_band_kernel<E, ND, DG, true>) : go(dwconv::dw_band_kernel<E, ND, DG, false>);
+    };
+    constexpr std::integral_constant<int, 1> c1{};
+    constexpr std::integral_constant<int, 2> c2{};
+    constexpr std::integral_constant<int, 3> c3{};
+    constexpr std::integral_constant<int, 4> c4{};
+    switch (8 * p.ND + p.g.dg_log) {
+    case 8: return form(c1, c1);
+    case 16: return form(c2, c1);
+    case 17: return form(c2, c2);
+    case 18: return form(c2, c4);
+    case 24: return form(c3, c1);
+    case 25: return form(c3, c2);
+    case 26: return form(c3, c4);
     default:
         if constexpr (std::is_same<E, float>::value) return DWCONV_ERR_LAUNCH;       // (never planned)
-        else return go(dwconv::dw_band_kernel<E, 4>);
+        else return form(c4, c4);
     }
 }
 

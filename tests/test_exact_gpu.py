@@ -247,6 +247,16 @@ def test_exact_dw_band_few_rows(oracle_mod, B, C, L, K, p, dtype):
     run_exact(oracle_mod, B, C, L, K, p, dtype, seed=37 + B + 3 * C + 5 * L, fused=False)
 
 
+# ... rows that a stage holds whole, one half of the waves bringing x and the other dY: the longest rows of two groups of eight and of one,
+# and one position more; batches that end inside a group; one window and several; offsets dealt to the waves in one direction and in both
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,C,L,K,p", [(17, 3, 256, 256, 255), (33, 2, 256, 256, 0), (16, 2, 257, 257, 128), (33, 2, 512, 512, 0), (18, 2, 513, 513, 512),
+                                       (9, 2, 481, 700, 350), (40, 2, 193, 130, 129), (5, 2, 225, 225, 30), (24, 260, 130, 131, 65)])
+def test_exact_dw_band_whole_rows(oracle_mod, B, C, L, K, p, dtype):
+    print(f"case exact dw_band whole rows {dtype} B{B} C{C} L{L} K{K} p{p}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=41 + B + 3 * C + 5 * L, fused=False)
+
+
 # dw_toep_kernel: one, two and several tiles of 1024 lags (and one lag more), first lags at every place of a block and a granule, rows
 # that end inside a granule, filters longer than the row on either side, one and several chunks of a row, several slices (with a
 # rest of batch entries), tensors off every alignment
