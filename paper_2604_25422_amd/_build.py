@@ -2,12 +2,16 @@
 from __future__ import annotations
 
 import glob
+import importlib.util
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libdwconv_gfx950.so")
+FASTCALL_PATH = os.path.join(HERE, "_fastcall.so")       # the Python calls as one native function each (csrc/dwconv_fastcall.cpp)
+FASTCALL_SOURCE = os.path.join(CSRC, "dwconv_fastcall.cpp")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -52,7 +56,22 @@ def sources():
 
 
 def dependencies():
-    return sources() + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [os.path.join(HERE, "..", "include", "dwconv.h")]
+    return sources() + [FASTCALL_SOURCE] + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [os.path.join(HERE, "..", "include", "dwconv.h")]
+
+
+def build_fastcall(verbose: bool = False, incremental: bool = False) -> str:
+    """The native form of the Python calls, against the installed PyTorch.  Host code only (g++)."""
+    if incremental and os.path.exists(FASTCALL_PATH) and os.path.getmtime(FASTCALL_PATH) > os.path.getmtime(FASTCALL_SOURCE):
+        return FASTCALL_PATH
+    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
+    include, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=1",
+           "-I" + sysconfig.get_paths()["include"], "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+           FASTCALL_SOURCE, "-o", FASTCALL_PATH, "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return FASTCALL_PATH
 
 
 def build(verbose: bool = False, extra_flags=(), jobs: int | None = None, incremental: bool = False) -> str:
@@ -94,7 +113,9 @@ def build(verbose: bool = False, extra_flags=(), jobs: int | None = None, increm
     if jobs is None:
         jobs = max(1, min(len(srcs), os.cpu_count() or 1, 8))
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        fastcall = pool.submit(build_fastcall, verbose, incremental)
         list(pool.map(compile_one, zip(srcs, objs)))
+        fastcall.result()
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH] + objs
     if verbose:
         print(" ".join(link), flush=True)
@@ -103,9 +124,9 @@ def build(verbose: bool = False, extra_flags=(), jobs: int | None = None, increm
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(FASTCALL_PATH):
         return True
-    t = os.path.getmtime(LIB_PATH)
+    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(FASTCALL_PATH))
     return any(os.path.getmtime(p) > t for p in dependencies())
 
 

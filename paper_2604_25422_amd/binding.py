@@ -4,11 +4,19 @@ Every function takes torch tensors living on the GPU, checks dtype / shape /
 contiguity, and hands raw device pointers plus the current HIP stream to the
 library.  All arithmetic runs in the HIP kernels; there is no CPU fallback: if
 the shared library is missing, loading fails with an error.
+
+The calls of a layer's step go to a native function first (``_fastcall``), which
+makes the whole call for plain device tensors that fit and returns None for
+everything else; the code here then checks, explains or does it.  It is the same
+call either way: without that module (a PyTorch it was not built for) only the
+way to the launch is longer.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 import torch
 
@@ -18,6 +26,28 @@ F32 = 0
 BF16 = 1
 
 _lib = None
+
+
+class _Declines:
+    """In the place of the native calls until the library is loaded, and where they cannot be."""
+    fwd = bwd_input = bwd_weight = bwd = staticmethod(lambda *args: None)
+
+
+_fast = _Declines
+
+
+def _load_fastcall(l):
+    global _fast
+    try:
+        fast = importlib.import_module(__package__ + "._fastcall")
+    except ImportError as e:
+        warnings.warn(f"the native form of the calls is not there ({e}): small calls take longer to launch; build it with "
+                      "python -m paper_2604_25422_amd._build", RuntimeWarning, stacklevel=3)
+        return
+    fast.setup(*(ctypes.cast(f, ctypes.c_void_p).value for f in (l.dwconv_fwd, l.dwconv_bwd_input, l.dwconv_bwd_weight, l.dwconv_bwd)),
+               _current_device, _raw_stream, _check)
+    _fast = fast
+
 
 SYMBOLS = (
     "dwconv_fwd", "dwconv_bwd_input", "dwconv_bwd_weight", "dwconv_bwd_weight_partial",
@@ -71,6 +101,7 @@ def lib():
         l.dwconv_status_string.restype = ctypes.c_char_p
         l.dwconv_version.argtypes = []
         l.dwconv_version.restype = i
+        _load_fastcall(l)
         _lib = l
     return _lib
 
@@ -134,6 +165,9 @@ def _stream():
 
 def dwconv_fwd(x: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tensor | None = None) -> torch.Tensor:
     """y[b,c,t] = sum_j x~[b,c,t+j-pad_left] w[c,j]  (Sec. IV-A eq. (dwconv))."""
+    done = _fast.fwd(x, w, pad_left, out)
+    if done is not None:
+        return done
     _dev3(x, "x"); B, C, L = x.shape
     _dev2(w, "w", C); K = w.shape[1]
     if w.dtype != x.dtype:
@@ -147,6 +181,9 @@ def dwconv_fwd(x: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tenso
 
 def dwconv_bwd_input(dy: torch.Tensor, w: torch.Tensor, pad_left: int, out: torch.Tensor | None = None) -> torch.Tensor:
     """dx[b,c,s] = sum_j dy~[b,c,s-j+pad_left] w[c,j]  (adjoint of eq. (dwconv); cf. eq. (dx_def))."""
+    done = _fast.bwd_input(dy, w, pad_left, out)
+    if done is not None:
+        return done
     _dev3(dy, "dy"); B, C, L = dy.shape
     _dev2(w, "w", C); K = w.shape[1]
     if w.dtype != dy.dtype:
@@ -194,6 +231,9 @@ def _dw_args(x, dy, K, pad_left, workspace):
 
 def dwconv_bwd_weight(x, dy, K: int, pad_left: int, workspace=None, out=None) -> torch.Tensor:
     """dw[c,j] = sum_b sum_t dy[b,c,t] x~[b,c,t+j-pad_left]  (Sec. IV-A eq. (dk_def)); both stages."""
+    done = _fast.bwd_weight(x, dy, K, pad_left, workspace, out)
+    if done is not None:
+        return done
     workspace, nbytes = _dw_args(x, dy, K, pad_left, workspace)
     B, C, L = x.shape
     dw = torch.empty((C, K), dtype=x.dtype, device=x.device) if out is None else _dev2(out, "out", C, int(K), x.dtype)
@@ -221,6 +261,9 @@ def dwconv_bwd_weight_noalloc(x, dy, K: int, pad_left: int, out: torch.Tensor) -
 
 def dwconv_bwd(dy, x, w, pad_left: int, workspace=None, out_dx=None, out_dw=None):
     """Both gradients in one call (fused kernel where it applies): returns (dx, dw)."""
+    done = _fast.bwd(dy, x, w, pad_left, workspace, out_dx, out_dw)
+    if done is not None:
+        return done
     K = int(w.shape[1])
     workspace, nbytes = _dw_args(x, dy, K, pad_left, workspace)
     B, C, L = x.shape

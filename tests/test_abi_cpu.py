@@ -224,3 +224,16 @@ def test_noalloc_argument_validation(lib):
     for shape in ((4, 64, 1024, 16, 15, 0), (32, 256, 4096, 64, 63, 0), (64, 512, 2048, 7, 3, 0),
                   (8, 256, 8192, 8192, 8191, 0), (128, 768, 1024, 32, 31, 1), (16384, 128, 48, 48, 24, 0)):
         assert 0 < lib.dwconv_bwd_weight_workspace_bytes(*shape) <= cap, shape
+
+
+def test_native_calls_decline_what_is_not_a_device_tensor(lib):
+    """The native form of the Python calls leaves everything but plain device tensors to the checks of binding.py."""
+    import torch
+    from paper_2604_25422_amd import _fastcall, binding
+    binding.lib()
+    assert binding._fast is _fastcall
+    x, w, ws = torch.zeros(2, 3, 16), torch.zeros(3, 5), torch.zeros(64, dtype=torch.uint8)
+    for call in (lambda: _fastcall.fwd(x, w, 2, None), lambda: _fastcall.bwd_input(x, w, 2, x), lambda: _fastcall.bwd_weight(x, x, 5, 2, ws, None),
+                 lambda: _fastcall.bwd(x, x, w, 2, ws, None, None), lambda: _fastcall.fwd(None, w, 2, None), lambda: _fastcall.fwd(x, w),
+                 lambda: _fastcall.bwd(x, x, w, 2.0, ws, None, None), lambda: _fastcall.bwd_weight(x, x, 1 << 40, 2, ws, None)):
+        assert call() is None
