@@ -162,7 +162,11 @@ DWCONV_API int dwconv_bwd(const void *dy, const void *x, const void *w, void *dx
                void *workspace, size_t workspace_bytes,
                int B, int C, int L, int K, int pad_left, int dtype, void *stream);
 
-/* 1 when dwconv_bwd runs the fused kernel for this shape (given tensors aligned as it needs: 16 bytes always do); 0 otherwise. */
+/*
+ * 1 when dwconv_bwd runs the fused kernel for this shape (given tensors aligned as it needs: 16 bytes always do); 0 otherwise.
+ * (bf16 rows of odd length: 0, although ordinary ones from 768 positions on take one pass too, where x, dy and dx start on the same
+ * half of a dword and the call is not one of the smallest.)
+ */
 DWCONV_API int dwconv_bwd_is_fused(int B, int C, int L, int K, int pad_left, int dtype);
 
 /* Number S of partial slices per coefficient stage 1 writes for this shape; 0 on bad arguments. */

@@ -22,6 +22,11 @@
 // which case the rest of it is cleared in LDS once it has landed: rows_granule8_byte_offset); B is then 1 and segs_per_row the number of segments of the
 // virtual row.  Every lane translates the position of its granule on the memory side of the loads, and the position of
 // its four outputs at the stores.
+//
+// ODD: ordinary rows that do not all start on a dword (odd lengths, 2-byte aligned tensors; x, dy and dx on the same half of one),
+// shifted to the dword in which they start as in the separate kernels (rows_odd_start; par0: 1 when the tensors themselves do not
+// start on one): the foreign elements at their ends are cleared in both windows, and the first and last outputs of a row are stored by
+// element.  One pass over dY instead of two: B32 C256 L4097 K64 57 -> 49 us for the two gradients, B100 C64 L1701 K33 29 -> 20.
 #pragma once
 #include "dwconv_dw_bf16.hip.h"
 
@@ -44,13 +49,15 @@ __host__ __device__ constexpr int bf16_dy_pos(int nb, int i)
     return 16 * bf16_block_pos(nb) + 4 * ((i >> 2) ^ (2 * ((nb >> 3) & 1))) + (i & 3);
 }
 
-template <int ND, int W, bool ROWS = false>
+template <int ND, int W, bool ROWS = false, bool ODD = false>
 __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kernel(
     const bf16_t *__restrict__ dy, const bf16_t *__restrict__ x, const bf16_t *__restrict__ f, bf16_t *__restrict__ dx,
     float *__restrict__ part, bf16_t *__restrict__ dw_out, int B, int C, int L, int K, int pad, int dmin,
-    int segs_per_row, const RowsMap rm)
+    int segs_per_row, const RowsMap rm, int par0)
 {
     static_assert(ND >= 2 && 16 * ND <= 128, "window tails are one 128-element load each");
+    static_assert(!ODD || 16 * ND < 512, "the first position of a row lies in the first half of either window");
+    static_assert(!(ROWS && ODD), "virtual rows of odd length: the two separate kernels");
     constexpr int XWE = kSegLen + 16 * ND;         // elements of either window that are ever read
     constexpr int WREG = bwd_fused_bf16_wave_floats(ND);
     extern __shared__ __align__(16) float dyn_lds[];
@@ -122,6 +129,7 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kern
     uintx4 rx, rg;
     int x_shift, g_shift;       // negative when a window starts before the row: added to the lane offsets
     int vx0 = 0, vg0 = 0;       // ROWS: virtual positions of the first elements of the two windows
+    int s_next = 0;             // ODD: first position of the row the next loads belong to
     auto aim = [&](int pbat, int pseg) {
         if constexpr (ROWS) {
             x_shift = g_shift = 0;
@@ -144,8 +152,15 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kern
             const int u0 = 2 * (t0 + 16 * dmin), v0 = 2 * (t0 + 16 * dmin_x);
             x_shift = u0 < 0 ? u0 : 0;
             g_shift = v0 < 0 ? v0 : 0;
-            rx = row_tail_resource(x + row, L, u0 > 0 ? u0 : 0);
-            rg = row_tail_resource(dy + row, L, v0 > 0 ? v0 : 0);
+            if constexpr (ODD) {
+                s_next = (((pbat * C + c) & L) ^ par0) & 1;
+                const int len = (s_next + L + 1) & ~1;
+                rx = row_tail_resource(x + (row - (size_t)s_next), len, u0 > 0 ? min(u0, 2 * len) : 0);
+                rg = row_tail_resource(dy + (row - (size_t)s_next), len, v0 > 0 ? min(v0, 2 * len) : 0);
+            } else {
+                rx = row_tail_resource(x + row, L, u0 > 0 ? u0 : 0);
+                rg = row_tail_resource(dy + row, L, v0 > 0 ? v0 : 0);
+            }
         } else {
             x_shift = g_shift = 0;
             rx = uintx4{0u, 0u, 0u, kBufferFlags};
@@ -186,8 +201,9 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kern
         const int carry = seg_n >= segs_per_row ? 1 : 0;
         seg_n -= carry ? segs_per_row : 0;
         const int b_n = b + step_b + carry;
-        bf16_t *out_seg = ROWS ? dx + (size_t)c * (size_t)L                                                  // wave-uniform
-                               : dx + ((size_t)b * (size_t)C + (size_t)c) * (size_t)L + (size_t)(seg * kSegLen);
+        const int s_cur = ODD ? s_next : 0, row_end = s_cur + L;
+        bf16_t *out_seg = (ROWS ? dx + (size_t)c * (size_t)L                                                 // wave-uniform
+                                : dx + ((size_t)b * (size_t)C + (size_t)c) * (size_t)L + (size_t)(seg * kSegLen)) - s_cur;
         const bool whole = !ROWS && (seg + 1) * kSegLen <= L;
         const int t_seg = seg * kSegLen;
         aim(b_n, seg_n);
@@ -205,6 +221,22 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kern
                 // what has just landed: x0 and g0 before chunk 0, x1 and g1 before chunk 1
                 if constexpr (c4 == 0) { zero_slot_tail(sx + 8 * lane, live_cur[0]); zero_slot_tail(sg + 8 * lane, live_cur[1]); }
                 if constexpr (c4 == 1) { zero_slot_tail(sx + 512 + 8 * lane, live_cur[2]); zero_slot_tail(sg + 512 + 8 * lane, live_cur[3]); }
+            }
+            if constexpr (ODD && c4 != 2) {
+                // the foreign elements of what has just landed (wave-uniform): position 0 of a row that starts at 1, and the position behind
+                // a row that ends in the middle of a dword
+                constexpr int lo = c4 == 3 ? 1024 : 512 * c4, hi = c4 == 3 ? XWE : 512 * c4 + 512;
+                short *wx = const_cast<short *>(sx), *wg = const_cast<short *>(sg);
+                const int hx = -(t_seg + 16 * dmin), hg = -(t_seg + 16 * dmin_x);       // window indexes of position 0
+                if (c4 == 0 && s_cur) {
+                    if (hx >= 0) wx[16 * bf16_block_pos(hx >> 4) + (hx & 15)] = 0;
+                    if (hg >= 0) wg[bf16_dy_pos(hg >> 4, hg & 15)] = 0;
+                }
+                if (row_end & 1) {
+                    const int xt = row_end + hx, gt = row_end + hg;
+                    if (xt >= lo && xt < hi) wx[16 * bf16_block_pos(xt >> 4) + (xt & 15)] = 0;
+                    if (gt >= lo && gt < hi) wg[bf16_dy_pos(gt >> 4, gt & 15)] = 0;
+                }
             }
             // ---- input gradient, tile c4
             shortx4 bv[ND];
@@ -237,6 +269,9 @@ __global__ __launch_bounds__(64 * W, kMfmaWavesPerSimd) void bwd_fused_bf16_kern
                 int n;
                 const int eo = rows_element_group(rm, t_seg + lt, n);   // four outputs: one row, one gap, or the end of a row
                 if (eo >= 0) st_rows_group(out_seg + eo, make_float4(acc[0], acc[1], acc[2], acc[3]), n);
+            } else if constexpr (ODD) {
+                const int t = t_seg + lt;
+                st_group_range(out_seg + lt, make_float4(acc[0], acc[1], acc[2], acc[3]), t < s_cur ? 1 : 0, row_end - t);
             } else {
                 if (whole) st_elem4_stream(out_seg + lt, make_float4(acc[0], acc[1], acc[2], acc[3]));
                 else st_elem4_stream_upto(out_seg + lt, make_float4(acc[0], acc[1], acc[2], acc[3]), t_seg + lt, L);

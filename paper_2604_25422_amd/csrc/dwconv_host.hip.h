@@ -134,6 +134,16 @@ inline bool bf16_odd_rows_ok(const Shape &s, const void *a, const void *b, const
            (long long)s.B * s.C < (1ll << 31);
 }
 
+// Forward and input gradient of such rows in calls of up to 1024 segments, which are a wait for memory each: the vector-ALU kernel waits
+// once less and keeps them while its arithmetic is short - B2175 C1 L41 K16 3.6 / 4.8 us, B200 C64 L47 K31 4.6 / 4.8, K64 5.3 -> 5.0,
+// B100 C256 L61, 1792 segments, K31 6.2 -> 5.7; ordinary rows B232 C2 L1989 K7 3.9 / 4.3, K48 4.7 -> 4.2.  (Its sums have another order,
+// so the fused backward kernel, whose input gradient is that of the separate call, keeps away from them too.)
+inline bool bf16_odd_small_call(const Shape &s, const RowsPlan &rp)
+{
+    const long long segs = rp.on ? (long long)rp.nvs * s.C : (long long)s.B * s.C * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen);
+    return segs <= 1024 && segs * s.K <= (rp.on ? 32768 : 16384);
+}
+
 // The same idea for the generic vector-ALU kernels, which take any row length and alignment: short rows are walked as
 // the virtual row of their channel (pitch L + max(pad, K-1-pad), no rounding: these kernels load by element) when at
 // least two rows fit a 1024-position tile and positions and element offsets stay 32-bit (B16384 C128 L50 K48, which no
@@ -293,6 +303,8 @@ int launch_dw_partial_wide_bf16(const void *x, const void *dy, float *part, void
                                 int dmin, int nd, hipStream_t st);
 int launch_bwd_fused_f32(const void *dy, const void *x, const void *w, void *dx, float *part, void *dw_out, bool *wrote_dw,
                          const Shape &s, const DwPlan &p, hipStream_t st);
+int launch_bwd_fused_bf16_odd(const void *dy, const void *x, const void *w, void *dx, float *part, void *dw_out, bool *wrote_dw,
+                              const Shape &s, const DwPlan &p, int dmin, int nd, hipStream_t st);
 int launch_bwd_fused_bf16(const void *dy, const void *x, const void *w, void *dx, float *part, void *dw_out,
                           bool *wrote_dw, const Shape &s, const DwPlan &p, hipStream_t st);
 

@@ -21,14 +21,14 @@ int launch_bwd_fused_ndw(const void *dy, const void *x, const void *w, void *dx,
             hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                                static_cast<const bf16_t *>(dy), static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(w),
                                static_cast<bf16_t *>(dx), part, static_cast<bf16_t *>(dw_out), 1, s.C, s.L, s.K, s.pad, dmin,
-                               p.tiles_per_row, p.rows.map);
+                               p.tiles_per_row, p.rows.map, 0);
         } else {
             auto kernel = dwconv::bwd_fused_bf16_kernel<ND, W, false>;
             if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
             hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.S), dim3(64 * W), lds, st,
                                static_cast<const bf16_t *>(dy), static_cast<const bf16_t *>(x), static_cast<const bf16_t *>(w),
                                static_cast<bf16_t *>(dx), part, static_cast<bf16_t *>(dw_out), s.B, s.C, s.L, s.K, s.pad, dmin,
-                               p.tiles_per_row, p.rows.map);
+                               p.tiles_per_row, p.rows.map, 0);
         }
         return launch_status();
     } else {
@@ -126,11 +126,14 @@ int launch_bwd_fused(const void *dy, const void *x, const void *w, void *dx, flo
     if (s.dtype == DWCONV_BF16 && p.rows.on &&
         ((s.L % 2) != 0 || (p.rows.map.P % 8) != 0 || !aligned_to(x, 4) || !aligned_to(dy, 4) || !aligned_to(dx, 4)))
         return -1;
-    // bf16: rows that start on a dword
-    if (s.dtype == DWCONV_BF16 && (s.L % 2) != 0) return -1;
     const int dmin = toeplitz_dmin(s.pad), dmax = toeplitz_dmax(s.K, s.pad);
     const int nd = dmax - dmin + 1;
     if (s.K < kMfmaMinK || nd < 2 || nd > kMfmaMaxND || s.L > kMfmaMaxL) return -1;
+    // bf16 rows that do not all start on a dword
+    if constexpr (std::is_same<T, bf16_t>::value) {
+        if (bf16_odd_rows(s, x, dy) || !aligned_to(dx, 4))
+            return launch_bwd_fused_bf16_odd(dy, x, w, dx, part, dw_out, wrote_dw, s, p, dmin, nd, st);
+    }
     // whole 16-byte granules; otherwise rows that start on a dword (see ragged_rows_ok), ordinary rows only
     const bool granular = (s.L % (s.dtype == DWCONV_BF16 ? 8 : 4)) == 0 && aligned_to(x, 16) && aligned_to(dy, 16) && aligned_to(dx, 16);
     if (!granular) {

@@ -196,12 +196,8 @@ int launch_corr_mfma(const void *in, const void *f, void *out, const Shape &s, i
     const bool rows_direct_f32 = sizeof(T) == 4 && rp.on && nd <= kMfmaMaxND;
     const bool odd = bf16_odd_rows(s, in, out);
     // (rows of a dozen positions are all gap as virtual rows: B50000 C128 L9 K9 fwd 249 us on the vector-ALU kernel, 323 us
-    // here; L25 K7 320 against 309 us.  Calls of up to 1024 segments are a wait for memory each, and the vector-ALU kernel waits
-    // once less: it keeps them while its arithmetic is short - B2175 C1 L41 K16 3.6 / 4.8 us, B200 C64 L47 K31 4.6 / 4.8, K64 5.3 -> 5.0,
-    // B100 C256 L61, 1792 segments, K31 6.2 -> 5.7; ordinary rows B232 C2 L1989 K7 3.9 / 4.3, K48 4.7 -> 4.2)
-    const long long odd_segs = rp.on ? (long long)rp.nvs * s.C : (long long)s.B * s.C * (((long long)s.L + dwconv::kSegLen - 1) / dwconv::kSegLen);
-    const bool odd_small = odd_segs <= 1024 && odd_segs * s.K <= (rp.on ? 32768 : 16384);
-    if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24) || odd_small)) return -1;
+    // here; L25 K7 320 against 309 us)
+    if (odd && (nd > kMfmaMaxND || !bf16_odd_rows_ok(s, in, out, rp) || (rp.on && s.L < 24) || bf16_odd_small_call(s, rp))) return -1;
     if (!odd && !granular && !rows_direct_bf16 && !rows_direct_f32 && (!ragged_rows_ok(s, nd) || !aligned_to(in, 4) || !aligned_to(out, 4))) return -1;
     const long long rows = (long long)s.B * s.C;
     const int L_walk = odd ? s.L + 1 : s.L;             // (a shifted row may reach one position further)

@@ -389,6 +389,22 @@ def test_band_kernel_takes_short_filters_of_huge_batches(oracle_mod, B, L, K, p,
     assert len(names) == 2 and all("corr_band_kernel" in n for n in names), names
 
 
+# ... both gradients in one pass (bwd_fused_bf16_kernel on shifted rows, none of them virtual): every number of block offsets, rows that end on the last position
+# of a segment and one behind it, waves that walk several segments, one workgroup of sixteen waves per channel (even rows on odd tensors)
+@pytest.mark.parametrize("B,C,L,K,p,offset", [
+    (9, 33, 4097, 64, 63, 0), (33, 40, 1023, 7, 3, 1), (5, 64, 2501, 48, 24, 0), (7, 20, 3071, 66, 0, 3), (20, 40, 1651, 20, 19, 0), (64, 256, 1022, 33, 16, 1),
+    (30, 50, 821, 2, 1, 0), (40, 256, 2047, 60, 59, 0),
+])
+def test_exact_bf16_odd_rows_fused_backward(oracle_mod, B, C, L, K, p, offset):
+    print(f"case exact bf16 odd rows fused B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    run_exact(oracle_mod, B, C, L, K, p, "bf16", seed=47 + B + 3 * C + 5 * L, offset=offset)
+    x = torch.randn(B * C * L + offset, device="cuda").to(torch.bfloat16)[offset:].view(B, C, L)
+    w, dx = torch.randn(C, K, device="cuda").to(torch.bfloat16), empty_device((B, C, L), torch.bfloat16, offset)
+    names = _kernels(lambda: binding.dwconv_bwd(x, x, w, p, out_dx=dx))
+    assert "bwd_fused_bf16_kernel" in names[0] and len(names) <= 2, names
+    assert torch.equal(dx, binding.dwconv_bwd_input(x, w, p, out=empty_device((B, C, L), torch.bfloat16, offset)))
+
+
 # bf16, sixteen rows per tile: one to eight blocks per row, two to six block offsets, one and two channels per wave, row ends inside
 # a granule of four, units that the batch does not fill, filters longer than the row
 @pytest.mark.parametrize("offset", [0, 2])
