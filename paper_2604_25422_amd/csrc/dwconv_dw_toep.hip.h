@@ -21,8 +21,8 @@ namespace dwconv {
 
 struct DwToepGeom {
     int B, C, L, K, pad;
-    int blk0, nblk;     // 32-blocks of lags, block m being lags 32 m + shift ..: the first (may be negative), how many hold a tap
-    int shift;          // and a lag inside (-L, L); the first lag opens the first block
+    int blk0, nblk;     // 32-blocks of lags, block m being lags 32 m + shift ..: the first (may be negative), how many there are (all
+    int shift;          // lags inside (-L, L) that have a tap are in them, and possibly more in front)
     int npiece;         // pieces of T tiles
     int F;              // positions of dY per chunk (a multiple of 32)
     int rows;           // batch entries per slice
