@@ -178,12 +178,14 @@ static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
 // have lost, are multiplied all the same.  dw_band_kernel has groups of eight rows to fill (fewer batch entries: virtual rows, whose
 // stages are small), and a stage of its own for every twelve (bf16 sixteen) offsets of 32.  us, dw_band_kernel -> dw_toep_kernel,
 // with the ratio of the products:
-//   fp32, five batch entries and more: B8 C256 L8192 K8192 (1.12) 778 -> 628, B17 C736 L889 K889 (1.06) 188 -> 126, B49 C32 L3184
-//     K3184 (1.20) 171 / 176, B97 C96 L1856 K1856 (1.56) 248 / 279, B284 C103 L768 K768 (1.70) 212 / 303
-//   bf16: B8 C256 L8192 K8192 (1.12) 201 -> 127, B12 C355 L1832 K1832 (1.28) 54 -> 37, B7 C128 L4367 K4367 (1.36) 55 -> 37, B275 C83
-//     L880 K880 (1.49) 52 / 66, B53 C264 L784 K784 (1.60) 36 / 46
+//   fp32, five batch entries and more: B8 C256 L8192 K8192 (1.12) 778 -> 628, B17 C736 L889 K889 (1.06) 188 -> 126, B161 C46 L1024
+//     K1024 (1.25) 102 -> 84, B7 C96 L896 K896 (1.30) 18 -> 14, B16 C83 L3328 K3328 (1.32) 117 -> 99, B98 C45 L2496 K2496 (1.36) 207 / 227,
+//     B284 C103 L768 K768 (1.70) 212 / 303
+//   bf16: B8 C256 L8192 K8192 (1.12) 201 -> 127, B12 C355 L1832 K1832 (1.28) 54 -> 37, B25 C328 L1020 K1020 (1.49) 38 -> 28, B25 C32 L1163
+//     K1163 (1.52) 17 -> 11; a stage is one row, and a short one has few products: B214 C64 L896 K896 (1.47) 33 / 43, B38 C45 L813 K813
+//     (1.55) 11 / 12
 //   fewer batch entries, fp32: B4 C71 L912 K912 (1.92) 11.1 / 12.0, B1 C365 L5675 K5675 (1.19) 215 -> 73, B4 C672 L1080 K1080 (1.84) 64 -> 52, B1 C396 L1104 K1104 (2.15)
-//     35 -> 14, B3 C64 L7667 K163 (4.7) 14 / 24; bf16: B3 C320 L3968 K3968 (0.96) 83 -> 28, B2 C384 L1150 K1150 (2.59) 17.1 -> 7.7
+//     35 -> 14, B2 C608 L416 K416 (2.64) 23 -> 11, B3 C64 L7667 K163 (4.7) 14 / 24; bf16: B3 C320 L3968 K3968 (0.96) 83 -> 28, B2 C384 L1150 K1150 (2.59) 17.1 -> 7.7
 static bool dw_takes_toep(const Shape &s, const DwPlan &p)
 {
     const double lo = std::min(s.pad, s.L - 1), hi = std::min(s.K - 1 - s.pad, s.L - 1);           // lags -lo .. hi
@@ -192,7 +194,7 @@ static bool dw_takes_toep(const Shape &s, const DwPlan &p)
     const double groups = (double)(((long long)s.B * nseg + 7) / 8);
     // (two blocks at a time: half a product lost per offset of 32 at the end of the row, and the offsets at both ends of the filter)
     const double band = groups * (8.0 * pairs / nseg / (1024 * 16) + 0.75 * ((lo + hi + 1) / 32 + 2));
-    const double most = s.dtype == DWCONV_F32 ? (nseg > 2 ? 2.2 : nseg > 1 ? 1.85 : 1.15) : (nseg > 1 ? 2.6 : 1.42);
+    const double most = s.dtype == DWCONV_F32 ? (nseg > 2 ? 2.65 : nseg > 1 ? 1.85 : 1.33) : (nseg > 1 ? 2.6 : s.L >= 1000 ? 1.54 : 1.42);
     return p.tp.work <= most * band;
 }
 
