@@ -11,6 +11,11 @@
 // summed where they are (no diagonals), and a single batch entry fills the operands as well as eight.  A tile is 1024 lags
 // whatever the filter, so shorter filters leave columns idle: dw_band_kernel has them (dw_takes_toep).
 //
+// What bounds it (counters, B8 C256 K = L = 8192): fp32 the matrix pipe, 80 % of the launch's cycles under a lowered clock (dw_band_kernel
+// 54 %): 775-793 -> 618-654 us, error against 64 bits 1.65e-7 -> 1.43e-7; bf16 LDS reads (79 %) and the matrix pipe (66 %; dw_band_kernel 59 % and
+// 30 %): 201 -> 125-132 us.  A few batch entries on few channels: the chain of one stage, some 1.2 us of loads, splitting, barriers and
+// products (fp32 B1 C365 L5675 K5675 215 -> 73 us, bf16 B2 C384 L1150 K1150 17.1 -> 7.7).
+//
 // Workgroup (c, slice, piece): T tiles of lags, the rows of its slice in chunks of F positions; the four waves split the e of a
 // chunk.  The next chunk's granules are loaded into registers while one is multiplied.  Pieces go out in falling order of
 // their work (lag 0 meets a whole row, lag L - 1 one position), so that the short ones fill in behind the long ones.
@@ -26,6 +31,7 @@ struct DwToepGeom {
     int npiece;         // pieces of T tiles
     int F;              // positions of dY per chunk (a multiple of 32)
     int rows;           // batch entries per slice
+    int chain;          // fp32: the e (of all four waves) between two additions to the totals, a multiple of 4
     int tap_off;        // byte offset of the taps in LDS
 };
 constexpr int kToepThreads = 256;
@@ -210,6 +216,19 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
             lo[t] = max(cur.e_lo, -2 * (m0 + 31) - before);
             hi[t] = m0 < g.blk0 + g.nblk ? min(cur.e_hi, nch - 1 - 2 * m0) : -(1 << 28);       // (a spare tile)
         }
+        // fp32: the sums of the tiles t0 .. t0 + n - 1 added to totals of their own, so that no chain of additions gets long
+        auto fold = [&](auto t0c, auto nc) {
+            if constexpr (NL == 3) {
+                constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
+#pragma unroll
+                for (int t = T0; t < T0 + N; ++t)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        total[t][i] += limb_sum(acc[t][i], mid[t][i], low[t][i]);
+                        acc[t][i] = mid[t][i] = low[t][i] = 0.f;
+                    }
+            }
+        };
         // e = ea .. eb (those of this wave: ks modulo 4) for the tiles T0 .. T0 + N - 1
         auto run = [&](auto t0c, auto nc, int ea, int eb) {
             constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
@@ -297,19 +316,18 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
                 int ea = lo[a], eb = hi[b];
                 if constexpr (a > 0) eb = min(eb, lo[a - 1] - 1);
                 if constexpr (b + 1 < T) ea = max(ea, hi[b + 1] + 1);
-                run(ac, std::integral_constant<int, b - a + 1>{}, ea, eb);
+                constexpr std::integral_constant<int, b - a + 1> n{};
+                if constexpr (NL == 3) {
+#pragma unroll 1
+                    for (; ea <= eb; ea += g.chain) {
+                        run(ac, n, ea, min(eb, ea + g.chain - 1));
+                        fold(ac, n);
+                    }
+                } else {
+                    run(ac, n, ea, eb);
+                }
             });
         });
-        if constexpr (NL == 3) {
-            // (totals of their own, so that no chain of additions is longer than the e of one chunk)
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    total[t][i] += limb_sum(acc[t][i], mid[t][i], low[t][i]);
-                    acc[t][i] = mid[t][i] = low[t][i] = 0.f;
-                }
-        }
         cur = nxt;
     }
 

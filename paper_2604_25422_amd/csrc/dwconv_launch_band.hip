@@ -66,7 +66,7 @@ int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, i
             while (((units - NBk * (dwconv::band_block_bytes(NL) / 16)) & 15) != 0) ++units;
             g.pitch = 16 * units;
             if (g.RW * wb * 4 <= dwconv::band_prefetch(NL) * dwconv::kBandThreads &&
-                (F >= s.K || (NL == 3 ? F / 8 + 1 <= dwconv::kBandThreads : dwconv::band_tap_dwords(F) <= dwconv::kBandTapPrefetch * dwconv::kBandThreads)) &&
+                (F >= s.K || dwconv::band_tap_dwords(F) <= dwconv::kBandTapPrefetch * dwconv::kBandThreads) &&
                 dwconv::band_lds_bytes(NL, g.RW, g.pitch, F) <= kMaxLdsBytes / 2) {
                 window_blocks = wb;
                 return true;

@@ -65,6 +65,13 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     long long S = 1;
     if (us > 10.0) S = std::min((long long)(us / 4.0), std::max((slots + wgs - 1) / wgs, (long long)(most * slots / (p->work * s.C) + 0.5)));
     S = std::max(1ll, std::min(S, (long long)std::min(s.B, slices)));
+    // fp32: the e between two additions to the totals (four waves).  The fewer products a gradient sums, the shorter were the chains of
+    // the kernel this one replaced; with these its error against 64 bits is what it was: few rows, as long chains of products as of totals
+    // (B1 L5664 1.5e-7 without a limit, 1.0e-7 with 32 and with 16, dw_band_kernel 1.0e-7); B9 L3000 1.26e-7, 1.05e-7 with 32 (1.07e-7);
+    // B8 L8192 1.43e-7 without one (1.65e-7).  What they cost: B8 C256 L8192 K8192 641 us, 667 with 64, 715 with 32
+    int root = 4;
+    while ((root + 1) * (root + 1) <= s.L / 64) ++root;
+    g.chain = s.B < 5 ? 4 * root : (long long)s.B * s.L < 65536 ? 32 : 1 << 24;
     g.rows = (int)((s.B + S - 1) / S);
     p->S = (s.B + g.rows - 1) / g.rows;
     p->work *= s.B;
