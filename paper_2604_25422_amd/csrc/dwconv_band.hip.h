@@ -199,6 +199,26 @@ inline size_t band_lds_bytes(int NL, int RW, int pitch, int F)
     return band_tap_offset(RW, pitch) + (size_t)NL * 8 * band_tap_dwords(F);
 }
 
+// Places 0 .. N - 1 of a wave, place i with work from lo[i] to hi[i], both falling with i: call f(a, n, from, to) for the runs in
+// which exactly the places a .. a + n - 1 have work, [lo[a], lo[a - 1]) and (hi[a + n], hi[a + n - 1]].  A place without any,
+// wherever it stands, has its lo beyond every hi and its hi before every lo (either alone would put it into the runs of the places
+// on one side of it).  (On the host too: a test follows the operand addresses of the kernels.)
+template <int N, typename F>
+__host__ __device__ __forceinline__ void active_runs(const int (&lo)[N], const int (&hi)[N], F &&f)
+{
+    static_for<0, N>([&](auto ac) {
+        constexpr int a = decltype(ac)::value;
+        static_for<a, N>([&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            int from = lo[a], to = hi[b];
+            if constexpr (a > 0) to = to < lo[a - 1] - 1 ? to : lo[a - 1] - 1;
+            if constexpr (b + 1 < N) from = from > hi[b + 1] + 1 ? from : hi[b + 1] + 1;
+            f(ac, std::integral_constant<int, b - a + 1>{}, from, to);
+        });
+    });
+}
+constexpr int kNoWorkLo = 1 << 28, kNoWorkHi = -(1 << 28);
+
 // A lane's number, hidden from the compiler at each use: it would keep every address that follows from it in a register
 // for the whole kernel.
 __device__ __forceinline__ int band_hide(int v)

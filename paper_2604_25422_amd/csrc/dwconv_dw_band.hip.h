@@ -63,6 +63,61 @@ inline size_t dw_band_lds_bytes(int NL, int RGN, int S32, int ndw, int ND)
     return stage > ep ? stage : ep;
 }
 
+// What a workgroup walks, as functions of the geometry: the kernel's, and those of a test on the host that follows its operand addresses.
+struct DwBandWindow {
+    int dlo, nd;        // first offset, offsets
+    int spare;          // places in front that have no offset
+};
+__host__ __device__ __forceinline__ DwBandWindow dw_band_window(const DwBandGeom &g, int win, bool dealt)
+{
+    const int left = g.nd - win * (g.ndw - 1), nd = left < g.ndw ? left : g.ndw;
+    return DwBandWindow{g.dmin + win * (g.ndw - 1), nd, dealt && g.fold && g.rev ? g.ndw - nd : 0};
+}
+// Blocks of a virtual row; blocks from the start of the first virtual row of a row to that of the last.
+__host__ __device__ __forceinline__ int dw_band_row_blocks(const DwBandGeom &g) { return g.nseg == 1 ? (g.L + 31) >> 5 : g.Lv >> 5; }
+__host__ __device__ __forceinline__ int dw_band_seg_blocks(const DwBandGeom &g) { return (g.nseg - 1) * dw_band_row_blocks(g); }
+// The offsets of the ND places of a wave of group dg, relative to the window's first (outside 0 .. nd - 1: none).  Dealt: one of every DG,
+// otherwise a range.
+template <int ND, int DG, bool DEALT>
+struct DwBandPlaces {
+    static constexpr int STEP = DEALT ? DG : 1;
+    int off0, swing;    // the i-th: off0 + STEP i, + swing in odd rounds
+    __host__ __device__ __forceinline__ DwBandPlaces(const DwBandGeom &g, const DwBandWindow &w, int dg)
+        : off0((DEALT ? dg : dg * ND) - w.spare), swing(DEALT ? (dg ^ g.fold) - dg : 0) {}
+    __host__ __device__ __forceinline__ int operator()(int i) const { return off0 + STEP * i + ((i & 1) ? swing : 0); }
+};
+// A stage: group vg of 8 RGN virtual rows, dY blocks yb0 .. yb0 + S32 - 1, x blocks xlo .. xlo + nx - 1 (nx <= 0: no offset of the
+// window meets a row in it).
+struct DwBandStage {
+    int st, vg, yb0, xlo, nx;
+};
+__host__ __device__ __forceinline__ void dw_band_set_stage(const DwBandGeom &g, int dlo, DwBandStage &s)
+{
+    s.vg = g.nstep == 1 ? s.st : g.step_magic ? (int)(((unsigned long long)(unsigned)s.st * g.step_magic) >> 32) : s.st / g.nstep;
+    s.yb0 = (s.st - s.vg * g.nstep) * g.S32;
+    s.xlo = s.yb0 + dlo;
+    int xhi = s.xlo + g.S32 + g.ndw - 2;
+    // (a block of zeros on both sides of the row: the other half of a pair that is half inside.  Blocks count from the start
+    // of each virtual row, of which the last starts seg_blocks into its row)
+    const int first = -1 - dw_band_seg_blocks(g), NB32 = (g.L + 31) >> 5;
+    s.xlo = s.xlo > first ? s.xlo : first;
+    xhi = xhi < NB32 ? xhi : NB32;
+    s.nx = xhi - s.xlo + 1;
+}
+// The block pairs p (dY blocks yb0 + 2 p, + 1) of an offset that meet the row from some virtual row: plo .. phi.
+__host__ __device__ __forceinline__ void dw_band_pairs(const DwBandGeom &g, const DwBandWindow &w, int yb0, int offset, int &plo, int &phi)
+{
+    const int d = w.dlo + offset, NB32 = (g.L + 31) >> 5;
+    const int lo = (-yb0 - d - dw_band_seg_blocks(g)) >> 1;              // ceil((-yb0 - d - 1 - seg_blocks) / 2)
+    const int rest = dw_band_row_blocks(g) - yb0 + 1, last = (rest < g.S32 ? rest : g.S32) / 2 - 1, hi = (NB32 - 1 - yb0 - d) >> 1;
+    plo = lo > 0 ? lo : 0;
+    phi = last < hi ? last : hi;
+    if ((unsigned)offset >= (unsigned)w.nd) {                            // (in front or behind: active_runs)
+        plo = kNoWorkLo;
+        phi = kNoWorkHi;
+    }
+}
+
 // Four consecutive elements at any element-aligned address.
 struct __attribute__((packed, aligned(4))) Raw4F { unsigned v[4]; };
 struct __attribute__((packed, aligned(2))) Raw4H { unsigned v[2]; };
@@ -129,7 +184,6 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int c = blockIdx.x, sl = (int)blockIdx.y;
     const int wz = g.win0 + (int)blockIdx.z, win = g.rev ? g.nwin - 1 - wz : wz;
     const int NB32 = (g.L + 31) >> 5;
-    const int dlo = g.dmin + win * (g.ndw - 1), nd_here = min(g.ndw, g.nd - win * (g.ndw - 1));
     constexpr int KS = 4 / DG;
     const int dg = wave & (DG - 1), ks = wave / DG;
     const int RGN = 1 << g.rg_log;
@@ -138,15 +192,13 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     // start from the near end, so that the places of the last window that have no offset are far ones.  bf16, both tensors by every
     // thread: a range, whose pairs are nearly the same ones: B3220 C123 L144 K144 75 us, 79 dealt)
     constexpr bool DEALT = SPLIT || NL == 3;
-    const int spare = DEALT && g.fold && g.rev ? g.ndw - nd_here : 0, swing = DEALT ? (dg ^ g.fold) - dg : 0;
-    constexpr int STEP = DEALT ? DG : 1;
-    const int off0 = (DEALT ? dg : dg * ND) - spare;                     // the i-th: off0 + STEP i, + swing in odd rounds
-    auto offset_of = [&](int i) { return off0 + STEP * i + ((i & 1) ? swing : 0); };
+    const DwBandWindow w = dw_band_window(g, win, DEALT);
+    const int dlo = w.dlo, nd_here = w.nd;
+    const DwBandPlaces<ND, DG, DEALT> place(g, w, dg);
+    constexpr int STEP = DwBandPlaces<ND, DG, DEALT>::STEP;
     const size_t CL = (size_t)g.C * (size_t)g.L;
     const E *x_c = x + (size_t)c * (size_t)g.L, *dy_c = dy + (size_t)c * (size_t)g.L;
     const int VR = g.B * g.nseg;
-    const int NBV = g.nseg == 1 ? NB32 : g.Lv >> 5;                      // blocks of a virtual row
-    const int seg_blocks = (g.nseg - 1) * NBV;
 
     floatx16 acc[ND], mid[NL == 3 ? ND : 1], low[NL == 3 ? ND : 1];
 #pragma unroll
@@ -157,27 +209,13 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             if constexpr (NL == 3) mid[i][k] = low[i][k] = 0.f;
         }
 
-    // A stage: group vg of 8 RGN virtual rows, dY blocks yb0 .. yb0 + S32 - 1, x blocks xlo .. xlo + nx - 1.
-    struct Stage {
-        int st, vg, yb0, xlo, nx;
-    };
-    auto set_stage = [&](Stage &s) {
-        s.vg = g.nstep == 1 ? s.st : g.step_magic ? (int)__umulhi((unsigned)s.st, g.step_magic) : s.st / g.nstep;
-        s.yb0 = (s.st - s.vg * g.nstep) * g.S32;
-        s.xlo = s.yb0 + dlo;
-        int xhi = s.xlo + g.S32 + g.ndw - 2;
-        // (a block of zeros on both sides of the row: the other half of a pair that is half inside.  Blocks count from the start
-        // of each virtual row, of which the last starts seg_blocks into its row)
-        s.xlo = max(s.xlo, -1 - seg_blocks);
-        xhi = min(xhi, NB32);
-        s.nx = xhi - s.xlo + 1;
-    };
+    typedef DwBandStage Stage;
     // the next stage in which some offset of the window meets a row (nx <= 0: none does); st >= stages: the end
     auto advance = [&](Stage &s) {
         do {
             s.st += (int)gridDim.y;
             if (s.st >= g.stages) return;
-            set_stage(s);
+            dw_band_set_stage(g, dlo, s);
         } while (s.nx <= 0);
     };
     // Staging: 64 WPR threads bring one group of eight rows, one item of four positions of x and one of dY each (the plan
@@ -316,11 +354,9 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         int plo[ND], phi[ND];                                            // block pairs p (blocks yb0 + 2 p, + 1) per offset
 #pragma unroll
         for (int i = 0; i < ND; ++i) {
-            const int d = dlo + offset_of(i);
-            // (the pairs that meet the row from some virtual row)
-            plo[i] = max(0, (-yb0 - d - seg_blocks) >> 1);               // ceil((-yb0 - d - 1 - seg_blocks) / 2)
-            phi[i] = min(min(g.S32, NBV - yb0 + 1) / 2 - 1, (NB32 - 1 - yb0 - d) >> 1);
-            if ((unsigned)offset_of(i) >= (unsigned)nd_here) phi[i] = -(1 << 28);
+            dw_band_pairs(g, w, yb0, place(i), plo[i], phi[i]);
+            // (hidden: the compiler would make a second set of loops for waves with an empty place, bf16 119 -> 157 registers)
+            asm volatile("" : "+s"(plo[i]), "+s"(phi[i]));
         }
         const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
         const int lane_off = (q ^ ((q >> 3) & 3)) * PB + kg * BB;
@@ -330,8 +366,8 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             pa += (ks - pa) & (KS - 1);
             if (pa > pb) return;
             const unsigned char *yp = yw + 2 * pa * BB, *xp[2];                      // (of the even and the odd rounds over the groups)
-            xp[0] = xw + (2 * pa + off0) * BB;
-            xp[1] = xp[0] + swing * BB;
+            xp[0] = xw + (2 * pa + place.off0) * BB;
+            xp[1] = xp[0] + place.swing * BB;
             uintx4 y[2][NL], xv[2][NL];
             auto read_y = [&](uintx4 (&to)[NL]) {
 #pragma unroll
@@ -383,18 +419,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
         for (int rg = 0; rg < RGN; ++rg) {
             const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + dlo - xlo) * BB;
             const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
-            // the bounds fall with the offset: those active at a pair are the offsets a .. b with p in [plo[a], plo[a - 1]) and
-            // (phi[b + 1], phi[b]]
-            static_for<0, ND>([&](auto ac) {
-                constexpr int a = decltype(ac)::value;
-                static_for<a, ND>([&](auto bc) {
-                    constexpr int b = decltype(bc)::value;
-                    int pa = plo[a], pb = phi[b];
-                    if constexpr (a > 0) pb = min(pb, plo[a - 1] - 1);
-                    if constexpr (b + 1 < ND) pa = max(pa, phi[b + 1] + 1);
-                    run(ac, std::integral_constant<int, b - a + 1>{}, xw, yw, pa, pb);
-                });
-            });
+            active_runs(plo, phi, [&](auto ac, auto nc, int pa, int pb) { run(ac, nc, xw, yw, pa, pb); });
         }
     }
 
@@ -446,9 +471,9 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
             for (int h = 1; h >= 0; --h) {
                 const int o = (t >> 5) - h, e = (t & 31) + 32 * h;
                 if (o >= 0 && o < nd_here && e < 63) {
-                    const int at_o = o + spare, i = DEALT ? at_o / DG : at_o % ND, r = DEALT ? at_o & (DG - 1) : at_o / ND;
+                    const int at_o = o + w.spare, i = DEALT ? at_o / DG : at_o % ND, r = DEALT ? at_o & (DG - 1) : at_o / ND;
                     const int at = (DEALT && (i & 1) ? r ^ g.fold : r) * TW + 64 * i + e;
-                    for (int w = 0; w < KS; ++w) sum += taps[w * DG * TW + at];
+                    for (int k = 0; k < KS; ++k) sum += taps[k * DG * TW + at];
                 }
             }
         }

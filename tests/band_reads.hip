@@ -1,0 +1,132 @@
+// Follows the operand addresses of the kernels for long filters on the host, with the plans and the walk the kernels use themselves:
+// every operand a wave reads from LDS must lie in what its stage has put there, and every product must be one of a place that has
+// work, formed once.  Built and run by tests/test_band_reads_cpu.py; prints the first fault of a shape and returns 1.
+#include "../paper_2604_25422_amd/csrc/dwconv_plan_band.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+
+using namespace dwhost;
+
+static bool fault(const char *kernel, const Shape &s, const char *what, long long v, long long lo, long long hi)
+{
+    printf("%s %s B%d C%d L%d K%d pad%d: %s %lld, expected %lld .. %lld\n", kernel, s.dtype == DWCONV_F32 ? "f32" : "bf16", s.B, s.C, s.L, s.K,
+           s.pad, what, v, lo, hi);
+    return false;
+}
+
+// One window of dw_band_kernel, one stage of it: the blocks every wave reads.
+template <int ND, int DG, bool DEALT>
+static bool dw_band_stage(const Shape &s, const dwconv::DwBandGeom &g, const dwconv::DwBandWindow &w, const dwconv::DwBandStage &st)
+{
+    constexpr int KS = 4 / DG;
+    std::vector<int> formed(w.nd, 0), due(w.nd, 0);
+    bool ok = true;
+    for (int wave = 0; wave < 4; ++wave) {
+        const int dg = wave & (DG - 1), ks = wave / DG;
+        const dwconv::DwBandPlaces<ND, DG, DEALT> place(g, w, dg);
+        int plo[ND], phi[ND];
+        for (int i = 0; i < ND; ++i) {
+            dwconv::dw_band_pairs(g, w, st.yb0, place(i), plo[i], phi[i]);
+            if (ks == 0 && (unsigned)place(i) < (unsigned)w.nd) due[place(i)] = std::max(0, phi[i] - plo[i] + 1);
+        }
+        dwconv::active_runs(plo, phi, [&](auto ac, auto nc, int pa, int pb) {
+            constexpr int I0 = decltype(ac)::value, N = decltype(nc)::value;
+            pa += (ks - pa) & (KS - 1);
+            for (int p = pa; p <= pb && ok; p += KS)
+                for (int i = I0; i < I0 + N && ok; ++i) {
+                    const int o = place(i), xb = st.yb0 + w.dlo + o + 2 * p - st.xlo;
+                    if (o < 0 || o >= w.nd) ok = fault("dw_band", s, "product of offset", o, 0, w.nd - 1);
+                    else if (xb < 0 || xb + 1 >= st.nx) ok = fault("dw_band", s, "block of x", xb, 0, st.nx - 2);
+                    else if (p < 0 || 2 * p + 1 >= g.S32) ok = fault("dw_band", s, "block of dY", 2 * p, 0, g.S32 - 2);
+                    else ++formed[o];
+                }
+        });
+    }
+    for (int o = 0; o < w.nd && ok; ++o)
+        if (formed[o] != due[o]) ok = fault("dw_band", s, "products", formed[o], due[o], due[o]);
+    return ok;
+}
+
+template <int ND, int DG>
+static bool dw_band_form(const Shape &s, const DwBandPlan &p)
+{
+    const bool dealt = p.split || s.dtype == DWCONV_F32;
+    const dwconv::DwBandGeom &g = p.g;
+    for (int win = 0; win < g.nwin; ++win) {
+        const dwconv::DwBandWindow w = dwconv::dw_band_window(g, win, dealt);
+        // (the stages of one group of rows: the others are like them)
+        for (int st = 0; st < g.nstep; ++st) {
+            dwconv::DwBandStage stage;
+            stage.st = st;
+            dwconv::dw_band_set_stage(g, w.dlo, stage);
+            if (stage.nx <= 0) continue;
+            const size_t bytes = (size_t)(1 << g.rg_log) * (size_t)(stage.nx + g.S32) * dwconv::dw_band_block_bytes(s.dtype == DWCONV_F32 ? 3 : 1);
+            if (bytes > p.lds) return fault("dw_band", s, "bytes of a stage", (long long)bytes, 0, (long long)p.lds);
+            if (!(dealt ? dw_band_stage<ND, DG, true>(s, g, w, stage) : dw_band_stage<ND, DG, false>(s, g, w, stage))) return false;
+        }
+    }
+    return true;
+}
+
+static int planned = 0;
+static bool check_dw_band(const Shape &s)
+{
+    DwBandPlan p;
+    if (!plan_dw_band(s, 1 << 20, &p)) return true;
+    ++planned;
+    switch (8 * p.ND + p.g.dg_log) {
+    case 8: return dw_band_form<1, 1>(s, p);
+    case 16: return dw_band_form<2, 1>(s, p);
+    case 17: return dw_band_form<2, 2>(s, p);
+    case 18: return dw_band_form<2, 4>(s, p);
+    case 24: return dw_band_form<3, 1>(s, p);
+    case 25: return dw_band_form<3, 2>(s, p);
+    case 26: return dw_band_form<3, 4>(s, p);
+    case 34: return dw_band_form<4, 4>(s, p);
+    default: return fault("dw_band", s, "form", 8 * p.ND + p.g.dg_log, 8, 34);
+    }
+}
+
+// Shapes over the range of the kernels: causal, nearly causal, centred, anti-causal and any other pad, few and many batch entries.
+static Shape draw(std::mt19937 &rng)
+{
+    auto upto = [&](int n) { return (int)(rng() % (unsigned)n); };
+    auto spread = [&](double lo, double hi) { return (int)(lo * std::pow(hi / lo, (rng() % 100001u) / 100000.0)); };
+    Shape s;
+    s.B = upto(3) ? spread(1, 12) : spread(1, 3000);
+    s.C = spread(1, 1000);
+    s.L = spread(8, 9000);
+    s.K = upto(4) ? std::min(s.L, spread(66, 9000)) : spread(66, 12000);
+    switch (upto(6)) {
+    case 0: s.pad = s.K - 1; break;
+    case 1: s.pad = 0; break;
+    case 2: s.pad = (s.K - 1) / 2; break;
+    case 3: s.pad = s.K - 1 - upto(std::max(1, s.K / 4)); break;
+    case 4: s.pad = upto(std::max(1, s.K / 4)); break;
+    default: s.pad = upto(s.K); break;
+    }
+    s.dtype = upto(2) ? DWCONV_F32 : DWCONV_BF16;
+    return s;
+}
+
+int main(int argc, char **argv)
+{
+    // kernel seed count, or kernel - and lines "B C L K pad dtype" on standard input
+    if (argc < 3) return 2;
+    bool (*check)(const Shape &) = nullptr;
+    if (!strcmp(argv[1], "dw_band")) check = check_dw_band;
+    if (!check) return 2;
+    int bad = 0;
+    if (!strcmp(argv[2], "-")) {
+        Shape s;
+        while (scanf("%d %d %d %d %d %d", &s.B, &s.C, &s.L, &s.K, &s.pad, &s.dtype) == 6) bad += !check(s);
+    } else {
+        std::mt19937 rng((unsigned)atoi(argv[2]));
+        for (int i = 0, n = argc > 3 ? atoi(argv[3]) : 1; i < n && bad < 20; ++i) bad += !check(draw(rng));
+    }
+    printf("%d shapes planned, %d at fault\n", planned, bad);
+    return bad ? 1 : 0;
+}

@@ -1,0 +1,37 @@
+"""Operand addresses of the kernels for long filters, followed on the host with the plans and the walk of the kernels (band_reads.hip): no
+read outside what a stage has put into LDS, no product of a place that has no work, every product once."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2604_25422_amd import _build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def reads(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("band_reads") / "band_reads")
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    r = subprocess.run([hipcc, "--offload-host-only"] + _build.HIPCC_FLAGS + ["-O1", os.path.join(HERE, "band_reads.hip"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return exe
+
+
+def run(exe, *args, shapes=()):
+    r = subprocess.run([exe, *map(str, args)], input="".join("%d %d %d %d %d %d\n" % s for s in shapes), capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-1000:]
+    planned = int(r.stdout.split()[-6])
+    return planned
+
+
+# causal filters whose last window has fewer offsets than places, in several stages along a row (the places in front are then the empty ones)
+DW_BAND = [(8, 256, 8192, 500, 499, 0), (32, 256, 4096, 257, 256, 0), (32, 256, 4096, 226, 225, 0), (1000, 64, 377, 100, 99, 0), (13, 582, 480, 8926, 8397, 0),
+           (1, 317, 568, 1205, 1204, 0), (100, 64, 1500, 520, 519, 0), (64, 256, 2048, 500, 250, 0), (64, 256, 2048, 500, 0, 1), (8, 256, 8192, 500, 499, 1)]
+
+
+def test_dw_band(reads):
+    assert run(reads, "dw_band", "-", shapes=DW_BAND) == len(DW_BAND)
+    assert run(reads, "dw_band", 1, 3000) > 2000
