@@ -169,36 +169,6 @@ constexpr int band_prefetch(int NL) { return NL == 3 ? 5 : 10; }
 constexpr int kBandPrefetchF32Few = 4;
 constexpr int kBandTapPrefetch = 4;
 
-struct BandGeom {
-    int B, C, L, K;
-    int pad;            // effective pad of this correlation
-    int reverse;        // filter index reversed (input gradient)
-    int nb_log;         // log2 of the blocks of a row that are columns of a tile
-    int RW;             // rows per item = 32 >> nb_log
-    int PB;             // 32-position blocks of a row per item (a whole number of tiles)
-    int NP;             // pieces per row
-    unsigned np_magic;  // floor(2^32 / NP) + 1: item / NP == umulhi(item, np_magic) for NP > 1
-    int items;          // row groups x pieces of a channel
-    int F;              // taps per chunk
-    int pitch;          // bytes of one staged row
-    int TG;             // tile groups; the e of a chunk are split W / TG ways
-    int fold;           // TG - 1 (TG is a power of two): every other round of tiles over the groups goes back to front (causal filters: the
-                        // work grows or falls along the row); otherwise 0
-    int tile0;          // the first tile of the first round: negative where there are spare tiles and the work grows
-};
-// dwords of one of the two copies of a chunk's taps (copies 16 banks apart: the even and the odd lanes of a read)
-__host__ __device__ inline int band_tap_dwords(int F) { return ((F + 2 * kBandTapMargin) / 2 + 1 + 31) / 32 * 32 + 16; }
-// the taps lie behind the window and behind the output image, which shares the window's place
-__host__ __device__ inline unsigned band_tap_offset(int RW, int pitch)
-{
-    const unsigned stage = (unsigned)(RW * pitch), red = (unsigned)(kBandWaves * 32 * kBandRedPitch * 4);
-    return stage > red ? stage : red;
-}
-inline size_t band_lds_bytes(int NL, int RW, int pitch, int F)
-{
-    return band_tap_offset(RW, pitch) + (size_t)NL * 8 * band_tap_dwords(F);
-}
-
 // Places 0 .. N - 1 of a wave, place i with work from lo[i] to hi[i], both falling with i: call f(a, n, from, to) for the runs in
 // which exactly the places a .. a + n - 1 have work, [lo[a], lo[a - 1]) and (hi[a + n], hi[a + n - 1]].  A place without any,
 // wherever it stands, has its lo beyond every hi and its hi before every lo (either alone would put it into the runs of the places
@@ -218,6 +188,80 @@ __host__ __device__ __forceinline__ void active_runs(const int (&lo)[N], const i
     });
 }
 constexpr int kNoWorkLo = 1 << 28, kNoWorkHi = -(1 << 28);
+
+struct BandGeom {
+    int B, C, L, K;
+    int pad;            // effective pad of this correlation
+    int reverse;        // filter index reversed (input gradient)
+    int nb_log;         // log2 of the blocks of a row that are columns of a tile
+    int RW;             // rows per item = 32 >> nb_log
+    int PB;             // 32-position blocks of a row per item (a whole number of tiles)
+    int NP;             // pieces per row
+    unsigned np_magic;  // floor(2^32 / NP) + 1: item / NP == umulhi(item, np_magic) for NP > 1
+    int items;          // row groups x pieces of a channel
+    int F;              // taps per chunk
+    int pitch;          // bytes of one staged row
+    int TG;             // tile groups; the e of a chunk are split W / TG ways
+    int fold;           // TG - 1 (TG is a power of two): every other round of tiles over the groups goes back to front (causal filters: the
+                        // work grows or falls along the row); otherwise 0
+    int tile0;          // the first tile of the first round: negative where there are spare tiles and the work grows
+};
+// One stage of the walk: an item (RW rows x PB blocks) and a chunk of taps.
+struct BandStage {
+    int round, item, j0;            // item < 0: the walk has ended
+    int b0, p0;                     // first row, first block of the item
+    int e_lo, e_hi;                 // the e that hold a tap of the chunk and meet the row from some block of the piece
+    int wb0, n8;                    // first window block any tile of the piece reads, granules of eight positions per row
+    int inside;                     // every row of the item is in the batch and all of the window inside the rows
+};
+// Its window, from item and chunk; false: no tap of the chunk meets the row.
+__host__ __device__ __forceinline__ bool band_set_window(const BandGeom &g, BandStage &s)
+{
+    const int NBk = 1 << g.nb_log, NCH = (g.L + 15) >> 4, NB32 = (g.L + 31) >> 5;
+    // (arithmetic shifts: floor division)
+    const int first = (s.j0 - g.pad) >> 4, e0 = -2 * (s.p0 + g.PB - 1);
+    s.e_lo = first > e0 ? first : e0;
+    const int j1 = s.j0 + g.F < g.K ? s.j0 + g.F : g.K, last = (j1 + 30 - g.pad) >> 4, e1 = NCH - 1 - 2 * s.p0;
+    s.e_hi = last < e1 ? last : e1;
+    if (s.e_lo > s.e_hi) return false;
+    const int w0 = s.p0 + (s.e_lo >> 1), w1 = s.p0 + g.PB - 1 + (s.e_hi >> 1);
+    s.wb0 = w0 > -(NBk - 1) ? w0 : -(NBk - 1);
+    s.n8 = 4 * ((w1 < NB32 + NBk - 2 ? w1 : NB32 + NBk - 2) - s.wb0 + 1);
+    s.inside = s.wb0 >= 0 && 32 * s.wb0 + 8 * s.n8 <= g.L && s.b0 + g.RW <= g.B;
+    return true;
+}
+// The t-th tile of a wave of a tile group; whether an item has such a tile (the first block of the row behind the last: a spare one).
+__host__ __device__ __forceinline__ int band_tile(const BandGeom &g, int group, int t) { return g.tile0 + g.TG * t + ((t & 1) ? group ^ g.fold : group); }
+__host__ __device__ __forceinline__ bool band_has_tile(const BandGeom &g, int p0, int tile)
+{
+    const int rel = tile << g.nb_log;
+    return p0 + rel < ((g.L + 31) >> 5) && (unsigned)rel < (unsigned)g.PB;
+}
+// The e of a stage that meet the row from a tile.
+__host__ __device__ __forceinline__ void band_tile_range(const BandGeom &g, const BandStage &s, int tile, int &lo, int &hi)
+{
+    const int m0 = s.p0 + (tile << g.nb_log), NBk = 1 << g.nb_log;
+    const int e0 = -2 * (m0 + NBk - 1), e1 = ((g.L + 15) >> 4) - 1 - 2 * m0;
+    lo = s.e_lo > e0 ? s.e_lo : e0;
+    hi = s.e_hi < e1 ? s.e_hi : e1;
+    if (!band_has_tile(g, s.p0, tile)) {                                 // (in front or behind: active_runs)
+        lo = kNoWorkLo;
+        hi = kNoWorkHi;
+    }
+}
+
+// dwords of one of the two copies of a chunk's taps (copies 16 banks apart: the even and the odd lanes of a read)
+__host__ __device__ inline int band_tap_dwords(int F) { return ((F + 2 * kBandTapMargin) / 2 + 1 + 31) / 32 * 32 + 16; }
+// the taps lie behind the window and behind the output image, which shares the window's place
+__host__ __device__ inline unsigned band_tap_offset(int RW, int pitch)
+{
+    const unsigned stage = (unsigned)(RW * pitch), red = (unsigned)(kBandWaves * 32 * kBandRedPitch * 4);
+    return stage > red ? stage : red;
+}
+inline size_t band_lds_bytes(int NL, int RW, int pitch, int F)
+{
+    return band_tap_offset(RW, pitch) + (size_t)NL * 8 * band_tap_dwords(F);
+}
 
 // A lane's number, hidden from the compiler at each use: it would keep every address that follows from it in a register
 // for the whole kernel.
@@ -246,8 +290,6 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     const int NBk = 1 << g.nb_log;
     const int c = blockIdx.x;
     const int tg = wave % g.TG, ks = wave / g.TG, KS = W / g.TG;
-    auto tile_of = [&](int group, int t) { return g.tile0 + g.TG * t + ((t & 1) ? group ^ g.fold : group); };
-    const int NCH = (g.L + 15) >> 4, NB32 = (g.L + 31) >> 5;
     constexpr int BS = band_block_bytes(NL);
     const int TP = band_tap_dwords(g.F);
     unsigned char *xs = band_smem;
@@ -256,15 +298,9 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     const E *in_c = in + (size_t)c * (size_t)g.L;
     const size_t CL = (size_t)g.C * (size_t)g.L;
 
-    // One stage of the walk: an item (RW rows x PB blocks; items y, 2 gy - 1 - y, 2 gy + y, ...: pieces of a causal filter
-    // cost what they lie from the start of the row, and this order evens them out) and a chunk of taps.
-    struct Stage {
-        int round, item, j0;            // item < 0: the walk has ended
-        int b0, p0;                     // first row, first block of the item
-        int e_lo, e_hi;                 // the e that hold a tap of the chunk and meet the row from some block of the piece
-        int wb0, n8;                    // first window block any tile of the piece reads, granules of eight positions per row
-        int inside;                     // every row of the item is in the batch and all of the window inside the rows
-    };
+    // (items y, 2 gy - 1 - y, 2 gy + y, ...: pieces of a causal filter cost what they lie from the start of the row, and this order
+    // evens them out)
+    typedef BandStage Stage;
     auto set_item = [&](Stage &s) {
         const int gy = (int)gridDim.y, y = (int)blockIdx.y;
         s.item = s.round * gy + ((s.round & 1) ? gy - 1 - y : y);
@@ -282,14 +318,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                 if (s.j0 >= g.K) { s.j0 = 0; ++s.round; set_item(s); }
             }
             if (s.item < 0) return;
-            // (arithmetic shifts: floor division)
-            s.e_lo = max((s.j0 - g.pad) >> 4, -2 * (s.p0 + g.PB - 1));
-            s.e_hi = min((min(s.j0 + g.F, g.K) + 30 - g.pad) >> 4, NCH - 1 - 2 * s.p0);
-            if (s.e_lo > s.e_hi) continue;
-            s.wb0 = max(s.p0 + (s.e_lo >> 1), -(NBk - 1));
-            s.n8 = 4 * (min(s.p0 + g.PB - 1 + (s.e_hi >> 1), NB32 + NBk - 2) - s.wb0 + 1);
-            s.inside = s.wb0 >= 0 && 32 * s.wb0 + 8 * s.n8 <= g.L && s.b0 + g.RW <= g.B;
-            return;
+            if (band_set_window(g, s)) return;
         }
     };
     // The window of a stage travels through registers: its loads are issued before the stage in front of it is multiplied.
@@ -500,11 +529,10 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
         int rel[T], lo[T], hi[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            rel[t] = tile_of(tg, t) << g.nb_log;
-            const int m0 = cur.p0 + rel[t];                              // first block of the tile
-            const bool any = m0 < NB32 && (unsigned)rel[t] < (unsigned)g.PB;     // (otherwise a spare tile)
-            lo[t] = max(cur.e_lo, -2 * (m0 + NBk - 1));
-            hi[t] = any ? min(cur.e_hi, NCH - 1 - 2 * m0) : -(1 << 28);
+            rel[t] = band_tile(g, tg, t) << g.nb_log;
+            band_tile_range(g, cur, band_tile(g, tg, t), lo[t], hi[t]);
+            // (hidden: the compiler would make a second set of loops for waves with a spare tile)
+            asm volatile("" : "+s"(lo[t]), "+s"(hi[t]));
         }
         // e = ea .. eb (those of this wave: cur.e_lo + ks modulo KS) for the tiles T0 .. T0 + N - 1.  The operands of the next
         // tile are read while this one's are multiplied.
@@ -578,18 +606,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                 }
             }
         };
-        // The tiles lie in increasing order along the row, so lo and hi fall with t: those active at an e are the tiles a .. b
-        // with e in [lo[a], lo[a - 1]) and (hi[b + 1], hi[b]].
-        static_for<0, T>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            static_for<a, T>([&](auto bc) {
-                constexpr int b = decltype(bc)::value;
-                int ea = lo[a], eb = hi[b];
-                if constexpr (a > 0) eb = min(eb, lo[a - 1] - 1);
-                if constexpr (b + 1 < T) ea = max(ea, hi[b + 1] + 1);
-                run(ac, std::integral_constant<int, b - a + 1>{}, ea, eb);
-            });
-        });
+        // (the tiles lie in increasing order along the row, so lo and hi fall with t)
+        active_runs(lo, hi, run);
         if constexpr (FOLD) {
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -650,8 +668,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                 if (KS == 1) {
                     // the wave's own tile
                     wave_lds_fence();
-                    const int tile = tile_of(tg, t);
-                    if (cur.p0 + (tile << g.nb_log) < NB32 && (unsigned)(tile << g.nb_log) < (unsigned)g.PB) {
+                    const int tile = band_tile(g, tg, t);
+                    if (band_has_tile(g, cur.p0, tile)) {
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
                             store4(tile, q, *reinterpret_cast<const floatx4 *>(r_base + (32 * wave + 8 * q) * kBandRedPitch));
@@ -664,8 +682,8 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
                         const float *r = r_base + (32 * gq + 8 * wave) * kBandRedPitch;
                         floatx4 v = *reinterpret_cast<const floatx4 *>(r);
                         for (int k = 1; k < KS; ++k) v += *reinterpret_cast<const floatx4 *>(r + k * g.TG * 32 * kBandRedPitch);
-                        const int tile = tile_of(gq, t);
-                        if (cur.p0 + (tile << g.nb_log) < NB32 && (unsigned)(tile << g.nb_log) < (unsigned)g.PB) store4(tile, wave, v);
+                        const int tile = band_tile(g, gq, t);
+                        if (band_has_tile(g, cur.p0, tile)) store4(tile, wave, v);
                     }
                 }
             }

@@ -237,6 +237,16 @@ bool allow_large_lds(Kernel kernel)
 
 enum DwKernel { DW_VALU_K8, DW_VALU_K32, DW_VALU_K64, DW_VALU_K256 };
 
+// Forward and input gradient on corr_band_kernel.
+struct BandPlan {
+    dwconv::BandGeom g;
+    int T;                 // tiles per wave (the kernel is compiled per number)
+    bool few;              // fp32, two tiles: the form that prefetches few granules
+    int gy;                // workgroups per channel
+    size_t lds;
+};
+bool plan_corr_band(const Shape &s, int pad_eff, int reverse, BandPlan *p);
+
 // Stage 1 on dw_band_kernel (filters of more than six block offsets).
 struct DwBandPlan {
     dwconv::DwBandGeom g;

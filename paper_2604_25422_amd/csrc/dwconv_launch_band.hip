@@ -1,137 +1,37 @@
 // Launchers of the forward / input-gradient kernels for long filters (dwconv_band.hip.h), both storage types.
 #include "dwconv_band.hip.h"
 #include "dwconv_host.hip.h"
-#include <algorithm>
 
 namespace dwhost {
 
 // Returns -1 when no geometry fits.
 template <typename E>
-int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
+static int launch_corr_band(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
 {
     constexpr int NL = dwconv::Limbs<E>::N;
-    const int nb32 = (s.L + 31) / 32;
-    dwconv::BandGeom g;
-    g.B = s.B; g.C = s.C; g.L = s.L; g.K = s.K; g.pad = pad_eff; g.reverse = reverse;
-    if (s.L < 8 || s.L > kMfmaMaxL) return -1;
-    constexpr int TMAX = NL == 3 ? 2 : 4;
-    int T = 1, NBk = 1, window_blocks = 0;
-    long long row_groups = 1;
-    // Geometry with columns of 2^nb_log blocks; false when window and taps do not fit (half the LDS of a compute unit, the
-    // prefetch registers).  whole_filter: only with all taps in one chunk.
-    auto fit = [&](int nb_log, bool whole_filter) -> bool {
-        g.nb_log = nb_log;
-        NBk = 1 << nb_log;
-        g.RW = 32 >> nb_log;
-        const int row_tiles = (nb32 + NBk - 1) / NBk;
-        row_groups = ((long long)s.B + g.RW - 1) / g.RW;
-        if (nb32 <= 32) {
-            // short rows: one item is RW whole rows, a tile for every wave first
-            g.TG = row_tiles >= 3 ? 4 : row_tiles;
-            T = (row_tiles + g.TG - 1) / g.TG;
-            if (T == 3) T = 4;
-            if (T > TMAX) return false;
-        } else {
-            // eight tiles per item.  Filters of up to 512 taps are bound by memory: every wave its own tiles, nothing to add
-            // up afterwards (bf16 B32 C256 L4096, TG = 4 / 2: K = 226 41 / 49 us, K = 300 46 / 51 us); longer ones by the
-            // matrix pipe and LDS: more tiles per tap operand and shorter sums (fp32 K = L = 8192 633 us, 818 us with TG = 4).
-            // Two tiles per wave in fp32 too, though one would leave room for a third workgroup (two / one: L4096 K200 104 / 108 us,
-            // K300 125 / 128, K500 182 / 196; B100 C256 L700 K400 100 / 129; short rows B2048 C128 L256 K256 178 / 200)
-            T = s.K <= 512 ? 2 : TMAX;
-            g.TG = T == 2 && s.K <= 512 ? 4 : 2;
-        }
-        // fewer tiles per item where there would be less than two workgroups per compute unit (one for items of two tiles:
-        // B1 C64 L13934 K226 fp32 7.0 us with two, 8.6 with one; B1 C130 L3148 K130 bf16 4.9 / 5.5)
-        while (T * g.TG > 1 && (T * g.TG / 2 >= row_tiles || s.C * row_groups * ((row_tiles + T * g.TG - 1) / (T * g.TG)) <
-                                                                 (T * g.TG > 2 ? 2 : 1) * kComputeUnits)) {
-            if (T > 1) T /= 2;
-            else g.TG /= 2;
-        }
-        // rows a little longer than one item: pieces of equal length instead of a second one of a tile or two (fp32 B16 C256
-        // L2100 K400 53 -> 44 us), bf16 also of half the tiles (B8 C512 L2300: K = 200 20.1 -> 17.5, 1000 35 -> 29)
-        const int rest = nb32 - T * g.TG * NBk;
-        const bool two = nb32 > 32 && rest > 0 && rest <= 2 * NBk;
-        if (two && NL == 1 && rest > 2 && T * g.TG == 8) T /= 2;
-        const int pieces = (row_tiles + T * g.TG - 1) / (T * g.TG);
-        g.PB = (two ? (row_tiles + pieces - 1) / pieces : std::min(T * g.TG, row_tiles)) * NBk;
-        const int whole = nb32 + 2 * (NBk - 1);
-        for (int F = s.K < 32768 ? (s.K + 1) & ~1 : 32768;; F = (F - 1) / 32 * 32) {
-            if (F < s.K && (F <= 64 || whole_filter)) return false;       // (a chunk is 65 taps at least; a shorter filter is one chunk)
-            g.F = F;
-            int wb = g.PB + (F + 46) / 32 + 2;
-            if (wb > whole) wb = whole;
-            // rows of the window lie as if their blocks went on from one row to the next (16-byte units modulo 16): sixteen
-            // neighbouring lanes then read sixteen different groups of banks
-            int units = wb * (dwconv::band_block_bytes(NL) / 16);
-            while (((units - NBk * (dwconv::band_block_bytes(NL) / 16)) & 15) != 0) ++units;
-            g.pitch = 16 * units;
-            if (g.RW * wb * 4 <= dwconv::band_prefetch(NL) * dwconv::kBandThreads &&
-                (F >= s.K || dwconv::band_tap_dwords(F) <= dwconv::kBandTapPrefetch * dwconv::kBandThreads) &&
-                dwconv::band_lds_bytes(NL, g.RW, g.pitch, F) <= kMaxLdsBytes / 2) {
-                window_blocks = wb;
-                return true;
-            }
-        }
-    };
-    // Columns of a tile: few blocks of many batch entries for short rows (every column is then at the same distance from the
-    // ends of its row, and block pairs outside the row cost nothing), more blocks where the batch is small.
-    int nb_min = nb32 <= 8 ? 0 : nb32 <= 16 ? 1 : nb32 <= 32 ? 2 : 3;
-    while (nb_min < 5 && (32 >> nb_min) >= 2 * s.B) ++nb_min;
-    bool ok = false;
-    // (all taps at once where some form holds them: B8 C256 L8192 K8192 bf16 141 us with 16 blocks and all taps, 177 us with 8
-    // blocks in chunks; otherwise chunks, the same shape in fp32 634 us with 16 blocks and 642 us with 8)
-    for (int nb = nb_min; nb <= 5 && !ok; ++nb) ok = fit(nb, true);
-    for (int nb = nb_min < 4 && nb32 > 32 ? 4 : nb_min; nb <= 5 && !ok; ++nb) ok = fit(nb, false);
-    if (!ok) return -1;
-    g.NP = (nb32 + g.PB - 1) / g.PB;
-    // Tiles q, 2 TG - 1 - q, ... for wave group q where the work of a tile falls along the row, the same from the end of the row where it
-    // grows (spare tiles are where there is little to do); q, TG + q, ... where it is largest in the middle, or an item is not the
-    // whole row and its tiles differ little (fp32 B19 C303 L1356 K1356 causal forward 85 us, 91 the other way).  Causal, forward and
-    // input gradient, us: fp32 B2048 C128 L256 K256 169 -> 163, 164 -> 157, B186 C69 L736 K736 61 -> 57, 59 -> 54, B1 C583 L3040 K3040
-    // 47 -> 42, 47 -> 42
-    g.fold = g.NP == 1 && (4ll * pad_eff < s.K || 4ll * (s.K - 1 - pad_eff) < s.K) ? g.TG - 1 : 0;
-    g.tile0 = g.fold && 2 * pad_eff > s.K ? (g.PB >> g.nb_log) - T * g.TG : 0;
-    g.np_magic = g.NP > 1 ? (unsigned)((1ull << 32) / (unsigned)g.NP) + 1u : 0u;
-    if (row_groups * g.NP * g.NP > 0xffffffffll || row_groups * g.NP > 0x3fffffff) return -1;
-    g.items = (int)(row_groups * g.NP);
-    const size_t lds = dwconv::band_lds_bytes(NL, g.RW, g.pitch, g.F);
-    // fp32, two tiles per wave: a third workgroup per compute unit where window and prefetch are small enough for it (two / three:
-    // B2048 C128 L160 K160 117 / 104 us, B16 C256 L2100 K400 48.4 / 42.5, B1000 C128 L224 K100 70 / 65)
-    const bool few = NL == 3 && T == 2 && g.F >= s.K && 3 * lds <= kMaxLdsBytes &&
-                     g.RW * window_blocks * 4 <= dwconv::kBandPrefetchF32Few * dwconv::kBandThreads;
-    // workgroups per channel: whole rounds of the resident ones, items spread evenly; a workgroup's start (its taps, a
-    // first window that nothing hides) counts as half an item
-    const int by_lds = (int)(kMaxLdsBytes / lds), by_regs = dwconv::band_waves(NL, T, few ? dwconv::kBandPrefetchF32Few : dwconv::band_prefetch(NL));
-    const long long slots = (long long)kComputeUnits * (by_lds < by_regs ? by_lds : by_regs);
-    int gy = 1;
-    double best = 0.0;
-    for (int y = 1; y <= g.items && y <= 4096; ++y) {
-        const double rounds = (double)(((long long)s.C * y + slots - 1) / slots);
-        const double cost = rounds * ((double)((g.items + y - 1) / y) + 0.5);
-        if (y == 1 || cost < best * 0.999) { best = cost; gy = y; }
-        if ((long long)s.C * y > 16 * slots) break;
-    }
+    BandPlan p;
+    if (!plan_corr_band(s, pad_eff, reverse, &p)) return -1;
     auto go = [&](auto kernel) -> int {
-        if (lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
+        if (p.lds > 64 * 1024 && !allow_large_lds(kernel)) return -1;
         // (a grid dimension holds fewer than 2^32 threads: further channels in launches of their own)
         for (int c0 = 0; c0 < s.C; c0 += kMaxGridChannels) {
             const int n = s.C - c0 < kMaxGridChannels ? s.C - c0 : kMaxGridChannels;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)gy), dim3(dwconv::kBandThreads), lds, st,
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.gy), dim3(dwconv::kBandThreads), p.lds, st,
                                static_cast<const E *>(in) + (size_t)c0 * (size_t)s.L, static_cast<const E *>(f) + (size_t)c0 * (size_t)s.K,
-                               static_cast<E *>(out) + (size_t)c0 * (size_t)s.L, g);
+                               static_cast<E *>(out) + (size_t)c0 * (size_t)s.L, p.g);
         }
         return launch_status();
     };
-    switch (T) {
+    switch (p.T) {
     case 1:
         if constexpr (NL == 3) {
-            if (g.F < s.K) return go(dwconv::corr_band_kernel<E, 1, true>);
+            if (p.g.F < s.K) return go(dwconv::corr_band_kernel<E, 1, true>);
         }
         return go(dwconv::corr_band_kernel<E, 1>);
     case 2:
         if constexpr (NL == 3) {
-            if (g.F < s.K) return go(dwconv::corr_band_kernel<E, 2, true>);
-            if (few) return go(dwconv::corr_band_kernel<E, 2, false, dwconv::kBandPrefetchF32Few>);
+            if (p.g.F < s.K) return go(dwconv::corr_band_kernel<E, 2, true>);
+            if (p.few) return go(dwconv::corr_band_kernel<E, 2, false, dwconv::kBandPrefetchF32Few>);
         }
         return go(dwconv::corr_band_kernel<E, 2>);
     default:

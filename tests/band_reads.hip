@@ -10,6 +10,7 @@
 
 using namespace dwhost;
 
+static int planned = 0;
 static bool fault(const char *kernel, const Shape &s, const char *what, long long v, long long lo, long long hi)
 {
     printf("%s %s B%d C%d L%d K%d pad%d: %s %lld, expected %lld .. %lld\n", kernel, s.dtype == DWCONV_F32 ? "f32" : "bf16", s.B, s.C, s.L, s.K,
@@ -71,7 +72,6 @@ static bool dw_band_form(const Shape &s, const DwBandPlan &p)
     return true;
 }
 
-static int planned = 0;
 static bool check_dw_band(const Shape &s)
 {
     DwBandPlan p;
@@ -88,6 +88,72 @@ static bool check_dw_band(const Shape &s)
     case 34: return dw_band_form<4, 4>(s, p);
     default: return fault("dw_band", s, "form", 8 * p.ND + p.g.dg_log, 8, 34);
     }
+}
+
+// An item and a chunk of corr_band_kernel: the blocks of the window and the taps every wave reads.
+template <int T>
+static bool corr_band_item(const Shape &s, const BandPlan &p, const dwconv::BandStage &st)
+{
+    const dwconv::BandGeom &g = p.g;
+    const int NL = s.dtype == DWCONV_F32 ? 3 : 1, BS = dwconv::band_block_bytes(NL), KS = dwconv::kBandWaves / g.TG, NBk = 1 << g.nb_log;
+    const int blocks = st.n8 / 4, TP = dwconv::band_tap_dwords(g.F), tiles = g.PB >> g.nb_log;
+    const int granules = p.few ? dwconv::kBandPrefetchF32Few : dwconv::band_prefetch(NL);
+    if (blocks * BS > g.pitch) return fault("corr_band", s, "bytes of a window", blocks * BS, 0, g.pitch);
+    if (g.RW * st.n8 > granules * dwconv::kBandThreads) return fault("corr_band", s, "granules of a window", g.RW * st.n8, 0, granules * dwconv::kBandThreads);
+    std::vector<int> formed(tiles, 0), due(tiles, 0);
+    bool ok = true;
+    for (int wave = 0; wave < dwconv::kBandWaves; ++wave) {
+        const int tg = wave % g.TG, ks = wave / g.TG;
+        int tile[T], lo[T], hi[T];
+        for (int t = 0; t < T; ++t) {
+            tile[t] = dwconv::band_tile(g, tg, t);
+            dwconv::band_tile_range(g, st, tile[t], lo[t], hi[t]);
+            if (ks == 0 && dwconv::band_has_tile(g, st.p0, tile[t])) due[tile[t]] += std::max(0, hi[t] - lo[t] + 1);
+        }
+        dwconv::active_runs(lo, hi, [&](auto t0c, auto nc, int ea, int eb) {
+            constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
+            ea += (st.e_lo + ks - ea) & (KS - 1);
+            for (int e = ea; e <= eb && ok; e += KS) {
+                // dwords of a tap operand: either copy, lanes 0 .. 31 and halves 0, 1
+                const int a = 16 * e + g.pad - st.j0 + dwconv::kBandTapMargin, d0 = (a - 31) >> 1, d1 = ((a + 8 + 1) >> 1) + 3;
+                if (d0 < 0 || d1 >= TP) ok = fault("corr_band", s, "dwords of taps from", d0, 0, TP - 1 - (d1 - d0));
+                for (int t = T0; t < T0 + N && ok; ++t) {
+                    const int b0 = st.p0 - st.wb0 + (tile[t] << g.nb_log) + (e >> 1), b1 = b0 + NBk - 1;
+                    if (!dwconv::band_has_tile(g, st.p0, tile[t])) ok = fault("corr_band", s, "product of tile", tile[t], 0, tiles - 1);
+                    else if (b0 < 0 || b1 >= blocks) ok = fault("corr_band", s, "block of the window", b0 < 0 ? b0 : b1, 0, blocks - 1);
+                    else ++formed[tile[t]];
+                }
+            }
+        });
+    }
+    for (int t = 0; t < tiles && ok; ++t)
+        if (formed[t] != due[t]) ok = fault("corr_band", s, "products", formed[t], due[t], due[t]);
+    // (tiles are dealt once, spare ones excepted)
+    for (int t = 0; t < tiles && ok; ++t) {
+        int n = 0;
+        for (int tg = 0; tg < g.TG; ++tg)
+            for (int i = 0; i < T; ++i) n += dwconv::band_tile(g, tg, i) == t;
+        if (n != 1) ok = fault("corr_band", s, "waves of a tile", n, 1, 1);
+    }
+    return ok;
+}
+
+static bool check_corr_band(const Shape &s)
+{
+    for (int reverse = 0; reverse < 2; ++reverse) {
+        BandPlan p;
+        if (!plan_corr_band(s, reverse ? s.K - 1 - s.pad : s.pad, reverse, &p)) continue;
+        ++planned;
+        for (int piece = 0; piece < p.g.NP; ++piece)
+            for (int j0 = 0; j0 < s.K; j0 += p.g.F) {
+                dwconv::BandStage st{};
+                st.j0 = j0;
+                st.p0 = piece * p.g.PB;
+                if (!dwconv::band_set_window(p.g, st)) continue;
+                if (!(p.T == 1 ? corr_band_item<1>(s, p, st) : p.T == 2 ? corr_band_item<2>(s, p, st) : corr_band_item<4>(s, p, st))) return false;
+            }
+    }
+    return true;
 }
 
 // Shapes over the range of the kernels: causal, nearly causal, centred, anti-causal and any other pad, few and many batch entries.
@@ -118,6 +184,7 @@ int main(int argc, char **argv)
     if (argc < 3) return 2;
     bool (*check)(const Shape &) = nullptr;
     if (!strcmp(argv[1], "dw_band")) check = check_dw_band;
+    if (!strcmp(argv[1], "corr_band")) check = check_corr_band;
     if (!check) return 2;
     int bad = 0;
     if (!strcmp(argv[2], "-")) {

@@ -35,3 +35,14 @@ DW_BAND = [(8, 256, 8192, 500, 499, 0), (32, 256, 4096, 257, 256, 0), (32, 256, 
 def test_dw_band(reads):
     assert run(reads, "dw_band", "-", shapes=DW_BAND) == len(DW_BAND)
     assert run(reads, "dw_band", 1, 3000) > 2000
+
+
+# nearly causal filters on rows of one item with fewer tiles than the waves have places for (the spare tile is then in front), forward and
+# input gradient, one chunk of taps and several
+CORR_BAND = [(1, 600, 3040, 600, 480, 0), (1, 1024, 3000, 600, 500, 0), (119, 47, 727, 1130, 117, 0), (456, 43, 709, 709, 6, 1), (1788, 128, 309, 309, 248, 0),
+             (2048, 128, 256, 256, 255, 0), (8, 256, 8192, 8192, 8191, 0), (8, 256, 8192, 8192, 8191, 1), (2, 3, 40000, 39000, 30000, 0)]
+
+
+def test_corr_band(reads):
+    assert run(reads, "corr_band", "-", shapes=CORR_BAND) == 2 * len(CORR_BAND)
+    assert run(reads, "corr_band", 1, 3000) > 4000
