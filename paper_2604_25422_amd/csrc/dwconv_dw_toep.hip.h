@@ -31,7 +31,8 @@ struct DwToepGeom {
     int npiece;         // pieces of T tiles
     int F;              // positions of dY per chunk (a multiple of 32)
     int rows;           // batch entries per slice
-    int chain;          // fp32: the e (of all four waves) between two additions to the totals, a multiple of 4
+    int run;            // the e (of all four waves) between two additions to the totals at most, a multiple of 4
+    int chain;          // bf16: the least e between two, at the ends of stages (fp32: after each run)
     int tap_off;        // byte offset of the taps in LDS
 };
 constexpr int kToepThreads = 256;
@@ -65,6 +66,8 @@ __device__ __forceinline__ void shift_up_raw8(Raw8H &r, int sh)
 #pragma unroll
     for (int i = 3; i >= 0; --i) r.v[i] = (sh & 1) ? __builtin_amdgcn_alignbit(r.v[i], i > 0 ? r.v[i - 1] : 0u, 16) : r.v[i];
 }
+// Sets of accumulators: bf16, one tile, two, for even and odd e, which halves the chains (of two tiles: B8 C256 K = L = 8192 133 -> 143 us)
+constexpr int toep_sets(int NL, int T) { return NL == 1 && T == 1 ? 2 : 1; }
 constexpr int toep_waves(int NL, int T) { return NL == 3 && T == 2 ? 2 : 3; }
 
 template <typename E, int T>
@@ -72,7 +75,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
     const E *__restrict__ x, const E *__restrict__ dy, float *__restrict__ part, E *__restrict__ dw_out, const DwToepGeom g, int slices)
 {
     constexpr int NL = Limbs<E>::N, BS = band_block_bytes(NL), THREADS = kToepThreads, KS = kBandWaves, PB = 32 * T;
-    static_assert(T == 1 || T == 2 || (T == 4 && NL == 1), "register budget");
+    static_assert(T == 1 || T == 2, "register budget");
     extern __shared__ __align__(16) unsigned char toep_smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -178,13 +181,14 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
         }
     };
 
-    floatx16 acc[T], mid[NL == 3 ? T : 1], low[NL == 3 ? T : 1], total[NL == 3 ? T : 1];
+    constexpr int SETS = toep_sets(NL, T);
+    floatx16 acc[SETS][T], mid[NL == 3 ? T : 1], low[NL == 3 ? T : 1], total[T];
 #pragma unroll
     for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            acc[t][i] = 0.f;
-            if constexpr (NL == 3) mid[t][i] = low[t][i] = total[t][i] = 0.f;
+            acc[0][t][i] = acc[SETS - 1][t][i] = total[t][i] = 0.f;
+            if constexpr (NL == 3) mid[t][i] = low[t][i] = 0.f;
         }
     Stage cur;
     cur.b = sl * g.rows; cur.t0 = 0;
@@ -195,6 +199,24 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
         if (m < kBandTapMargin / 2 || m >= kBandTapMargin / 2 + g.F / 2)
 #pragma unroll
             for (int l = 0; l < 2 * NL; ++l) fs[l * TP + m] = 0u;
+    // The sums of the tiles t0 .. t0 + n - 1 added to totals of their own, so that no chain of additions gets long.
+    auto fold = [&](auto t0c, auto nc) {
+        constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
+#pragma unroll
+        for (int t = T0; t < T0 + N; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if constexpr (NL == 3) {
+                    total[t][i] += limb_sum(acc[0][t][i], mid[t][i], low[t][i]);
+                    mid[t][i] = low[t][i] = 0.f;
+                } else {
+                    total[t][i] += SETS == 2 ? acc[0][t][i] + acc[SETS - 1][t][i] : acc[0][t][i];
+                    acc[SETS - 1][t][i] = 0.f;
+                }
+                acc[0][t][i] = 0.f;
+            }
+    };
+    int since = 0;                                                       // bf16: the e since the totals were added to
     while (cur.b < b_end) {
         __syncthreads();                                                 // everyone is done with what LDS holds
         put(cur);
@@ -216,19 +238,6 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
             lo[t] = max(cur.e_lo, -2 * (m0 + 31) - before);
             hi[t] = m0 < g.blk0 + g.nblk ? min(cur.e_hi, nch - 1 - 2 * m0) : -(1 << 28);       // (a spare tile)
         }
-        // fp32: the sums of the tiles t0 .. t0 + n - 1 added to totals of their own, so that no chain of additions gets long
-        auto fold = [&](auto t0c, auto nc) {
-            if constexpr (NL == 3) {
-                constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
-#pragma unroll
-                for (int t = T0; t < T0 + N; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        total[t][i] += limb_sum(acc[t][i], mid[t][i], low[t][i]);
-                        acc[t][i] = mid[t][i] = low[t][i] = 0.f;
-                    }
-            }
-        };
         // e = ea .. eb (those of this wave: ks modulo 4) for the tiles T0 .. T0 + N - 1
         auto run = [&](auto t0c, auto nc, int ea, int eb) {
             constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
@@ -272,7 +281,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
                                 low[tt] = mfma32x32x16(a[1], bb[1], low[tt]);
                                 mid[tt] = mfma32x32x16(a[1], bb[0], mid[tt]);
                                 if (last) read_limb(a, 1);
-                                acc[tt] = mfma32x32x16(a[0], bb[0], acc[tt]);
+                                acc[0][tt] = mfma32x32x16(a[0], bb[0], acc[0][tt]);
                                 mid[tt] = mfma32x32x16(a[0], bb[1], mid[tt]);
                                 low[tt] = mfma32x32x16(a[0], bb[2], low[tt]);
                                 if (last) read_limb(a, 0);
@@ -299,7 +308,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
                             read_e(1 - u);
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int t = 0; t < N; ++t) acc[T0 + t] = mfma32x32x16(a[u][0], b[u][t][0], acc[T0 + t]);
+                            for (int t = 0; t < N; ++t) acc[u % SETS][T0 + t] = mfma32x32x16(a[u][0], b[u][t][0], acc[u % SETS][T0 + t]);
                             __builtin_amdgcn_sched_barrier(0);
                             e += KS;
                         }
@@ -317,17 +326,20 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
                 if constexpr (a > 0) eb = min(eb, lo[a - 1] - 1);
                 if constexpr (b + 1 < T) ea = max(ea, hi[b + 1] + 1);
                 constexpr std::integral_constant<int, b - a + 1> n{};
-                if constexpr (NL == 3) {
 #pragma unroll 1
-                    for (; ea <= eb; ea += g.chain) {
-                        run(ac, n, ea, min(eb, ea + g.chain - 1));
-                        fold(ac, n);
-                    }
-                } else {
-                    run(ac, n, ea, eb);
+                for (; ea <= eb; ea += g.run) {
+                    run(ac, n, ea, min(eb, ea + g.run - 1));
+                    if (NL == 3 || ea + g.run <= eb) fold(ac, n);
                 }
             });
         });
+        if constexpr (NL == 1) {
+            since += cur.e_hi - cur.e_lo + 1;
+            if (since >= g.chain || nxt.b >= b_end) {
+                since = 0;
+                fold(std::integral_constant<int, 0>{}, std::integral_constant<int, T>{});
+            }
+        }
         cur = nxt;
     }
 
@@ -348,10 +360,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
             for (int q = 0; q < 4; ++q) {
                 floatx4 v;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if constexpr (NL == 3) v[i] = total[t][4 * q + i];
-                    else v[i] = acc[t][4 * q + i];
-                }
+                for (int i = 0; i < 4; ++i) v[i] = total[t][4 * q + i];
                 *reinterpret_cast<floatx4 *>(wr + 8 * q) = v;
             }
             __syncthreads();

@@ -33,9 +33,10 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     g.blk0 = (int)(o0 >> 5);
     g.shift = (int)(o0 & 31);
     g.nblk = (int)((last - o0) >> 5) + 1;
-    // tiles per workgroup: as many as registers hold while there are three workgroups per compute unit (bf16 B8 C256 K = L = 8192,
-    // 512 workgroups of four tiles 140 us, 1024 of two 125, 2048 of one 152; fp32 there 1024 of two 618, 2048 of one 658)
-    p->T = NL == 3 ? 2 : 4;
+    // tiles per workgroup: two while there are three workgroups per compute unit (B8 C256 K = L = 8192: 1024 workgroups of two, 2048 of
+    // one: bf16 125 / 152 us, fp32 618 / 658.  Four, bf16, take the registers of a third workgroup: B16 C400 L8192 437 us with two, 470 with
+    // four, B8 C768 L4096 121 / 125, B8 C1024 L4096 centred 205 / 192)
+    p->T = 2;
     while (p->T > 1 && (p->T / 2 >= tiles || (long long)s.C * ((tiles + p->T - 1) / p->T) < 3 * kComputeUnits)) p->T /= 2;
     g.npiece = (tiles + p->T - 1) / p->T;
     if (g.npiece > 65535) return false;
@@ -65,15 +66,28 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     long long S = 1;
     if (us > 10.0) S = std::min((long long)(us / 4.0), std::max((slots + wgs - 1) / wgs, (long long)(most * slots / (p->work * s.C) + 0.5)));
     S = std::max(1ll, std::min(S, (long long)std::min(s.B, slices)));
-    // fp32: the e between two additions to the totals (four waves).  The fewer products a gradient sums, the shorter were the chains of
+    g.rows = (int)((s.B + S - 1) / S);
+    p->S = (s.B + g.rows - 1) / g.rows;
+    // The e between two additions to the totals (four waves).  An element sums N = rows x L / 64 products of the instruction and wave; chains of
+    // root N of them, and as many totals, are the shortest of two levels.
+    // bf16: chains end with a stage, a break costs 5 % (B1 C544 L6988 46.4 -> 48.8 us): only few batch entries, whose error was small on
+    // dw_band_kernel's virtual rows, have them inside one.  Error of the sums before they are rounded to bf16, dw_band_kernel -> here
+    // without totals -> with (normal data): B8 L8192 2.3e-7, 6.7e-7, 1.9e-7, B32 L4097 3.3e-7, 9.5e-7, 1.9e-7, B1 L5952 0.91e-7, 1.9e-7,
+    // 0.85e-7, B2 L1150 0.78e-7, 1.2e-7, 0.77e-7; what they cost: B8 C256 L8192 130 -> 131 us, B12 C355 L1832 43 -> 46, B2 C384 L1150 7.2 -> 8.4
+    const int sets = dwconv::toep_sets(NL, p->T);
+    int root = 4;
+    while ((long long)(root + 1) * (root + 1) <= (long long)g.rows * s.L / (64 * sets)) ++root;
+    g.chain = 4 * sets * root;
+    g.run = s.B < 5 ? 4 * sets * root : 1 << 24;
+    // fp32: the fewer products a gradient sums, the shorter were the chains of
     // the kernel this one replaced; with these its error against 64 bits is what it was: few rows, as long chains of products as of totals
     // (B1 L5664 1.5e-7 without a limit, 1.0e-7 with 32 and with 16, dw_band_kernel 1.0e-7); B9 L3000 1.26e-7, 1.05e-7 with 32 (1.07e-7);
     // B8 L8192 1.43e-7 without one (1.65e-7).  What they cost: B8 C256 L8192 K8192 641 us, 667 with 64, 715 with 32
-    int root = 4;
-    while ((root + 1) * (root + 1) <= s.L / 64) ++root;
-    g.chain = s.B < 5 ? 4 * root : (long long)s.B * s.L < 65536 ? 32 : 1 << 24;
-    g.rows = (int)((s.B + S - 1) / S);
-    p->S = (s.B + g.rows - 1) / g.rows;
+    if (NL == 3) {
+        int root_l = 4;
+        while ((root_l + 1) * (root_l + 1) <= s.L / 64) ++root_l;
+        g.run = s.B < 5 ? 4 * root_l : (long long)s.B * s.L < 65536 ? 32 : 1 << 24;
+    }
     p->work *= s.B;
     return true;
 }
@@ -93,13 +107,7 @@ static int launch_dw_toep(const void *x, const void *dy, float *part, void *dw_o
         }
         return launch_status();
     };
-    switch (p.T) {
-    case 1: return go(dwconv::dw_toep_kernel<E, 1>);
-    case 2: return go(dwconv::dw_toep_kernel<E, 2>);
-    default:
-        if constexpr (std::is_same<E, float>::value) return DWCONV_ERR_LAUNCH;       // (never planned)
-        else return go(dwconv::dw_toep_kernel<E, 4>);
-    }
+    return p.T == 1 ? go(dwconv::dw_toep_kernel<E, 1>) : go(dwconv::dw_toep_kernel<E, 2>);
 }
 
 int launch_dw_toep_f32(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
