@@ -81,6 +81,16 @@ struct Call {
     bool bad() const { return PyErr_Occurred() != nullptr; }
 };
 
+// Without the interpreter's lock while it lives: around allocation and launch, either of which may wait (for memory, for a place in the
+// queue, for code to be loaded) while other threads, or a host function the queue waits for, want the lock.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked &) = delete;
+    Unlocked &operator=(const Unlocked &) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 PyObject *decline() { Py_RETURN_NONE; }
 bool raised(int status)
 {
@@ -114,15 +124,24 @@ PyObject *corr(CorrFn fn, PyObject *const *a, Py_ssize_t n)
     if (!x || !w || w->scalar_type() != x->scalar_type() || w->size(0) != x->size(1) || !dims_of(*x, w->size(1), d)) return decline();
     const int code = dtype_code(*x);
     if (code < 0) return decline();
-    at::Tensor made;
-    const at::Tensor *y = &made;
-    if (a[3] == Py_None) {
-        made = at::empty_like(*x);
-    } else {
-        y = plain(a[3], 3, call.device);
-        if (!y || y->sizes() != x->sizes() || y->scalar_type() != x->scalar_type()) return decline();
+    const at::Tensor *out = nullptr;
+    if (a[3] != Py_None) {
+        out = plain(a[3], 3, call.device);
+        if (!out || out->sizes() != x->sizes() || out->scalar_type() != x->scalar_type()) return decline();
     }
-    if (raised(fn(x->const_data_ptr(), w->const_data_ptr(), y->mutable_data_ptr(), d.B, d.C, d.L, d.K, pad, code, call.stream))) return nullptr;
+    const void *px = x->const_data_ptr(), *pw = w->const_data_ptr();
+    void *py = out ? out->mutable_data_ptr() : nullptr;
+    at::Tensor made;
+    int status;
+    {
+        Unlocked unlocked;
+        if (!out) {
+            made = at::empty_like(*x);
+            py = made.mutable_data_ptr();
+        }
+        status = fn(px, pw, py, d.B, d.C, d.L, d.K, pad, code, call.stream);
+    }
+    if (raised(status)) return nullptr;
     if (a[3] == Py_None) return THPVariable_Wrap(std::move(made));
     Py_INCREF(a[3]);
     return a[3];
@@ -131,13 +150,9 @@ PyObject *corr(CorrFn fn, PyObject *const *a, Py_ssize_t n)
 PyObject *fwd(PyObject *, PyObject *const *a, Py_ssize_t n) { return corr(fn_fwd, a, n); }
 PyObject *bwd_input(PyObject *, PyObject *const *a, Py_ssize_t n) { return corr(fn_bwd_input, a, n); }
 
-// A [C, K] output: the caller's, or a new one in `made`.
-const at::Tensor *weight_out(PyObject *o, const at::Tensor &x, const Dims &d, long device, at::Tensor &made)
+// A [C, K] output of the caller's.
+const at::Tensor *weight_out(PyObject *o, const at::Tensor &x, const Dims &d, long device)
 {
-    if (o == Py_None) {
-        made = at::empty({d.C, d.K}, x.options());
-        return &made;
-    }
     const at::Tensor *dw = plain(o, 2, device);
     return dw && dw->size(0) == d.C && dw->size(1) == d.K && dw->scalar_type() == x.scalar_type() ? dw : nullptr;
 }
@@ -155,12 +170,22 @@ PyObject *bwd_weight(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (!x || !dy || !ws || dy->sizes() != x->sizes() || dy->scalar_type() != x->scalar_type() || !dims_of(*x, K, d)) return decline();
     const int code = dtype_code(*x);
     if (code < 0) return decline();
+    const at::Tensor *out = nullptr;
+    if (a[5] != Py_None && !(out = weight_out(a[5], *x, d, call.device))) return decline();
+    const void *px = x->const_data_ptr(), *pdy = dy->const_data_ptr();
+    void *pdw = out ? out->mutable_data_ptr() : nullptr, *pws = ws->mutable_data_ptr();
+    const size_t bytes = ws->nbytes();
     at::Tensor made;
-    const at::Tensor *dw = weight_out(a[5], *x, d, call.device, made);
-    if (!dw) return decline();
-    if (raised(fn_bwd_weight(x->const_data_ptr(), dy->const_data_ptr(), dw->mutable_data_ptr(), ws->mutable_data_ptr(), ws->nbytes(), d.B, d.C, d.L,
-                             d.K, pad, code, call.stream)))
-        return nullptr;
+    int status;
+    {
+        Unlocked unlocked;
+        if (!out) {
+            made = at::empty({d.C, d.K}, x->options());
+            pdw = made.mutable_data_ptr();
+        }
+        status = fn_bwd_weight(px, pdy, pdw, pws, bytes, d.B, d.C, d.L, d.K, pad, code, call.stream);
+    }
+    if (raised(status)) return nullptr;
     if (a[5] == Py_None) return THPVariable_Wrap(std::move(made));
     Py_INCREF(a[5]);
     return a[5];
@@ -183,19 +208,30 @@ PyObject *bwd(PyObject *, PyObject *const *a, Py_ssize_t n)
         return decline();
     const int code = dtype_code(*x);
     if (code < 0) return decline();
-    at::Tensor made_dx, made_dw;
-    const at::Tensor *dx = &made_dx;
-    if (a[5] == Py_None) {
-        made_dx = at::empty_like(*dy);
-    } else {
+    const at::Tensor *dx = nullptr, *dw = nullptr;
+    if (a[5] != Py_None) {
         dx = plain(a[5], 3, call.device);
         if (!dx || dx->sizes() != dy->sizes() || dx->scalar_type() != dy->scalar_type()) return decline();
     }
-    const at::Tensor *dw = weight_out(a[6], *x, d, call.device, made_dw);
-    if (!dw) return decline();
-    if (raised(fn_bwd(dy->const_data_ptr(), x->const_data_ptr(), w->const_data_ptr(), dx->mutable_data_ptr(), dw->mutable_data_ptr(),
-                      ws->mutable_data_ptr(), ws->nbytes(), d.B, d.C, d.L, d.K, pad, code, call.stream)))
-        return nullptr;
+    if (a[6] != Py_None && !(dw = weight_out(a[6], *x, d, call.device))) return decline();
+    const void *pdy = dy->const_data_ptr(), *px = x->const_data_ptr(), *pw = w->const_data_ptr();
+    void *pdx = dx ? dx->mutable_data_ptr() : nullptr, *pdw = dw ? dw->mutable_data_ptr() : nullptr, *pws = ws->mutable_data_ptr();
+    const size_t bytes = ws->nbytes();
+    at::Tensor made_dx, made_dw;
+    int status;
+    {
+        Unlocked unlocked;
+        if (!dx) {
+            made_dx = at::empty_like(*dy);
+            pdx = made_dx.mutable_data_ptr();
+        }
+        if (!dw) {
+            made_dw = at::empty({d.C, d.K}, x->options());
+            pdw = made_dw.mutable_data_ptr();
+        }
+        status = fn_bwd(pdy, px, pw, pdx, pdw, pws, bytes, d.B, d.C, d.L, d.K, pad, code, call.stream);
+    }
+    if (raised(status)) return nullptr;
     PyObject *out_dx = a[5], *out_dw = a[6];
     if (out_dx == Py_None) out_dx = THPVariable_Wrap(std::move(made_dx));
     else Py_INCREF(out_dx);

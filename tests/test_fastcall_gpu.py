@@ -1,5 +1,8 @@
 """The native form of the Python calls (csrc/dwconv_fastcall.cpp) against the general one of binding.py: the same bits for what it takes,
 and everything else left to binding.py - its errors, its conversions, wrappers of transforms, torch function and dispatch modes."""
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -129,3 +132,60 @@ def test_leaves_wrappers_of_transforms_to_the_general_form(general):
             form()
         kinds.append((type(e.value), str(e.value)))
     assert kinds[0] == kinds[1]
+
+
+def _all_calls(x, dy, w, ws, given):
+    out = (lambda t: torch.empty_like(t)) if given else (lambda t: None)
+    return (lambda: binding.dwconv_fwd(x, w, 4, out=out(x)), lambda: binding.dwconv_bwd_input(dy, w, 4, out=out(dy)),
+            lambda: binding.dwconv_bwd_weight(x, dy, 9, 4, workspace=ws, out=out(w)),
+            lambda: binding.dwconv_bwd(dy, x, w, 4, workspace=ws, out_dx=out(dy), out_dw=out(w)))
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_library_calls_run_without_the_interpreter_lock(given):
+    """In the place of the library's functions one that says whether its thread holds the lock: 1, a status that is raised, or 0."""
+    from paper_2604_25422_amd import _fastcall
+    x, dy, w, ws = _tensors()
+    held = ctypes.cast(ctypes.pythonapi.PyGILState_Check, ctypes.c_void_p).value
+    assert ctypes.PYFUNCTYPE(ctypes.c_int)(held)() == 1
+    _fastcall.setup(held, held, held, held, binding._current_device, binding._raw_stream, binding._check)
+    try:
+        for call in _all_calls(x, dy, w, ws, given):
+            call()
+        # ... and the lock is back when the status is raised
+        status = ctypes.cast(ctypes.pythonapi.Py_IsInitialized, ctypes.c_void_p).value
+        _fastcall.setup(status, status, status, status, binding._current_device, binding._raw_stream, binding._check)
+        for call in _all_calls(x, dy, w, ws, given):
+            with pytest.raises(binding.DwconvError):
+                call()
+    finally:
+        binding._load_fastcall(binding.lib())
+
+
+def test_calls_from_two_threads(general):
+    """Each thread on a stream of its own, with tensors and a workspace of its own."""
+    jobs, wrong = [], []
+    for i, dtype in enumerate((torch.float32, torch.bfloat16)):
+        x, dy, w, ws = _tensors(dtype, L=100 + 40 * i)
+        jobs.append((_all_calls(x, dy, w, ws, False), [general(call) for call in _all_calls(x, dy, w, ws, False)]))
+    torch.cuda.synchronize()
+
+    def work(calls, want):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(50):
+                    got = [call() for call in calls]
+                    torch.cuda.current_stream().synchronize()
+                    for a, b in zip(got, want):
+                        for s, t in zip(a, b) if isinstance(a, tuple) else ((a, b),):
+                            if not torch.equal(s, t):
+                                wrong.append("another result")
+        except Exception as e:
+            wrong.append(repr(e))
+
+    threads = [threading.Thread(target=work, args=job) for job in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not any(t.is_alive() for t in threads) and not wrong, wrong[:3]
