@@ -4,8 +4,11 @@ from __future__ import annotations
 import glob
 import importlib.util
 import os
+import re
 import subprocess
+import sys
 import sysconfig
+import warnings
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -35,7 +38,6 @@ def check_no_scratch(remarks: str, unit: str):
     """Parse -Rpass-analysis=kernel-resource-usage output; raise if a kernel with untracked prefetch uses scratch
     memory or accumulation registers (the compiler spills vector registers to either; a register it parks there
     between an untracked load and the manual wait would be saved before its data has arrived)."""
-    import re
     name = None
     bad = []
     for line in remarks.splitlines():
@@ -59,18 +61,49 @@ def dependencies():
     return sources() + [FASTCALL_SOURCE] + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [os.path.join(HERE, "..", "include", "dwconv.h")]
 
 
-def build_fastcall(verbose: bool = False, incremental: bool = False) -> str:
-    """The native form of the Python calls, against the installed PyTorch.  Host code only (g++)."""
-    if incremental and os.path.exists(FASTCALL_PATH) and os.path.getmtime(FASTCALL_PATH) > os.path.getmtime(FASTCALL_SOURCE):
+def fastcall_mark() -> str | None:
+    """What the native form of the calls is built for: it reads the objects of one PyTorch and one Python.  None: no PyTorch."""
+    spec = importlib.util.find_spec("torch")
+    if spec is None or not spec.submodule_search_locations:
+        return None
+    try:
+        with open(os.path.join(spec.submodule_search_locations[0], "version.py")) as f:
+            text = f.read()
+    except OSError:
+        return None
+    version, git = (re.search(rf"^{name}\b.*?=\s*['\"](.*?)['\"]", text, re.M) for name in ("__version__", "git_version"))
+    return f"torch {version.group(1) if version else '?'} {git.group(1) if git else '?'}, Python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
+def _fastcall_is_current() -> bool:
+    if not os.path.exists(FASTCALL_PATH) or os.path.getmtime(FASTCALL_PATH) <= os.path.getmtime(FASTCALL_SOURCE):
+        return False
+    mark = fastcall_mark()
+    with open(FASTCALL_PATH, "rb") as f:
+        return mark is not None and mark.encode() + b"\0" in f.read()
+
+
+def build_fastcall(verbose: bool = False, incremental: bool = False) -> str | None:
+    """The native form of the Python calls, against the installed PyTorch.  Host code only (g++).  The library does without it
+    (binding.py), so what it needs and does not find - PyTorch, its headers or Python's, a compiler - is a warning: None."""
+    if incremental and _fastcall_is_current():
         return FASTCALL_PATH
-    torch_dir = importlib.util.find_spec("torch").submodule_search_locations[0]
-    include, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D_GLIBCXX_USE_CXX11_ABI=1",
-           "-I" + sysconfig.get_paths()["include"], "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
-           FASTCALL_SOURCE, "-o", FASTCALL_PATH, "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    if os.path.exists(FASTCALL_PATH):
+        os.remove(FASTCALL_PATH)                             # (one that is not current is worse than none)
+    try:
+        import torch
+        torch_dir = os.path.dirname(torch.__file__)
+        include, lib = os.path.join(torch_dir, "include"), os.path.join(torch_dir, "lib")
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", f'-DDWCONV_BUILT_FOR="{fastcall_mark()}"',
+               "-I" + sysconfig.get_paths()["include"], "-isystem", include, "-isystem", os.path.join(include, "torch", "csrc", "api", "include"),
+               FASTCALL_SOURCE, "-o", FASTCALL_PATH, "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        warnings.warn(f"the native form of the Python calls was not built ({e}): small calls take longer to launch", RuntimeWarning, stacklevel=2)
+        return None
     return FASTCALL_PATH
 
 
@@ -115,21 +148,21 @@ def build(verbose: bool = False, extra_flags=(), jobs: int | None = None, increm
     with ThreadPoolExecutor(max_workers=jobs) as pool:
         fastcall = pool.submit(build_fastcall, verbose, incremental)
         list(pool.map(compile_one, zip(srcs, objs)))
-        fastcall.result()
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH] + objs
     if verbose:
         print(" ".join(link), flush=True)
     subprocess.run(link, check=True)
+    fastcall.result()
     return LIB_PATH
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH) or not os.path.exists(FASTCALL_PATH):
+    """Whether something is missing or older than its sources.  (The native form of the calls may be missing: it was not to be had.)"""
+    if not os.path.exists(LIB_PATH):
         return True
-    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(FASTCALL_PATH))
-    return any(os.path.getmtime(p) > t for p in dependencies())
+    t = os.path.getmtime(LIB_PATH)
+    return any(os.path.getmtime(p) > t for p in dependencies()) or (os.path.exists(FASTCALL_PATH) and not _fastcall_is_current())
 
 
 if __name__ == "__main__":
-    import sys
     print(build(verbose=True, incremental="--incremental" in sys.argv))

@@ -40,6 +40,8 @@ def _load_fastcall(l):
     global _fast
     try:
         fast = importlib.import_module(__package__ + "._fastcall")
+        if fast.built_for != _build.fastcall_mark():
+            raise ImportError(f"built for {fast.built_for}, this is {_build.fastcall_mark()}")
     except ImportError as e:
         warnings.warn(f"the native form of the calls is not there ({e}): small calls take longer to launch; build it with "
                       "python -m paper_2604_25422_amd._build", RuntimeWarning, stacklevel=3)

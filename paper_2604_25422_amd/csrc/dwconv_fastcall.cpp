@@ -7,6 +7,8 @@
 // library takes them, on the current device (subclasses, wrappers of transforms, active torch function or dispatch modes, traces,
 // arguments that are not exact ints, mismatched shapes) is left to binding.py, whose checks and messages are the only ones.
 // A status other than 0 is raised by binding.py's own exception.
+//
+// Built for one PyTorch and one Python (DWCONV_BUILT_FOR names them): it reads their objects by its headers' layouts.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -280,4 +282,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+// (binding.py compares `built_for` with the PyTorch and the Python that are there before it calls anything)
+PyMODINIT_FUNC PyInit__fastcall()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", DWCONV_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -237,3 +237,37 @@ def test_native_calls_decline_what_is_not_a_device_tensor(lib):
                  lambda: _fastcall.bwd(x, x, w, 2, ws, None, None), lambda: _fastcall.fwd(None, w, 2, None), lambda: _fastcall.fwd(x, w),
                  lambda: _fastcall.bwd(x, x, w, 2.0, ws, None, None), lambda: _fastcall.bwd_weight(x, x, 1 << 40, 2, ws, None)):
         assert call() is None
+
+
+def test_build_does_without_the_native_calls(tmp_path, monkeypatch):
+    """What the native form of the Python calls needs (a host compiler, PyTorch's and Python's headers) may be missing: the library is built all
+    the same, with a warning, and is not stale for ever."""
+    from paper_2604_25422_amd import _build
+    hipcc = tmp_path / "hipcc"                               # (stands for the compiler: leaves the file it is asked for)
+    hipcc.write_text('#!/bin/sh\nwhile [ $# -gt 1 ]; do [ "$1" = -o ] && : > "$2"; shift; done\n')
+    hipcc.chmod(0o755)
+    fastcall = tmp_path / "_fastcall.so"
+    fastcall.write_text("of another time")
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    monkeypatch.setenv("CXX", "/bin/false")
+    monkeypatch.setattr(_build, "sources", lambda: [])
+    monkeypatch.setattr(_build, "OBJ_DIR", str(tmp_path))
+    monkeypatch.setattr(_build, "LIB_PATH", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(_build, "FASTCALL_PATH", str(fastcall))
+    with pytest.warns(RuntimeWarning, match="was not built"):
+        assert _build.build() == str(tmp_path / "lib.so")
+    assert (tmp_path / "lib.so").exists() and not fastcall.exists() and not _build.is_stale()
+
+
+def test_native_calls_of_another_pytorch_are_not_used(lib, tmp_path, monkeypatch):
+    from paper_2604_25422_amd import _build, _fastcall, binding
+    import torch
+    assert _fastcall.built_for == _build.fastcall_mark() and torch.__version__ in _fastcall.built_for and torch.version.git_version in _fastcall.built_for
+    assert not _build.is_stale()
+    monkeypatch.setattr(binding, "_fast", binding._Declines)
+    monkeypatch.setattr(_build, "fastcall_mark", lambda: "torch 0.1 of another layout, Python 3.10")
+    with pytest.warns(RuntimeWarning, match="of another layout"):
+        binding._load_fastcall(lib)
+    assert binding._fast is binding._Declines
+    # ... and are built again
+    assert _build.is_stale() and not _build._fastcall_is_current()
