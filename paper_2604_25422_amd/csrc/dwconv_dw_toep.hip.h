@@ -31,7 +31,7 @@ struct DwToepGeom {
     int npiece;         // pieces of T tiles
     int F;              // positions of dY per chunk (a multiple of 32)
     int rows;           // batch entries per slice
-    int run;            // the e (of all four waves) between two additions to the totals at most, a multiple of 4
+    int run;            // the e (of all four waves) between two additions to the totals (fp32: up to half as many more), a multiple of 4
     int chain;          // bf16: the least e between two, at the ends of stages (fp32: after each run)
     int tap_off;        // byte offset of the taps in LDS
 };
@@ -66,6 +66,43 @@ __device__ __forceinline__ void shift_up_raw8(Raw8H &r, int sh)
 #pragma unroll
     for (int i = 3; i >= 0; --i) r.v[i] = (sh & 1) ? __builtin_amdgcn_alignbit(r.v[i], i > 0 ? r.v[i - 1] : 0u, 16) : r.v[i];
 }
+// A stage: positions t0 .. t0 + F - 1 of dY of one batch entry and the blocks of X that the piece's lags reach from them.
+struct DwToepStage {
+    int b, t0;
+    int e_lo, e_hi;                 // the e that hold a position of the chunk and meet the row from some lag of the piece
+    int wb0, n8;                    // first window block, granules of eight positions
+    int inside;                     // all of the window inside the row
+};
+// Block m + e / 2, half e % 2, of the window is positions 32 m + 16 e + shift .. + 15: inside the row from some k for 2 m + e in
+// [-before, nch).
+__host__ __device__ __forceinline__ int dw_toep_before(const DwToepGeom &g) { return (15 + g.shift) >> 4; }
+__host__ __device__ __forceinline__ int dw_toep_chunks(const DwToepGeom &g) { return ((g.L - 1 - g.shift) >> 4) + 1; }
+// Its window, from t0, for the PB blocks of lags from p0 on; false: no position of the chunk meets the row.
+__host__ __device__ __forceinline__ bool dw_toep_set_window(const DwToepGeom &g, int p0, int PB, DwToepStage &s)
+{
+    const int before = dw_toep_before(g), nch = dw_toep_chunks(g);
+    const int first = s.t0 >> 4, e0 = -2 * (p0 + PB - 1) - before, t1 = s.t0 + g.F < g.L ? s.t0 + g.F : g.L, last = (t1 + 30) >> 4, e1 = nch - 1 - 2 * p0;
+    s.e_lo = first > e0 ? first : e0;
+    s.e_hi = last < e1 ? last : e1;
+    if (s.e_lo > s.e_hi) return false;
+    const int wb_min = -31 - ((before + 1) >> 1), wb_max = ((nch - 1) >> 1) + 31;        // blocks that any tile reads
+    const int w0 = p0 + (s.e_lo >> 1), w1 = p0 + PB - 1 + (s.e_hi >> 1);
+    s.wb0 = w0 > wb_min ? w0 : wb_min;
+    s.n8 = 4 * ((w1 < wb_max ? w1 : wb_max) - s.wb0 + 1);
+    s.inside = s.wb0 >= 0 && 32 * s.wb0 + g.shift + 8 * s.n8 <= g.L;
+    return true;
+}
+// The e of a stage that meet the row from the tile that starts with block m0 of lags (behind the last block: a spare one).
+__host__ __device__ __forceinline__ void dw_toep_tile_range(const DwToepGeom &g, const DwToepStage &s, int m0, int &lo, int &hi)
+{
+    const int e0 = -2 * (m0 + 31) - dw_toep_before(g), e1 = dw_toep_chunks(g) - 1 - 2 * m0;
+    lo = s.e_lo > e0 ? s.e_lo : e0;
+    hi = s.e_hi < e1 ? s.e_hi : e1;
+    if (m0 >= g.blk0 + g.nblk) {
+        lo = kNoWorkLo;
+        hi = kNoWorkHi;
+    }
+}
 // Sets of accumulators: bf16, one tile, two, for even and odd e, which halves the chains (of two tiles: B8 C256 K = L = 8192 133 -> 143 us)
 constexpr int toep_sets(int NL, int T) { return NL == 1 && T == 1 ? 2 : 1; }
 constexpr int toep_waves(int NL, int T) { return NL == 3 && T == 2 ? 2 : 3; }
@@ -89,34 +126,19 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
         else piece = zero > both ? g.npiece - 1 - k : k;
     }
     const int p0 = g.blk0 + piece * PB;
-    // block m + e / 2, half e % 2, of the window is positions 32 m + 16 e + shift .. + 15: inside the row from some k for
-    // 2 m + e in [-before, nch)
-    const int before = (15 + g.shift) >> 4, nch = ((g.L - 1 - g.shift) >> 4) + 1;
-    const int wb_min = -31 - ((before + 1) >> 1), wb_max = ((nch - 1) >> 1) + 31;        // blocks that any tile reads
     const int TP = band_tap_dwords(g.F);
     unsigned char *xs = toep_smem;
     unsigned *fs = reinterpret_cast<unsigned *>(toep_smem + g.tap_off);          // limb l, copy p at (2 l + p) TP
     const size_t CL = (size_t)g.C * (size_t)g.L;
     const int b_end = min(g.B, (sl + 1) * g.rows);
 
-    // A stage: positions t0 .. t0 + F - 1 of dY of one batch entry and the blocks of X that the piece's lags reach from them.
-    struct Stage {
-        int b, t0;
-        int e_lo, e_hi;                 // the e that hold a position of the chunk and meet the row from some lag of the piece
-        int wb0, n8;                    // first window block, granules of eight positions
-        int inside;                     // all of the window inside the row
-    };
+    typedef DwToepStage Stage;
     auto settle = [&](Stage &s) {       // the first stage from s on that has work; b >= b_end: none
         for (;; s.t0 += g.F) {
             if (s.t0 >= g.L) { s.t0 = 0; ++s.b; }
             if (s.b >= b_end) return;
-            s.e_lo = max(s.t0 >> 4, -2 * (p0 + PB - 1) - before);
-            s.e_hi = min((min(s.t0 + g.F, g.L) + 30) >> 4, nch - 1 - 2 * p0);
-            if (s.e_lo <= s.e_hi) break;
+            if (dw_toep_set_window(g, p0, PB, s)) return;
         }
-        s.wb0 = max(p0 + (s.e_lo >> 1), wb_min);
-        s.n8 = 4 * (min(p0 + PB - 1 + (s.e_hi >> 1), wb_max) - s.wb0 + 1);
-        s.inside = s.wb0 >= 0 && 32 * s.wb0 + g.shift + 8 * s.n8 <= g.L;
     };
     decltype(load_raw8(x)) px[kToepX], py[kToepY];
     E prev[kToepY];                                                      // the element in front of each granule of dY
@@ -234,9 +256,8 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
         int lo[T], hi[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            const int m0 = p0 + 32 * t;
-            lo[t] = max(cur.e_lo, -2 * (m0 + 31) - before);
-            hi[t] = m0 < g.blk0 + g.nblk ? min(cur.e_hi, nch - 1 - 2 * m0) : -(1 << 28);       // (a spare tile)
+            dw_toep_tile_range(g, cur, p0 + 32 * t, lo[t], hi[t]);
+            asm volatile("" : "+s"(lo[t]), "+s"(hi[t]));                // (hidden, as in corr_band_kernel)
         }
         // e = ea .. eb (those of this wave: ks modulo 4) for the tiles T0 .. T0 + N - 1
         auto run = [&](auto t0c, auto nc, int ea, int eb) {
@@ -316,22 +337,23 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
                 }
             }
         };
-        // The tiles lie in increasing order of their lags, so lo and hi fall with t: those active at an e are the tiles a .. b
-        // with e in [lo[a], lo[a - 1]) and (hi[b + 1], hi[b]].
-        static_for<0, T>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            static_for<a, T>([&](auto bc) {
-                constexpr int b = decltype(bc)::value;
-                int ea = lo[a], eb = hi[b];
-                if constexpr (a > 0) eb = min(eb, lo[a - 1] - 1);
-                if constexpr (b + 1 < T) ea = max(ea, hi[b + 1] + 1);
-                constexpr std::integral_constant<int, b - a + 1> n{};
+        // (the tiles lie in increasing order of their lags, so lo and hi fall with t)
+        active_runs(lo, hi, [&](auto ac, auto nc, int ea, int eb) {
+            if constexpr (NL == 3) {
+#pragma unroll 1
+                while (ea <= eb) {
+                    const int to = ea + g.run + (g.run >> 1) > eb ? eb : ea + g.run - 1;      // (no short rest)
+                    run(ac, nc, ea, to);
+                    fold(ac, nc);
+                    ea = to + 1;
+                }
+            } else {
 #pragma unroll 1
                 for (; ea <= eb; ea += g.run) {
-                    run(ac, n, ea, min(eb, ea + g.run - 1));
-                    if (NL == 3 || ea + g.run <= eb) fold(ac, n);
+                    run(ac, nc, ea, min(eb, ea + g.run - 1));
+                    if (ea + g.run <= eb) fold(ac, nc);
                 }
-            });
+            }
         });
         if constexpr (NL == 1) {
             since += cur.e_hi - cur.e_lo + 1;

@@ -156,6 +156,63 @@ static bool check_corr_band(const Shape &s)
     return true;
 }
 
+// A piece and a chunk of dw_toep_kernel: the blocks of X and the taps every wave reads.
+template <int T>
+static bool dw_toep_stage(const Shape &s, const DwToepPlan &p, int p0, const dwconv::DwToepStage &st)
+{
+    const dwconv::DwToepGeom &g = p.g;
+    const int NL = s.dtype == DWCONV_F32 ? 3 : 1, BS = dwconv::band_block_bytes(NL), KS = dwconv::kBandWaves, blocks = st.n8 / 4, TP = dwconv::band_tap_dwords(g.F);
+    if (blocks * BS > g.tap_off) return fault("dw_toep", s, "bytes of a window", blocks * BS, 0, g.tap_off);
+    if (st.n8 > dwconv::kToepX * dwconv::kToepThreads) return fault("dw_toep", s, "granules of a window", st.n8, 0, dwconv::kToepX * dwconv::kToepThreads);
+    if (g.F > 8 * dwconv::kToepY * dwconv::kToepThreads) return fault("dw_toep", s, "positions of a chunk", g.F, 0, 8 * dwconv::kToepY * dwconv::kToepThreads);
+    int formed[T] = {}, due[T] = {};
+    bool ok = true;
+    for (int ks = 0; ks < KS; ++ks) {
+        int lo[T], hi[T];
+        for (int t = 0; t < T; ++t) {
+            dwconv::dw_toep_tile_range(g, st, p0 + 32 * t, lo[t], hi[t]);
+            due[t] = std::max(0, hi[t] - lo[t] + 1);
+        }
+        dwconv::active_runs(lo, hi, [&](auto t0c, auto nc, int ea, int eb) {
+            constexpr int T0 = decltype(t0c)::value, N = decltype(nc)::value;
+            ea += (st.e_lo + ks - ea) & (KS - 1);
+            for (int e = ea; e <= eb && ok; e += KS) {
+                const int a = 16 * e - st.t0 + dwconv::kBandTapMargin, d0 = (a - 31 + 1) >> 1, d1 = ((a + 8 + 1) >> 1) + 3;
+                if (d0 < 0 || d1 >= TP) ok = fault("dw_toep", s, "dwords of taps from", d0, 0, TP - 1 - (d1 - d0));
+                for (int t = T0; t < T0 + N && ok; ++t) {
+                    const int b0 = p0 + 32 * t - st.wb0 + (e >> 1), b1 = b0 + 31;
+                    if (b0 < 0 || b1 >= blocks) ok = fault("dw_toep", s, "block of the window", b0 < 0 ? b0 : b1, 0, blocks - 1);
+                    else ++formed[t];
+                }
+            }
+        });
+    }
+    for (int t = 0; t < T && ok; ++t)
+        if (formed[t] != due[t]) ok = fault("dw_toep", s, "products", formed[t], due[t], due[t]);
+    return ok;
+}
+
+static bool check_dw_toep(const Shape &s)
+{
+    DwToepPlan p;
+    if (!plan_dw_toep(s, 1 << 20, &p)) return true;
+    ++planned;
+    const dwconv::DwToepGeom &g = p.g;
+    // fp32: chains of about the root of the products an element sums on a wave
+    const double root = std::max(4.0, std::sqrt((double)g.rows * s.L / 64));
+    if (s.dtype == DWCONV_F32 && (g.run > 4 * root || g.run < 4 * (root - 1) || (g.run & 3) != 0))
+        return fault("dw_toep", s, "e of a chain", g.run, (long long)(4 * (root - 1)), (long long)(4 * root));
+    for (int piece = 0; piece < g.npiece; ++piece)
+        for (int t0 = 0; t0 < s.L; t0 += g.F) {
+            dwconv::DwToepStage st{};
+            st.t0 = t0;
+            const int p0 = g.blk0 + piece * 32 * p.T;
+            if (!dwconv::dw_toep_set_window(g, p0, 32 * p.T, st)) continue;
+            if (!(p.T == 1 ? dw_toep_stage<1>(s, p, p0, st) : dw_toep_stage<2>(s, p, p0, st))) return false;
+        }
+    return true;
+}
+
 // Shapes over the range of the kernels: causal, nearly causal, centred, anti-causal and any other pad, few and many batch entries.
 static Shape draw(std::mt19937 &rng)
 {
@@ -185,6 +242,7 @@ int main(int argc, char **argv)
     bool (*check)(const Shape &) = nullptr;
     if (!strcmp(argv[1], "dw_band")) check = check_dw_band;
     if (!strcmp(argv[1], "corr_band")) check = check_corr_band;
+    if (!strcmp(argv[1], "dw_toep")) check = check_dw_toep;
     if (!check) return 2;
     int bad = 0;
     if (!strcmp(argv[2], "-")) {

@@ -46,3 +46,13 @@ CORR_BAND = [(1, 600, 3040, 600, 480, 0), (1, 1024, 3000, 600, 500, 0), (119, 47
 def test_corr_band(reads):
     assert run(reads, "corr_band", "-", shapes=CORR_BAND) == 2 * len(CORR_BAND)
     assert run(reads, "corr_band", 1, 3000) > 4000
+
+
+# one tile of lags per workgroup and two, lags that end in a spare tile, several chunks; chains of additions on both sides of B L = 65536
+DW_TOEP = [(8, 256, 8192, 8192, 8191, 0), (7, 256, 8192, 8192, 8191, 0), (5, 256, 8192, 8192, 8191, 0), (32, 256, 4097, 4097, 4096, 1), (1, 300, 2049, 2050, 2049, 0),
+           (1, 2, 8, 20, 9, 1), (9, 32, 3000, 3000, 2999, 0), (17, 736, 889, 889, 444, 0), (1, 2, 40000, 70000, 39000, 0)]
+
+
+def test_dw_toep(reads):
+    assert run(reads, "dw_toep", "-", shapes=DW_TOEP) == len(DW_TOEP)
+    assert run(reads, "dw_toep", 1, 3000) > 2000
