@@ -194,6 +194,24 @@ static bool dw_takes_toep(const Shape &s, const DwPlan &p)
     const double groups = (double)(((long long)s.B * nseg + 7) / 8);
     // (two blocks at a time: half a product lost per offset of 32 at the end of the row, and the offsets at both ends of the filter)
     const double band = groups * (8.0 * pairs / nseg / (1024 * 16) + 0.75 * ((lo + hi + 1) / 32 + 2));
+    // Calls that leave compute units idle (at most two workgroups for each) are a chain on a workgroup: here of its batch entries one after the
+    // other, 1.2 us each and what they multiply, there of groups of eight at once.  Both as measured over 420 calls of up to 45 us
+    // (error 7 % here, 9 % there): fp32 B4 C77 L1023 K1023 11.0 / 19.1, B5 C27 L937 K937 11.8 / 18.0, B2 C69 L946 K946 9.7 / 11.6, but B1 C71 L843 K256
+    // 8.8 / 6.8; bf16 B6 C48 L753 K753 7.2 / 11.7, B4 C30 L2496 K717 9.9 / 15.2, B5 C220 L818 K818 8.4 / 10.3, but B5 C100 L1342 K1342 15.8 / 12.3.
+    // (Not with fewer than sixteen channels: no layer's, and it is with them that the tests reach the edges of dw_toep_kernel.)
+    const double wgs = (double)s.C * p.tp.g.npiece * p.tp.S;
+    if (s.C >= 16 && wgs <= 2 * kComputeUnits) {
+        const bool f32 = s.dtype == DWCONV_F32;
+        const double rows = p.tp.g.rows, chunks = (s.L + p.tp.g.F - 1) / p.tp.g.F, products = s.L / 16.0 + 2;
+        const double over = wgs > kComputeUnits ? wgs / kComputeUnits - 1 : 0.0;            // (second workgroups of compute units)
+        const double here = f32 ? 3.2 + (p.tp.S > 1 ? 1.6 : 0.0) + rows * (1.2 * chunks + (0.051 + 0.028 * over) * products)
+                                : 3.0 + (p.tp.S > 1 ? 1.9 : 0.0) + rows * (0.84 * chunks + (0.014 + 0.006 * over) * products);
+        const double stages = (p.bp.g.stages + p.bp.S - 1) / p.bp.S, rounds = (double)s.C * p.bp.g.nwin * p.bp.S / (2 * kComputeUnits);
+        const double pairs = stages * p.bp.g.S32 * p.bp.ND * std::max(1.0, rounds);
+        const double there = f32 ? 6.6 + (p.bp.S > 1 ? 0.9 : 0.0) + 0.4 * (stages - 1) + 0.056 * pairs + 5.9 * rounds
+                                 : 6.1 + (p.bp.S > 1 ? 1.2 : 0.0) + 2.6 * (stages - 1) + 0.011 * pairs + 3.4 * rounds;
+        if (here > there) return false;
+    }
     const double most = s.dtype == DWCONV_F32 ? (nseg > 2 ? 2.65 : nseg > 1 ? 1.85 : 1.33) : (nseg > 1 ? 2.6 : s.L >= 1000 ? 1.54 : 1.42);
     return p.tp.work <= most * band;
 }

@@ -374,6 +374,18 @@ def test_dw_toep_takes_long_filters(B, C, L, K, p, dtype, offset):
     assert "dw_toep_kernel" in names[0] and len(names) <= 2, names
 
 
+# ... but not in calls that leave the chip idle, where its chain of batch entries is the longer one (us, dw_band_kernel / dw_toep_kernel: 11.0 / 19.1,
+# 11.8 / 18.0, 7.2 / 11.7, 9.9 / 15.2), and again where it is not (26.0 / 13.5, 15.8 / 12.3)
+@pytest.mark.parametrize("B,C,L,K,p,dtype,kernel", [(4, 77, 1023, 1023, 1022, "f32", "dw_band"), (5, 27, 937, 937, 561, "f32", "dw_band"),
+                                                    (6, 48, 753, 753, 376, "bf16", "dw_band"), (4, 30, 2496, 717, 0, "bf16", "dw_band"),
+                                                    (2, 359, 815, 815, 814, "f32", "dw_toep"), (5, 100, 1342, 1342, 1292, "bf16", "dw_toep")])
+def test_small_calls_of_long_filters(oracle_mod, B, C, L, K, p, dtype, kernel):
+    run_exact(oracle_mod, B, C, L, K, p, dtype, seed=53 + B + 3 * C + 5 * L, fused=False)
+    x = torch.zeros(B, C, L, device="cuda", dtype=torch.float32 if dtype == "f32" else torch.bfloat16)
+    names = _kernels(lambda: binding.dwconv_bwd_weight(x, x, K, p))
+    assert kernel + "_kernel" in names[0], names
+
+
 @pytest.mark.parametrize("B,L,K,p,dtype", [(47300, 364, 19, 9, "f32"), (16000, 512, 64, 63, "f32"), (35000, 364, 2, 0, "f32"),
                                            (46000, 304, 7, 3, "bf16"), (42000, 320, 66, 10, "bf16")])
 def test_band_kernel_takes_short_filters_of_huge_batches(oracle_mod, B, L, K, p, dtype):
