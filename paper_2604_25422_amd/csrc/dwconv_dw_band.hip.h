@@ -38,7 +38,6 @@ struct DwBandGeom {
                         // divisors with the reciprocals they need: a division by a number of run time is some 200 cycles, and
                         // a small call is a few thousand)
     int nwin;           // window w: offsets from dmin + w (ndw - 1)
-    int win0;           // the launch's first (in its order)
     int nseg, Lv;       // virtual rows per row and their length (a multiple of 64; nseg == 1: the row)
     unsigned seg_magic; // floor(2^16 / nseg) + 1: v / nseg == v * seg_magic >> 16 for the at most eight virtual rows there are
     int rg_log;         // log2 of the groups of eight virtual rows per stage (RGN)
@@ -182,7 +181,7 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = blockIdx.x, sl = (int)blockIdx.y;
-    const int wz = g.win0 + (int)blockIdx.z, win = g.rev ? g.nwin - 1 - wz : wz;
+    const int win = g.rev ? g.nwin - 1 - (int)blockIdx.z : (int)blockIdx.z;
     const int NB32 = (g.L + 31) >> 5;
     constexpr int KS = 4 / DG;
     const int dg = wave & (DG - 1), ks = wave / DG;

@@ -29,6 +29,7 @@ struct DwToepGeom {
     int blk0, nblk;     // 32-blocks of lags, block m being lags 32 m + shift ..: the first (may be negative), how many there are (all
     int shift;          // lags inside (-L, L) that have a tap are in them, and possibly more in front)
     int npiece;         // pieces of T tiles
+    int piece0;         // the launch's first (in its order)
     int F;              // positions of dY per chunk (a multiple of 32)
     int rows;           // batch entries per slice
     int run;            // the e (of all four waves) between two additions to the totals (fp32: up to half as many more), a multiple of 4
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
     int piece;
     {
         // rank z counts from the piece that holds lag 0 outwards, on both sides while there are two
-        const int zero = min(max(-g.blk0 / PB, 0), g.npiece - 1), k = (int)blockIdx.z;
+        const int zero = min(max(-g.blk0 / PB, 0), g.npiece - 1), k = g.piece0 + (int)blockIdx.z;
         const int both = min(zero, g.npiece - 1 - zero);
         if (k <= 2 * both) piece = (k & 1) ? zero - (k + 1) / 2 : zero + k / 2;
         else piece = zero > both ? g.npiece - 1 - k : k;
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(kToepThreads, toep_waves(Limbs<E>::N, T)) void dw_t
         }
         // taps whose lag lies outside (-L, L), and the slices of the workspace beyond those of this launch: zeros
         const int j_lo = 32 * g.blk0 + g.shift + g.pad, j_hi = j_lo + 32 * g.nblk;
-        if (blockIdx.z == 0) {
+        if (g.piece0 + (int)blockIdx.z == 0) {
             for (int j = tid; j < g.K; j += THREADS)
                 if (j < j_lo || j >= j_hi) {
                     if (dw_out) st_elem(dw_out + row + j, 0.f);

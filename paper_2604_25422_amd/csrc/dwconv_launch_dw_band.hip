@@ -9,17 +9,14 @@ static int launch_dw_band(const void *x, const void *dy, float *part, void *dw_o
 {
     auto go = [&](auto kernel) -> int {
         if (p.lds > 64 * 1024 && !allow_large_lds(kernel)) return DWCONV_ERR_LAUNCH;
-        // (a grid holds fewer than 2^32 threads along channels and 65536 windows: what is beyond in launches of their own)
-        dwconv::DwBandGeom g = p.g;
-        for (g.win0 = 0; g.win0 < p.g.nwin; g.win0 += 65535) {
-            const int nz = p.g.nwin - g.win0 < 65535 ? p.g.nwin - g.win0 : 65535;
-            for (int c0 = 0; c0 < g.C; c0 += kMaxGridChannels) {
-                const int n = g.C - c0 < kMaxGridChannels ? g.C - c0 : kMaxGridChannels;
-                const size_t row = (size_t)c0 * (size_t)g.L, taps = (size_t)c0 * (size_t)g.K;
-                hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.S, (unsigned)nz), dim3(dwconv::kDwBandThreads), p.lds, st,
-                                   static_cast<const E *>(x) + row, static_cast<const E *>(dy) + row, part + taps,
-                                   dw_out ? static_cast<E *>(dw_out) + taps : nullptr, g, slices);
-            }
+        if (p.g.nwin > 65535) return DWCONV_ERR_LAUNCH;                  // (filters of 23 million taps: dw_toep_kernel's)
+        // (a grid dimension holds fewer than 2^32 threads: further channels in launches of their own)
+        for (int c0 = 0; c0 < p.g.C; c0 += kMaxGridChannels) {
+            const int n = p.g.C - c0 < kMaxGridChannels ? p.g.C - c0 : kMaxGridChannels;
+            const size_t row = (size_t)c0 * (size_t)p.g.L, taps = (size_t)c0 * (size_t)p.g.K;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.S, (unsigned)p.g.nwin), dim3(dwconv::kDwBandThreads), p.lds, st,
+                               static_cast<const E *>(x) + row, static_cast<const E *>(dy) + row, part + taps,
+                               dw_out ? static_cast<E *>(dw_out) + taps : nullptr, p.g, slices);
         }
         return launch_status();
     };

@@ -5,18 +5,25 @@
 
 namespace dwhost {
 
+// Pieces of lags per launch: 16384 fill the chip as well as 65535, and a test reaches the second launch (23 million lags).
+constexpr int kMaxGridPieces = 16384;
+
 template <typename E>
 static int launch_dw_toep(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
 {
     auto go = [&](auto kernel) -> int {
         if (p.lds > 64 * 1024 && !allow_large_lds(kernel)) return DWCONV_ERR_LAUNCH;
-        // (a grid dimension holds fewer than 2^32 threads: further channels in launches of their own)
-        for (int c0 = 0; c0 < p.g.C; c0 += kMaxGridChannels) {
-            const int n = p.g.C - c0 < kMaxGridChannels ? p.g.C - c0 : kMaxGridChannels;
-            const size_t row = (size_t)c0 * (size_t)p.g.L, taps = (size_t)c0 * (size_t)p.g.K;
-            hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.S, (unsigned)p.g.npiece), dim3(dwconv::kToepThreads), p.lds, st,
-                               static_cast<const E *>(x) + row, static_cast<const E *>(dy) + row, part + taps,
-                               dw_out ? static_cast<E *>(dw_out) + taps : nullptr, p.g, slices);
+        // (a grid holds fewer than 2^32 threads along channels and 65536 pieces: what is beyond in launches of their own)
+        dwconv::DwToepGeom g = p.g;
+        for (g.piece0 = 0; g.piece0 < g.npiece; g.piece0 += kMaxGridPieces) {
+            const int nz = g.npiece - g.piece0 < kMaxGridPieces ? g.npiece - g.piece0 : kMaxGridPieces;
+            for (int c0 = 0; c0 < g.C; c0 += kMaxGridChannels) {
+                const int n = g.C - c0 < kMaxGridChannels ? g.C - c0 : kMaxGridChannels;
+                const size_t row = (size_t)c0 * (size_t)g.L, taps = (size_t)c0 * (size_t)g.K;
+                hipLaunchKernelGGL(kernel, dim3((unsigned)n, (unsigned)p.S, (unsigned)nz), dim3(dwconv::kToepThreads), p.lds, st,
+                                   static_cast<const E *>(x) + row, static_cast<const E *>(dy) + row, part + taps,
+                                   dw_out ? static_cast<E *>(dw_out) + taps : nullptr, g, slices);
+            }
         }
         return launch_status();
     };

@@ -200,7 +200,7 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
 
 // ---- ... dw_toep_kernel
 
-// Depends on the shape only.  False: no geometry (rows of fewer than eight positions, more pieces than a grid holds).
+// Depends on the shape only.  False: no geometry (rows of fewer than eight positions).
 // slices: those of the workspace, at least as many as the plan uses.
 bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
 {
@@ -233,7 +233,7 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     p->T = 2;
     while (p->T > 1 && (p->T / 2 >= tiles || (long long)s.C * ((tiles + p->T - 1) / p->T) < 3 * kComputeUnits)) p->T /= 2;
     g.npiece = (tiles + p->T - 1) / p->T;
-    if (g.npiece > 65535) return false;
+    g.piece0 = 0;
     // chunks of equal length, as few as fit half the LDS of a compute unit (a third where registers allow a third workgroup)
     const size_t budget = kMaxLdsBytes / (size_t)dwconv::toep_waves(NL, p->T);
     const int whole = (s.L + 31) / 32 + 64;                               // blocks of X that any tile can reach

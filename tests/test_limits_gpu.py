@@ -178,8 +178,8 @@ def test_infinity_on_the_limb_kernels(B, C, L, K, p):
     assert (y[:, 1, t0:t1 + 1] == float("-inf")).all()
 
 
-# More channels than a grid dimension holds workgroups of 256 threads (2^24), and more windows of block offsets than its third
-# dimension holds (65535): the band kernels launch what is beyond separately.
+# More channels than a grid dimension holds workgroups of 256 threads (2^24), and a filter of more windows of block offsets than its third
+# dimension holds (65535), which dw_toep_kernel takes in two launches of its pieces: what is beyond a grid is launched separately.
 def test_band_kernels_with_2_to_the_24_channels():
     B, C, L, K, p = 1, (1 << 24) + 3, 9, 97, 40
     tdt = torch.bfloat16
