@@ -5,8 +5,8 @@
 
 namespace dwhost {
 
-// Pieces of lags per launch: 16384 fill the chip as well as 65535, and a test reaches the second launch (23 million lags).
-constexpr int kMaxGridPieces = 16384;
+// Pieces of lags per launch: 8192 fill the chip as well as 65535, and a test reaches the second launch (23 million lags, 11280 pieces).
+constexpr int kMaxGridPieces = 8192;
 
 template <typename E>
 static int launch_dw_toep(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st)
