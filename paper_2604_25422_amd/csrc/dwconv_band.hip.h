@@ -173,19 +173,22 @@ constexpr int kBandTapPrefetch = 4;
 // which exactly the places a .. a + n - 1 have work, [lo[a], lo[a - 1]) and (hi[a + n], hi[a + n - 1]].  A place without any,
 // wherever it stands, has its lo beyond every hi and its hi before every lo (either alone would put it into the runs of the places
 // on one side of it).  (On the host too: a test follows the operand addresses of the kernels.)
+template <int A, int B, int N, typename F>
+__host__ __device__ __forceinline__ void active_runs_from(const int (&lo)[N], const int (&hi)[N], F &f)
+{
+    if constexpr (A < N) {
+        int from = lo[A], to = hi[B];
+        if constexpr (A > 0) to = to < lo[A - 1] - 1 ? to : lo[A - 1] - 1;
+        if constexpr (B + 1 < N) from = from > hi[B + 1] + 1 ? from : hi[B + 1] + 1;
+        f(std::integral_constant<int, A>{}, std::integral_constant<int, B - A + 1>{}, from, to);
+        if constexpr (B + 1 < N) active_runs_from<A, B + 1>(lo, hi, f);
+        else active_runs_from<A + 1, A + 1>(lo, hi, f);
+    }
+}
 template <int N, typename F>
 __host__ __device__ __forceinline__ void active_runs(const int (&lo)[N], const int (&hi)[N], F &&f)
 {
-    static_for<0, N>([&](auto ac) {
-        constexpr int a = decltype(ac)::value;
-        static_for<a, N>([&](auto bc) {
-            constexpr int b = decltype(bc)::value;
-            int from = lo[a], to = hi[b];
-            if constexpr (a > 0) to = to < lo[a - 1] - 1 ? to : lo[a - 1] - 1;
-            if constexpr (b + 1 < N) from = from > hi[b + 1] + 1 ? from : hi[b + 1] + 1;
-            f(ac, std::integral_constant<int, b - a + 1>{}, from, to);
-        });
-    });
+    active_runs_from<0, 0>(lo, hi, f);
 }
 constexpr int kNoWorkLo = 1 << 28, kNoWorkHi = -(1 << 28);
 

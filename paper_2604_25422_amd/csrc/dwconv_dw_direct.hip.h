@@ -73,7 +73,7 @@ __device__ __forceinline__ void wait_vmcnt_at_most()
 // Compile-time loop: f(std::integral_constant<int, I>) for I = BEGIN .. END-1.  The chunk loop below must
 // be unrolled with every index a constant (register arrays, wait counts), which a pragma does not guarantee.
 template <int BEGIN, int END, typename F>
-__host__ __device__ __forceinline__ void static_for(F &&f)
+__device__ __forceinline__ void static_for(F &&f)
 {
     if constexpr (BEGIN < END) {
         f(std::integral_constant<int, BEGIN>{});

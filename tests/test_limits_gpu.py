@@ -78,6 +78,8 @@ NONFINITE = [
     (40, 4, 48, 48, 24, "f32"), (40, 4, 48, 48, 24, "bf16"), (60, 4, 200, 31, 15, "f32"),
     (2, 3, 1024, 700, 699, "f32"), (2, 3, 1024, 700, 350, "bf16"),
     (2, 3, 1001, 9, 4, "f32"), (2, 3, 1001, 300, 299, "f32"),
+    # ... dw_toep_kernel with several chunks of a row
+    (2, 3, 4100, 900, 899, "f32"), (2, 3, 9000, 1500, 700, "bf16"),
 ]
 SLOP = 63
 
@@ -155,7 +157,8 @@ def test_products_at_the_top_of_the_range(B, C, L, K, p):
 
 
 # An infinity among operands of one sign: the outputs it enters are that infinity (all taps in one chunk; the zero taps that fill up a
-# chunk make the outputs at its edges NaN)
+# chunk make the outputs at its edges NaN; the weight gradient on dw_band_kernel: on dw_toep_kernel the zeros beside a chunk of dY make
+# NaN of the lags that reach the infinity from there)
 @pytest.mark.parametrize("B,C,L,K,p", BIG[:3])
 def test_infinity_on_the_limb_kernels(B, C, L, K, p):
     g = torch.Generator(device="cpu"); g.manual_seed(5)
