@@ -178,14 +178,14 @@ static bool dw_takes_band(const Shape &s, const RowsPlan &rp)
 // have lost, are multiplied all the same.  dw_band_kernel has groups of eight rows to fill (fewer batch entries: virtual rows, whose
 // stages are small), and a stage of its own for every twelve (bf16 sixteen) offsets of 32.  us, dw_band_kernel -> dw_toep_kernel,
 // with the ratio of the products:
-//   fp32, five batch entries and more: B8 C256 L8192 K8192 (1.12) 778 -> 628, B17 C736 L889 K889 (1.06) 188 -> 126, B161 C46 L1024
-//     K1024 (1.25) 102 -> 84, B7 C96 L896 K896 (1.30) 18 -> 14, B16 C83 L3328 K3328 (1.32) 117 -> 99, B98 C45 L2496 K2496 (1.36) 207 / 227,
-//     B284 C103 L768 K768 (1.70) 212 / 303
-//   bf16: B8 C256 L8192 K8192 (1.12) 201 -> 127, B12 C355 L1832 K1832 (1.28) 54 -> 37, B25 C328 L1020 K1020 (1.49) 38 -> 28, B25 C32 L1163
-//     K1163 (1.52) 17 -> 11; a stage is one row, and a short one has few products: B214 C64 L896 K896 (1.47) 33 / 43, B38 C45 L813 K813
-//     (1.55) 11 / 12
-//   fewer batch entries, fp32: B4 C71 L912 K912 (1.92) 11.1 / 12.0, B1 C365 L5675 K5675 (1.19) 215 -> 73, B4 C672 L1080 K1080 (1.84) 64 -> 52, B1 C396 L1104 K1104 (2.15)
-//     35 -> 14, B2 C608 L416 K416 (2.64) 23 -> 11, B3 C64 L7667 K163 (4.7) 14 / 24; bf16: B3 C320 L3968 K3968 (0.96) 83 -> 28, B2 C384 L1150 K1150 (2.59) 17.1 -> 7.7
+//   fp32, five batch entries and more: B8 C256 L8192 K8192 (1.12) 792 -> 644, B17 C736 L889 K889 (1.06) 173 -> 130, B161 C46 L1024
+//     K1024 (1.25) 104 -> 86, B7 C96 L896 K896 (1.30) 17.6 -> 16.5, B16 C83 L3328 K3328 (1.32) 109 -> 104, B98 C45 L2496 K2496 (1.36) 209 / 232,
+//     B284 C103 L768 K768 (1.70) 195 / 308
+//   bf16: B8 C256 L8192 K8192 (1.12) 193 -> 131, B12 C355 L1832 K1832 (1.19) 51 -> 40, B25 C328 L1020 K1020 (1.49) 38 -> 29, B25 C32 L1163
+//     K1163 (1.52) 17 -> 11; a stage is one row, and a short one has few products: B214 C64 L896 K896 (1.47) 34 / 46, B38 C45 L813 K813
+//     (1.55) 11 / 13
+//   fewer batch entries, fp32: B4 C672 L1080 K1080 (1.84) 62 -> 54, B1 C365 L5675 K5675 (1.19) 210 -> 73, B1 C396 L1104 K1104 (2.15) 34 -> 10, B2 C608 L416
+//     K416 (2.64) 22 -> 12, B4 C71 L912 K912 (1.92) 11.1 / 13.8; bf16: B3 C320 L3968 K3968 (0.92) 80 -> 28, B2 C384 L1150 K1150 (1.62) 16.5 -> 8.3
 static bool dw_takes_toep(const Shape &s, const DwPlan &p)
 {
     const double lo = std::min(s.pad, s.L - 1), hi = std::min(s.K - 1 - s.pad, s.L - 1);           // lags -lo .. hi

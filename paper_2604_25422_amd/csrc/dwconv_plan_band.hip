@@ -263,7 +263,8 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     g.rows = (int)((s.B + S - 1) / S);
     p->S = (s.B + g.rows - 1) / g.rows;
     // The e between two additions to the totals (four waves).  An element sums N = rows x L / 64 products of the instruction and wave; chains of
-    // root N of them, and as many totals, are the shortest of two levels: longer ones add up errors, shorter ones cost time.
+    // root N of them, and as many totals, are the shortest of two levels: longer ones add up errors, shorter ones cost time (fp32, short sums:
+    // chains of eight, B9 C49 L1147 15.1 us, of five 16.4).
     // fp32, where each run is a chain: error against 64 bits (normal data), dw_band_kernel -> here, and us: B9 L3000 1.07e-7 -> 1.03e-7 (1.26e-7
     // without a limit), B1 C348 L5664 0.96e-7 -> 0.97e-7 (1.5e-7), 209 -> 105; C256 L8192: B8 2.3e-7 -> 1.7e-7, 789 -> 632 (chains of
     // eight: 715), B7 2.2e-7 -> 1.7e-7, 764 -> 555 (chains of eight: 1.9e-7, 622), B5 2.0e-7 -> 1.4e-7, 732 -> 404 (446)
@@ -272,7 +273,7 @@ bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p)
     // without totals -> with: B8 L8192 2.3e-7, 6.7e-7, 1.9e-7, B32 L4097 3.3e-7, 9.5e-7, 1.9e-7, B1 L5952 0.91e-7, 1.9e-7, 0.85e-7,
     // B2 L1150 0.78e-7, 1.2e-7, 0.77e-7; what they cost: B8 C256 L8192 130 -> 131 us, B12 C355 L1832 43 -> 46, B2 C384 L1150 7.2 -> 8.4
     const int sets = dwconv::toep_sets(NL, p->T);
-    int root = 4;
+    int root = NL == 3 && s.B >= 5 ? 8 : 4;
     while ((long long)(root + 1) * (root + 1) <= (long long)g.rows * s.L / (64 * sets)) ++root;
     g.chain = 4 * sets * root;
     g.run = NL == 3 || s.B < 5 ? 4 * sets * root : 1 << 24;

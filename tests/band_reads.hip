@@ -199,7 +199,7 @@ static bool check_dw_toep(const Shape &s)
     ++planned;
     const dwconv::DwToepGeom &g = p.g;
     // fp32: chains of about the root of the products an element sums on a wave
-    const double root = std::max(4.0, std::sqrt((double)g.rows * s.L / 64));
+    const double root = std::max(s.B < 5 ? 4.0 : 8.0, std::sqrt((double)g.rows * s.L / 64));
     if (s.dtype == DWCONV_F32 && (g.run > 4 * root || g.run < 4 * (root - 1) || (g.run & 3) != 0))
         return fault("dw_toep", s, "e of a chain", g.run, (long long)(4 * (root - 1)), (long long)(4 * root));
     for (int piece = 0; piece < g.npiece; ++piece)
