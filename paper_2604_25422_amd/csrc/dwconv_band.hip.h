@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     if (cur.item < 0) return;
     advance(cur, true);
     prefetch(cur);
-    // (K >= 1024: bf16 B1 C224 L5952 K5952 20.0 -> 17.1 us; in the kernels of fewer tiles the code alone, not run, took the registers of
+    // (K >= 1024: bf16 B8 C256 L8192 K8192 125.9 -> 122.8 us, B1 C544 L6988 K6988 40.3 -> 39.4; in the kernels of fewer tiles the code alone, not run, took the registers of
     // their stages: bf16 B1579 C472 L112 K108 111 -> 125 us)
     const bool granules = FOLD || (LONG && one_chunk && g.K >= 1024);
     if (granules) {

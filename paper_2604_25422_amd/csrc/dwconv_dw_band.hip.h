@@ -23,8 +23,8 @@
 // 44 %, vector ALU 39 % (splitting and transposing), 150-166 us of which two reads of memory are 104 (204-210 before the waves of a
 // group shared its items and the offsets were dealt, 27 % and 42 %; 366 on the fp32 instruction): one stage in LDS at a time, so that
 // these only overlap across the two workgroups of a compute unit.  The reads of the next operand go out ahead of each group of
-// products, the loads of the next stage ahead of a stage's.  Error against 64 bits: fp32 B8 C256 K = L = 8192 2.4e-7, the fp32
-// instruction 9.4e-7.
+// products, the loads of the next stage ahead of a stage's.  Relative error against 64 bits (2-norm, normal data): fp32 B8 C256
+// K = L = 8192 2.3e-7, the fp32 instruction 9.4e-7.
 #pragma once
 #include "dwconv_band.hip.h"
 

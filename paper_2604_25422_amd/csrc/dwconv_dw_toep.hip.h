@@ -11,10 +11,11 @@
 // summed where they are (no diagonals), and a single batch entry fills the operands as well as eight.  A tile is 1024 lags
 // whatever the filter, so shorter filters leave columns idle: dw_band_kernel has them (dw_takes_toep).
 //
-// What bounds it (counters, B8 C256 K = L = 8192): fp32 the matrix pipe, 80 % of the launch's cycles under a lowered clock (dw_band_kernel
-// 54 %): 775-793 -> 618-654 us, error against 64 bits 1.65e-7 -> 1.43e-7; bf16 LDS reads (79 %) and the matrix pipe (66 %; dw_band_kernel 59 % and
-// 30 %): 201 -> 125-132 us.  A few batch entries on few channels: the chain of one stage, some 1.2 us of loads, splitting, barriers and
-// products (fp32 B1 C365 L5675 K5675 215 -> 73 us, bf16 B2 C384 L1150 K1150 17.1 -> 7.7).
+// What bounds it (counters, B8 C256 K = L = 8192): fp32 the matrix pipe, 78 % of the launch's cycles under a lowered clock (dw_band_kernel
+// 54 %): 775-793 -> 619-654 us; bf16 LDS reads (78 %) and the matrix pipe (65 %; dw_band_kernel 59 % and 30 %): 201 -> 131-135 us.  Relative
+// error of the fp32 gradient against 64 bits there (2-norm, normal data) 2.3e-7 -> 1.7e-7.  A few batch entries on few channels: the chain of
+// a stage, some 1.2 us of loads, splitting, barriers, and its products (fp32 B1 C365 L5675 K5675 causal 215 -> 73 us, bf16 B2 C384
+// L1150 K1150 17 -> 8.3).
 //
 // Workgroup (c, slice, piece): T tiles of lags, the rows of its slice in chunks of F positions; the four waves split the e of a
 // chunk.  The next chunk's granules are loaded into registers while one is multiplied.  Pieces go out in falling order of
