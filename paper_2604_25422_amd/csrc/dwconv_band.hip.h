@@ -331,14 +331,22 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
     decltype(load_raw8(in)) pre[NPF];
     auto prefetch = [&](const Stage &s) {
         const int tl = band_hide(tid), ld_row = tl >> tpr_log, ld_g = tl & (TPR - 1);
-        if (s.inside) {
+        // (granules past the window: its last one again; rows past the batch, positions outside the row: loaded from inside, zeroed later)
+        if constexpr (NL == 3) {
+            // (one place for the loads: from two the compiler copies what one of them loads, and waits for it ahead of the products.  fp32 B285
+            // C114 L2718 K140 forward 292 -> 275 us, B2048 C128 L256 K256 161 -> 152; bf16, whose registers fall the other way: L2718 121, 155 us)
+            const E *row = in_c + (size_t)min(s.b0 + ld_row, g.B - 1) * CL;
+            const int u0 = 32 * s.wb0 + 8 * ld_g, last = s.inside ? 32 * s.wb0 + 8 * (s.n8 - 1) : g.L - 8;
+#pragma unroll
+            for (int i = 0; i < NPF; ++i)
+                if (i * TPR < s.n8) pre[i] = load_raw8(row + max(0, min(u0 + 8 * i * TPR, last)));
+        } else if (s.inside) {
             const E *p = in_c + (size_t)(s.b0 + ld_row) * CL + (32 * s.wb0 + 8 * ld_g);
-            const E *last = p + 8 * (s.n8 - 1 - ld_g);                   // (granules past the window: its last one again)
+            const E *last = p + 8 * (s.n8 - 1 - ld_g);
 #pragma unroll
             for (int i = 0; i < NPF; ++i)
                 if (i * TPR < s.n8) pre[i] = load_raw8(ld_g + i * TPR < s.n8 ? p + 8 * i * TPR : last);
         } else {
-            // (rows past the batch, positions outside the row: loaded from inside, zeroed later)
             const E *row = in_c + (size_t)min(s.b0 + ld_row, g.B - 1) * CL;
             const int u0 = 32 * s.wb0 + 8 * ld_g;
 #pragma unroll
@@ -459,6 +467,9 @@ __global__ __launch_bounds__(kBandThreads, FOLD ? 2 : band_waves(Limbs<E>::N, T,
             if (gi + THREADS < n_taps8) load_taps(0, gi + THREADS, ahead, ahead_beside);
             store_taps(0, gi, raw, beside);
         }
+        // (vmcnt 0: every load ahead has been used, but the compiler cannot tell, and would wait for its registers in every stage, also in
+        // launches without granules: for the window that was just asked for)
+        __builtin_amdgcn_s_waitcnt(0x0f70);
     } else {
         for (int m = tid; m < TP; m += THREADS) {
             E t3[3];
