@@ -22,6 +22,7 @@
 #include "dwconv_corr_direct.hip.h"
 #include "dwconv_dw_band.hip.h"
 #include "dwconv_dw_toep.hip.h"
+#include "dwconv_window.hip.h"
 
 namespace dwhost {
 
@@ -247,6 +248,14 @@ struct BandPlan {
 };
 bool plan_corr_band(const Shape &s, int pad_eff, int reverse, BandPlan *p);
 
+// Forward and input gradient on corr_window_kernel (fp32 filters of about 65 to 260 taps, calls that fill the chip).
+struct WindowPlan {
+    dwconv::WindowGeom g;
+    int NW;                // chunks a tile reads (the kernel is compiled per number)
+    int gy;                // workgroups per channel
+};
+bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p);
+
 // Stage 1 on dw_band_kernel (filters of more than six block offsets).
 struct DwBandPlan {
     dwconv::DwBandGeom g;
@@ -295,6 +304,7 @@ DwPlan plan_dw(const Shape &s);
 // Launch entry points of the per-path units.  A return value of -1 (fused backward only) means "does not apply".
 int launch_corr_band_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_band_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
+int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,

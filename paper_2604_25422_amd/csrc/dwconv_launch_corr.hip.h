@@ -486,6 +486,13 @@ template <typename T>
 int launch_corr(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
 {
     int rc = -1;
+    if constexpr (std::is_same<T, float>::value) {
+        // (up to six offsets: memory bounds the fp32 instruction's kernels already)
+        if (toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1 > kMfmaMaxND) {
+            rc = launch_corr_window_f32(in, f, out, s, pad_eff, reverse, st);
+            if (rc >= 0) return rc;
+        }
+    }
     if (corr_takes_band(s, pad_eff, in, out)) {
         if constexpr (std::is_same<T, float>::value) rc = launch_corr_band_f32(in, f, out, s, pad_eff, reverse, st);
         else rc = launch_corr_band_bf16(in, f, out, s, pad_eff, reverse, st);

@@ -1,0 +1,60 @@
+"""corr_window_kernel (fp32 forward and input gradient, filters of about 65 to 260 taps, calls that fill the chip) against the oracle, bit for
+bit on small integers and on values that need all three limbs."""
+import pytest
+import torch
+
+from _parity import empty_device, small_ints, to_device
+from paper_2604_25422_amd import binding
+from paper_2604_25422_amd.workloads import as_f32_numpy
+from test_exact_gpu import _kernels, _same, test_exact_fp32_needs_every_limb
+
+pytestmark = pytest.mark.gpu
+
+# every number of chunks a tile reads, rows in one piece and in several, rows that end inside a granule, units that the batch does not fill
+SHAPES = [
+    (374, 160, 180, 75, 20), (482, 128, 179, 81, 40), (159, 96, 824, 97, 0), (42, 128, 2263, 88, 44), (188, 160, 320, 108, 54), (388, 131, 249, 108, 54),
+    (49, 128, 1996, 106, 53), (19, 256, 2478, 110, 0), (871, 64, 228, 134, 77), (158, 131, 625, 160, 80), (94, 131, 888, 133, 129), (137, 64, 1343, 141, 0),
+    (817, 64, 248, 191, 95), (793, 64, 247, 171, 0), (62, 96, 2128, 189, 0), (81, 64, 2169, 189, 87), (190, 160, 352, 211, 0), (189, 131, 310, 218, 109),
+    (19, 256, 2536, 212, 106), (158, 96, 638, 196, 86), (288, 96, 376, 237, 118), (801, 64, 249, 226, 113), (46, 256, 992, 255, 0), (191, 64, 874, 241, 240),
+    (511, 128, 255, 250, 125), (512, 128, 256, 256, 255),
+]
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("B,C,L,K,p", SHAPES)
+def test_exact_corr_window(oracle_mod, B, C, L, K, p, offset):
+    print(f"case window B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    tdt, what = torch.float32, f"B{B} C{C} L{L} K{K} p{p} offset {offset}"
+    x, w = small_ints((B, C, L), 71, 3, tdt), small_ints((C, K), 72, 3, tdt)
+    xd, wd = to_device(x, offset), to_device(w, offset)
+    y, dx = empty_device((B, C, L), tdt, offset), empty_device((B, C, L), tdt, offset)
+    names = _kernels(lambda: binding.dwconv_fwd(xd, wd, p, out=y)) + _kernels(lambda: binding.dwconv_bwd_input(xd, wd, p, out=dx))
+    assert len(names) == 2 and any("corr_window_kernel" in n for n in names), names
+    xn, wn = as_f32_numpy(x), as_f32_numpy(w)
+    _same("fwd", y, oracle_mod.fwd(xn, wn, p)[0], tdt, what)
+    _same("dx", dx, oracle_mod.bwd_input(xn, wn, p)[0], tdt, what)
+
+
+@pytest.mark.parametrize("B,C,L,K,p", [(62, 64, 2251, 114, 65), (512, 128, 256, 256, 255)])
+def test_every_limb_corr_window(B, C, L, K, p):
+    test_exact_fp32_needs_every_limb(B, C, L, K, p)
+
+
+def test_non_finite_values_stay_where_the_definition_puts_them():
+    """An infinity or NaN reaches outputs of its own row up to 63 positions beyond what the definition says, and the other outputs are what they are
+    without it; sums above 10^19 are as good as any."""
+    B, C, L, K, p = 62, 64, 2251, 114, 65
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, w = torch.randn(B, C, L, generator=g, device="cuda"), torch.randn(C, K, generator=g, device="cuda")
+    clean = binding.dwconv_fwd(x, w, p)
+    for at, v in ((700, float("inf")), (0, float("nan")), (L - 1, float("-inf"))):
+        bad = x.clone()
+        bad[30, 7, at] = v
+        y = binding.dwconv_fwd(bad, w, p)
+        lo, hi = max(0, at - (K - 1 - p) - 63), min(L, at + p + 64)
+        touched = torch.zeros_like(y, dtype=torch.bool)
+        touched[30, 7, lo:hi] = True
+        assert torch.equal(y[~touched], clean[~touched])
+        assert not torch.isfinite(y[30, 7, max(0, at - (K - 1 - p)):min(L, at + p + 1)]).any()
+    big = binding.dwconv_fwd(x * 2.0 ** 100, w, p)
+    assert torch.equal(big, clean * 2.0 ** 100)
