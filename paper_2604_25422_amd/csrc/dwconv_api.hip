@@ -216,6 +216,17 @@ static bool dw_takes_toep(const Shape &s, const DwPlan &p)
     return p.tp.work <= most * band;
 }
 
+// Which fp32 filters of seven and more block offsets go to dw_window_kernel instead of the register-resident kernels of the fp32 instruction: where
+// the products of these, with the padding of rows to regions of 256 positions or of virtual rows to their pitch, take longer than its
+// own estimate.  (Both in us at the clock under load; 1.2 and 1.3 are what either takes beyond its products.)  us, inputs from memory, before ->
+// here: taken B1964 C286 L144 K97 352 -> 225, B3525 C155 L132 K132 342 -> 220, B59 C250 L1333 K86 65 -> 51, B1918 C32 L1248 K111 219 -> 182, B32 C256
+// L4096 K128 100 -> 85; left B114 C192 L3769 K110 231 / 235, B18 C766 L3761 K120 139 / 152, B2670 C32 L880 K77 168 / 185, B18 C276 L1079 K86 29 / 41.
+static bool dw_takes_window(const Shape &s, const DwPlan &p, int nd)
+{
+    const double positions = (double)s.B * s.C * (p.rows.on ? p.rows.map.P : (s.L + 255) / 256 * 256);
+    return 1.3 * p.wp.cycles / 2000.0 < 1.2 * positions / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0;
+}
+
 // Slices of the workspace for the filters of dw_band_kernel.  Callers keep workspaces and read slices by these numbers
 // (dwconv_bwd_weight_slices), so they stay what they have been although the kernel mostly uses fewer (DwBandPlan::S, chosen from
 // the channels, windows and stages there are): a call that takes the gradient sums only those used, dwconv_bwd_weight_partial
@@ -317,6 +328,7 @@ DwPlan plan_dw(const Shape &s)
     p.band_fits = (nd > kMfmaMaxND || p.rows.tall) && plan_dw_band(s, p.S, &p.bp);
     p.band = p.band && p.band_fits;
     p.toep = p.band && plan_dw_toep(s, p.S, &p.tp) && dw_takes_toep(s, p);
+    p.window = !p.band && !p.rows.batch && nd > kMfmaMaxND && plan_dw_window(s, p.S, &p.wp) && dw_takes_window(s, p, nd);
     // the fused backward kernel of these shapes works on one channel per block: its own slice count
     p.S_fused = p.S;
     if (p.rows.batch && s.L <= dwconv::kRbBwdMaxL) {

@@ -23,6 +23,7 @@
 #include "dwconv_dw_band.hip.h"
 #include "dwconv_dw_toep.hip.h"
 #include "dwconv_window.hip.h"
+#include "dwconv_dw_window.hip.h"
 
 namespace dwhost {
 
@@ -276,12 +277,23 @@ struct DwToepPlan {
 };
 bool plan_dw_toep(const Shape &s, int slices, DwToepPlan *p);
 
+// Stage 1 on dw_window_kernel (fp32 filters of about 65 to 130 taps).
+struct DwWinPlan {
+    dwconv::DwWinGeom g;
+    int ND;                // offsets of a wave (the kernel is compiled per number)
+    int S;                 // slices it uses: at most those of the workspace
+    double cycles;         // its estimate
+};
+bool plan_dw_window(const Shape &s, int slices, DwWinPlan *p);
+
 struct DwPlan {
     bool band;             // dw_band_kernel (dw_takes_band)
     bool band_fits;        // it can run: where the kernel of the plan does not take the tensors (bf16 bases off a 16-byte granule)
     DwBandPlan bp;
     bool toep;             // dw_toep_kernel in its place (dw_takes_toep)
     DwToepPlan tp;
+    bool window;           // dw_window_kernel in the place of the register-resident kernels (dw_takes_window)
+    DwWinPlan wp;
     DwKernel kernel;
     int S;                 // partial slices per coefficient
     RowsPlan rows;         // short rows: stage 1 walks the virtual row of a channel
@@ -315,6 +327,7 @@ int launch_dw_band_f32(const void *x, const void *dy, float *part, void *dw_out,
 int launch_dw_band_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwBandPlan &p, int slices, hipStream_t st);
 int launch_dw_toep_f32(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st);
 int launch_dw_toep_bf16(const void *x, const void *dy, float *part, void *dw_out, const DwToepPlan &p, int slices, hipStream_t st);
+int launch_dw_window_f32(const void *x, const void *dy, float *part, void *dw_out, const DwWinPlan &p, int slices, hipStream_t st);
 // (fp32, seven to sixteen block offsets; returns -1 when it does not apply)
 int launch_dw_partial_wide_f32(const void *x, const void *dy, float *part, void *dw_out, const Shape &s, const DwPlan &p,
                                int dmin, int nd, hipStream_t st);

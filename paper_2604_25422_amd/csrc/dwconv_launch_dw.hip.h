@@ -222,6 +222,15 @@ int launch_dw_partial(const void *x, const void *dy, float *part, void *dw_out, 
 {
     // dw_out: where a single-slice matrix-core launch may put the gradient itself (nullptr: always write part, all p.S slices);
     // *slices tells the caller how many slices of part hold the sums (0: dw_out holds the gradient).
+    if constexpr (std::is_same<T, float>::value) {
+        if (p.window) {
+            // (a caller that takes the gradient needs no more slices than the launch uses)
+            const int used = dw_out ? p.wp.S : p.S;
+            void *to = p.wp.S == 1 ? dw_out : nullptr;
+            if (slices) *slices = to ? 0 : used;
+            return launch_dw_window_f32(x, dy, part, to, p.wp, used, st);
+        }
+    }
     void *direct = (p.single && p.S == 1) ? dw_out : nullptr;
     int rc = p.band ? -1 : launch_dw_partial_mfma<T>(x, dy, part, direct, s, p, st);
     if (slices) *slices = direct ? 0 : p.S;

@@ -1,5 +1,5 @@
-"""corr_window_kernel (fp32 forward and input gradient, filters of about 65 to 260 taps, calls that fill the chip) against the oracle, bit for
-bit on small integers and on values that need all three limbs."""
+"""corr_window_kernel (fp32 forward and input gradient, filters of about 65 to 260 taps, calls that fill the chip) and dw_window_kernel (weight
+gradient, about 65 to 130 taps) against the oracle, bit for bit on small integers and on values that need all three limbs."""
 import pytest
 import torch
 
@@ -58,3 +58,39 @@ def test_non_finite_values_stay_where_the_definition_puts_them():
         assert not torch.isfinite(y[30, 7, max(0, at - (K - 1 - p)):min(L, at + p + 1)]).any()
     big = binding.dwconv_fwd(x * 2.0 ** 100, w, p)
     assert torch.equal(big, clean * 2.0 ** 100)
+
+
+# dw_window_kernel (fp32 weight gradient, at most five 32-blocks): four and five offsets, rows in one piece and in several, one slice and more,
+# rows that end inside a granule, units that the batch does not fill
+DW_SHAPES = [
+    (179, 256, 240, 85, 84), (128, 256, 348, 96, 95), (56, 256, 780, 104, 52), (148, 256, 272, 118, 117), (58, 256, 541, 111, 55), (57, 256, 566, 113, 56),
+    (349, 128, 244, 119, 118), (463, 128, 192, 125, 96), (96, 256, 817, 89, 59), (31, 255, 2836, 85, 84), (32, 250, 2848, 87, 0), (32, 250, 1840, 121, 0),
+    (42, 255, 1305, 104, 52), (42, 255, 1281, 101, 50), (41, 250, 2096, 127, 126), (191, 128, 848, 112, 56), (64, 128, 2617, 124, 123), (192, 128, 886, 123, 122),
+]
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("B,C,L,K,p", DW_SHAPES)
+def test_exact_dw_window(oracle_mod, B, C, L, K, p, offset):
+    print(f"case dw window B{B} C{C} L{L} K{K} p{p} offset {offset}", flush=True)
+    tdt, what = torch.float32, f"B{B} C{C} L{L} K{K} p{p} offset {offset}"
+    assert 9 * B * L < 2 ** 24
+    x, dy = small_ints((B, C, L), 73, 3, tdt), small_ints((B, C, L), 74, 3, tdt)
+    xd, dyd = to_device(x, offset), to_device(dy, offset)
+    dw = torch.empty(C, K, device="cuda")
+    names = _kernels(lambda: binding.dwconv_bwd_weight(xd, dyd, K, p, out=dw))
+    ref = oracle_mod.bwd_weight(as_f32_numpy(x), as_f32_numpy(dy), K, p)[0]
+    _same("dw", dw, ref, tdt, what)
+    if offset == 0:
+        assert "dw_window_kernel" in names[0], names
+        # the partial sums alone: every slice of the workspace is written, and their sum is the gradient
+        ws = binding.new_workspace(xd, K, p)
+        ws.fill_(255)
+        S = binding.dwconv_bwd_weight_slices(B, C, L, K, p, binding.F32)
+        binding.dwconv_bwd_weight_partial(xd, dyd, K, p, workspace=ws)
+        _same("partial", ws.view(torch.float32)[:S * C * K].view(S, C, K).sum(0), ref, tdt, what)
+
+
+@pytest.mark.parametrize("B,C,L,K,p", [(179, 256, 240, 85, 84), (58, 256, 541, 111, 55)])
+def test_every_limb_dw_window(B, C, L, K, p):
+    test_exact_fp32_needs_every_limb(B, C, L, K, p)
