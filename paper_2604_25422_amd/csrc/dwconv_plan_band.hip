@@ -190,10 +190,23 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     // slices that are used: about two rounds of two workgroups per compute unit (a workgroup's start and its diagonal sums do
     // not shrink with its stages: B8 C256 K = L = 8192 with one slice 745 us, two 837 us; bf16 232 / 286), partial sums of at
     // most 16 MiB
-    long long S = (4ll * kComputeUnits + (long long)s.C * g.nwin - 1) / ((long long)s.C * g.nwin);
+    const long long wgs = (long long)s.C * g.nwin, slots = 2ll * kComputeUnits;
+    long long S = (2 * slots + wgs - 1) / wgs;
     S = std::min(S, (16ll << 20) / ((long long)s.C * s.K * 4));
-    S = std::min(S, (long long)std::min(g.stages, slices));
-    p->S = S < 1 ? 1 : (int)S;
+    S = std::max(1ll, std::min(S, (long long)std::min(g.stages, slices)));
+    p->S = p->S_most = (int)S;
+    // ... fp32, one window of offsets (its workgroups then take equally long): fewer where that fills the last round of workgroups, which was a nearly
+    // empty one (us, of a start with its diagonal sums and of a stage).  B1310 C48 L192 K192, 528 workgroups of which 512 run at once -> 480: 57 -> 39 us,
+    // B2294 C96 L144 K176 155 -> 104, B3217 C36 L189 K189 103 -> 71, B109 C96 L3056 K223 145 -> 126.  (bf16 waits for memory, and a workgroup more
+    // than fits takes up some of the wait: B254 C508 L306 K243 53 / 61, B225 C288 L144 K228 24 / 32)
+    if (NL == 3 && g.nwin == 1) {
+        double best = 0.0;
+        for (long long t = S; t >= 1 && 2 * t >= S; --t) {
+            const long long rounds = (wgs * t + slots - 1) / slots;
+            const double cost = (double)rounds * (5.9 + (0.4 + 0.056 * g.S32 * p->ND) * (double)((g.stages + t - 1) / t));
+            if (t == S || (cost < 0.95 * best && 20 * wgs * t >= 17 * rounds * slots)) { best = cost; p->S = (int)t; }
+        }
+    }
     p->lds = dwconv::dw_band_lds_bytes(NL, 1 << g.rg_log, g.S32, x_blocks(g.S32) - g.S32 + 1, p->ND);
     return true;
 }
