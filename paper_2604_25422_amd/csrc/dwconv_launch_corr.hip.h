@@ -487,8 +487,15 @@ int launch_corr(const void *in, const void *f, void *out, const Shape &s, int pa
 {
     int rc = -1;
     if constexpr (std::is_same<T, float>::value) {
-        // (up to six offsets: memory bounds the fp32 instruction's kernels already)
-        if (toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1 > kMfmaMaxND) {
+        // Up to six offsets memory bounds the fp32 instruction's kernels already (virtual rows of whole cache lines with five and six offsets are 1.1 to 1.25 times as
+        // fast here alone, but a step of separate calls is not: B1024 C64 L224 K56 87 / 93 us, B2048 C128 L384 K64 544 / 529).  Seven and more: by
+        // the plan's own estimate, but seven on virtual rows of more than 512 positions that are not whole cache lines, where memory is
+        // nearer than the fp32 instruction's products and pieces of lines cost (us, corr_mfma_kernel / here: B500 C128 L516 K72 70 / 88, B250 C192
+        // L688 K80 70 / 81, B1383 C64 L520 K97 97 / 106, B400 C128 L560 K84 65 / 69; more offsets B500 C96 L592 K110 80 / 71, B600 C64 L720 K100 78 / 74).
+        const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
+        bool window = nd > kMfmaMaxND;
+        if (nd == kMfmaMaxND + 1 && s.L > 512 && (s.L % 32) != 0) window = !plan_rows(s).on;
+        if (window) {
             rc = launch_corr_window_f32(in, f, out, s, pad_eff, reverse, st);
             if (rc >= 0) return rc;
         }

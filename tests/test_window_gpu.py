@@ -35,6 +35,18 @@ def test_exact_corr_window(oracle_mod, B, C, L, K, p, offset):
     _same("dx", dx, oracle_mod.bwd_input(xn, wn, p)[0], tdt, what)
 
 
+@pytest.mark.parametrize("B,C,L,K,p,window", [(600, 64, 520, 97, 48, False), (500, 64, 688, 80, 40, False), (600, 64, 544, 97, 48, True), (600, 64, 520, 110, 55, True)])
+def test_seven_offsets_on_virtual_rows(oracle_mod, B, C, L, K, p, window):
+    """Rows of more than 512 positions off cache lines keep the register-resident kernel at seven block offsets; whole lines and more offsets do not."""
+    print(f"case window B{B} C{C} L{L} K{K} p{p}", flush=True)
+    x, w = small_ints((B, C, L), 75, 3, torch.float32), small_ints((C, K), 76, 3, torch.float32)
+    xd, wd = x.cuda(), w.cuda()
+    y = torch.empty_like(xd)
+    names = _kernels(lambda: binding.dwconv_fwd(xd, wd, p, out=y))
+    assert len(names) == 1 and ("corr_window_kernel" in names[0]) == window, names
+    _same("fwd", y, oracle_mod.fwd(as_f32_numpy(x), as_f32_numpy(w), p)[0], torch.float32, f"B{B} C{C} L{L} K{K} p{p}")
+
+
 @pytest.mark.parametrize("B,C,L,K,p", [(62, 64, 2251, 114, 65), (512, 128, 256, 256, 255)])
 def test_every_limb_corr_window(B, C, L, K, p):
     test_exact_fp32_needs_every_limb(B, C, L, K, p)
