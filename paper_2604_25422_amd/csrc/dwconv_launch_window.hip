@@ -67,8 +67,8 @@ bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p)
     // Where at least 0.6 of that is steps that a full chip could not do without: pieces of few columns, waves without a unit and the chunks in front
     // of a piece cost more than corr_band_kernel's barriers.  us, the kernels before -> here, inputs from memory: below the line B2 C712 L4000
     // K208 24 / 31, B96 C352 L304 K230 35 / 45, B107 C106 L533 K118 22.7 / 23.5; above it B59 C250 L1333 K86 61 -> 53, B743 C84 L727 K236 192 ->
-    // 143, B1918 C32 L1248 K111 200 -> 152, B41 C79 L5677 K167 70 -> 58, but B277 C128 L498 K143 54 / 58, B254 C160 L560 K88 56 / 61.  Of 63 calls
-    // above the line the mean is 1.12, five are below 0.97.
+    // 143, B1918 C32 L1248 K111 200 -> 152, B41 C79 L5677 K167 70 -> 58, but B277 C128 L498 K143 54 / 58.  Of 63 calls
+    // above the line the mean is 1.12, five are below 0.97 (of these, seven offsets on virtual rows off cache lines now stay away: launch_corr).
     return positions / (1024.0 * 1024.0) * step >= 0.60 * best;
 }
 
