@@ -240,6 +240,12 @@ __global__ __launch_bounds__(kWinThreads, kWinPerSimd) void corr_window_kernel(c
 #pragma unroll
                 for (int v = 0; v < 4; ++v) res[par + 2 * j][v] = 4.f * low[j][v];
         };
+        // Behind products that a branch may have passed by: the compiler counts the wait states from a product to the read of its sum along
+        // the way through the branch only, and along the other one the sum was read two states behind it instead of eight, without that
+        // product in it
+        auto settle = [](floatx4 (&big)[G], floatx4 (&mid)[G], floatx4 (&low)[G]) {
+            asm volatile("s_nop 7" : "+v"(big[0]), "+v"(big[1]), "+v"(mid[0]), "+v"(mid[1]), "+v"(low[0]), "+v"(low[1]));
+        };
         constexpr unsigned ALL = (1u << (NW + 1)) - 1u;
         if (tiles >= 4 && (live & ALL) == ALL && ks[0] == ALL >> 1) {
 #pragma unroll
@@ -309,6 +315,7 @@ __global__ __launch_bounds__(kWinThreads, kWinPerSimd) void corr_window_kernel(c
                         for (int l = NL - 1; l >= 0; --l) read_limb(an, l, granule(i + 1));
                     }
                 }
+                settle(big, mid, low);
                 finish(par, big, mid, low);
             }
         }

@@ -35,6 +35,30 @@ def test_exact_corr_window(oracle_mod, B, C, L, K, p, offset):
     _same("dx", dx, oracle_mod.bwd_input(xn, wn, p)[0], tdt, what)
 
 
+# ... with every limb of the rows, tap by tap: a tap's product is now the first and now the last of a tile, and the first and the last tile of
+# a step alone in it.  And the same bits again from normal data, where a product that is not there yet would be there another time.
+@pytest.mark.parametrize("B,C,L,K,p", SHAPES + [(857, 96, 144, 160, 159), (528, 96, 272, 145, 0)])
+def test_every_tap_alone_corr_window(B, C, L, K, p):
+    print(f"case window tap by tap B{B} C{C} L{L} K{K} p{p}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(B, C, L, generator=g, device="cuda")
+    y, want = torch.empty_like(x), torch.zeros_like(x)
+    for j in sorted({*range(0, K, 11), max(p - 1, 0), p, min(p + 1, K - 1), K - 1}):
+        w = torch.zeros(C, K, device="cuda"); w[:, j] = 1.0
+        for call, o in ((binding.dwconv_fwd, j - p), (binding.dwconv_bwd_input, p - j)):      # y[t] takes x[t + o]
+            a, b = max(0, -o), min(L, L - o)
+            call(x, w, p, out=y)
+            want.zero_()
+            if a < b:
+                want[..., a:b] = x[..., a + o:b + o]
+            assert torch.equal(y, want), f"{call.__name__} tap {j}: {int((y != want).sum())} outputs differ"
+    w = torch.randn(C, K, generator=g, device="cuda")
+    for call in (binding.dwconv_fwd, binding.dwconv_bwd_input):
+        first = call(x, w, p)
+        for _ in range(4):
+            assert torch.equal(call(x, w, p), first), f"{call.__name__}: other bits"
+
+
 @pytest.mark.parametrize("B,C,L,K,p,window", [(600, 64, 520, 97, 48, False), (500, 64, 688, 80, 40, False), (600, 64, 544, 97, 48, True), (600, 64, 520, 110, 55, True)])
 def test_seven_offsets_on_virtual_rows(oracle_mod, B, C, L, K, p, window):
     """Rows of more than 512 positions off cache lines keep the register-resident kernel at seven block offsets; whole lines and more offsets do not."""
