@@ -45,6 +45,7 @@ struct DwBandGeom {
     int nstep;          // stages along a virtual row
     unsigned step_magic;// floor(2^32 / nstep) + 1: st / nstep == umulhi(st, step_magic); 0: too many stages for that
     int stages;         // all stages
+    int chain;          // stages whose products a workgroup sums in one chain of additions (0: all of them)
     int rev;            // windows in falling order (the dear ones first)
     int fold;           // DG - 1: a wave's second offset (and fourth) counts from the other end of the groups; otherwise 0
 };
@@ -170,7 +171,9 @@ __device__ __forceinline__ void transpose_limbs(const Raw4H (&r)[8], int pos, ui
     for (int i = 0; i < 4; ++i) out[0][i] = __builtin_amdgcn_perm(r[2 * i + 1].v[pos >> 1], r[2 * i].v[pos >> 1], sel);
 }
 
-template <typename E, int ND, int DG, bool SPLIT>
+// CHAINS (fp32): the products of g.chain stages at a time are summed by themselves (plan_dw_band).  A form of its own: with the registers of its second
+// start the others take 3 % longer (B2048 C128 L256 K256 150 / 154 us).
+template <typename E, int ND, int DG, bool SPLIT, bool CHAINS = false>
 __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__restrict__ x, const E *__restrict__ dy,
                                                                      float *__restrict__ part, E *__restrict__ dw_out,
                                                                      const DwBandGeom g, int slices)
@@ -200,13 +203,6 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     const int VR = g.B * g.nseg;
 
     floatx16 acc[ND], mid[NL == 3 ? ND : 1], low[NL == 3 ? ND : 1];
-#pragma unroll
-    for (int i = 0; i < ND; ++i)
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            acc[i][k] = 0.f;
-            if constexpr (NL == 3) mid[i][k] = low[i][k] = 0.f;
-        }
 
     typedef DwBandStage Stage;
     // the next stage in which some offset of the window meets a row (nx <= 0: none does); st >= stages: the end
@@ -329,161 +325,182 @@ __global__ __launch_bounds__(kDwBandThreads, 2) void dw_band_kernel(const E *__r
     cur.st = sl - (int)gridDim.y;
     cur.nx = 0;
     advance(cur);
-    if (cur.st < g.stages) {
-        load_items(cur);
-        if constexpr (SPLIT) {
-            // (x blocks -1 and NB32; one stage is like the other)
-            for (int rg = 0; rg < RGN; ++rg)
-                for (int i = tid; i < 2 * (BB / 16); i += kDwBandThreads) {
-                    const int at = (i < BB / 16 ? -1 : NB32) - cur.xlo;
-                    if (at >= 0 && at < cur.nx)
-                        *reinterpret_cast<uintx4 *>(dwb_smem + rg * ((cur.nx + g.S32) * BB) + at * BB + 16 * (i < BB / 16 ? i : i - BB / 16)) = uintx4{0u, 0u, 0u, 0u};
-                }
+    for (bool first = true;; first = false) {
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                acc[i][k] = 0.f;
+                if constexpr (NL == 3) mid[i][k] = low[i][k] = 0.f;
+            }
+        int left = CHAINS ? g.chain : 1;
+        if (cur.st < g.stages) {
+            load_items(cur);
+            if constexpr (SPLIT) {
+                // (x blocks -1 and NB32; one stage is like the other)
+                for (int rg = 0; rg < RGN; ++rg)
+                    for (int i = tid; i < 2 * (BB / 16); i += kDwBandThreads) {
+                        const int at = (i < BB / 16 ? -1 : NB32) - cur.xlo;
+                        if (at >= 0 && at < cur.nx)
+                            *reinterpret_cast<uintx4 *>(dwb_smem + rg * ((cur.nx + g.S32) * BB) + at * BB + 16 * (i < BB / 16 ? i : i - BB / 16)) =
+                                uintx4{0u, 0u, 0u, 0u};
+                    }
+            }
         }
-    }
-    while (cur.st < g.stages) {
-        const int yb0 = cur.yb0, xlo = cur.xlo, nx = cur.nx;
-        const int rg_bytes = (nx + g.S32) * BB;                          // one group of eight rows: x blocks, dY blocks
-        __syncthreads();                                                 // everyone is done with the stage before
-        store_items(cur);
-        __syncthreads();
-        advance(cur);
-        if (cur.st < g.stages) load_items(cur);
+        while (cur.st < g.stages && left > 0) {
+            const int yb0 = cur.yb0, xlo = cur.xlo, nx = cur.nx;
+            const int rg_bytes = (nx + g.S32) * BB;                          // one group of eight rows: x blocks, dY blocks
+            __syncthreads();                                                 // everyone is done with the stage before
+            store_items(cur);
+            __syncthreads();
+            advance(cur);
+            if constexpr (CHAINS) --left;
+            if (cur.st < g.stages && left > 0) load_items(cur);
 
-        int plo[ND], phi[ND];                                            // block pairs p (blocks yb0 + 2 p, + 1) per offset
+            int plo[ND], phi[ND];                                            // block pairs p (blocks yb0 + 2 p, + 1) per offset
+#pragma unroll
+            for (int i = 0; i < ND; ++i) {
+                dw_band_pairs(g, w, yb0, place(i), plo[i], phi[i]);
+                // (hidden: the compiler would make a second set of loops for waves with an empty place, bf16 119 -> 157
+                // registers)
+                asm volatile("" : "+s"(plo[i]), "+s"(phi[i]));
+            }
+            const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
+            const int lane_off = (q ^ ((q >> 3) & 3)) * PB + kg * BB;
+            // pairs p = pa .. pb (those of this wave) for the offsets I0 .. I0 + N - 1
+            auto run = [&](auto i0c, auto nc, const unsigned char *xw, const unsigned char *yw, int pa, int pb) {
+                constexpr int I0 = decltype(i0c)::value, N = decltype(nc)::value;
+                pa += (ks - pa) & (KS - 1);
+                if (pa > pb) return;
+                const unsigned char *yp = yw + 2 * pa * BB, *xp[2];                      // (of the even and the odd rounds over the groups)
+                xp[0] = xw + (2 * pa + place.off0) * BB;
+                xp[1] = xp[0] + place.swing * BB;
+                uintx4 y[2][NL], xv[2][NL];
+                auto read_y = [&](uintx4 (&to)[NL]) {
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(yp + 16 * l);
+                };
+                auto read_x = [&](uintx4 (&to)[NL], int i) {
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(xp[DEALT ? (I0 + i) & 1 : 0] + (I0 + i) * STEP * BB + 16 * l);
+                };
+                auto multiply = [&](int i, const uintx4 (&a)[NL], const uintx4 (&b)[NL]) {
+                    if constexpr (NL == 3) {
+                        low[i] = mfma32x32x16(a[2], b[0], low[i]);
+                        acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+                        mid[i] = mfma32x32x16(a[1], b[0], mid[i]);
+                        low[i] = mfma32x32x16(a[0], b[2], low[i]);
+                        mid[i] = mfma32x32x16(a[0], b[1], mid[i]);
+                        low[i] = mfma32x32x16(a[1], b[1], low[i]);
+                    } else {
+                        acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+                    }
+                };
+                read_y(y[0]);
+                read_x(xv[0], 0);
+#pragma unroll 1
+                for (int p = pa; p <= pb;) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if (u == 0 || p <= pb) {
+                            const int by = p + KS <= pb ? 2 * KS * BB : 0;   // (past the last pair: the same addresses again)
+#pragma unroll
+                            for (int i = 0; i < N; ++i) {
+                                const int k = u * N + i;
+                                if (i + 1 < N) {
+                                    read_x(xv[(k + 1) & 1], i + 1);
+                                } else {
+                                    yp += by;
+                                    xp[0] += by;
+                                    if constexpr (DEALT) xp[1] += by;
+                                    read_y(y[1 - u]);
+                                    read_x(xv[(k + 1) & 1], 0);
+                                }
+                                multiply(I0 + i, xv[k & 1], y[u]);
+                            }
+                            p += KS;
+                        }
+                    }
+                }
+            };
+            for (int rg = 0; rg < RGN; ++rg) {
+                const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + dlo - xlo) * BB;
+                const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
+                active_runs(plo, phi, [&](auto ac, auto nc, int pa, int pb) { run(ac, nc, xw, yw, pa, pb); });
+            }
+        }
+
+        // ---- diagonal sums: every wave those of its offsets (e = q' - q + 31 of each), then the two offsets a tap belongs to and the
+        // waves' parts of each added in order
+        __syncthreads();
+        float *img = reinterpret_cast<float *>(dwb_smem) + wave * kDwBandDiag;
+        float *taps = reinterpret_cast<float *>(dwb_smem) + 4 * kDwBandDiag;
+        constexpr int TW = 64 * ND;
+        float *tap = taps + wave * TW;
+        // (the cells a diagonal has no entry in stay zero: a sum is 32 columns whatever its length.  A loop over the columns it
+        // has, one LDS round trip after the other, took 5 us of a call: B1 C257 L480 K105 bf16 11.7 us)
+        // (hidden: what follows from them would stay in registers from one chain to the next)
+        const int ld = CHAINS ? band_hide(lane) : lane;
+        const float zero = CHAINS ? __int_as_float(band_hide(0)) : 0.f;
+        for (int i = ld; i < kDwBandDiag / 4; i += 64) *reinterpret_cast<floatx4 *>(img + 4 * i) = floatx4{zero, zero, zero, zero};
+        wave_lds_fence();
 #pragma unroll
         for (int i = 0; i < ND; ++i) {
-            dw_band_pairs(g, w, yb0, place(i), plo[i], phi[i]);
-            // (hidden: the compiler would make a second set of loops for waves with an empty place, bf16 119 -> 157 registers)
-            asm volatile("" : "+s"(plo[i]), "+s"(phi[i]));
+            // lane (column q, half kg) holds rows q' = 8 (k / 4) + 4 kg + k % 4 in element k
+            const int q = ld & 31, kg = ld >> 5;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                float v = acc[i][k];
+                if constexpr (NL == 3) v = limb_sum(v, mid[i][k], low[i][k]);
+                img[(8 * (k >> 2) + 4 * kg + (k & 3) - q + 31) * kDwBandDiagPitch + q] = v;
+            }
+            wave_lds_fence();
+            if (ld < 63) {
+                floatx4 v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const floatx4 *>(img + ld * kDwBandDiagPitch + 4 * j);
+                floatx4 sum = v[0];
+#pragma unroll
+                for (int j = 1; j < 8; ++j) sum += v[j];
+                tap[64 * i + ld] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            }
+            wave_lds_fence();
         }
-        const int ln = band_hide(lane), q = ln & 31, kg = ln >> 5;
-        const int lane_off = (q ^ ((q >> 3) & 3)) * PB + kg * BB;
-        // pairs p = pa .. pb (those of this wave) for the offsets I0 .. I0 + N - 1
-        auto run = [&](auto i0c, auto nc, const unsigned char *xw, const unsigned char *yw, int pa, int pb) {
-            constexpr int I0 = decltype(i0c)::value, N = decltype(nc)::value;
-            pa += (ks - pa) & (KS - 1);
-            if (pa > pb) return;
-            const unsigned char *yp = yw + 2 * pa * BB, *xp[2];                      // (of the even and the odd rounds over the groups)
-            xp[0] = xw + (2 * pa + place.off0) * BB;
-            xp[1] = xp[0] + place.swing * BB;
-            uintx4 y[2][NL], xv[2][NL];
-            auto read_y = [&](uintx4 (&to)[NL]) {
+        __syncthreads();
+        // tap T = 0 .. 32 nd_here + 30 of the window is j = 32 dlo - 31 + pad + T; it owns lags j - pad in [32 dlo, 32 dhi), the first
+        // and the last window whatever lies beyond (taps no offset reaches are zero)
+        const int jw = 32 * dlo - 31 + g.pad;
+        const int j_lo = win == 0 ? 0 : 32 * dlo + g.pad, j_hi = win + 1 == g.nwin ? g.K : min(g.K, 32 * (dlo + nd_here - 1) + g.pad);
+        float *dst = part + ((size_t)sl * (size_t)g.C + (size_t)c) * (size_t)g.K;
+        const bool more = CHAINS && cur.st < g.stages;
+        for (int j = max(0, j_lo) + (CHAINS ? band_hide(tid) : tid); j < j_hi; j += kDwBandThreads) {
+            const int t = j - jw;
+            float sum = 0.f;
+            if (t >= 0 && t < 32 * nd_here + 31) {
+                // diagonal t % 32 of offset t / 32 and t % 32 + 32 of the one before it; waves (dg, 0), (dg, 1) .. have an offset
 #pragma unroll
-                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(yp + 16 * l);
-            };
-            auto read_x = [&](uintx4 (&to)[NL], int i) {
-#pragma unroll
-                for (int l = 0; l < NL; ++l) to[l] = *reinterpret_cast<const uintx4 *>(xp[DEALT ? (I0 + i) & 1 : 0] + (I0 + i) * STEP * BB + 16 * l);
-            };
-            auto multiply = [&](int i, const uintx4 (&a)[NL], const uintx4 (&b)[NL]) {
-                if constexpr (NL == 3) {
-                    low[i] = mfma32x32x16(a[2], b[0], low[i]);
-                    acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
-                    mid[i] = mfma32x32x16(a[1], b[0], mid[i]);
-                    low[i] = mfma32x32x16(a[0], b[2], low[i]);
-                    mid[i] = mfma32x32x16(a[0], b[1], mid[i]);
-                    low[i] = mfma32x32x16(a[1], b[1], low[i]);
-                } else {
-                    acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
-                }
-            };
-            read_y(y[0]);
-            read_x(xv[0], 0);
-#pragma unroll 1
-            for (int p = pa; p <= pb;) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u == 0 || p <= pb) {
-                        const int by = p + KS <= pb ? 2 * KS * BB : 0;   // (past the last pair: the same addresses again)
-#pragma unroll
-                        for (int i = 0; i < N; ++i) {
-                            const int k = u * N + i;
-                            if (i + 1 < N) {
-                                read_x(xv[(k + 1) & 1], i + 1);
-                            } else {
-                                yp += by;
-                                xp[0] += by;
-                                if constexpr (DEALT) xp[1] += by;
-                                read_y(y[1 - u]);
-                                read_x(xv[(k + 1) & 1], 0);
-                            }
-                            multiply(I0 + i, xv[k & 1], y[u]);
-                        }
-                        p += KS;
+                for (int h = 1; h >= 0; --h) {
+                    const int o = (t >> 5) - h, e = (t & 31) + 32 * h;
+                    if (o >= 0 && o < nd_here && e < 63) {
+                        const int at_o = o + w.spare, i = DEALT ? at_o / DG : at_o % ND, r = DEALT ? at_o & (DG - 1) : at_o / ND;
+                        const int at = (DEALT && (i & 1) ? r ^ g.fold : r) * TW + 64 * i + e;
+                        for (int k = 0; k < KS; ++k) sum += taps[k * DG * TW + at];
                     }
                 }
             }
-        };
-        for (int rg = 0; rg < RGN; ++rg) {
-            const unsigned char *xw = dwb_smem + rg * rg_bytes + lane_off + (yb0 + dlo - xlo) * BB;
-            const unsigned char *yw = dwb_smem + rg * rg_bytes + lane_off + nx * BB;
-            active_runs(plo, phi, [&](auto ac, auto nc, int pa, int pb) { run(ac, nc, xw, yw, pa, pb); });
-        }
-    }
-
-    // ---- diagonal sums: every wave those of its offsets (e = q' - q + 31 of each), then the two offsets a tap belongs to and the
-    // waves' parts of each added in order
-    __syncthreads();
-    float *img = reinterpret_cast<float *>(dwb_smem) + wave * kDwBandDiag;
-    float *taps = reinterpret_cast<float *>(dwb_smem) + 4 * kDwBandDiag;
-    constexpr int TW = 64 * ND;
-    float *tap = taps + wave * TW;
-    // (the cells a diagonal has no entry in stay zero: a sum is 32 columns whatever its length.  A loop over the columns it
-    // has, one LDS round trip after the other, took 5 us of a call: B1 C257 L480 K105 bf16 11.7 us)
-    for (int i = lane; i < kDwBandDiag / 4; i += 64) *reinterpret_cast<floatx4 *>(img + 4 * i) = floatx4{0.f, 0.f, 0.f, 0.f};
-    wave_lds_fence();
-#pragma unroll
-    for (int i = 0; i < ND; ++i) {
-        // lane (column q, half kg) holds rows q' = 8 (k / 4) + 4 kg + k % 4 in element k
-        const int q = lane & 31, kg = lane >> 5;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            float v = acc[i][k];
-            if constexpr (NL == 3) v = limb_sum(v, mid[i][k], low[i][k]);
-            img[(8 * (k >> 2) + 4 * kg + (k & 3) - q + 31) * kDwBandDiagPitch + q] = v;
-        }
-        wave_lds_fence();
-        if (lane < 63) {
-            floatx4 v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const floatx4 *>(img + lane * kDwBandDiagPitch + 4 * j);
-            floatx4 sum = v[0];
-#pragma unroll
-            for (int j = 1; j < 8; ++j) sum += v[j];
-            tap[64 * i + lane] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
-        }
-        wave_lds_fence();
-    }
-    __syncthreads();
-    // tap T = 0 .. 32 nd_here + 30 of the window is j = 32 dlo - 31 + pad + T; it owns lags j - pad in [32 dlo, 32 dhi), the first
-    // and the last window whatever lies beyond (taps no offset reaches are zero)
-    const int jw = 32 * dlo - 31 + g.pad;
-    const int j_lo = win == 0 ? 0 : 32 * dlo + g.pad, j_hi = win + 1 == g.nwin ? g.K : min(g.K, 32 * (dlo + nd_here - 1) + g.pad);
-    float *dst = part + ((size_t)sl * (size_t)g.C + (size_t)c) * (size_t)g.K;
-    for (int j = max(0, j_lo) + tid; j < j_hi; j += kDwBandThreads) {
-        const int t = j - jw;
-        float sum = 0.f;
-        if (t >= 0 && t < 32 * nd_here + 31) {
-            // diagonal t % 32 of offset t / 32 and t % 32 + 32 of the one before it; waves (dg, 0), (dg, 1) .. have an offset
-#pragma unroll
-            for (int h = 1; h >= 0; --h) {
-                const int o = (t >> 5) - h, e = (t & 31) + 32 * h;
-                if (o >= 0 && o < nd_here && e < 63) {
-                    const int at_o = o + w.spare, i = DEALT ? at_o / DG : at_o % ND, r = DEALT ? at_o & (DG - 1) : at_o / ND;
-                    const int at = (DEALT && (i & 1) ? r ^ g.fold : r) * TW + 64 * i + e;
-                    for (int k = 0; k < KS; ++k) sum += taps[k * DG * TW + at];
-                }
+            if (dw_out) {                                                // (one slice: one chain)
+                st_elem(dw_out + (size_t)c * (size_t)g.K + (size_t)j, sum);
+            } else {
+                if (CHAINS && !first) sum += dst[j];                    // (what this thread wrote of the chain before)
+                dst[j] = sum;
+                // (slices beyond those of this launch are part of the workspace's layout: zeros)
+                if (!more)
+                    for (int o = sl + (int)gridDim.y; o < slices; o += (int)gridDim.y)
+                        part[((size_t)o * (size_t)g.C + (size_t)c) * (size_t)g.K + (size_t)j] = 0.f;
             }
         }
-        if (dw_out) {
-            st_elem(dw_out + (size_t)c * (size_t)g.K + (size_t)j, sum);
-        } else {
-            dst[j] = sum;
-            // (slices beyond those of this launch are part of the workspace's layout: zeros)
-            for (int o = sl + (int)gridDim.y; o < slices; o += (int)gridDim.y)
-                part[((size_t)o * (size_t)g.C + (size_t)c) * (size_t)g.K + (size_t)j] = 0.f;
-        }
+        if (!more) break;
+        __syncthreads();                                                     // (of tap sums, before the next chain's blocks take their place)
     }
 }
 

@@ -22,6 +22,9 @@ static int launch_dw_band(const void *x, const void *dy, float *part, void *dw_o
     };
     auto form = [&](auto nd, auto dg) -> int {
         constexpr int ND = decltype(nd)::value, DG = decltype(dg)::value;
+        if constexpr (std::is_same<E, float>::value) {
+            if (p.g.chain > 0) return p.split ? go(dwconv::dw_band_kernel<E, ND, DG, true, true>) : go(dwconv::dw_band_kernel<E, ND, DG, false, true>);
+        }
         return p.split ? go(dwconv::dw_band_kernel<E, ND, DG, true>) : go(dwconv::dw_band_kernel<E, ND, DG, false>);
     };
     constexpr std::integral_constant<int, 1> c1{};

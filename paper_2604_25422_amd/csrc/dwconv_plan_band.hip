@@ -195,16 +195,25 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     S = std::min(S, (16ll << 20) / ((long long)s.C * s.K * 4));
     S = std::max(1ll, std::min(S, (long long)std::min(g.stages, slices)));
     p->S = p->S_most = (int)S;
-    // ... fp32, one window of offsets (its workgroups then take equally long): fewer where that fills the last round of workgroups, which was a nearly
-    // empty one (us, of a start with its diagonal sums and of a stage).  B1310 C48 L192 K192, 528 workgroups of which 512 run at once -> 480: 57 -> 39 us,
-    // B2294 C96 L144 K176 155 -> 104, B3217 C36 L189 K189 103 -> 71, B109 C96 L3056 K223 145 -> 126.  (bf16 waits for memory, and a workgroup more
-    // than fits takes up some of the wait: B254 C508 L306 K243 53 / 61, B225 C288 L144 K228 24 / 32)
+    // ... fp32, one window of offsets (its workgroups then take equally long): fewer, at least half, where that fills the last round of workgroups,
+    // which was a nearly empty one.  A workgroup then sums its stages in two chains of additions (CHAINS), so that none is longer than with S
+    // slices; what the second one costs (its start and its sums, 8 us a round) is only there from five stages on.  (Both in us: a start with its
+    // diagonal sums, a stage.)  S slices -> fewer, us and error against 64 bits (normal data): B1310 C48 L192 K192, 528 workgroups of which 512 run at
+    // once -> 480, 56 -> 43, 1.28e-7 -> 1.12e-7; B2294 C96 L144 K176 155 -> 108, 1.7e-7 -> 1.5e-7; B3217 C36 L189 K189 99 -> 71, 1.6e-7 -> 1.4e-7;
+    // B109 C96 L3056 K223 140 -> 128, 2.0e-7 -> 1.6e-7; of 156 calls the mean gain is 1.19, the worst 0.99, the mean error 0.83 of that
+    // of S slices.  (In one chain the error was up to 1.46 times that of S slices.  bf16 waits for memory, and a workgroup more than fits takes up some
+    // of the wait: B254 C508 L306 K243 53 / 61, B225 C288 L144 K228 24 / 32)
+    g.chain = 0;
     if (NL == 3 && g.nwin == 1) {
         double best = 0.0;
-        for (long long t = S; t >= 1 && 2 * t >= S; --t) {
-            const long long rounds = (wgs * t + slots - 1) / slots;
-            const double cost = (double)rounds * (5.9 + (0.4 + 0.056 * g.S32 * p->ND) * (double)((g.stages + t - 1) / t));
-            if (t == S || (cost < 0.95 * best && 20 * wgs * t >= 17 * rounds * slots)) { best = cost; p->S = (int)t; }
+        for (long long t = S; t == S || (t > 1 && 2 * t >= S); --t) {          // (one slice would be the gradient, written once)
+            const long long rounds = (wgs * t + slots - 1) / slots, stages = (g.stages + t - 1) / t;
+            const double cost = (double)rounds * ((t < S ? 13.9 : 5.9) + (0.4 + 0.056 * g.S32 * p->ND) * (double)stages);
+            if (t == S || (cost < 0.95 * best && 20 * wgs * t >= 17 * rounds * slots && stages >= 5)) {
+                best = cost;
+                p->S = (int)t;
+                g.chain = t < S ? (int)(stages + 1) / 2 : 0;
+            }
         }
     }
     p->lds = dwconv::dw_band_lds_bytes(NL, 1 << g.rg_log, g.S32, x_blocks(g.S32) - g.S32 + 1, p->ND);

@@ -77,6 +77,12 @@ static bool check_dw_band(const Shape &s)
     DwBandPlan p;
     if (!plan_dw_band(s, 1 << 20, &p)) return true;
     ++planned;
+    if (s.dtype == DWCONV_F32) {
+        // a chain of additions is no longer than with two rounds of workgroups, as far as stages and 16 MiB of partial sums go
+        const long long wgs = (long long)s.C * p.g.nwin, slices = std::max(1ll, std::min({(1024 + wgs - 1) / wgs, (16ll << 20) / (4ll * s.C * s.K), (long long)p.g.stages}));
+        const long long all = (p.g.stages + p.S - 1ll) / p.S, chain = p.g.chain > 0 ? std::min((long long)p.g.chain, all) : all, most = (p.g.stages + slices - 1) / slices;
+        if (chain < 1 || chain > most) return fault("dw_band", s, "stages of a chain", chain, 1, most);
+    }
     switch (8 * p.ND + p.g.dg_log) {
     case 8: return dw_band_form<1, 1>(s, p);
     case 16: return dw_band_form<2, 1>(s, p);

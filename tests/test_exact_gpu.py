@@ -374,6 +374,30 @@ def test_dw_toep_takes_long_filters(B, C, L, K, p, dtype, offset):
     assert "dw_toep_kernel" in names[0] and len(names) <= 2, names
 
 
+# fp32 dw_band_kernel with fewer slices than two rounds of workgroups, so that a workgroup sums two chains: rows a stage holds whole and others, two
+# and three offsets of a wave, stages that the slices share evenly and not, rows that end inside a granule
+CHAINS = [(201, 153, 163, 87, 86), (744, 51, 164, 84, 0), (1564, 37, 133, 83, 82), (615, 119, 136, 83, 0), (854, 37, 179, 67, 33), (403, 76, 176, 104, 0),
+          (530, 55, 267, 69, 34), (303, 249, 136, 103, 102), (2294, 96, 144, 176, 175), (109, 96, 3056, 223, 0)]
+
+
+@pytest.mark.parametrize("B,C,L,K,p", CHAINS)
+def test_two_chains_of_dw_band(oracle_mod, B, C, L, K, p):
+    print(f"case two chains B{B} C{C} L{L} K{K} p{p}", flush=True)
+    assert 9 * B * L < 2 ** 24
+    x, dy = small_ints((B, C, L), 91, 3, torch.float32), small_ints((B, C, L), 92, 3, torch.float32)
+    xd, dyd = x.cuda(), dy.cuda()
+    dw = torch.empty(C, K, device="cuda")
+    names = _kernels(lambda: binding.dwconv_bwd_weight(xd, dyd, K, p, out=dw))
+    assert "dw_band_kernel" in names[0], names
+    ref = oracle_mod.bwd_weight(as_f32_numpy(x), as_f32_numpy(dy), K, p)[0]
+    _same("dw", dw, ref, torch.float32, f"B{B} C{C} L{L} K{K} p{p}")
+    ws = binding.new_workspace(xd, K, p)
+    ws.fill_(255)
+    S = binding.dwconv_bwd_weight_slices(B, C, L, K, p, binding.F32)
+    binding.dwconv_bwd_weight_partial(xd, dyd, K, p, workspace=ws)
+    _same("partial", ws.view(torch.float32)[:S * C * K].view(S, C, K).sum(0), ref, torch.float32, f"B{B} C{C} L{L} K{K} p{p}")
+
+
 # ... but not in calls that leave the chip idle, where its chain of batch entries is the longer one (us, dw_band_kernel / dw_toep_kernel: 11.0 / 19.1,
 # 11.8 / 18.0, 7.2 / 11.7, 9.9 / 15.2), and again where it is not (26.0 / 13.5, 15.8 / 12.3)
 @pytest.mark.parametrize("B,C,L,K,p,dtype,kernel", [(4, 77, 1023, 1023, 1022, "f32", "dw_band"), (5, 27, 937, 937, 561, "f32", "dw_band"),
