@@ -206,10 +206,10 @@ static bool dw_takes_toep(const Shape &s, const DwPlan &p)
         const double over = wgs > kComputeUnits ? wgs / kComputeUnits - 1 : 0.0;            // (second workgroups of compute units)
         const double here = f32 ? 3.2 + (p.tp.S > 1 ? 1.6 : 0.0) + rows * (1.2 * chunks + (0.051 + 0.028 * over) * products)
                                 : 3.0 + (p.tp.S > 1 ? 1.9 : 0.0) + rows * (0.84 * chunks + (0.014 + 0.006 * over) * products);
-        const double stages = (p.bp.g.stages + p.bp.S_most - 1) / p.bp.S_most, rounds = (double)s.C * p.bp.g.nwin * p.bp.S_most / (2 * kComputeUnits);
+        const double stages = (p.bp.g.stages + p.bp.S - 1) / p.bp.S, rounds = (double)s.C * p.bp.g.nwin * p.bp.S / (2 * kComputeUnits);
         const double pairs = stages * p.bp.g.S32 * p.bp.ND * std::max(1.0, rounds);
-        const double there = f32 ? 6.6 + (p.bp.S_most > 1 ? 0.9 : 0.0) + 0.4 * (stages - 1) + 0.056 * pairs + 5.9 * rounds
-                                 : 6.1 + (p.bp.S_most > 1 ? 1.2 : 0.0) + 2.6 * (stages - 1) + 0.011 * pairs + 3.4 * rounds;
+        const double there = f32 ? 6.6 + (p.bp.S > 1 ? 0.9 : 0.0) + 0.4 * (stages - 1) + 0.056 * pairs + 5.9 * rounds
+                                 : 6.1 + (p.bp.S > 1 ? 1.2 : 0.0) + 2.6 * (stages - 1) + 0.011 * pairs + 3.4 * rounds;
         if (here > there) return false;
     }
     const double most = s.dtype == DWCONV_F32 ? (nseg > 2 ? 2.65 : nseg > 1 ? 1.85 : 1.33) : (nseg > 1 ? 2.6 : s.L >= 1000 ? 1.54 : 1.42);

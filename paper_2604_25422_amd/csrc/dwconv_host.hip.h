@@ -263,7 +263,6 @@ struct DwBandPlan {
     int ND;                // offsets per wave (the kernel is compiled per number)
     bool split;            // one half of the waves of a group of rows brings x, the other dY
     int S;                 // slices it uses: at most those of the workspace
-    int S_most;            // ... and would use if rounds of workgroups did not count
     size_t lds;
 };
 bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p);

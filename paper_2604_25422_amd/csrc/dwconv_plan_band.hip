@@ -194,7 +194,7 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     long long S = (2 * slots + wgs - 1) / wgs;
     S = std::min(S, (16ll << 20) / ((long long)s.C * s.K * 4));
     S = std::max(1ll, std::min(S, (long long)std::min(g.stages, slices)));
-    p->S = p->S_most = (int)S;
+    p->S = (int)S;
     // ... fp32, one window of offsets (its workgroups then take equally long): fewer, at least half, where that fills the last round of workgroups,
     // which was a nearly empty one.  A workgroup then sums its stages in two chains of additions (CHAINS), so that none is longer than with S
     // slices; what the second one costs (its start and its sums, 8 us a round) is only there from five stages on.  (Both in us: a start with its
