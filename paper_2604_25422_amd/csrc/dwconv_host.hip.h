@@ -254,6 +254,7 @@ struct WindowPlan {
     dwconv::WindowGeom g;
     int NW;                // chunks a tile reads (the kernel is compiled per number)
     int gy;                // workgroups per channel
+    double cycles;         // its estimate
 };
 bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p);
 
@@ -316,7 +317,7 @@ DwPlan plan_dw(const Shape &s);
 // Launch entry points of the per-path units.  A return value of -1 (fused backward only) means "does not apply".
 int launch_corr_band_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_band_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
-int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
+int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, WindowPlan p, hipStream_t st);
 int launch_corr_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_corr_bf16(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st);
 int launch_dw_partial_f32(const void *x, const void *dy, float *part, void *dw_out, int *slices, const Shape &s,

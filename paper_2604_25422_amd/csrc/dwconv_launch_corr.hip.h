@@ -482,25 +482,43 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
     return (s.L % 8) != 0 || !granules || nd >= (filled || segs <= 1024 ? 11 : 7);
 }
 
+// Which fp32 filters of seven and more block offsets that plan_corr_window takes go to corr_window_kernel (us per 2^20 positions unless said
+// otherwise, inputs from memory, the kernel before / here; over 1000 calls, forward and input gradient).
+//   in the place of corr_mfma_kernel: nine offsets and more always (mean gain 1.2).  Seven and eight where an estimate of that kernel - its products
+//     with the padding of rows to whole segments of 1024 positions, or of virtual rows to their pitch, 1.15 times as long as at the clock under
+//     load; at least 2.2, its memory - is above one of this: 1.2 of the plan's, at least 2.6 for rows that are not whole cache lines, whose
+//     pieces cost memory time, or 1.8.  Taken B61 C576 L1163 K94 4.3 / 2.7, B109 C256 L1082 K80 3.6 / 2.6, B974 C64 L1216 K80 2.2 / 1.9; left B244 C96 L2988 K88
+//     2.1 / 2.6, B139 C544 L896 K75 2.3 / 2.7, B86 C128 L5680 K80 2.1 / 2.4, B500 C128 L516 K72 70 / 88 us
+//   in the place of corr_band_kernel: all but rows of at most three steps of 64 positions off half cache lines, where both wait for
+//     memory (B3967 C96 L186 K99 2.3 / 2.5, B702 C453 L186 K85 2.3 / 2.5, B3217 C36 L189 K189 2.6 / 2.6; half lines B3244 C96 L144 K144 2.5 / 2.3)
+// (Up to six offsets memory bounds the fp32 instruction's kernels already: virtual rows of whole cache lines with five and six offsets are 1.1 to
+// 1.25 times as fast here alone, but a step of separate calls is not: B1024 C64 L224 K56 87 / 93 us, B2048 C128 L384 K64 544 / 529.)
+inline bool corr_takes_window(const Shape &s, int pad_eff, const WindowPlan &p, bool band)
+{
+    const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
+    const RowsPlan rp = plan_rows(s);
+    // (tensors off a 16-byte granule send virtual rows to corr_band_kernel: seven offsets stay there where the estimates below would leave them)
+    if (band) return (s.L > 192 || (s.L % 16) == 0) && !(nd == kMfmaMaxND + 1 && rp.on && s.L > 512 && (s.L % 32) != 0);
+    if (nd > 8) return true;
+    const double rows = (double)s.B * s.C, millions = rows * s.L / (1024.0 * 1024.0);
+    const double padded = rows * (rp.on ? rp.map.P : (s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
+    const double there = std::max(1.15 * padded / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0, 2.2 * millions);
+    const double here = std::max(1.2 * p.cycles / 2000.0, (s.L % 32) == 0 ? 1.8 * millions : 2.6 * millions);
+    return here < there;
+}
+
 template <typename T>
 int launch_corr(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
 {
     int rc = -1;
+    const bool band = corr_takes_band(s, pad_eff, in, out);
     if constexpr (std::is_same<T, float>::value) {
-        // Up to six offsets memory bounds the fp32 instruction's kernels already (virtual rows of whole cache lines with five and six offsets are 1.1 to 1.25 times as
-        // fast here alone, but a step of separate calls is not: B1024 C64 L224 K56 87 / 93 us, B2048 C128 L384 K64 544 / 529).  Seven and more: by
-        // the plan's own estimate, but seven on virtual rows of more than 512 positions that are not whole cache lines, where memory is
-        // nearer than the fp32 instruction's products and pieces of lines cost (us, corr_mfma_kernel / here: B500 C128 L516 K72 70 / 88, B250 C192
-        // L688 K80 70 / 81, B1383 C64 L520 K97 97 / 106, B400 C128 L560 K84 65 / 69; more offsets B500 C96 L592 K110 80 / 71, B600 C64 L720 K100 78 / 74).
-        const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
-        bool window = nd > kMfmaMaxND;
-        if (nd == kMfmaMaxND + 1 && s.L > 512 && (s.L % 32) != 0) window = !plan_rows(s).on;
-        if (window) {
-            rc = launch_corr_window_f32(in, f, out, s, pad_eff, reverse, st);
-            if (rc >= 0) return rc;
-        }
+        WindowPlan p;
+        if (toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) >= kMfmaMaxND && plan_corr_window(s, pad_eff, reverse, &p) &&
+            corr_takes_window(s, pad_eff, p, band))
+            return launch_corr_window_f32(in, f, out, s, p, st);
     }
-    if (corr_takes_band(s, pad_eff, in, out)) {
+    if (band) {
         if constexpr (std::is_same<T, float>::value) rc = launch_corr_band_f32(in, f, out, s, pad_eff, reverse, st);
         else rc = launch_corr_band_bf16(in, f, out, s, pad_eff, reverse, st);
         if (rc >= 0) return rc;

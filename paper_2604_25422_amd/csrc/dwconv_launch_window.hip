@@ -29,11 +29,12 @@ bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p)
     const int w0 = (g.q0 + 1) >> 1, G = 2;
     // Pieces of a row, waves of a workgroup and units of a wave: the least of what a wave has to do in the rounds it takes (cycles of its
     // SIMD).  A step is 24 NW products and some 300 vector instructions, one that only brings chunks has the latencies and half of those; a
-    // wave alone on its SIMD takes a third longer than its share of two, and where every wave has one unit they all wait for their first chunks and store their
-    // last tiles at once (B32 C256 L4096 K128, pieces of 1024 / 512: 82 / 67 us).
+    // wave alone on its SIMD takes a third longer than its share of two.  These, 8000 for the start of a workgroup and 1.06 for one unit a wave are a
+    // fit to some sixty calls; the last one is not the same everywhere (pieces of 1024, one unit, and of 512, two: B32 C256 L4096 K128 82 / 67 us,
+    // but of 400 calls those with one unit gain as much over the kernels before as the others).
     const int per_cu = 4 * dwconv::kWinPerSimd;
     const double step = 384.0 * NW + 1000.0;
-    double best = 0.0;
+    double best = 0.0, crowded = 1.0;
     for (int np = 1; np <= 12 && np <= (s.L + 63) / 64; ++np) {
         const int P = ((s.L + np - 1) / np + 63) / 64 * 64, NP = (s.L + P - 1) / P;
         if (NP != np) continue;
@@ -59,23 +60,26 @@ bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p)
                     g.clo = clo; g.chi = NP > 1 ? 1 << 28 : (s.L + g.phi + 31) / 32 - 1;
                     p->gy = (int)gy;
                     g.waves = waves;
+                    const int on_cu = (int)((std::min(wgs, slots) + kComputeUnits - 1) / kComputeUnits) * (int)std::min((long long)waves, units);
+                    crowded = (0.6 + 0.7 * ((on_cu + 3) / 4)) / (0.6 + 0.7 * resident);
                 }
                 if (r == 1) break;
             }
         }
     }
     // Where at least 0.6 of that is steps that a full chip could not do without: pieces of few columns, waves without a unit and the chunks in front
-    // of a piece cost more than corr_band_kernel's barriers.  us, the kernels before -> here, inputs from memory: below the line B2 C712 L4000
-    // K208 24 / 31, B96 C352 L304 K230 35 / 45, B107 C106 L533 K118 22.7 / 23.5; above it B59 C250 L1333 K86 61 -> 53, B743 C84 L727 K236 192 ->
-    // 143, B1918 C32 L1248 K111 200 -> 152, B41 C79 L5677 K167 70 -> 58, but B277 C128 L498 K143 54 / 58.  Of 63 calls
-    // above the line the mean is 1.12, five are below 0.97 (of these, seven offsets on virtual rows off cache lines now stay away: launch_corr).
-    return positions / (1024.0 * 1024.0) * step >= 0.60 * best;
+    // of a piece cost more than corr_band_kernel's barriers (us, the kernels before / here, inputs from memory: B2 C712 L4000 K208 24 / 31, B96 C352 L304
+    // K230 35 / 45).  And where, with the SIMD that has most waves in the place of the mean one (405 workgroups of four waves leave some SIMDs with two and
+    // most with one), it is still 0.46, or 0.57 in pieces of at most four steps, whose starts weigh more.  Of 567 calls in the place of
+    // corr_band_kernel the 35 below that gain nothing (mean 0.995; B26 C538 L2665 K233 147 / 175, B549 C59 L561 K247 70 / 80, B277 C128 L498 K143
+    // 55 / 61, B94 C651 L208 K181 38 / 44), the others 1.14 in the mean, 15 of them less than 0.97 (B1184 C384 L176 K124 179 / 202).
+    p->cycles = best;
+    const double need = positions / (1024.0 * 1024.0) * step / best;
+    return need >= 0.60 && need >= (g.ns <= 4 ? 0.57 : 0.46) * crowded;
 }
 
-int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, int pad_eff, int reverse, hipStream_t st)
+int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, WindowPlan p, hipStream_t st)
 {
-    WindowPlan p;
-    if (!plan_corr_window(s, pad_eff, reverse, &p)) return -1;
     p.g.lines = (s.L % 32) == 0 && aligned_to(out, 128);
     auto go = [&](auto kernel, int NW) -> int {
         hipLaunchKernelGGL(kernel, dim3((unsigned)s.C, (unsigned)p.gy), dim3(64u * (unsigned)p.g.waves), dwconv::win_lds_bytes(3, NW, p.g.waves), st,
@@ -93,7 +97,7 @@ int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape
     case 9:
         if (p.g.chi < 8) return go(dwconv::corr_window_kernel<9, 8>, 9);
         return go(dwconv::corr_window_kernel<9, 10>, 9);
-    default: return -1;
+    default: return DWCONV_ERR_LAUNCH;                                   // (never planned)
     }
 }
 

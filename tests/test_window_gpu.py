@@ -10,13 +10,16 @@ from test_exact_gpu import _kernels, _same, test_exact_fp32_needs_every_limb
 
 pytestmark = pytest.mark.gpu
 
-# every number of chunks a tile reads, rows in one piece and in several, rows that end inside a granule, units that the batch does not fill
+# every form of the kernel (chunks a tile reads, chunks in registers), rows in one piece and in several, waves of one unit and of more, rows that end
+# inside a granule, units that the batch does not fill
 SHAPES = [
-    (374, 160, 180, 75, 20), (482, 128, 179, 81, 40), (159, 96, 824, 97, 0), (42, 128, 2263, 88, 44), (188, 160, 320, 108, 54), (388, 131, 249, 108, 54),
-    (49, 128, 1996, 106, 53), (19, 256, 2478, 110, 0), (871, 64, 228, 134, 77), (158, 131, 625, 160, 80), (94, 131, 888, 133, 129), (137, 64, 1343, 141, 0),
-    (817, 64, 248, 191, 95), (793, 64, 247, 171, 0), (62, 96, 2128, 189, 0), (81, 64, 2169, 189, 87), (190, 160, 352, 211, 0), (189, 131, 310, 218, 109),
-    (19, 256, 2536, 212, 106), (158, 96, 638, 196, 86), (288, 96, 376, 237, 118), (801, 64, 249, 226, 113), (46, 256, 992, 255, 0), (191, 64, 874, 241, 240),
-    (511, 128, 255, 250, 125), (512, 128, 256, 256, 255),
+    (124, 256, 252, 79, 39), (861, 64, 230, 67, 33), (39, 192, 1273, 67, 33), (162, 128, 768, 75, 25), (166, 128, 557, 69, 34),
+    (42, 128, 2263, 88, 44), (188, 160, 320, 108, 54), (388, 131, 249, 108, 54), (49, 128, 1996, 106, 53), (54, 160, 1276, 102, 51), (314, 64, 542, 99, 49),
+    (313, 128, 315, 129, 22), (628, 96, 176, 137, 68), (158, 131, 625, 160, 80), (94, 131, 888, 133, 129), (137, 64, 1343, 141, 0), (210, 96, 553, 130, 0),
+    (817, 64, 248, 191, 95), (267, 192, 246, 163, 81), (477, 64, 237, 162, 81), (62, 96, 2128, 189, 0), (81, 64, 2169, 189, 87), (27, 192, 2077, 162, 81),
+    (478, 64, 242, 199, 99), (430, 128, 192, 207, 103), (190, 160, 352, 211, 0), (189, 131, 310, 218, 109), (19, 256, 2536, 212, 106), (158, 96, 638, 196, 86),
+    (49, 256, 933, 192, 129), (288, 96, 376, 237, 118), (801, 64, 249, 226, 113), (46, 256, 992, 255, 0), (191, 64, 874, 241, 240), (511, 128, 255, 250, 125),
+    (512, 128, 256, 256, 255), (103, 192, 547, 229, 228),
 ]
 
 
@@ -29,7 +32,7 @@ def test_exact_corr_window(oracle_mod, B, C, L, K, p, offset):
     xd, wd = to_device(x, offset), to_device(w, offset)
     y, dx = empty_device((B, C, L), tdt, offset), empty_device((B, C, L), tdt, offset)
     names = _kernels(lambda: binding.dwconv_fwd(xd, wd, p, out=y)) + _kernels(lambda: binding.dwconv_bwd_input(xd, wd, p, out=dx))
-    assert len(names) == 2 and any("corr_window_kernel" in n for n in names), names
+    assert len(names) == 2 and all("corr_window_kernel" in n for n in names), names
     xn, wn = as_f32_numpy(x), as_f32_numpy(w)
     _same("fwd", y, oracle_mod.fwd(xn, wn, p)[0], tdt, what)
     _same("dx", dx, oracle_mod.bwd_input(xn, wn, p)[0], tdt, what)
@@ -59,9 +62,14 @@ def test_every_tap_alone_corr_window(B, C, L, K, p):
             assert torch.equal(call(x, w, p), first), f"{call.__name__}: other bits"
 
 
-@pytest.mark.parametrize("B,C,L,K,p,window", [(600, 64, 520, 97, 48, False), (500, 64, 688, 80, 40, False), (600, 64, 544, 97, 48, True), (600, 64, 520, 110, 55, True)])
-def test_seven_offsets_on_virtual_rows(oracle_mod, B, C, L, K, p, window):
-    """Rows of more than 512 positions off cache lines keep the register-resident kernel at seven block offsets; whole lines and more offsets do not."""
+# Calls that the kernel could make and leaves to others, and their neighbours: seven and eight block offsets where memory is near (off cache lines and
+# not), virtual rows, rows of three steps off half cache lines, pieces of few steps and workgroups that crowd some SIMDs
+@pytest.mark.parametrize("B,C,L,K,p,window", [
+    (600, 64, 520, 97, 48, False), (500, 64, 688, 80, 40, False), (600, 64, 520, 110, 55, True), (139, 96, 896, 75, 37, False), (109, 256, 1082, 80, 40, True),
+    (84, 32, 7952, 79, 39, False), (374, 160, 180, 75, 20, False), (373, 160, 176, 68, 34, True), (277, 128, 498, 143, 71, False), (94, 651, 208, 181, 90, False),
+    (62, 64, 2251, 114, 65, False),
+])
+def test_which_calls_corr_window_takes(oracle_mod, B, C, L, K, p, window):
     print(f"case window B{B} C{C} L{L} K{K} p{p}", flush=True)
     x, w = small_ints((B, C, L), 75, 3, torch.float32), small_ints((C, K), 76, 3, torch.float32)
     xd, wd = x.cuda(), w.cuda()
@@ -100,7 +108,7 @@ def test_non_finite_values_stay_where_the_definition_puts_them():
 # rows that end inside a granule, units that the batch does not fill
 DW_SHAPES = [
     (179, 256, 240, 85, 84), (128, 256, 348, 96, 95), (56, 256, 780, 104, 52), (148, 256, 272, 118, 117), (58, 256, 541, 111, 55), (57, 256, 566, 113, 56),
-    (349, 128, 244, 119, 118), (463, 128, 192, 125, 96), (96, 256, 817, 89, 59), (31, 255, 2836, 85, 84), (32, 250, 2848, 87, 0), (32, 250, 1840, 121, 0),
+    (349, 128, 244, 119, 118), (463, 128, 192, 125, 96), (89, 256, 1029, 95, 94), (93, 250, 1264, 86, 85), (460, 64, 526, 83, 82), (38, 256, 1796, 117, 0), (32, 250, 1840, 121, 0),
     (42, 255, 1305, 104, 52), (42, 255, 1281, 101, 50), (41, 250, 2096, 127, 126), (191, 128, 848, 112, 56), (64, 128, 2617, 124, 123), (192, 128, 886, 123, 122),
 ]
 
