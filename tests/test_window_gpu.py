@@ -1,12 +1,14 @@
 """corr_window_kernel (fp32 forward and input gradient, filters of about 65 to 260 taps, calls that fill the chip) and dw_window_kernel (weight
-gradient, about 65 to 130 taps) against the oracle, bit for bit on small integers and on values that need all three limbs."""
+gradient, about 65 to 130 taps): against the oracle on small integers, on values that need all three limbs and at the edges of the range, bit for
+bit; and which calls go to them."""
 import pytest
 import torch
 
 from _parity import empty_device, small_ints, to_device
 from paper_2604_25422_amd import binding
 from paper_2604_25422_amd.workloads import as_f32_numpy
-from test_exact_gpu import _kernels, _same, test_exact_fp32_needs_every_limb
+from test_exact_gpu import _kernels, _same, test_exact_fp32_needs_every_limb as every_limb
+from test_limits_gpu import PAIRS
 
 pytestmark = pytest.mark.gpu
 
@@ -38,24 +40,42 @@ def test_exact_corr_window(oracle_mod, B, C, L, K, p, offset):
     _same("dx", dx, oracle_mod.bwd_input(xn, wn, p)[0], tdt, what)
 
 
-# ... with every limb of the rows, tap by tap: a tap's product is now the first and now the last of a tile, and the first and the last tile of
-# a step alone in it.  And the same bits again from normal data, where a product that is not there yet would be there another time.
+def _shifted(v, o, out):                                 # v[t + o], zeros outside the row
+    L = v.shape[-1]
+    a, b = max(0, -o), min(L, L - o)
+    out.zero_()
+    if a < b:
+        out[..., a:b] = v[..., a + o:b + o]
+    return out
+
+
+# ... with every limb of the rows, tap by tap - a tap's product is now the first and now the last of a tile, and the first and the last tile of
+# a step alone in it - and of the taps, position by position.  And the same bits again from normal data, where a product that is not there yet
+# would be there another time.  (The last two calls: rows whose last step is one tile.)
 @pytest.mark.parametrize("B,C,L,K,p", SHAPES + [(857, 96, 144, 160, 159), (528, 96, 272, 145, 0)])
-def test_every_tap_alone_corr_window(B, C, L, K, p):
-    print(f"case window tap by tap B{B} C{C} L{L} K{K} p{p}", flush=True)
+def test_every_limb_corr_window(B, C, L, K, p):
+    print(f"case window every limb B{B} C{C} L{L} K{K} p{p}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(6)
-    x = torch.randn(B, C, L, generator=g, device="cuda")
-    y, want = torch.empty_like(x), torch.zeros_like(x)
+    x, w = torch.randn(B, C, L, generator=g, device="cuda"), torch.randn(C, K, generator=g, device="cuda")
+    if (B, C, L, K, p) in SHAPES:
+        names = _kernels(lambda: (binding.dwconv_fwd(x, w, p), binding.dwconv_bwd_input(x, w, p)))
+        assert len(names) == 2 and all("corr_window_kernel" in n for n in names), names
+    y, want, one_w, one_x = torch.empty_like(x), torch.empty_like(x), torch.zeros_like(w), torch.zeros_like(x)
     for j in sorted({*range(0, K, 11), max(p - 1, 0), p, min(p + 1, K - 1), K - 1}):
-        w = torch.zeros(C, K, device="cuda"); w[:, j] = 1.0
+        one_w.zero_()
+        one_w[:, j] = 1.0
         for call, o in ((binding.dwconv_fwd, j - p), (binding.dwconv_bwd_input, p - j)):      # y[t] takes x[t + o]
-            a, b = max(0, -o), min(L, L - o)
-            call(x, w, p, out=y)
-            want.zero_()
-            if a < b:
-                want[..., a:b] = x[..., a + o:b + o]
-            assert torch.equal(y, want), f"{call.__name__} tap {j}: {int((y != want).sum())} outputs differ"
-    w = torch.randn(C, K, generator=g, device="cuda")
+            call(x, one_w, p, out=y)
+            assert torch.equal(y, _shifted(x, o, want)), f"{call.__name__} tap {j}: {int((y != want).sum())} outputs differ"
+    t = torch.arange(L, device="cuda")
+    for u in sorted({0, 1, L // 3, L // 2, L - 17, L - 1}):
+        one_x.zero_()
+        one_x[:, :, u] = 1.0
+        for call, sign in ((binding.dwconv_fwd, -1), (binding.dwconv_bwd_input, 1)):          # tap p + sign (t - u) reaches position t
+            j = p + sign * (t - u)
+            rows = torch.where((j >= 0) & (j < K), w[:, j.clamp(0, K - 1)], torch.zeros((), device="cuda"))
+            call(one_x, w, p, out=y)
+            assert torch.equal(y, rows.expand(B, C, L)), f"{call.__name__} position {u}: outputs differ"
     for call in (binding.dwconv_fwd, binding.dwconv_bwd_input):
         first = call(x, w, p)
         for _ in range(4):
@@ -79,29 +99,61 @@ def test_which_calls_corr_window_takes(oracle_mod, B, C, L, K, p, window):
     _same("fwd", y, oracle_mod.fwd(as_f32_numpy(x), as_f32_numpy(w), p)[0], torch.float32, f"B{B} C{C} L{L} K{K} p{p}")
 
 
-@pytest.mark.parametrize("B,C,L,K,p", [(62, 64, 2251, 114, 65), (512, 128, 256, 256, 255)])
-def test_every_limb_corr_window(B, C, L, K, p):
-    test_exact_fp32_needs_every_limb(B, C, L, K, p)
+# Rows in one piece and in several that end inside a granule, in one unit a wave and more
+EDGE = [(49, 128, 1996, 106, 53), (314, 64, 542, 99, 49), (512, 128, 256, 256, 255), (313, 128, 315, 129, 22)]
 
 
-def test_non_finite_values_stay_where_the_definition_puts_them():
+@pytest.mark.parametrize("B,C,L,K,p", EDGE)
+def test_non_finite_values_of_corr_window(B, C, L, K, p):
     """An infinity or NaN reaches outputs of its own row up to 63 positions beyond what the definition says, and the other outputs are what they are
-    without it; sums above 10^19 are as good as any."""
-    B, C, L, K, p = 62, 64, 2251, 114, 65
+    without it; among operands of one sign an infinity stays one; sums above 10^19 are as good as any."""
+    print(f"case window not finite B{B} C{C} L{L} K{K} p{p}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(5)
     x, w = torch.randn(B, C, L, generator=g, device="cuda"), torch.randn(C, K, generator=g, device="cuda")
-    clean = binding.dwconv_fwd(x, w, p)
-    for at, v in ((700, float("inf")), (0, float("nan")), (L - 1, float("-inf"))):
-        bad = x.clone()
-        bad[30, 7, at] = v
-        y = binding.dwconv_fwd(bad, w, p)
-        lo, hi = max(0, at - (K - 1 - p) - 63), min(L, at + p + 64)
-        touched = torch.zeros_like(y, dtype=torch.bool)
-        touched[30, 7, lo:hi] = True
-        assert torch.equal(y[~touched], clean[~touched])
-        assert not torch.isfinite(y[30, 7, max(0, at - (K - 1 - p)):min(L, at + p + 1)]).any()
-    big = binding.dwconv_fwd(x * 2.0 ** 100, w, p)
-    assert torch.equal(big, clean * 2.0 ** 100)
+    for call, before, behind in ((binding.dwconv_fwd, K - 1 - p, p), (binding.dwconv_bwd_input, p, K - 1 - p)):
+        names = _kernels(lambda: call(x, w, p))
+        assert "corr_window_kernel" in names[0], names
+        clean = call(x, w, p)
+        for at, v in ((L // 2 + 3, float("inf")), (0, float("nan")), (L - 1, float("-inf"))):
+            bad = x.clone()
+            bad[B // 2, 7, at] = v
+            y = call(bad, w, p)
+            touched = torch.zeros_like(y, dtype=torch.bool)
+            touched[B // 2, 7, max(0, at - before - 63):min(L, at + behind + 64)] = True
+            assert torch.equal(y[~touched], clean[~touched])
+            assert not torch.isfinite(y[B // 2, 7, max(0, at - before):min(L, at + behind + 1)]).any()
+            if at != 0:
+                bad = x.abs()
+                bad[B // 2, 7, at] = v
+                y = call(bad, w.abs() + 0.5, p)
+                assert (y[B // 2, 7, max(0, at - before):min(L, at + behind + 1)] == v).all()
+        assert torch.equal(call(x * 2.0 ** 100, w, p), clean * 2.0 ** 100)
+
+
+def _top_of_the_range(B, C, L, K, p, dw):
+    u, j = L // 2, p + 20 if p + 20 < K else p - 20
+    x, w, dy = torch.zeros(B, C, L, device="cuda"), torch.zeros(C, K, device="cuda"), torch.zeros(B, C, L, device="cuda")
+    for a, b in PAIRS:
+        x[:, :, u], w[:, j], dy[0, :, u + 3] = a, b, b                          # one product per output, one pair per coefficient
+        exp = (torch.tensor([a], dtype=torch.float32).double() * torch.tensor([b], dtype=torch.float32).double()).float().cuda()
+        if dw:                                                                  # dw[j] takes dy[u + 3] x[u + 3 + j - p]
+            cases = [(binding.dwconv_bwd_weight(x, dy, K, p), (slice(None), p - 3))]
+        else:
+            cases = [(binding.dwconv_fwd(x, w, p), (slice(None), slice(None), u - j + p)), (binding.dwconv_bwd_input(x, w, p), (slice(None), slice(None), u + j - p))]
+        for got, at in cases:
+            want = torch.zeros_like(got)
+            want[at] = exp
+            assert not torch.isnan(got).any(), f"{a!r} x {b!r}: a NaN from finite inputs"
+            assert torch.equal(torch.isinf(got), torch.isinf(want)) and torch.equal(got.sign(), want.sign()), f"{a!r} x {b!r}"
+            # (three limbs per operand, the products of the small ones left out: 2^-24 of the product, and roundings of the sums)
+            fin = torch.isfinite(want)
+            assert float(((got[fin].double() - want[fin].double()).abs() / want[fin].double().abs().clamp_min(1e-30)).max()) <= 2.0 ** -22, f"{a!r} x {b!r}"
+
+
+@pytest.mark.parametrize("B,C,L,K,p", EDGE)
+def test_products_at_the_top_of_the_range_corr_window(B, C, L, K, p):
+    print(f"case window top of the range B{B} C{C} L{L} K{K} p{p}", flush=True)
+    _top_of_the_range(B, C, L, K, p, False)
 
 
 # dw_window_kernel (fp32 weight gradient, at most five 32-blocks): four and five offsets, rows in one piece and in several, one slice and more,
@@ -125,8 +177,8 @@ def test_exact_dw_window(oracle_mod, B, C, L, K, p, offset):
     names = _kernels(lambda: binding.dwconv_bwd_weight(xd, dyd, K, p, out=dw))
     ref = oracle_mod.bwd_weight(as_f32_numpy(x), as_f32_numpy(dy), K, p)[0]
     _same("dw", dw, ref, tdt, what)
+    assert "dw_window_kernel" in names[0], names
     if offset == 0:
-        assert "dw_window_kernel" in names[0], names
         # the partial sums alone: every slice of the workspace is written, and their sum is the gradient
         ws = binding.new_workspace(xd, K, p)
         ws.fill_(255)
@@ -135,6 +187,42 @@ def test_exact_dw_window(oracle_mod, B, C, L, K, p, offset):
         _same("partial", ws.view(torch.float32)[:S * C * K].view(S, C, K).sum(0), ref, tdt, what)
 
 
-@pytest.mark.parametrize("B,C,L,K,p", [(179, 256, 240, 85, 84), (58, 256, 541, 111, 55)])
+# Rows in one piece and in several, rows that end inside a granule
+DW_EDGE = [(179, 256, 240, 85, 84), (58, 256, 541, 111, 55), (41, 250, 2096, 127, 126), (89, 256, 1029, 95, 94)]
+
+
+@pytest.mark.parametrize("B,C,L,K,p", DW_EDGE)
 def test_every_limb_dw_window(B, C, L, K, p):
-    test_exact_fp32_needs_every_limb(B, C, L, K, p)
+    every_limb(B, C, L, K, p)
+
+
+@pytest.mark.parametrize("B,C,L,K,p", DW_EDGE)
+def test_non_finite_values_of_dw_window(B, C, L, K, p):
+    """Other channels keep their bits, also where the value stands next to them in memory; the coefficients that the definition reaches are not finite, and
+    an infinity among operands of one sign stays one."""
+    print(f"case dw window not finite B{B} C{C} L{L} K{K} p{p}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x, dy = torch.randn(B, C, L, generator=g, device="cuda"), torch.randn(B, C, L, generator=g, device="cuda")
+    names = _kernels(lambda: binding.dwconv_bwd_weight(x, dy, K, p))
+    assert "dw_window_kernel" in names[0], names
+    clean = binding.dwconv_bwd_weight(x, dy, K, p)
+    others = [c for c in range(C) if c != 7]
+    for at, v in ((L // 2 + 3, float("inf")), (0, float("nan")), (L - 1, float("-inf"))):
+        for which, jlo, jhi in (("x", at + p - L + 1, at + p), ("dy", p - at, p - at + L - 1)):
+            jlo, jhi = max(jlo, 0), min(jhi, K - 1)
+            bad = [x.clone(), dy.clone()]
+            bad[which == "dy"][B - 1, 7, at] = v
+            dw = binding.dwconv_bwd_weight(*bad, K, p)
+            assert torch.equal(dw[others], clean[others]), f"{which}: another channel changed"
+            assert not torch.isfinite(dw[7, jlo:jhi + 1]).any()
+            if at != 0:
+                bad = [x.abs(), dy.abs() + 0.5]
+                bad[which == "dy"][B - 1, 7, at] = v
+                assert (binding.dwconv_bwd_weight(*bad, K, p)[7, jlo:jhi + 1] == v).all()
+    assert torch.equal(binding.dwconv_bwd_weight(x * 2.0 ** 100, dy, K, p), clean * 2.0 ** 100)
+
+
+@pytest.mark.parametrize("B,C,L,K,p", DW_EDGE)
+def test_products_at_the_top_of_the_range_dw_window(B, C, L, K, p):
+    print(f"case dw window top of the range B{B} C{C} L{L} K{K} p{p}", flush=True)
+    _top_of_the_range(B, C, L, K, p, True)
