@@ -11,11 +11,11 @@
 // One wave per SIMD: 48 ND accumulator registers for the scales of all offsets, 72 for x and 24 for dY.  What hides the splitting is then the wave
 // itself: a step's 6 ND products are issued with the 136 vector instructions that split the next step's blocks between them (a product of
 // 32 cycles leaves half of them to vector instructions), with one branch per step.  Tried: two waves per SIMD with three offsets each, both
-// splitting everything (B32 C256 L4096 K128 100 us, here 85, inputs from memory), or eight offsets on two groups of waves (B2048 C128 L256 K256
+// splitting everything (B32 C256 L4096 K128 100 us, here 77-85, inputs from memory), or eight offsets on two groups of waves (B2048 C128 L256 K256
 // 224 us, dw_band_kernel 167: short rows are all starts of columns).
-// What bounds it: in a training step, B32 C256 L4096 K128 79 us (dw_partial_direct_kernel, on the fp32 instruction, 80 behind a kernel that leaves
-// dY in the last-level cache and 96-102 without), 52 without its loads and 57 without its products.  Relative error against 64 bits 2.1e-7, the fp32
-// instruction 4.2e-7.
+// What bounds it: B32 C256 L4096 K128 77 us with inputs from memory (dw_partial_direct_kernel, on the fp32 instruction, 96) and 74 in a training step, behind
+// a kernel that leaves dY in the last-level cache (80 there); 52 without its loads and 57 without its products.  Relative error against 64 bits
+// 2.0e-7, the fp32 instruction 4.2e-7 (of 140 calls half in the mean).
 #pragma once
 #include "dwconv_dw_band.hip.h"
 #include "dwconv_dw_direct.hip.h"
