@@ -490,9 +490,9 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
 //     pieces cost memory time, or 1.8.  Taken B61 C576 L1163 K94 4.3 / 2.7, B109 C256 L1082 K80 3.6 / 2.6, B974 C64 L1216 K80 2.2 / 1.9; left B244 C96 L2988 K88
 //     2.1 / 2.6, B139 C544 L896 K75 2.3 / 2.7, B86 C128 L5680 K80 2.1 / 2.4, B500 C128 L516 K72 70 / 88 us
 //   in the place of corr_band_kernel: all but rows of at most three steps of 64 positions off half cache lines, where both wait for
-//     memory (B3967 C96 L186 K99 2.3 / 2.5, B702 C453 L186 K85 2.3 / 2.5, B3217 C36 L189 K189 2.6 / 2.6; half lines B3244 C96 L144 K144 2.5 / 2.3), and
-//     rows in one piece with as many steps in front that only bring chunks as steps: the input gradient of causal filters as long as the row (B2048 C128
-//     L256 K256 in a training step 152 / 155 us, alone 150 / 148, its forward 153 / 141; B3208 C114 L232 K232 221 / 230)
+//     memory (B3967 C96 L186 K99 2.3 / 2.5, B702 C453 L186 K85 2.3 / 2.5, B3217 C36 L189 K189 2.6 / 2.6; half lines B3244 C96 L144 K144 2.5 / 2.3).
+//     (Also rows in one piece with as many steps in front that only bring chunks as steps, the input gradient of causal filters as long as the row: in a training
+//     step of B2048 C128 L256 K256 it takes 148 / 151 us, but forward and weight gradient 143 / 138 and 151 / 149 beside it, the step 443 / 439)
 // (Up to six offsets memory bounds the fp32 instruction's kernels already: virtual rows of whole cache lines with five and six offsets are 1.1 to
 // 1.25 times as fast here alone, but a step of separate calls is not: B1024 C64 L224 K56 87 / 93 us, B2048 C128 L384 K64 544 / 529.)
 inline bool corr_takes_window(const Shape &s, int pad_eff, const WindowPlan &p, bool band)
@@ -500,7 +500,7 @@ inline bool corr_takes_window(const Shape &s, int pad_eff, const WindowPlan &p, 
     const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
     const RowsPlan rp = plan_rows(s);
     // (tensors off a 16-byte granule send virtual rows to corr_band_kernel: seven offsets stay there where the estimates below would leave them)
-    if (band) return (s.L > 192 || (s.L % 16) == 0) && !(p.g.NP == 1 && -p.g.s_first >= p.g.ns) && !(nd == kMfmaMaxND + 1 && rp.on && s.L > 512 && (s.L % 32) != 0);
+    if (band) return (s.L > 192 || (s.L % 16) == 0) && !(nd == kMfmaMaxND + 1 && rp.on && s.L > 512 && (s.L % 32) != 0);
     if (nd > 8) return true;
     const double rows = (double)s.B * s.C, millions = rows * s.L / (1024.0 * 1024.0);
     const double padded = rows * (rp.on ? rp.map.P : (s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
