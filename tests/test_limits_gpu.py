@@ -71,7 +71,8 @@ def test_tensors_above_4_GiB(oracle_mod, B, C, L, K, p, dtype, lim):
 # outputs the definition gives it, at most the outputs of the same row within 63 positions of those and the last 63
 # positions of row (b - 1, c) / the first 63 of row (b + 1, c) (short rows of a channel are processed end to end); no
 # other channel is touched.  In the weight gradient it may reach every coefficient of its channel and no other channel.
-# (B, C, L, K, pad_left, storage): one shape per kernel family.
+# (B, C, L, K, pad_left, storage): one shape per kernel family (those that take large calls only, corr_window_kernel and dw_window_kernel: in
+# test_window_gpu.py, with the top of the range and the infinities).
 NONFINITE = [
     (2, 3, 2600, 64, 63, "f32"), (2, 3, 2600, 64, 20, "f32"), (2, 3, 2600, 7, 3, "f32"), (2, 3, 2600, 130, 129, "f32"),
     (2, 3, 2608, 64, 63, "bf16"), (2, 3, 2608, 200, 100, "bf16"),
