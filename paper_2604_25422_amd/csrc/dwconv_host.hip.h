@@ -255,6 +255,7 @@ struct WindowPlan {
     int NW;                // chunks a tile reads (the kernel is compiled per number)
     int gy;                // workgroups per channel
     double cycles;         // its estimate
+    double share;          // of that what a full chip could not do without, with the SIMD that has most waves in the place of the mean one
 };
 bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p);
 

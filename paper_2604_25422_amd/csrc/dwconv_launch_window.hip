@@ -69,13 +69,11 @@ bool plan_corr_window(const Shape &s, int pad_eff, int reverse, WindowPlan *p)
     }
     // Where at least 0.6 of that is steps that a full chip could not do without: pieces of few columns, waves without a unit and the chunks in front
     // of a piece cost more than corr_band_kernel's barriers (us, the kernels before / here, inputs from memory: B2 C712 L4000 K208 24 / 31, B96 C352 L304
-    // K230 35 / 45).  And where, with the SIMD that has most waves in the place of the mean one (405 workgroups of four waves leave some SIMDs with two and
-    // most with one), it is still 0.46, or 0.57 in pieces of at most four steps, whose starts weigh more.  Of 567 calls in the place of
-    // corr_band_kernel the 35 below that gain nothing (mean 0.995; B26 C538 L2665 K233 147 / 175, B549 C59 L561 K247 70 / 80, B277 C128 L498 K143
-    // 55 / 61, B94 C651 L208 K181 38 / 44), the others 1.14 in the mean, 15 of them less than 0.97 (B1184 C384 L176 K124 179 / 202).
+    // K230 35 / 45; further lines in corr_takes_window).
     p->cycles = best;
     const double need = positions / (1024.0 * 1024.0) * step / best;
-    return need >= 0.60 && need >= (g.ns <= 4 ? 0.57 : 0.46) * crowded;
+    p->share = need / crowded;
+    return need >= 0.60;
 }
 
 int launch_corr_window_f32(const void *in, const void *f, void *out, const Shape &s, WindowPlan p, hipStream_t st)
