@@ -218,17 +218,16 @@ static bool dw_takes_toep(const Shape &s, const DwPlan &p)
 
 // Which fp32 filters of seven and more block offsets go to dw_window_kernel instead of the register-resident kernels of the fp32 instruction (those of
 // the band and Toeplitz kernels are asked first): where the products of these, with the padding of rows to regions of 256 positions or of virtual
-// rows to their pitch, take longer than its own estimate, by a tenth for seven offsets on ordinary rows that fill their segments of 1024 positions
-// to three quarters, which are near memory on either.  (Both in us at the clock under load; 1.2 and 1.3 are what either takes beyond its products.)  us, inputs from memory, before -> here: taken B1407 C162 L256 K123
-// pad 122 227 -> 133, B3038 C32 L666 K127 pad 63 265 -> 165, B59 C250 L1333 K86 pad 85 64 -> 47, B1918 C32 L1248 K111 pad 110 191 -> 166, B32 C256 L4096
-// K128 causal 96 -> 77, of 140 calls 1.23 in the mean, the worst 0.99 (B365 C32 L8032 K103); left B393 C256 L823 K89 179 / 196, B1033 C32 L2869 K94
-// 195 / 210, B33 C256 L6464 K86 114 / 119, B913 C32 L1671 K87 112 / 107, B114 C192 L3769 K110 231 / 235, B18 C766 L3761 K120 139 / 152.
+// rows to their pitch, take longer than its own estimate.  (Both in us at the clock under load; 1.2 and 1.3 are what either takes beyond its
+// products.)  us, inputs from memory, before -> here: taken B1407 C162 L256 K123 pad 122 227 -> 133, B3038 C32 L666 K127 pad 63 265 -> 165, B59 C250
+// L1333 K86 pad 85 64 -> 47, B1918 C32 L1248 K111 pad 110 191 -> 166, B32 C256 L4096 K128 causal 96 -> 77.  Close above the line (the estimates within a tenth,
+// seven offsets on ordinary rows) the mean of 60 calls is 1.10, the best B157 C224 L2384 K84 pad 0 227 -> 172, the worst B209 C256 L999 K88 pad 87 107 ->
+// 127; of 61 others above it 1.33, the worst 1.04; of 269 below it 1.03, so that it could lie lower, but not by much (B18 C766 L3761 K120
+// 139 / 152, B2670 C32 L880 K77 168 / 185, B18 C276 L1079 K86 29 / 41).
 static bool dw_takes_window(const Shape &s, const DwPlan &p, int nd)
 {
     const double positions = (double)s.B * s.C * (p.rows.on ? p.rows.map.P : (s.L + 255) / 256 * 256);
-    const bool filled = 4ll * s.L >= 3ll * ((s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
-    const double near_memory = nd == kMfmaMaxND + 1 && !p.rows.on && filled ? 1.1 : 1.0;
-    return near_memory * 1.3 * p.wp.cycles / 2000.0 < 1.2 * positions / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0;
+    return 1.3 * p.wp.cycles / 2000.0 < 1.2 * positions / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0;
 }
 
 // Slices of the workspace for the filters of dw_band_kernel.  Callers keep workspaces and read slices by these numbers

@@ -160,8 +160,9 @@ def test_products_at_the_top_of_the_range_corr_window(B, C, L, K, p):
 # rows that end inside a granule, units that the batch does not fill
 DW_SHAPES = [
     (179, 256, 240, 85, 84), (128, 256, 348, 96, 95), (56, 256, 780, 104, 52), (148, 256, 272, 118, 117), (58, 256, 541, 111, 55), (57, 256, 566, 113, 56),
-    (349, 128, 244, 119, 118), (463, 128, 192, 125, 96), (89, 256, 1029, 95, 94), (93, 250, 1264, 86, 85), (460, 64, 526, 83, 82), (38, 256, 1796, 117, 0), (32, 250, 1840, 121, 0),
+    (349, 128, 244, 119, 118), (463, 128, 192, 125, 96), (96, 256, 817, 89, 59), (31, 255, 2836, 85, 84), (32, 250, 2848, 87, 0), (32, 250, 1840, 121, 0),
     (42, 255, 1305, 104, 52), (42, 255, 1281, 101, 50), (41, 250, 2096, 127, 126), (191, 128, 848, 112, 56), (64, 128, 2617, 124, 123), (192, 128, 886, 123, 122),
+    (89, 256, 1029, 95, 94), (93, 250, 1264, 86, 85), (460, 64, 526, 83, 82), (38, 256, 1796, 117, 0),
 ]
 
 
