@@ -485,12 +485,14 @@ inline bool corr_takes_band(const Shape &s, int pad_eff, const void *in, const v
 // Which fp32 filters of seven and more block offsets that plan_corr_window takes go to corr_window_kernel (us per 2^20 positions unless said
 // otherwise, inputs from memory, the kernel before / here; over 1000 calls, forward and input gradient).
 //   in the place of corr_mfma_kernel: nine offsets and more always (mean gain 1.2; B11 C623 L3040 K138 58 / 71 us).  Seven and eight where an estimate of that
-//     kernel - its products with the padding of rows to whole segments of 1024 positions, or of virtual rows to their pitch, 1.15 or 1.18 times as long as
+//     kernel - its products with the padding of rows to whole segments of 1024 positions, or of virtual rows to their pitch, 1.15 or 1.25 times as long as
 //     at the clock under load; at least 2.2, its memory - is above one of this: 1.2 of the plan's, at least 2.6 for rows that are not whole cache lines,
 //     whose pieces cost memory time, or 1.8.  Taken B61 C576 L1163 K94 4.3 / 2.7, B109 C256 L1082 K80 3.6 / 2.6, B974 C64 L1216 K80 2.2 / 1.9; left B244 C96
-//     L2988 K88 2.1 / 2.6, B139 C544 L896 K75 2.3 / 2.7, B86 C128 L5680 K80 2.1 / 2.4, B500 C128 L516 K72 70 / 88 us
-//   in the place of corr_band_kernel: not rows of at most three steps of 64 positions off half cache lines, where both wait for
-//     memory (B3967 C96 L186 K99 2.3 / 2.5, B702 C453 L186 K85 2.3 / 2.5, B3217 C36 L189 K189 2.6 / 2.6; half lines B3244 C96 L144 K144 2.5 / 2.3), and not
+//     L2988 K88 2.1 / 2.6, B139 C544 L896 K75 2.3 / 2.7, B86 C128 L5680 K80 2.1 / 2.4, B500 C128 L516 K72 70 / 88 us.  (Eight offsets at 1.18: B9 C620
+//     L4615 K107 4.4 / 3.2, B234 C64 L1184 K107 3.3 / 2.5, B42 C477 L1488 K98 2.9 / 2.4 stayed away)
+//   in the place of corr_band_kernel: not rows of at most three steps of 64 positions off half cache lines where inputs and outputs are more than
+//     the 256 MiB of the last-level cache and both wait for memory (B3967 C96 L186 K99 2.3 / 2.5, B702 C453 L186 K85 2.3 / 2.5; half lines B3244 C96 L144
+//     K144 2.5 / 2.3; 16 calls of such a size 2.67 / 2.74 in the mean, 11 smaller ones 3.08 / 3.00, B374 C160 L180 K75 34 / 31 us), and not
 //     calls that leave some SIMDs with two waves and most with one (405 workgroups of four waves): where, with the SIMD that has most waves in the place of
 //     the mean one, less than 0.46 of the plan's estimate, or 0.57 in pieces of at most four steps, whose starts weigh more, is work that a full chip could not do
 //     without.  Of 567 calls the 35 below that gain nothing (mean 0.995; us, B26 C538 L2665 K233 147 / 175, B549 C59 L561 K247 70 / 80, B277 C128
@@ -503,13 +505,13 @@ inline bool corr_takes_window(const Shape &s, int pad_eff, const WindowPlan &p, 
 {
     const int nd = toeplitz_dmax(s.K, pad_eff) - toeplitz_dmin(pad_eff) + 1;
     const RowsPlan rp = plan_rows(s);
+    const double rows = (double)s.B * s.C, millions = rows * s.L / (1024.0 * 1024.0);
     // (tensors off a 16-byte granule send virtual rows to corr_band_kernel: seven offsets stay there where the estimates below would leave them)
     if (band)
-        return (s.L > 192 || (s.L % 16) == 0) && p.share >= (p.g.ns <= 4 ? 0.57 : 0.46) && !(nd == kMfmaMaxND + 1 && rp.on && s.L > 512 && (s.L % 32) != 0);
+        return (s.L > 192 || (s.L % 16) == 0 || millions < 32.0) && p.share >= (p.g.ns <= 4 ? 0.57 : 0.46) && !(nd == kMfmaMaxND + 1 && rp.on && s.L > 512 && (s.L % 32) != 0);
     if (nd > 8) return true;
-    const double rows = (double)s.B * s.C, millions = rows * s.L / (1024.0 * 1024.0);
     const double padded = rows * (rp.on ? rp.map.P : (s.L + dwconv::kSegLen - 1) / dwconv::kSegLen * dwconv::kSegLen);
-    const double there = std::max((nd == 8 ? 1.18 : 1.15) * padded / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0, 2.2 * millions);
+    const double there = std::max((nd == 8 ? 1.25 : 1.15) * padded / 1024.0 * 16 * nd * 32 / (4 * kComputeUnits) / 2100.0, 2.2 * millions);
     const double here = std::max(1.2 * p.cycles / 2000.0, (s.L % 32) == 0 ? 1.8 * millions : 2.6 * millions);
     return here < there;
 }
