@@ -196,23 +196,26 @@ bool plan_dw_band(const Shape &s, int slices, DwBandPlan *p)
     S = std::max(1ll, std::min(S, (long long)std::min(g.stages, slices)));
     p->S = (int)S;
     // ... fp32, one window of offsets (its workgroups then take equally long): fewer, at least half, where that fills the last round of workgroups,
-    // which was a nearly empty one.  A workgroup then sums its stages in two chains of additions (CHAINS), so that none is longer than with S
-    // slices; what the second one costs (its start and its sums, 8 us a round) is only there from five stages on.  (Both in us: a start with its
-    // diagonal sums, a stage.)  S slices -> fewer, us and error against 64 bits (normal data): B1310 C48 L192 K192, 528 workgroups of which 512 run at
-    // once -> 480, 56 -> 43, 1.28e-7 -> 1.12e-7; B2294 C96 L144 K176 155 -> 108, 1.7e-7 -> 1.5e-7; B3217 C36 L189 K189 99 -> 71, 1.6e-7 -> 1.4e-7;
-    // B109 C96 L3056 K223 140 -> 128, 2.0e-7 -> 1.6e-7; of 156 calls the mean gain is 1.19, the worst 0.99, the mean error 0.83 of that
-    // of S slices.  (In one chain the error was up to 1.46 times that of S slices.  bf16 waits for memory, and a workgroup more than fits takes up some
+    // which was a nearly empty one.  Where a slice then has more stages, a workgroup sums them in two chains of additions (CHAINS), so that none is longer
+    // than with S slices; what the second one costs (its start and its sums, 8 us a round) is only there from five stages on.  (Both in us: a start
+    // with its diagonal sums, a stage.)  S slices -> fewer, us and error against 64 bits (normal data): B1310 C48 L192 K192, 528 workgroups of which 512
+    // run at once -> 480, 56 -> 43, 1.28e-7 -> 1.12e-7; B2294 C96 L144 K176 155 -> 108, 1.7e-7 -> 1.5e-7; B3217 C36 L189 K189 99 -> 70, 1.6e-7 -> 1.4e-7;
+    // in one chain, which is as long as before, B109 C96 L3056 K223 138 -> 118, 2.0e-7 -> 2.1e-7, B552 C69 L130 K130 35 -> 29, 1.10e-7 -> 1.13e-7.  Of
+    // 412 calls 44 take two chains (mean gain 1.25, the worst 1.03, mean error 0.84 of that of S slices) and 29 fewer slices in one (1.19, 1.02, 1.01).
+    // (One chain of more stages: error up to 1.46 times that of S slices.  bf16 waits for memory, and a workgroup more than fits takes up some
     // of the wait: B254 C508 L306 K243 53 / 61, B225 C288 L144 K228 24 / 32)
     g.chain = 0;
     if (NL == 3 && g.nwin == 1) {
+        const long long most = (g.stages + S - 1) / S;
         double best = 0.0;
         for (long long t = S; t == S || (t > 1 && 2 * t >= S); --t) {          // (one slice would be the gradient, written once)
             const long long rounds = (wgs * t + slots - 1) / slots, stages = (g.stages + t - 1) / t;
-            const double cost = (double)rounds * ((t < S ? 13.9 : 5.9) + (0.4 + 0.056 * g.S32 * p->ND) * (double)stages);
-            if (t == S || (cost < 0.95 * best && 20 * wgs * t >= 17 * rounds * slots && stages >= 5)) {
+            const bool one = stages <= most;                                   // (chain)
+            const double cost = (double)rounds * ((one ? 5.9 : 13.9) + (0.4 + 0.056 * g.S32 * p->ND) * (double)stages);
+            if (t == S || (cost < 0.95 * best && 20 * wgs * t >= 17 * rounds * slots && (one || stages >= 5))) {
                 best = cost;
                 p->S = (int)t;
-                g.chain = t < S ? (int)(stages + 1) / 2 : 0;
+                g.chain = one ? 0 : (int)(stages + 1) / 2;
             }
         }
     }

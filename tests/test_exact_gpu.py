@@ -374,10 +374,12 @@ def test_dw_toep_takes_long_filters(B, C, L, K, p, dtype, offset):
     assert "dw_toep_kernel" in names[0] and len(names) <= 2, names
 
 
-# fp32 dw_band_kernel with fewer slices than two rounds of workgroups, so that a workgroup sums two chains: rows a stage holds whole and others, two
-# and three offsets of a wave, stages that the slices share evenly and not, rows that end inside a granule
+# fp32 dw_band_kernel with fewer slices than two rounds of workgroups, where a workgroup sums two chains and where one is as long as before: rows a
+# stage holds whole and others, two and three offsets of a wave, stages that the slices share evenly and not, rows that end inside a granule
 CHAINS = [(201, 153, 163, 87, 86), (744, 51, 164, 84, 0), (1564, 37, 133, 83, 82), (615, 119, 136, 83, 0), (854, 37, 179, 67, 33), (403, 76, 176, 104, 0),
-          (530, 55, 267, 69, 34), (303, 249, 136, 103, 102), (2294, 96, 144, 176, 175), (109, 96, 3056, 223, 0)]
+          (530, 55, 267, 69, 34), (303, 249, 136, 103, 102), (2294, 96, 144, 176, 175), (109, 96, 3056, 223, 0), (2869, 37, 208, 186, 185),
+          (332, 103, 960, 183, 182), (1262, 110, 193, 216, 108)]
+ONE_CHAIN = [(744, 51, 164, 84, 0), (1564, 37, 133, 83, 82), (530, 55, 267, 69, 34), (109, 96, 3056, 223, 0)]
 
 
 @pytest.mark.parametrize("B,C,L,K,p", CHAINS)
@@ -388,7 +390,8 @@ def test_two_chains_of_dw_band(oracle_mod, B, C, L, K, p):
     xd, dyd = x.cuda(), dy.cuda()
     dw = torch.empty(C, K, device="cuda")
     names = _kernels(lambda: binding.dwconv_bwd_weight(xd, dyd, K, p, out=dw))
-    assert "dw_band_kernel" in names[0], names
+    one = (B, C, L, K, p) in ONE_CHAIN
+    assert "dw_band_kernel" in names[0] and ("false>" if one else "true>") in names[0].split("(")[0], names
     ref = oracle_mod.bwd_weight(as_f32_numpy(x), as_f32_numpy(dy), K, p)[0]
     _same("dw", dw, ref, torch.float32, f"B{B} C{C} L{L} K{K} p{p}")
     ws = binding.new_workspace(xd, K, p)
