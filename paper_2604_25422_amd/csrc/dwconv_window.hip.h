@@ -15,10 +15,10 @@
 //
 // What bounds it: vector instructions (limbs, sums) and these products of 16 cycles take turns on a SIMD (a product of 32 x 32 x 16 hides vector
 // instructions for half of its 32 cycles, this one for none), together 40 us of the 69 us of B32 C256 L4096 K128 (inputs from memory, mean of four
-// boxes), whose memory takes 52 (pieces of rows cost some: a walk of whole segments takes 50); corr_mfma_kernel on the fp32 instruction takes 81. B2048
+// cards), whose memory takes 52 (pieces of rows cost some: a walk of whole segments takes 50); corr_mfma_kernel on the fp32 instruction takes 81. B2048
 // C128 L256 K256 causal: forward 140 us, input gradient, which brings four steps of chunks in front of every row, 148 (corr_band_kernel 152 and
-// 150; in a training step 138 and 151, corr_band_kernel 150 and 148, the step 439 and 449), memory 103.  Three waves per SIMD in place of two (168 registers): no faster, and 90 us where they spill.  Relative error against 64
-// bits (2-norm, normal data): 5-9e-8, as corr_band_kernel; the fp32 instruction 1.5-2.1e-7.
+// 150; in a training step 138 and 151, corr_band_kernel 150 and 148, the step 439 and 449), memory 103.  Three waves per SIMD in place of two (168
+// registers): no faster, and 90 us where they spill.  Relative error against 64 bits (2-norm, normal data): 5-9e-8, as corr_band_kernel; the fp32 instruction 1.5-2.1e-7.
 #pragma once
 #include "dwconv_band.hip.h"
 
